@@ -21,6 +21,12 @@ bool is_rsr_kind(int kind) {
     return kind == RSR_BINARY || kind == RSR_TERNARY_2PASS || kind == RSR_TERNARY_FUSED;
 }
 
+// Whether a batch is multiplied on the matrix cores.  From four vectors on that is faster for
+// every kind and size measured (8B layers, 4 vectors: 10 us a launch against 22 for the stream of
+// the block patterns, which costs the same for every vector; three vectors on 1001 x 2999: 14 us
+// against 9).
+bool use_packed(const rsr_handle_s *h, int batch) { return h->packed && batch >= 4; }
+
 template <typename T>
 hipError_t dev_alloc(T **p, size_t count) {
     *p = nullptr;
@@ -89,13 +95,14 @@ int read_flags(const Temps &t, int (&host)[kFlagWords]) {
 int run_dense(rsr_handle_s *h, const int8_t *M, const Temps &t) {
     int host[kFlagWords];
     if (rsr::launch_fill_u32(reinterpret_cast<uint32_t *>(t.flags), 0u, kFlagWords) != hipSuccess ||
-        rsr::launch_pack2(M, h->rows, h->cols, h->row_bytes, h->packed, t.flags + kFlagErr) != hipSuccess)
+        rsr::launch_pack_codes(M, h->rows, h->cols, h->code_bits, h->packed, t.flags + kFlagErr) != hipSuccess)
         return RSR_EHIP;
     if (int rc = read_flags(t, host)) return rc;
     return host[kFlagErr] ? RSR_EVALUE : RSR_OK;
 }
 
-// encode -> counting sort -> stream statistics, per pass
+// encode -> counting sort -> stream statistics, per pass; and the packed codes, if the handle has
+// room for them
 int run_sort_passes(rsr_handle_s *h, const int8_t *M, const Temps &t, StreamStats *st) {
     static const int modes[3][2] = {{rsr::MODE_BINARY, 0}, {rsr::MODE_POS, rsr::MODE_NEG},
                                     {rsr::MODE_FUSED3, 0}};
@@ -113,6 +120,9 @@ int run_sort_passes(rsr_handle_s *h, const int8_t *M, const Temps &t, StreamStat
                 hipSuccess)
             return RSR_EHIP;
     }
+    if (h->packed && rsr::launch_pack_codes(M, h->rows, h->cols, h->code_bits, h->packed,
+                                            t.flags + kFlagErr) != hipSuccess)
+        return RSR_EHIP;
     if (int rc = read_flags(t, host)) return rc;
     if (host[kFlagErr]) return RSR_EVALUE;
     for (int ps = 0; ps < h->npass; ++ps) {
@@ -158,9 +168,7 @@ int preprocess_dense(rsr_handle_s *h, const int8_t *M) {
     Temps t;
     const int64_t ntiles = (h->cols + rsr::kDenseTileCols - 1) / rsr::kDenseTileCols;
     h->row_bytes = ntiles * (rsr::kDenseTileCols / 4);
-    const size_t bytes =
-        (size_t)((h->rows + rsr::kDenseRows - 1) / rsr::kDenseRows) * rsr::kDenseRows * h->row_bytes;
-    RSR_TRY(dev_alloc(&h->packed, bytes));
+    RSR_TRY(dev_alloc(&h->packed, (size_t)rsr::packed_bytes(h->rows, h->cols, h->code_bits)));
     RSR_TRY(dev_alloc(&t.flags, kFlagWords));
     rc = run_dense(h, M, t);
 done:
@@ -168,7 +176,9 @@ done:
     return rc;
 }
 
-int preprocess_rsr(rsr_handle_s *h, const int8_t *M, bool allow_narrow) {
+// Stacked handles multiply one vector at a time through the general kernel: no packed codes and
+// no narrow layout.
+int preprocess_rsr(rsr_handle_s *h, const int8_t *M, bool stacked) {
     int rc = RSR_OK;
     Temps t;
     const int64_t nb = h->nb, cols = h->cols, P = h->P;
@@ -176,6 +186,7 @@ int preprocess_rsr(rsr_handle_s *h, const int8_t *M, bool allow_narrow) {
 
     RSR_TRY(dev_alloc(&t.code, (size_t)(nb * cols)));
     RSR_TRY(dev_alloc(&t.flags, kFlagWords));
+    if (!stacked) RSR_TRY(dev_alloc(&h->packed, (size_t)rsr::packed_bytes(h->rows, cols, h->code_bits)));
     for (int ps = 0; ps < h->npass; ++ps) {
         RSR_TRY(dev_alloc(&h->pass[ps].pi, (size_t)(nb * cols)));
         RSR_TRY(dev_alloc(&h->pass[ps].off, (size_t)(nb * (P + 1))));
@@ -184,7 +195,7 @@ int preprocess_rsr(rsr_handle_s *h, const int8_t *M, bool allow_narrow) {
     {
         // narrow matrices: 8-bit entries, one wave per block
         const int fw = h->base == 2 ? 1 : 2;
-        if (allow_narrow && cols <= rsr::kNarrowCols && h->k * fw <= 32) {
+        if (!stacked && cols <= rsr::kNarrowCols && h->k * fw <= 32) {
             int64_t most = st.groups[0] > st.groups[1] ? st.groups[0] : st.groups[1];
             h->narrow = 1;
             h->narrow_fw = fw;
@@ -252,7 +263,7 @@ namespace {
 
 // Preprocessing with a given block height (k is ignored for the dense kind).
 rsr_handle_s *preprocess_with_k(const int8_t *M, int64_t rows, int64_t cols, int k, int kind,
-                                bool allow_narrow = true) {
+                                bool stacked = false) {
     rsr_handle_s *h = new (std::nothrow) rsr_handle_s();
     if (!h) { fail(RSR_ENOMEM); return nullptr; }
     h->magic = rsr::kMagic;
@@ -269,11 +280,12 @@ rsr_handle_s *preprocess_with_k(const int8_t *M, int64_t rows, int64_t cols, int
         const int kmax = fused ? 10 : 15;
         h->k = k;
         h->base = fused ? 3 : 2;
+        h->code_bits = (kind == RSR_BINARY) ? 1 : 2;
         h->npass = (kind == RSR_TERNARY_2PASS) ? 2 : 1;
         if (k > kmax) { free_handle(h); fail(RSR_EUNSUPPORTED); return nullptr; }
         h->P = ipow(h->base, k);
         h->nb = (rows + k - 1) / k;
-        rc = preprocess_rsr(h, M, allow_narrow);
+        rc = preprocess_rsr(h, M, stacked);
     }
     if (rc == RSR_OK && hipDeviceSynchronize() != hipSuccess) rc = RSR_EHIP;
     if (rc != RSR_OK) {
@@ -380,8 +392,7 @@ rsr_handle_s *preprocess_stacked_with_k(const int8_t *const *Ms, const int64_t *
         (void)hipGetLastError();
         fail(RSR_EHIP);
     } else {
-        // (the narrow kernel writes one output vector: stacked handles take the general one)
-        h = preprocess_with_k(T, padded, cols, k, kind, false);  // synchronises before returning
+        h = preprocess_with_k(T, padded, cols, k, kind, true);  // synchronises before returning
     }
     (void)hipFree(T);
     if (h) {
@@ -629,6 +640,30 @@ std::vector<Piece> pieces_of(rsr_handle_s *h) {
     return p;
 }
 
+// The packed codes are not in the byte string: they are rebuilt from the permutation and the
+// boundaries.  RSR_EINVAL when those are not what a matrix gives.
+int restore_codes(rsr_handle_s *h) {
+    int rc = RSR_OK, err = 0;
+    int8_t *M = nullptr;
+    int *flag = nullptr;
+    h->code_bits = (h->kind == RSR_BINARY) ? 1 : 2;
+    RSR_TRY(dev_alloc(&h->packed, (size_t)rsr::packed_bytes(h->rows, h->cols, h->code_bits)));
+    RSR_TRY(dev_alloc(&M, (size_t)(h->rows * h->cols + 3) / 4 * 4));
+    RSR_TRY(dev_alloc(&flag, 1));
+    RSR_TRY(rsr::launch_fill_u32(reinterpret_cast<uint32_t *>(flag), 0u, 1));
+    RSR_TRY(rsr::launch_fill_u32(reinterpret_cast<uint32_t *>(M), 0u, (h->rows * h->cols + 3) / 4));
+    for (int ps = 0; ps < h->npass; ++ps)
+        RSR_TRY(rsr::launch_unsort(h->pass[ps].pi, h->pass[ps].off, h->rows, h->cols, h->k, h->base, h->P,
+                                   ps == 0 ? 1 : -1, M));
+    RSR_TRY(rsr::launch_pack_codes(M, h->rows, h->cols, h->code_bits, h->packed, flag));
+    RSR_TRY(hipMemcpy(&err, flag, sizeof(err), hipMemcpyDeviceToHost));
+    if (err) rc = RSR_EINVAL;
+done:
+    if (M) (void)hipFree(M);
+    if (flag) (void)hipFree(flag);
+    return rc;
+}
+
 }  // namespace
 
 extern "C" {
@@ -732,6 +767,7 @@ rsr_handle_t rsr_deserialize(const void *host_buf, int64_t size) {
         if (e != hipSuccess) rc = hip_code(e);
         at += pieces[i].bytes;
     }
+    if (rc == RSR_OK && !dense) rc = restore_codes(h);
     if (rc != RSR_OK) {
         (void)hipGetLastError();
         free_handle(h);
@@ -754,7 +790,10 @@ int rsr_matvec_ex(rsr_handle_t h, const void *v, int v_dtype, float scale, void 
     if (hipGetDevice(&device) != hipSuccess) return fail(RSR_EHIP);
     if (device != h->device) return fail(RSR_EINVAL);  // the handle's buffers live on another GPU
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    hipError_t e = (h->kind == RSR_DENSE_TERNARY_P2)
+    // several vectors: a contraction, on the matrix cores, whatever the kind
+    hipError_t e = use_packed(h, batch)
+                       ? rsr::launch_packed(h, v, v_dtype, scale, static_cast<float *>(out), batch, ldv, ldo, s)
+                   : (h->kind == RSR_DENSE_TERNARY_P2)
                        ? rsr::launch_dense_matvec(h, v, v_dtype, scale, static_cast<float *>(out),
                                                   batch, ldv, ldo, s)
                    : h->narrow
@@ -879,8 +918,8 @@ int64_t rsr_algorithmic_bytes(rsr_handle_t h, int v_dtype, int batch) {
     }
     const int64_t vb = (v_dtype == RSR_BF16) ? 2 : 4;
     int64_t weight_side;
-    if (h->kind == RSR_DENSE_TERNARY_P2) {
-        weight_side = (h->rows + rsr::kDenseRows - 1) / rsr::kDenseRows * rsr::kDenseRows * h->row_bytes;
+    if (h->kind == RSR_DENSE_TERNARY_P2 || use_packed(h, batch)) {
+        weight_side = rsr::packed_bytes(h->rows, h->cols, h->code_bits);
     } else {
         weight_side = 0;
         for (int ps = 0; h->narrow && ps < h->npass; ++ps)

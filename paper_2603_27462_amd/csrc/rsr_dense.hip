@@ -31,37 +31,6 @@ constexpr int kDenseWaves = 8;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void k_pack2_tiled(const int8_t *__restrict__ M, int64_t rows,
-                                                     int64_t cols, int64_t ntiles,
-                                                     uint32_t *__restrict__ tiled,
-                                                     int *__restrict__ err_flag) {
-    const int64_t ngroups = (rows + kDenseRows - 1) / kDenseRows;
-    const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (gid >= ngroups * ntiles * 256) return;
-    const int d = (int)(gid & 3);
-    const int lane = (int)((gid >> 2) & 63);
-    const int64_t gt = gid >> 8;
-    const int64_t G = gt / ntiles, t = gt % ntiles;
-    const int64_t i = G * kDenseRows + (lane & 15);
-    const int kq = lane >> 4;
-    uint32_t word = 0;
-    bool bad = false;
-    if (i < rows) {
-        for (int p = 0; p < 8; ++p) {
-            for (int hi = 0; hi < 2; ++hi) {
-                const int64_t j = t * kDenseTileCols + (2 * d + (p >> 2)) * 32 + 8 * kq + 2 * (p & 3) + hi;
-                if (j < cols) {
-                    const int m = M[i * cols + j];
-                    if (m < -1 || m > 1) bad = true;
-                    word |= ((uint32_t)m & 3u) << ((hi ? 30 : 14) - 2 * p);
-                }
-            }
-        }
-    }
-    if (bad) atomicOr(err_flag, 1);
-    tiled[gid] = word;
-}
-
 // Stages columns [c0, c0 + ncols) of one vector (zero past n_in) into LDS at byte address
 // `at` as bf16 planes of `plane` bytes each: one plane for bf16 input, three for float32.
 template <typename VT>
@@ -265,16 +234,6 @@ hipError_t launch(const rsr_handle_s *h, const void *v, float scale, float *out,
 }
 
 }  // namespace
-
-// packed: [ceil(rows/16)][row_bytes/64 tiles][64 lanes][4] dwords; row_bytes = tiles*64.
-hipError_t launch_pack2(const int8_t *M, int64_t rows, int64_t cols, int64_t row_bytes,
-                        uint8_t *packed, int *err_flag) {
-    const int64_t ntiles = row_bytes / (kDenseTileCols / 4);
-    const int64_t total = (rows + kDenseRows - 1) / kDenseRows * ntiles * 256;
-    hipLaunchKernelGGL(k_pack2_tiled, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, 0, M,
-                       rows, cols, ntiles, reinterpret_cast<uint32_t *>(packed), err_flag);
-    return hipGetLastError();
-}
 
 hipError_t launch_dense_matvec(const rsr_handle_s *h, const void *v, int v_dtype, float scale,
                                float *out, int batch, int64_t ldv, int64_t ldo,

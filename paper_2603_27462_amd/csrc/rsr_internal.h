@@ -98,8 +98,11 @@ struct rsr_handle_s {
     int64_t layer_rows[rsr::kMaxLayers] = {};
     int64_t layer_first[rsr::kMaxLayers + 1] = {};  // first unit (block / group of 16 rows) of a layer
     bool stale = false;          // a failed rsr_preprocess_into left the buffers half-written
-    uint8_t *packed = nullptr;   // dense kind: [rows/16][tiles][64 lanes][16 bytes], row_bytes = 64 tiles
-    int64_t row_bytes = 0;
+    // packed codes (rsr_packed.hip), [rows/16][tiles of 256 columns][64 lanes][8 * code_bits bytes]:
+    // all a dense handle has; the other kinds multiply batches with them
+    uint8_t *packed = nullptr;
+    int code_bits = 2;           // bits per entry: 1 for the binary kind
+    int64_t row_bytes = 0;       // dense kind: 64 * tiles
 };
 
 namespace rsr {
@@ -129,9 +132,16 @@ hipError_t launch_stream_stats(const uint32_t *off, int64_t nb, int64_t cols, in
 // (by rank only).  *err_flag |= 2 when a block does not hold the expected number of tails.
 hipError_t launch_pack_pass(const rsr_handle_s *h, int pass, uint16_t *logical, uint16_t *gcode,
                             int *err_flag);
+// Entries of the matrix from the canonical pi / off of one pass: M (zeroed by the caller) gets
+// the digits that are not zero, 2 as -1, times sign.
+hipError_t launch_unsort(const uint16_t *pi, const uint32_t *off, int64_t rows, int64_t cols, int k, int base,
+                         int64_t P, int sign, int8_t *M);
 hipError_t launch_transpose(const int8_t *M, int64_t rows, int64_t cols, int8_t *T);
-hipError_t launch_pack2(const int8_t *M, int64_t rows, int64_t cols, int64_t row_bytes,
-                        uint8_t *packed, int *err_flag);
+// Packed codes of the matrix (bits = 1 or 2 per entry), packed_bytes() of them; *err_flag |= 1
+// for an entry outside the alphabet.
+int64_t packed_bytes(int64_t rows, int64_t cols, int bits);
+hipError_t launch_pack_codes(const int8_t *M, int64_t rows, int64_t cols, int bits, void *packed,
+                             int *err_flag);
 
 // --- multiply launches ---------------------------------------------------------
 // `layers` (may be null): per-layer outputs and scales of a stacked handle; then out, scale
@@ -142,6 +152,9 @@ hipError_t launch_rsr_matvec(const rsr_handle_s *h, const void *v, int v_dtype, 
 hipError_t launch_dense_matvec(const rsr_handle_s *h, const void *v, int v_dtype, float scale,
                                float *out, int batch, int64_t ldv, int64_t ldo, hipStream_t stream,
                                const LayerTable *layers = nullptr);
+// Product of several vectors on the matrix cores, from the packed codes of any kind.
+hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, float scale, float *out,
+                         int batch, int64_t ldv, int64_t ldo, hipStream_t stream);
 // Writes the name of the multiply kernel h launches for (v_dtype, batch) into buf.
 void rsr_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, char *buf, size_t len);
 const char *dense_matvec_kernel_name(const rsr_handle_s *h, int v_dtype);

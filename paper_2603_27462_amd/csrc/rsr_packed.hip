@@ -1,0 +1,565 @@
+// Products of packed codes on the matrix cores (gfx950).
+//
+// A batch of vectors turns the product into a contraction, so it runs on the matrix cores
+// straight from the matrix entries, packed to 2 bits (ternary) or 1 bit (binary), whatever
+// the kind of the handle; the redundancy a block of rows has is worth less there than the 32
+// vectors that share one decoded weight.  Two kernels, both around v_mfma_f32_32x32x16_bf16
+// (measured 15.1 ns per instruction and SIMD against 12.7 for v_mfma_f32_16x16x32_bf16, which
+// does half the work):
+//   split  32 rows x 32 vectors per workgroup, the columns dealt to its eight waves; bound by the
+//          latency of its loads (4096 x 14336, 16 bf16 vectors: 14.4 us; as 16 products of one
+//          vector 78 us)
+//   tile   128 rows x 128 vectors per workgroup, a 64 x 64 quarter per wave; bound by the matrix
+//          cores (4096 x 14336, 2048 bf16 vectors: 211 us = 1.14 PFLOP/s, 8.2 ms as single
+//          products; a library product of 8192^3 reaches 1.21 PFLOP/s on the same card)
+//
+// Layout: [row group of 16][tile of 256 columns][lane][2 * BITS dwords], one load of 16
+// (8) bytes per lane and tile.  Lane l holds row l%16 and the column slices 8*(l/16).. of the
+// tile's eight 32-column steps.  A ternary dword d feeds steps 2d and 2d+1; pair slot p (0..7)
+// has its even column in bits 14-2p.. and its odd column in bits 30-2p.., two's complement.  A
+// binary dword d feeds steps 4d..4d+3; every step owns one bit of each of the eight nibbles.
+//
+// Decoding: after one AND (and a shift) every nibble of a dword is the 4-bit float of one
+// entry (0100 = 2.0, 1100 = -2.0), and v_cvt_scalef32_pk_bf16_fp4 turns a byte, that is two
+// entries, into two bf16: 11 instructions for 16 ternary entries of a lane where shifting and
+// masking pairs into place took 15.  The nibbles come out in the order 4 0 5 1 6 2 7 3 of a
+// slice's eight columns; v is brought into the same order when it is staged.
+//
+// float32 vectors are split exactly into three bf16 planes (top, middle and bottom 8
+// significant bits) that take one MFMA each, so integer-valued inputs stay exact and nothing
+// is lost against float32 inputs.  Accumulation is float32 throughout and the order of the
+// sums is fixed.
+#ifdef RSR_TUNING
+#include <cstdlib>
+#endif
+
+#include "rsr_internal.h"
+
+namespace rsr {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// rows of v start anywhere: 16 bytes at the alignment of an element (the hardware takes any)
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
+
+constexpr int kTileCols = kDenseTileCols;  // 256: eight 32-column steps
+constexpr int kTileSteps = kTileCols / 32;
+
+// ---- packing ---------------------------------------------------------------------------------
+// One thread per (row group, tile, lane): eight loads of eight entries each.
+template <int BITS>
+__global__ __launch_bounds__(256) void k_pack_codes(const int8_t *__restrict__ M, int64_t rows, int64_t cols,
+                                                    int64_t ntiles, uint32_t *__restrict__ tiled,
+                                                    int *__restrict__ err_flag) {
+    const int64_t ngroups = (rows + kDenseRows - 1) / kDenseRows;
+    const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (gid >= ngroups * ntiles * 64) return;
+    const int lane = (int)(gid & 63);
+    const int64_t gt = gid >> 6, G = gt / ntiles, t = gt - G * ntiles;
+    const int64_t i = G * kDenseRows + (lane & 15);
+    const int64_t j0 = t * kTileCols + 8 * (lane >> 4);
+    uint32_t word[2 * BITS];
+#pragma unroll
+    for (int d = 0; d < 2 * BITS; ++d) word[d] = 0;
+    uint32_t bad = 0;
+    if (i < rows) {
+        const int8_t *row = M + i * cols;
+#pragma unroll
+        for (int st = 0; st < kTileSteps; ++st) {
+            const int64_t j = j0 + 32 * st;
+            uint32_t x[2] = {0, 0};
+            if (j + 8 <= cols) {
+                const u32x2 y = *reinterpret_cast<const u32x2_any *>(row + j);
+                x[0] = y.x;
+                x[1] = y.y;
+            } else {
+                for (int e = 0; e < 8 && j + e < cols; ++e)
+                    x[e >> 2] |= (uint32_t)(uint8_t)row[j + e] << (8 * (e & 3));
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                // entries outside the alphabet: bits 2..7 not all equal to bit 1, or the code 10
+                const uint32_t s = (x[h] >> 1) & 0x01010101u, o = x[h] & 0x01010101u;
+                bad |= BITS == 2 ? ((x[h] ^ (s * 255u)) & 0xfcfcfcfcu) | (s & ~o) : x[h] & 0xfefefefeu;
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t code = (x[e >> 2] >> (8 * (e & 3))) & (BITS == 2 ? 3u : 1u);
+                if (BITS == 2) {
+                    const int p = 4 * (st & 1) + (e >> 1);
+                    word[st >> 1] |= code << ((e & 1 ? 30 : 14) - 2 * p);
+                } else {
+                    constexpr int bit_of[4] = {2, 1, 0, 3};
+                    const int nibble = e < 4 ? 2 * e + 1 : 2 * (e - 4);
+                    word[st >> 2] |= code << (4 * nibble + bit_of[st & 3]);
+                }
+            }
+        }
+    }
+    if (bad) atomicOr(err_flag, 1);
+#pragma unroll
+    for (int d = 0; d < 2 * BITS; ++d) tiled[gid * 2 * BITS + d] = word[d];
+}
+
+// ---- decoding --------------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t two_bf16(uint32_t nibbles, int byte) {
+    // scale 0.5: the nibbles are 0, 2.0 and -2.0
+    switch (byte) {
+        case 0: return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(nibbles, 0.5f, 0));
+        case 1: return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(nibbles, 0.5f, 1));
+        case 2: return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(nibbles, 0.5f, 2));
+        default: return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(nibbles, 0.5f, 3));
+    }
+}
+
+// The eight entries of a lane for 32-column step st of a tile.
+template <int BITS>
+__device__ __forceinline__ bf16x8 decode(const uint32_t (&w)[2 * BITS], int st) {
+    u32x4 a;
+    if (BITS == 2) {
+        const uint32_t d = w[st >> 1];
+        const uint32_t hi = d & 0xccccccccu, lo = (d << 2) & 0xccccccccu;
+        const int b = st & 1 ? 0 : 1;
+        a.x = two_bf16(hi, b);
+        a.y = two_bf16(hi, b + 2);
+        a.z = two_bf16(lo, b);
+        a.w = two_bf16(lo, b + 2);
+    } else {
+        const uint32_t d = w[st >> 2];
+        const int j = st & 3;
+        const uint32_t t = (j == 0 ? d : j == 1 ? d << 1 : j == 2 ? d << 2 : d >> 1) & 0x44444444u;
+        a.x = two_bf16(t, 0);
+        a.y = two_bf16(t, 1);
+        a.z = two_bf16(t, 2);
+        a.w = two_bf16(t, 3);
+    }
+    return __builtin_bit_cast(bf16x8, a);
+}
+
+template <int BITS>
+__device__ __forceinline__ void load_codes(const uint32_t *__restrict__ p, uint32_t (&w)[2 * BITS]) {
+    if (BITS == 2) {
+        const u32x4 x = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+        w[0] = x.x; w[1] = x.y; w[2 * BITS - 2] = x.z; w[2 * BITS - 1] = x.w;
+    } else {
+        const u32x2 x = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(p));
+        w[0] = x.x; w[1] = x.y;
+    }
+}
+
+// Two row groups for the 32-row MFMA: afterwards `a` holds, lane rows 0..3, slice 0 of group a,
+// slice 0 of group b, slice 2 of a, slice 2 of b, and `b` the slices 1 and 3: with the MFMA's
+// lane = 32 * (half of the columns) + row, `a` is one 16-column operand and `b` the next.
+template <int N>
+__device__ __forceinline__ void pair_groups(uint32_t (&a)[N], uint32_t (&b)[N]) {
+#pragma unroll
+    for (int d = 0; d < N; ++d) {
+        const auto r = __builtin_amdgcn_permlane16_swap(a[d], b[d], false, false);
+        a[d] = r[0];
+        b[d] = r[1];
+    }
+}
+
+// ---- vectors ---------------------------------------------------------------------------------
+// Eight consecutive elements of a vector, as loaded (col past the end: zeros).
+template <typename VT>
+struct Piece {
+    u32x4 q[sizeof(VT) / 2];
+};
+
+template <typename VT>
+__device__ __forceinline__ Piece<VT> load_piece(const VT *__restrict__ row, int col, int n_in, bool whole) {
+    Piece<VT> p;
+    if (whole || col + 8 <= n_in) {
+#pragma unroll
+        for (int i = 0; i < (int)sizeof(VT) / 2; ++i)
+            p.q[i] = *reinterpret_cast<const u32x4_any *>(reinterpret_cast<const unsigned char *>(row + col) + 16 * i);
+        return p;
+    }
+    uint32_t e[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        e[i] = 0;
+        if (col + i < n_in)
+            e[i] = sizeof(VT) == 4 ? reinterpret_cast<const uint32_t *>(row)[col + i]
+                                   : reinterpret_cast<const uint16_t *>(row)[col + i];
+    }
+    if (sizeof(VT) == 4) {
+        p.q[0] = u32x4{e[0], e[1], e[2], e[3]};
+        p.q[sizeof(VT) / 2 - 1] = u32x4{e[4], e[5], e[6], e[7]};
+    } else {
+        p.q[0] = u32x4{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
+    }
+    return p;
+}
+
+// low halves of (a, b): a in the low half of the result; and the high halves
+__device__ __forceinline__ uint32_t low_halves(uint32_t a, uint32_t b) {
+    return __builtin_amdgcn_perm(b, a, 0x05040100u);
+}
+__device__ __forceinline__ uint32_t high_halves(uint32_t a, uint32_t b) {
+    return __builtin_amdgcn_perm(b, a, 0x07060302u);
+}
+
+// Writes the piece to LDS, in the order 4 0 5 1 6 2 7 3 of its elements: one plane for bf16,
+// three (`plane` bytes apart) for float32.
+__device__ __forceinline__ void store_piece(unsigned char *at, int plane, const Piece<uint16_t> &p) {
+    (void)plane;
+    const u32x4 q = p.q[0];
+    *reinterpret_cast<u32x4 *>(at) = u32x4{low_halves(q.z, q.x), high_halves(q.z, q.x), low_halves(q.w, q.y),
+                                           high_halves(q.w, q.y)};
+}
+__device__ __forceinline__ void store_piece(unsigned char *at, int plane, const Piece<float> &p) {
+    uint32_t x[8] = {p.q[0].x, p.q[0].y, p.q[0].z, p.q[0].w, p.q[1].x, p.q[1].y, p.q[1].z, p.q[1].w};
+#pragma unroll
+    for (int pl = 0; pl < 3; ++pl) {
+        // x = top + rest exactly: each plane keeps 8 of the 24 significant bits
+        *reinterpret_cast<u32x4 *>(at + pl * plane) = u32x4{high_halves(x[4], x[0]), high_halves(x[5], x[1]),
+                                                            high_halves(x[6], x[2]), high_halves(x[7], x[3])};
+        if (pl < 2) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                x[i] = __float_as_uint(__uint_as_float(x[i]) - __uint_as_float(x[i] & 0xffff0000u));
+        }
+    }
+}
+
+__device__ __forceinline__ bf16x8 lds_operand(const unsigned char *at) {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(at));
+}
+
+__device__ __forceinline__ f32x16 mfma32(bf16x8 v, bf16x8 w, f32x16 acc) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, w, acc, 0, 0, 0);
+}
+
+// Vector (row of the MFMA result) of accumulator register i in lane half h.
+__device__ __forceinline__ int acc_vector(int i, int h) { return 8 * (i >> 2) + 4 * h + (i & 3); }
+
+// ---- split: 32 rows x 32 vectors, the columns dealt to eight waves ---------------------------
+// For batches too small to fill the chip with tiles of 128 x 128.  Every wave works through
+// its own share of the tiles and stages its own columns of the 32 vectors in LDS of its own:
+// nothing in the loop waits for another wave, the partial results are added at the end.
+template <typename VT>
+struct Split {
+    static constexpr int planes = sizeof(VT) == 4 ? 3 : 1;
+    static constexpr int cols = sizeof(VT) == 4 ? 64 : 128;  // columns staged at a time
+    static constexpr int pieces = cols / 8;
+    static constexpr int stride = cols * 2 + 16;  // bytes between vectors: an odd number of 16-byte units
+    static constexpr int plane = 32 * stride;
+    static constexpr int wave_bytes = planes * plane;
+    static constexpr int stages = kTileCols / cols;
+};
+constexpr int kSplitWaves = 8;
+
+template <typename VT, int BITS>
+__global__ __launch_bounds__(kSplitWaves * 64) void k_packed_split(
+    const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ntiles, int ngroups, int n_in, int n_out,
+    long long ldv, int batch, float *__restrict__ out, long long ldo, float scale) {
+    using S = Split<VT>;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int vec0 = blockIdx.y * 32;
+    const int g0 = blockIdx.x * 2, g1 = min(g0 + 1, ngroups - 1);
+    const int t0 = ntiles * w / kSplitWaves, t1 = ntiles * (w + 1) / kSplitWaves;
+    unsigned char *mine = smem + w * S::wave_bytes;
+    constexpr int kLoads = 32 * S::pieces / 64;
+
+    const VT *row[kLoads];
+    int at[kLoads];
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+        const int n = (j * 64 + lane) / S::pieces;
+        row[j] = v + (long long)min(vec0 + n, batch - 1) * ldv;
+        at[j] = n * S::stride;
+    }
+    const int piece_col = 8 * (lane % S::pieces);
+    const uint32_t *c0 = codes + ((long long)g0 * ntiles * 64 + lane) * (2 * BITS);
+    const uint32_t *c1 = codes + ((long long)g1 * ntiles * 64 + lane) * (2 * BITS);
+
+    Piece<VT> p[kLoads];
+    auto request = [&](int col0) {
+        const bool whole = col0 + S::cols <= n_in;
+        if (whole) {
+#pragma unroll
+            for (int j = 0; j < kLoads; ++j) p[j] = load_piece<VT>(row[j], col0 + piece_col, n_in, true);
+        } else {
+#pragma unroll
+            for (int j = 0; j < kLoads; ++j) p[j] = load_piece<VT>(row[j], col0 + piece_col, n_in, false);
+        }
+    };
+    f32x16 acc = {};
+    uint32_t a[2 * BITS], b[2 * BITS];
+    if (t0 < t1) {
+        load_codes<BITS>(c0 + (long long)t0 * 128 * BITS, a);
+        load_codes<BITS>(c1 + (long long)t0 * 128 * BITS, b);
+        request(t0 * kTileCols);
+    }
+    for (int t = t0; t < t1; ++t) {
+        uint32_t an[2 * BITS], bn[2 * BITS];
+        const long long next = (long long)min(t + 1, t1 - 1) * 128 * BITS;
+        load_codes<BITS>(c0 + next, an);
+        load_codes<BITS>(c1 + next, bn);
+        pair_groups(a, b);
+#pragma unroll
+        for (int s = 0; s < S::stages; ++s) {
+#pragma unroll
+            for (int j = 0; j < kLoads; ++j) store_piece(mine + at[j] + piece_col * 2, S::plane, p[j]);
+            const int ahead = t * kTileCols + (s + 1) * S::cols;
+            if (ahead < t1 * kTileCols) request(ahead);
+            // the wave's LDS operations execute in order: no barrier inside a wave
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int k = 0; k < S::cols / 32; ++k) {
+                const int st = s * (S::cols / 32) + k;
+                const bf16x8 w0 = decode<BITS>(a, st), w1 = decode<BITS>(b, st);
+                const unsigned char *x = mine + (lane & 31) * S::stride + (4 * k + 2 * half) * 16;
+#pragma unroll
+                for (int pl = 0; pl < S::planes; ++pl) {
+                    acc = mfma32(lds_operand(x + pl * S::plane), w0, acc);
+                    acc = mfma32(lds_operand(x + pl * S::plane + 16), w1, acc);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+#pragma unroll
+        for (int d = 0; d < 2 * BITS; ++d) { a[d] = an[d]; b[d] = bn[d]; }
+    }
+    __syncthreads();  // the staging areas become the partial results [wave][register][lane]
+    float *red = reinterpret_cast<float *>(smem);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) red[(w * 16 + i) * 64 + lane] = acc[i];
+    __syncthreads();
+    for (int e = tid; e < 1024; e += kSplitWaves * 64) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < kSplitWaves; ++i) sum += red[i * 1024 + e];
+        const int n = vec0 + acc_vector(e >> 6, half);
+        const int r = blockIdx.x * 32 + (e & 31);
+        if (n < batch && r < n_out) out[(long long)n * ldo + r] = scale * sum;
+    }
+}
+
+// ---- tile: 128 rows x 128 vectors, four waves ------------------------------------------------
+// Wave (wr, wn) owns rows 64 wr.. and vectors 64 wn.. of the tile: two weight operands and two
+// vector operands make four MFMAs, so a decoded weight is used twice and an LDS read twice.
+// The vectors are staged in LDS, double buffered, one barrier per stage; the codes come
+// straight from memory, every wave those of its own rows.
+template <typename VT>
+struct Tile {
+    static constexpr int planes = sizeof(VT) == 4 ? 3 : 1;
+    static constexpr int cols = sizeof(VT) == 4 ? 32 : 64;
+    static constexpr int pieces = cols / 8;
+    static constexpr int stride = cols * 2 + 16;
+    static constexpr int plane = 128 * stride;
+    static constexpr int buffer = planes * plane;
+    static constexpr int stages = kTileCols / cols;
+};
+
+template <typename VT, int BITS>
+__global__ __launch_bounds__(256, 2) void k_packed_tile(
+    const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ntiles, int ngroups, int n_in, int n_out,
+    long long ldv, int batch, float *__restrict__ out, long long ldo, float scale, int row_tiles, int vec_tiles) {
+    using S = Tile<VT>;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wr = w & 1, wn = w >> 1;
+    // consecutive workgroups go to the eight XCDs in turn: each XCD gets a contiguous run of
+    // tiles, eight row tiles for every vector tile, so that its L2 sees the same vectors again
+    const int all = row_tiles * vec_tiles, per = (all + 7) / 8;
+    const int lin = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || lin >= all) return;
+    const int band = lin / (8 * vec_tiles), in_band = lin - band * 8 * vec_tiles;
+    const int band_rows = min(8, row_tiles - band * 8);
+    const int rt = band * 8 + in_band % band_rows, vt = in_band / band_rows;
+    const int vec0 = vt * 128;
+    constexpr int kLoads = 128 * S::pieces / 256;
+
+    const VT *row[kLoads];
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j)
+        row[j] = v + (long long)min(vec0 + (j * 256 + tid) / S::pieces, batch - 1) * ldv;
+    const int piece_col = 8 * (tid % S::pieces);
+    unsigned char *put = smem + (tid / S::pieces) * S::stride + piece_col * 2;
+    const uint32_t *code[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        code[g] = codes + ((long long)min(rt * 8 + wr * 4 + g, ngroups - 1) * ntiles * 64 + lane) * (2 * BITS);
+
+    Piece<VT> p[kLoads];
+    auto request = [&](int col0) {
+        if (col0 + S::cols <= n_in) {
+#pragma unroll
+            for (int j = 0; j < kLoads; ++j) p[j] = load_piece<VT>(row[j], col0 + piece_col, n_in, true);
+        } else {
+#pragma unroll
+            for (int j = 0; j < kLoads; ++j) p[j] = load_piece<VT>(row[j], col0 + piece_col, n_in, false);
+        }
+    };
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j)
+            store_piece(put + buf * S::buffer + j * (256 / S::pieces) * S::stride, S::plane, p[j]);
+    };
+    f32x16 acc[2][2] = {};
+    uint32_t c[4][2 * BITS];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) load_codes<BITS>(code[g], c[g]);
+    request(0);
+    stage(0);
+    const int end = ntiles * kTileCols;
+    request(S::cols);
+    __syncthreads();
+    for (int t = 0; t < ntiles; ++t) {
+        uint32_t cn[4][2 * BITS];
+        const long long next = (long long)min(t + 1, ntiles - 1) * 128 * BITS;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) load_codes<BITS>(code[g] + next, cn[g]);
+        pair_groups(c[0], c[1]);
+        pair_groups(c[2], c[3]);
+#pragma unroll
+        for (int s = 0; s < S::stages; ++s) {
+            const unsigned char *buf = smem + (s & 1) * S::buffer + (wn * 64 + (lane & 31)) * S::stride + 32 * half;
+#pragma unroll
+            for (int k = 0; k < S::cols / 32; ++k) {
+                const int st = s * (S::cols / 32) + k;
+#pragma unroll
+                for (int xy = 0; xy < 2; ++xy) {
+                    const bf16x8 w0 = decode<BITS>(c[xy], st), w1 = decode<BITS>(c[2 + xy], st);
+#pragma unroll
+                    for (int pl = 0; pl < S::planes; ++pl) {
+                        const unsigned char *x = buf + pl * S::plane + 64 * k + 16 * xy;
+                        const bf16x8 v0 = lds_operand(x), v1 = lds_operand(x + 32 * S::stride);
+                        acc[0][0] = mfma32(v0, w0, acc[0][0]);
+                        acc[0][1] = mfma32(v1, w0, acc[0][1]);
+                        acc[1][0] = mfma32(v0, w1, acc[1][0]);
+                        acc[1][1] = mfma32(v1, w1, acc[1][1]);
+                    }
+                }
+            }
+            // the next stage goes to the other buffer, which nobody reads any more
+            stage((s + 1) & 1);
+            const int ahead = t * kTileCols + (s + 2) * S::cols;
+            if (ahead < end) request(ahead);
+            __syncthreads();
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int d = 0; d < 2 * BITS; ++d) c[g][d] = cn[g][d];
+    }
+#pragma unroll
+    for (int rg = 0; rg < 2; ++rg) {
+        const int r = rt * 128 + wr * 64 + rg * 32 + (lane & 31);
+#pragma unroll
+        for (int ng = 0; ng < 2; ++ng)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int n = vec0 + wn * 64 + ng * 32 + acc_vector(i, half);
+                if (n < batch && r < n_out) out[(long long)n * ldo + r] = scale * acc[rg][ng][i];
+            }
+    }
+}
+
+struct Args {
+    const uint32_t *codes;
+    const void *v;
+    int ntiles, ngroups, n_in, n_out, batch, device;
+    long long ldv, ldo;
+    float *out;
+    float scale;
+    hipStream_t stream;
+};
+
+template <typename VT, int BITS>
+hipError_t launch_split(const Args &x) {
+    static std::atomic<size_t> enabled[kMaxDevices];
+    auto kern = k_packed_split<VT, BITS>;
+    constexpr size_t lds = (size_t)kSplitWaves * Split<VT>::wave_bytes;
+    static_assert(lds >= (size_t)kSplitWaves * 1024 * 4 && lds <= (size_t)kLdsBytes, "partial results share the staging area");
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, x.device, enabled)) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((x.n_out + 31) / 32), (unsigned)((x.batch + 31) / 32)),
+                       dim3(kSplitWaves * 64), lds, x.stream, x.codes, static_cast<const VT *>(x.v), x.ntiles,
+                       x.ngroups, x.n_in, x.n_out, x.ldv, x.batch, x.out, x.ldo, x.scale);
+    return hipGetLastError();
+}
+
+template <typename VT, int BITS>
+hipError_t launch_tile(const Args &x) {
+    static std::atomic<size_t> enabled[kMaxDevices];
+    auto kern = k_packed_tile<VT, BITS>;
+    constexpr size_t lds = 2 * (size_t)Tile<VT>::buffer;
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, x.device, enabled)) return e;
+    const int row_tiles = (x.n_out + 127) / 128, vec_tiles = (x.batch + 127) / 128;
+    const int per = (row_tiles * vec_tiles + 7) / 8;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(per * 8)), dim3(256), lds, x.stream, x.codes,
+                       static_cast<const VT *>(x.v), x.ntiles, x.ngroups, x.n_in, x.n_out, x.ldv, x.batch, x.out,
+                       x.ldo, x.scale, row_tiles, vec_tiles);
+    return hipGetLastError();
+}
+
+// Tiles of 128 x 128 need about 160 workgroups to be worth their size: 4096 x 4096 x 512 bf16
+// vectors (128 workgroups) 38.8 us against 37.9 with the columns split over waves, 6912 x 2560 x
+// 512 (216) 29 against 48, 14336 x 4096 x 192 (224) 40.5 against 45.2.  Up to 32 vectors one
+// workgroup of the split kernel holds them all, and only matrices that leave most of its waves
+// without a tile of columns are better off with tiles (100000 x 256, 16 vectors: 13.5 against 17.5).
+bool use_tile(const Args &x) {
+#ifdef RSR_TUNING
+    if (const char *s = std::getenv("RSR_TILE")) return std::atoi(s) != 0;
+#endif
+    const long long workgroups = (long long)((x.n_out + 127) / 128) * ((x.batch + 127) / 128);
+    return workgroups >= 160 && (x.batch > 32 || x.ntiles < 4);
+}
+
+template <typename VT>
+hipError_t launch(const Args &x, int bits) {
+    if (use_tile(x)) return bits == 1 ? launch_tile<VT, 1>(x) : launch_tile<VT, 2>(x);
+    return bits == 1 ? launch_split<VT, 1>(x) : launch_split<VT, 2>(x);
+}
+
+}  // namespace
+
+int64_t packed_bytes(int64_t rows, int64_t cols, int bits) {
+    return (rows + kDenseRows - 1) / kDenseRows * ((cols + kTileCols - 1) / kTileCols) * 512 * bits;
+}
+
+hipError_t launch_pack_codes(const int8_t *M, int64_t rows, int64_t cols, int bits, void *packed, int *err_flag) {
+    const int64_t ntiles = (cols + kTileCols - 1) / kTileCols;
+    const int64_t total = (rows + kDenseRows - 1) / kDenseRows * ntiles * 64;
+    const dim3 grid((unsigned)((total + 255) / 256));
+    if (bits == 1)
+        hipLaunchKernelGGL(k_pack_codes<1>, grid, dim3(256), 0, 0, M, rows, cols, ntiles,
+                           static_cast<uint32_t *>(packed), err_flag);
+    else
+        hipLaunchKernelGGL(k_pack_codes<2>, grid, dim3(256), 0, 0, M, rows, cols, ntiles,
+                           static_cast<uint32_t *>(packed), err_flag);
+    return hipGetLastError();
+}
+
+hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, float scale, float *out, int batch,
+                         int64_t ldv, int64_t ldo, hipStream_t stream) {
+    Args x;
+    x.codes = reinterpret_cast<const uint32_t *>(h->packed);
+    x.v = v;
+    x.ntiles = (int)((h->cols + kTileCols - 1) / kTileCols);
+    x.ngroups = (int)((h->rows + kDenseRows - 1) / kDenseRows);
+    x.n_in = (int)h->cols;
+    x.n_out = (int)h->rows;
+    x.batch = batch;
+    x.device = h->device;
+    x.ldv = ldv;
+    x.ldo = ldo;
+    x.out = out;
+    x.scale = scale;
+    x.stream = stream;
+    return v_dtype == RSR_BF16 ? launch<uint16_t>(x, h->code_bits) : launch<float>(x, h->code_bits);
+}
+
+}  // namespace rsr

@@ -453,6 +453,30 @@ __global__ __launch_bounds__(kThreads) void k_fill_u32(uint32_t *__restrict__ p,
     if (i < count) p[i] = value;
 }
 
+// One thread per (block, position): the code of the position is the last one whose boundary is
+// not behind it.  Columns and rows are checked: pi and off may come from a file.
+__global__ __launch_bounds__(kThreads) void k_unsort(const uint16_t *__restrict__ pi,
+                                                     const uint32_t *__restrict__ off, int64_t nb, int64_t rows,
+                                                     int64_t cols, int k, int base, int64_t P, int sign,
+                                                     int8_t *__restrict__ M) {
+    const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (gid >= nb * cols) return;
+    const int64_t b = gid / cols, t = gid - b * cols;
+    const uint32_t *ob = off + b * (P + 1);
+    int64_t lo = 0, hi = P;  // ob[lo] <= t < ob[hi]
+    while (hi - lo > 1) {
+        const int64_t mid = (lo + hi) / 2;
+        if ((int64_t)ob[mid] <= t) lo = mid; else hi = mid;
+    }
+    const int64_t j = pi[gid];
+    if (j >= cols) return;
+    uint32_t c = (uint32_t)lo;
+    for (int r = 0; r < k && b * k + r < rows; ++r, c /= (uint32_t)base) {
+        const uint32_t d = c % (uint32_t)base;
+        if (d) M[(b * k + r) * cols + j] = (int8_t)(d == 1 ? sign : -sign);
+    }
+}
+
 int grid_for_blocks(int64_t nb) { return (int)(nb < 4096 ? nb : 4096); }
 
 // T[j][i] = M[i][j] through 64 x 64 tiles in LDS (coalesced on both sides).
@@ -506,6 +530,14 @@ hipError_t launch_sort(const uint16_t *code, int64_t nb, int64_t cols, int k, in
         hipLaunchKernelGGL(k_sort<9>, dim3(grid_for_blocks(nb)), dim3(kThreads), lds, 0, code, nb,
                            n, passes, P, pi, off);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_unsort(const uint16_t *pi, const uint32_t *off, int64_t rows, int64_t cols, int k, int base,
+                         int64_t P, int sign, int8_t *M) {
+    const int64_t nb = (rows + k - 1) / k;
+    hipLaunchKernelGGL(k_unsort, dim3((unsigned)((nb * cols + kThreads - 1) / kThreads)), dim3(kThreads), 0, 0, pi,
+                       off, nb, rows, cols, k, base, P, sign, M);
     return hipGetLastError();
 }
 

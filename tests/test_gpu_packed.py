@@ -1,0 +1,80 @@
+"""Batches: products of several vectors from the packed codes on the matrix cores, at the edges
+of their tiles.  Integer-valued vectors, so every output is exact (sums of at most 14336 products
+of magnitude 8 stay far below 2^24) and the reference is the oracle's dense definition."""
+import numpy as np
+import pytest
+
+import oracle
+import rsr_inputs as gen
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+rsr = pytest.importorskip("paper_2603_27462_amd")
+DEV = "cuda:0"
+
+
+def _matrix(kind, rows, cols, seed):
+    return gen.binary_matrix(rows, cols, 0.6, seed) if kind == rsr.RSR_BINARY else gen.ternary_matrix(rows, cols, 0.35, seed)
+
+
+def _check(h, M, batch, bf16, pad, seed, distinct=None):
+    """Vectors pad elements apart beyond their length (odd pads: rows of v off every alignment);
+    `distinct`: how many different vectors, repeated in a fixed order, to keep the oracle quick."""
+    rows, cols = M.shape
+    distinct = min(batch, distinct or batch)
+    vi = np.stack([gen.integer_f32(cols, seed=seed + i) for i in range(distinct)])
+    order = np.random.default_rng(seed).permutation(np.arange(batch) % distinct)
+    vbuf = torch.full((batch, cols + pad), float("nan"), dtype=torch.bfloat16 if bf16 else torch.float32, device=DEV)
+    vbuf[:, :cols] = torch.from_numpy(vi).to(DEV).to(vbuf.dtype)[torch.from_numpy(order).to(DEV)]
+    out = torch.full((batch, rows + 3), -5.0, dtype=torch.float32, device=DEV)
+    rsr.rsr_matvec_ex(h, vbuf[:, :cols], scale=-2.0, out=out[:, :rows])
+    got = out.cpu().numpy()
+    assert np.all(got[:, rows:] == -5.0)                     # nothing past the rows
+    want = np.stack([oracle.dense_matvec(M, x.astype(np.float64), -2.0) for x in vi])
+    assert np.array_equal(got[:, :rows].astype(np.float64), want[order])
+
+
+# one workgroup holds 32 rows x 32 vectors, eight waves share the columns in tiles of 256
+@pytest.mark.parametrize("kind,rows,cols,k,batch,bf16,pad", [
+    (rsr.RSR_BINARY, 1, 1, 1, 4, True, 0),
+    (rsr.RSR_TERNARY_FUSED, 31, 7, 2, 5, False, 1),
+    (rsr.RSR_TERNARY_2PASS, 33, 255, 4, 31, True, 3),
+    (rsr.RSR_BINARY, 32, 257, 8, 32, False, 1),
+    (rsr.RSR_TERNARY_FUSED, 65, 2049, 5, 33, True, 1),
+    (rsr.RSR_DENSE_TERNARY_P2, 48, 1791, 0, 63, False, 0),
+    (rsr.RSR_BINARY, 50, 2305, 6, 64, True, 0),
+    (rsr.RSR_TERNARY_FUSED, 40, 14336, 8, 17, True, 0),
+    (rsr.RSR_TERNARY_2PASS, 20, 32766, 6, 9, False, 2)])
+def test_columns_split_over_waves(kind, rows, cols, k, batch, bf16, pad):
+    M = _matrix(kind, rows, cols, 300 + rows + cols)
+    _check(rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), k, kind), M, batch, bf16, pad, rows)
+
+
+# one workgroup holds 128 rows x 128 vectors
+@pytest.mark.parametrize("kind,rows,cols,k,batch,bf16,pad", [
+    (rsr.RSR_TERNARY_FUSED, 128 * 24, 256, 4, 128 * 8, True, 0),
+    (rsr.RSR_BINARY, 128 * 24 + 1, 255, 8, 128 * 8 + 1, False, 1),
+    (rsr.RSR_DENSE_TERNARY_P2, 128 * 33 - 17, 777, 0, 128 * 7 - 1, True, 1),
+    (rsr.RSR_TERNARY_2PASS, 128 * 100 - 1, 33, 6, 129, False, 0),
+    (rsr.RSR_BINARY, 128 * 193, 40, 8, 65, True, 5)])
+def test_tiles_of_rows_and_vectors(kind, rows, cols, k, batch, bf16, pad):
+    M = _matrix(kind, rows, cols, 500 + cols)
+    _check(rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), k, kind), M, batch, bf16, pad, cols, distinct=40)
+
+
+@pytest.mark.parametrize("kind,rows,cols,k", [(rsr.RSR_BINARY, 77, 300, 6), (rsr.RSR_BINARY, 90, 200, 8),
+                                              (rsr.RSR_TERNARY_2PASS, 45, 513, 7),
+                                              (rsr.RSR_TERNARY_FUSED, 203, 1500, 8)])
+def test_codes_after_loading_and_after_a_new_matrix(kind, rows, cols, k):
+    """The packed codes of a handle made from bytes, and of a handle whose matrix was replaced."""
+    M = _matrix(kind, rows, cols, 8)
+    h = rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), k, kind)
+    _check(rsr.rsr_deserialize(rsr.rsr_serialize(h)), M, 6, True, 1, 4)
+    M2 = M[::-1].copy()          # rows in another order: the streams keep their lengths' bounds
+    try:
+        rsr.rsr_preprocess_into(h, torch.from_numpy(M2).to(DEV))
+    except rsr.RsrError as e:
+        assert e.code == 3       # other blocks may not fit the layout of the first matrix
+        return
+    _check(h, M2, 6, False, 0, 5)
