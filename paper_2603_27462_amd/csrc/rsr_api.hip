@@ -25,7 +25,9 @@ bool is_rsr_kind(int kind) {
 // every kind and size measured (8B layers, 4 vectors: 10 us a launch against 22 for the stream of
 // the block patterns, which costs the same for every vector; three vectors on 1001 x 2999: 14 us
 // against 9).
-bool use_packed(const rsr_handle_s *h, int batch) { return h->packed && batch >= 4; }
+bool use_packed(const rsr_handle_s *h, int batch) {
+    return h->kind == RSR_DENSE_TERNARY_P2 || (h->packed && batch >= 2);
+}
 
 template <typename T>
 hipError_t dev_alloc(T **p, size_t count) {
@@ -464,7 +466,7 @@ int rsr_matvec_stacked(rsr_handle_t h, const void *v, int v_dtype, const float *
         lt.first[i] = (int)h->layer_first[i <= h->nlayers ? i : h->nlayers];
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const hipError_t e = (h->kind == RSR_DENSE_TERNARY_P2)
-                             ? rsr::launch_dense_matvec(h, v, v_dtype, 1.0f, nullptr, 1, h->cols, h->rows, s, &lt)
+                             ? rsr::launch_packed(h, v, v_dtype, 1.0f, nullptr, 1, h->cols, h->rows, s, &lt)
                              : rsr::launch_rsr_matvec(h, v, v_dtype, 1.0f, nullptr, 1, h->cols, h->rows, s, &lt);
     if (e != hipSuccess) return fail(hip_code(e));
     return RSR_OK;
@@ -793,9 +795,6 @@ int rsr_matvec_ex(rsr_handle_t h, const void *v, int v_dtype, float scale, void 
     // several vectors: a contraction, on the matrix cores, whatever the kind
     hipError_t e = use_packed(h, batch)
                        ? rsr::launch_packed(h, v, v_dtype, scale, static_cast<float *>(out), batch, ldv, ldo, s)
-                   : (h->kind == RSR_DENSE_TERNARY_P2)
-                       ? rsr::launch_dense_matvec(h, v, v_dtype, scale, static_cast<float *>(out),
-                                                  batch, ldv, ldo, s)
                    : h->narrow
                        ? rsr::launch_narrow_matvec(h, v, v_dtype, scale, static_cast<float *>(out), batch, ldv,
                                                    ldo, s)
@@ -918,7 +917,7 @@ int64_t rsr_algorithmic_bytes(rsr_handle_t h, int v_dtype, int batch) {
     }
     const int64_t vb = (v_dtype == RSR_BF16) ? 2 : 4;
     int64_t weight_side;
-    if (h->kind == RSR_DENSE_TERNARY_P2 || use_packed(h, batch)) {
+    if (use_packed(h, batch)) {
         weight_side = rsr::packed_bytes(h->rows, h->cols, h->code_bits);
     } else {
         weight_side = 0;
@@ -938,10 +937,12 @@ const char *rsr_kernel_name(rsr_handle_t h, int v_dtype) {
         fail(RSR_EINVAL);
         return nullptr;
     }
-    if (h->kind == RSR_DENSE_TERNARY_P2) return rsr::dense_matvec_kernel_name(h, v_dtype);
     if (h->narrow) return v_dtype == RSR_BF16 ? "k_rsr_narrow<unsigned short>" : "k_rsr_narrow<float>";
     static thread_local char name[96];
-    rsr::rsr_matvec_kernel_name(h, v_dtype, name, sizeof(name));
+    if (h->kind == RSR_DENSE_TERNARY_P2)
+        rsr::packed_matvec_kernel_name(h, v_dtype, name, sizeof(name));
+    else
+        rsr::rsr_matvec_kernel_name(h, v_dtype, name, sizeof(name));
     return name;
 }
 

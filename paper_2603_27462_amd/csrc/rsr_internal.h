@@ -16,8 +16,8 @@ constexpr int kGroupSlabs = 4;         // slabs a wave requests together
 constexpr int kMaxCols = 32766;        // index 'cols' is the zero slot and must fit 15 bits
 constexpr int kSmallCols = 16383;      // up to here an entry is tail<<15 | idx<<1
 constexpr int kLdsBytes = 160 * 1024;  // LDS per workgroup on gfx950
-constexpr int kDenseRows = 16;         // dense comparison kernel: rows per workgroup
-constexpr int kDenseTileCols = 256;    // and columns per 16-byte-per-lane tile
+constexpr int kDenseRows = 16;         // packed codes: rows of a group
+constexpr int kDenseTileCols = 256;    // and columns of a tile
 
 constexpr int kMaxLayers = 8;          // sibling layers one stacked handle can hold
 
@@ -149,15 +149,13 @@ hipError_t launch_pack_codes(const int8_t *M, int64_t rows, int64_t cols, int bi
 hipError_t launch_rsr_matvec(const rsr_handle_s *h, const void *v, int v_dtype, float scale,
                              float *out, int batch, int64_t ldv, int64_t ldo, hipStream_t stream,
                              const LayerTable *layers = nullptr);
-hipError_t launch_dense_matvec(const rsr_handle_s *h, const void *v, int v_dtype, float scale,
-                               float *out, int batch, int64_t ldv, int64_t ldo, hipStream_t stream,
-                               const LayerTable *layers = nullptr);
-// Product of several vectors on the matrix cores, from the packed codes of any kind.
+// Product on the matrix cores, from the packed codes of any kind.
 hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, float scale, float *out,
-                         int batch, int64_t ldv, int64_t ldo, hipStream_t stream);
+                         int batch, int64_t ldv, int64_t ldo, hipStream_t stream,
+                         const LayerTable *layers = nullptr);
 // Writes the name of the multiply kernel h launches for (v_dtype, batch) into buf.
 void rsr_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, char *buf, size_t len);
-const char *dense_matvec_kernel_name(const rsr_handle_s *h, int v_dtype);
+void packed_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, char *buf, size_t len);
 
 // --- narrow matrices (cols <= kNarrowCols) ---------------------------------------------
 constexpr int kNarrowCols = 256;

@@ -2,16 +2,19 @@
 //
 // A batch of vectors turns the product into a contraction, so it runs on the matrix cores
 // straight from the matrix entries, packed to 2 bits (ternary) or 1 bit (binary), whatever
-// the kind of the handle; the redundancy a block of rows has is worth less there than the 32
-// vectors that share one decoded weight.  Two kernels, both around v_mfma_f32_32x32x16_bf16
-// (measured 15.1 ns per instruction and SIMD against 12.7 for v_mfma_f32_16x16x32_bf16, which
-// does half the work):
+// the kind of the handle; the redundancy a block of rows has is worth less there than the
+// vectors that share one decoded weight.  The dense kind, the comparison point without any
+// preprocessing beyond packing (the role the paper gives its low-bit multiplier baseline in
+// Benchmarking Results), multiplies a single vector this way too.  Three kernels:
+//   few    16 rows x up to 4 vectors per wave, for 1 to 4 vectors
 //   split  32 rows x 32 vectors per workgroup, the columns dealt to its eight waves; bound by the
 //          latency of its loads (4096 x 14336, 16 bf16 vectors: 14.4 us; as 16 products of one
 //          vector 78 us)
 //   tile   128 rows x 128 vectors per workgroup, a 64 x 64 quarter per wave; bound by the matrix
 //          cores (4096 x 14336, 2048 bf16 vectors: 211 us = 1.14 PFLOP/s, 8.2 ms as single
 //          products; a library product of 8192^3 reaches 1.21 PFLOP/s on the same card)
+// The last two use v_mfma_f32_32x32x16_bf16 (measured 15.1 ns per instruction and SIMD against
+// 12.7 for v_mfma_f32_16x16x32_bf16, which does half the work), the first the smaller one.
 //
 // Layout: [row group of 16][tile of 256 columns][lane][2 * BITS dwords], one load of 16
 // (8) bytes per lane and tile.  Lane l holds row l%16 and the column slices 8*(l/16).. of the
@@ -29,6 +32,7 @@
 // significant bits) that take one MFMA each, so integer-valued inputs stay exact and nothing
 // is lost against float32 inputs.  Accumulation is float32 throughout and the order of the
 // sums is fixed.
+#include <cstdio>
 #ifdef RSR_TUNING
 #include <cstdlib>
 #endif
@@ -40,6 +44,7 @@ namespace rsr {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -172,20 +177,27 @@ struct Piece {
     u32x4 q[sizeof(VT) / 2];
 };
 
+// The piece of `row` at column `col`, which lies wholly before or wholly behind `end`.
 template <typename VT>
-__device__ __forceinline__ Piece<VT> load_piece(const VT *__restrict__ row, int col, int n_in, bool whole) {
-    Piece<VT> p;
-    if (whole || col + 8 <= n_in) {
+__device__ __forceinline__ Piece<VT> load_piece(const VT *__restrict__ row, int col, int end) {
+    Piece<VT> p = {};
+    if (col + 8 <= end) {
 #pragma unroll
         for (int i = 0; i < (int)sizeof(VT) / 2; ++i)
             p.q[i] = *reinterpret_cast<const u32x4_any *>(reinterpret_cast<const unsigned char *>(row + col) + 16 * i);
-        return p;
     }
+    return p;
+}
+
+// Element by element what load_piece leaves out: a piece that straddles `end`.
+template <typename VT>
+__device__ __forceinline__ void finish_piece(Piece<VT> &p, const VT *__restrict__ row, int col, int end) {
+    if (col >= end || col + 8 <= end) return;
     uint32_t e[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         e[i] = 0;
-        if (col + i < n_in)
+        if (col + i < end)
             e[i] = sizeof(VT) == 4 ? reinterpret_cast<const uint32_t *>(row)[col + i]
                                    : reinterpret_cast<const uint16_t *>(row)[col + i];
     }
@@ -195,7 +207,24 @@ __device__ __forceinline__ Piece<VT> load_piece(const VT *__restrict__ row, int 
     } else {
         p.q[0] = u32x4{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
     }
-    return p;
+}
+
+// One staging step's pieces, row[j] at column col0 + piece_col.  (The branch on a whole step
+// costs nothing where a mask per load made large batches 3 % slower.)
+template <typename VT, int N>
+__device__ __forceinline__ void load_pieces(Piece<VT> (&p)[N], const VT *const (&row)[N], int col0, int cols,
+                                            int piece_col, int end) {
+    if (col0 + cols <= end) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) p[j] = load_piece<VT>(row[j], piece_col + col0, 0x7fffffff);
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) p[j] = load_piece<VT>(row[j], col0 + piece_col, end);
+    if (end & 7) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) finish_piece<VT>(p[j], row[j], col0 + piece_col, end);
+    }
 }
 
 // low halves of (a, b): a in the low half of the result; and the high halves
@@ -240,6 +269,125 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 v, bf16x8 w, f32x16 acc) {
 // Vector (row of the MFMA result) of accumulator register i in lane half h.
 __device__ __forceinline__ int acc_vector(int i, int h) { return 8 * (i >> 2) + 4 * h + (i & 3); }
 
+// ---- few: up to four vectors -----------------------------------------------------------------
+// A wave takes 16 rows and a share of the columns; `wk` waves of a workgroup share the columns of
+// a row group and add their partial results at the end, the only place where waves wait for each
+// other.  Every wave stages its own columns of v in LDS of its own, so a wave starts on its codes
+// as soon as they and its part of v are there.  The vectors are the rows of the MFMA: vector q
+// sits in rows 4q.. (float32: its three planes in rows 4q, 4q+1, 4q+2), so that lane 16 q + r of
+// the result holds everything about (vector q, row r), and one MFMA serves all planes.
+constexpr int few_waves(int wk) { return wk < 4 ? 4 : wk; }
+
+template <typename VT, int NV>
+struct Few {
+    static constexpr int planes = sizeof(VT) == 4 ? 3 : 1;
+    static constexpr int tiles = NV == 1 ? 4 : sizeof(VT) == 4 ? 1 : 2;  // staged at a time
+    static constexpr int cols = tiles * kTileCols;
+    static constexpr int pieces = cols / 8;
+    static constexpr int loads = NV * pieces / 64;
+    static constexpr int stride = cols * 2 + 16;  // bytes between slots: an odd number of 16-byte units
+    static constexpr int wave_bytes = NV * planes * stride;
+};
+
+template <typename VT, int BITS, int NV, int WK>
+__global__ __launch_bounds__(few_waves(WK) * 64) void k_packed_few(
+    const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ntiles, int ngroups, int n_in, int n_out,
+    long long ldv, int nv, float scale, float *__restrict__ out, long long ldo, const LayerTable layers) {
+    using S = Few<VT, NV>;
+    constexpr int WR = few_waves(WK) / WK;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wr = w / WK, wk = w % WK;
+    const int g = min((int)blockIdx.x * WR + wr, ngroups - 1);
+    const int t0 = ntiles * wk / WK, t1 = ntiles * (wk + 1) / WK;
+    const int end = min(n_in, t1 * kTileCols);
+    const uint32_t *c0 = codes + ((long long)g * ntiles * 64 + lane) * (2 * BITS);
+    unsigned char *mine = smem + w * S::wave_bytes;
+
+    Piece<VT> p[S::loads];
+    auto request_v = [&](int t) {
+        const int col0 = t * kTileCols;
+#pragma unroll
+        for (int j = 0; j < S::loads; ++j) {
+            const int i = j * 64 + lane, n = NV == 1 ? 0 : min(i / S::pieces, nv - 1);
+            p[j] = load_piece<VT>(v + n * ldv, col0 + 8 * (i % S::pieces), end);
+        }
+        if ((end & 7) && end <= col0 + S::cols) {
+#pragma unroll
+            for (int j = 0; j < S::loads; ++j) {
+                const int i = j * 64 + lane, n = NV == 1 ? 0 : min(i / S::pieces, nv - 1);
+                finish_piece<VT>(p[j], v + n * ldv, col0 + 8 * (i % S::pieces), end);
+            }
+        }
+    };
+    uint32_t c[S::tiles][2 * BITS];
+    auto request_codes = [&](int t) {
+#pragma unroll
+        for (int i = 0; i < S::tiles; ++i)
+            if (t + i < t1) load_codes<BITS>(c0 + (long long)(t + i) * 128 * BITS, c[i]);
+    };
+    // the MFMA row of this lane: vector m/4, float32 plane m%4
+    const int m = lane & 15;
+    const int slot = (NV == 1 ? 0 : m >> 2) * S::planes + (S::planes == 3 ? min(m & 3, 2) : 0);
+    const unsigned char *operand = mine + slot * S::stride + (lane >> 4) * 16;
+    f32x4 acc0 = {}, acc1 = {};
+    if (t0 < t1) {
+        request_v(t0);
+        request_codes(t0);
+    }
+    for (int t = t0; t < t1; t += S::tiles) {
+#pragma unroll
+        for (int j = 0; j < S::loads; ++j) {
+            const int i = j * 64 + lane;
+            store_piece(mine + (i / S::pieces) * S::planes * S::stride + 16 * (i % S::pieces), S::stride, p[j]);
+        }
+        if (t + S::tiles < t1) request_v(t + S::tiles);
+        // the wave's LDS operations execute in order: no barrier inside a wave
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < S::tiles; ++i) {
+            if (t + i >= t1) break;
+#pragma unroll
+            for (int st = 0; st < kTileSteps; st += 2) {
+                acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_operand(operand + i * 512 + st * 64),
+                                                               decode<BITS>(c[i], st), acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_operand(operand + i * 512 + st * 64 + 64),
+                                                               decode<BITS>(c[i], st + 1), acc1, 0, 0, 0);
+            }
+        }
+        if (t + S::tiles < t1) request_codes(t + S::tiles);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    float sum = acc0.x + acc1.x;
+    if (S::planes == 3) sum += (acc0.y + acc1.y) + (acc0.z + acc1.z);
+    int group = (int)blockIdx.x * WR + wr;
+    if (WK > 1) {
+        float *red = reinterpret_cast<float *>(smem + few_waves(WK) * S::wave_bytes);
+        red[w * 64 + lane] = sum;
+        __syncthreads();
+        if (tid >= WR * 64) return;
+        sum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < WK; ++i) sum += red[(w * WK + i) * 64 + lane];
+        group = (int)blockIdx.x * WR + w;
+    }
+    const int q = lane >> 4;
+    const long long row = (long long)group * kDenseRows + m;
+    if (layers.n == 0) {
+        if (q < nv && row < n_out) out[q * ldo + row] = scale * sum;
+    } else if (q == 0 && group < ngroups) {
+        // stacked handle: the group belongs to one layer (layers start on group boundaries)
+        int s = 0;
+#pragma unroll
+        for (int i = 1; i < kMaxLayers; ++i)
+            if (i < layers.n && group >= layers.first[i]) s = i;
+        const int local = (group - layers.first[s]) * kDenseRows + m;
+        if (local < layers.rows[s]) layers.out[s][local] = layers.scale[s] * sum;
+    }
+}
+
 // ---- split: 32 rows x 32 vectors, the columns dealt to eight waves ---------------------------
 // For batches too small to fill the chip with tiles of 128 x 128.  Every wave works through
 // its own share of the tiles and stages its own columns of the 32 vectors in LDS of its own:
@@ -283,16 +431,7 @@ __global__ __launch_bounds__(kSplitWaves * 64) void k_packed_split(
     const uint32_t *c1 = codes + ((long long)g1 * ntiles * 64 + lane) * (2 * BITS);
 
     Piece<VT> p[kLoads];
-    auto request = [&](int col0) {
-        const bool whole = col0 + S::cols <= n_in;
-        if (whole) {
-#pragma unroll
-            for (int j = 0; j < kLoads; ++j) p[j] = load_piece<VT>(row[j], col0 + piece_col, n_in, true);
-        } else {
-#pragma unroll
-            for (int j = 0; j < kLoads; ++j) p[j] = load_piece<VT>(row[j], col0 + piece_col, n_in, false);
-        }
-    };
+    auto request = [&](int col0) { load_pieces<VT>(p, row, col0, S::cols, piece_col, n_in); };
     f32x16 acc = {};
     uint32_t a[2 * BITS], b[2 * BITS];
     if (t0 < t1) {
@@ -394,15 +533,7 @@ __global__ __launch_bounds__(256, 2) void k_packed_tile(
         code[g] = codes + ((long long)min(rt * 8 + wr * 4 + g, ngroups - 1) * ntiles * 64 + lane) * (2 * BITS);
 
     Piece<VT> p[kLoads];
-    auto request = [&](int col0) {
-        if (col0 + S::cols <= n_in) {
-#pragma unroll
-            for (int j = 0; j < kLoads; ++j) p[j] = load_piece<VT>(row[j], col0 + piece_col, n_in, true);
-        } else {
-#pragma unroll
-            for (int j = 0; j < kLoads; ++j) p[j] = load_piece<VT>(row[j], col0 + piece_col, n_in, false);
-        }
-    };
+    auto request = [&](int col0) { load_pieces<VT>(p, row, col0, S::cols, piece_col, n_in); };
     auto stage = [&](int buf) {
 #pragma unroll
         for (int j = 0; j < kLoads; ++j)
@@ -476,7 +607,44 @@ struct Args {
     float *out;
     float scale;
     hipStream_t stream;
+    LayerTable layers;
 };
+
+template <typename VT, int BITS, int NV, int WK>
+hipError_t launch_few_wk(const Args &x) {
+    static std::atomic<size_t> enabled[kMaxDevices];
+    auto kern = k_packed_few<VT, BITS, NV, WK>;
+    constexpr size_t lds = (size_t)few_waves(WK) * (Few<VT, NV>::wave_bytes + 64 * 4);
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, x.device, enabled)) return e;
+    constexpr int WR = few_waves(WK) / WK;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((x.ngroups + WR - 1) / WR)), dim3(few_waves(WK) * 64), lds, x.stream,
+                       x.codes, static_cast<const VT *>(x.v), x.ntiles, x.ngroups, x.n_in, x.n_out, x.ldv, x.batch,
+                       x.scale, x.out, x.ldo, x.layers);
+    return hipGetLastError();
+}
+
+// Waves that share the columns of a row group: one per tile of columns up to eight, so that all
+// loads of a product leave at once; from 24 tiles on sixteen waves, whose loads, decoding and MFMAs
+// overlap better.  Measured with 4 / 8 / 16 waves, one bf16 vector: 4096 x 14336 (56 tiles) 7.9 /
+// 5.9 / 5.4 us, 2560 x 6912 (27) 4.6 / 3.7 / 3.6, 4096 x 4096 (16) 3.3 / 3.0 / 3.2, 14336 x 4096
+// 5.3 / 4.9 / 6.1; 100000 x 256 (one tile) 3.3 with one wave, 4.3 with two.
+int few_wk(int ntiles) {
+#ifdef RSR_TUNING
+    if (const char *s = std::getenv("RSR_WK")) return std::atoi(s);
+#endif
+    return ntiles >= 24 ? 16 : ntiles >= 8 ? 8 : ntiles >= 4 ? 4 : ntiles >= 2 ? 2 : 1;
+}
+
+template <typename VT, int BITS, int NV>
+hipError_t launch_few(const Args &x) {
+    switch (few_wk(x.ntiles)) {
+        case 16: return launch_few_wk<VT, BITS, NV, 16>(x);
+        case 8: return launch_few_wk<VT, BITS, NV, 8>(x);
+        case 4: return launch_few_wk<VT, BITS, NV, 4>(x);
+        case 2: return launch_few_wk<VT, BITS, NV, 2>(x);
+        default: return launch_few_wk<VT, BITS, NV, 1>(x);
+    }
+}
 
 template <typename VT, int BITS>
 hipError_t launch_split(const Args &x) {
@@ -518,10 +686,11 @@ bool use_tile(const Args &x) {
     return workgroups >= 160 && (x.batch > 32 || x.ntiles < 4);
 }
 
-template <typename VT>
-hipError_t launch(const Args &x, int bits) {
-    if (use_tile(x)) return bits == 1 ? launch_tile<VT, 1>(x) : launch_tile<VT, 2>(x);
-    return bits == 1 ? launch_split<VT, 1>(x) : launch_split<VT, 2>(x);
+template <typename VT, int BITS>
+hipError_t launch(const Args &x) {
+    if (x.batch == 1) return launch_few<VT, BITS, 1>(x);
+    if (x.batch <= 4) return launch_few<VT, BITS, 4>(x);
+    return use_tile(x) ? launch_tile<VT, BITS>(x) : launch_split<VT, BITS>(x);
 }
 
 }  // namespace
@@ -544,7 +713,7 @@ hipError_t launch_pack_codes(const int8_t *M, int64_t rows, int64_t cols, int bi
 }
 
 hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, float scale, float *out, int batch,
-                         int64_t ldv, int64_t ldo, hipStream_t stream) {
+                         int64_t ldv, int64_t ldo, hipStream_t stream, const LayerTable *layers) {
     Args x;
     x.codes = reinterpret_cast<const uint32_t *>(h->packed);
     x.v = v;
@@ -559,7 +728,18 @@ hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, floa
     x.out = out;
     x.scale = scale;
     x.stream = stream;
-    return v_dtype == RSR_BF16 ? launch<uint16_t>(x, h->code_bits) : launch<float>(x, h->code_bits);
+    if (layers)
+        x.layers = *layers;
+    else
+        x.layers.n = 0;
+    if (h->code_bits == 1) return v_dtype == RSR_BF16 ? launch<uint16_t, 1>(x) : launch<float, 1>(x);
+    return v_dtype == RSR_BF16 ? launch<uint16_t, 2>(x) : launch<float, 2>(x);
+}
+
+void packed_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, char *buf, size_t len) {
+    // the instantiation a single vector launches, as a profiler prints it
+    std::snprintf(buf, len, "k_packed_few<%s, %d, 1, %d>", v_dtype == RSR_BF16 ? "unsigned short" : "float",
+                  h->code_bits, few_wk((int)((h->cols + kTileCols - 1) / kTileCols)));
 }
 
 }  // namespace rsr

@@ -78,3 +78,15 @@ def test_codes_after_loading_and_after_a_new_matrix(kind, rows, cols, k):
         assert e.code == 3       # other blocks may not fit the layout of the first matrix
         return
     _check(h, M2, 6, False, 0, 5)
+
+
+# up to four vectors: 1, 2, 4, 8 or 16 waves share the columns of 16 rows (1, 2, 4, 8 or 24 tiles of
+# 256 columns and more), steps of one, two or four tiles
+@pytest.mark.parametrize("cols", [1, 256, 257, 768, 1025, 2047, 2305, 5888, 6145, 14336, 32766])
+@pytest.mark.parametrize("kind,rows,batch,bf16,pad", [
+    (rsr.RSR_DENSE_TERNARY_P2, 17, 1, True, 0), (rsr.RSR_DENSE_TERNARY_P2, 65, 1, False, 0),
+    (rsr.RSR_BINARY, 15, 2, True, 1), (rsr.RSR_TERNARY_FUSED, 33, 3, False, 1),
+    (rsr.RSR_TERNARY_2PASS, 16, 4, True, 0), (rsr.RSR_BINARY, 40, 4, False, 3)])
+def test_few_vectors(kind, rows, batch, bf16, pad, cols):
+    M = _matrix(kind, rows, cols, 700 + rows + cols)
+    _check(rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), 5, kind), M, batch, bf16, pad, rows)
