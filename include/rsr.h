@@ -64,7 +64,9 @@ enum {
  *         the best k moves with the device and the matrix shape): it preprocesses with
  *         k = 4, 6, 8, 10, 12 (4..8 for RSR_TERNARY_FUSED), times the multiply kernel of
  *         each on this device with both vector types and keeps the fastest;
- *         rsr_block_height() tells the choice.  RSR_BINARY / RSR_TERNARY_2PASS: 1..15;
+ *         rsr_block_height() tells the choice.  A handle made with k = 0 multiplies single
+ *         vectors from its packed codes where that was timed faster than the best block
+ *         height; with a k given it always takes the block patterns.  RSR_BINARY / RSR_TERNARY_2PASS: 1..15;
  *         RSR_TERNARY_FUSED: 1..10.  The vector, one float per pattern (P = 2^k or 3^k;
  *         or, when P is much larger than cols, one float per non-empty pattern of a
  *         block) and about 10 KiB must fit the 160 KiB of LDS, else RSR_EUNSUPPORTED.
@@ -77,7 +79,8 @@ enum {
  * compact stream the multiply kernel reads: 16-bit column entries with one tail flag per
  * group (8-bit entries, tail bits and one sign word per existing group when cols <= 256);
  * the per-group prefix array of the kernel is indexed by pattern code, or by the rank of the
- * group among the existing ones when P is much larger than cols.
+ * group among the existing ones when P is much larger than cols.  It also keeps the entries
+ * packed to 2 bits (1 bit for RSR_BINARY), from which batches are multiplied.
  *
  * Runs on the current HIP device, on the null stream, and synchronises
  * before returning.  Returns NULL on failure (see rsr_last_error()).
@@ -111,10 +114,10 @@ int rsr_matvec(rsr_handle_t h, const void *v, void *out, void *stream);
  *   batch   number of vectors (>= 1); vector i starts at v + i*ldv elements,
  *           its result at out + i*ldo elements (ldv >= cols, ldo >= rows)
  *
- * A batch is one launch.  The dense kind multiplies up to 16 vectors per pass over the
- * weights.  The RSR kinds give every vector its own workgroups (the weight side is then
- * read from HBM once and from the caches by the other vectors).  The result of a vector
- * does not depend on the batch it is part of (bit for bit).
+ * A batch is one launch.  Several vectors are a contraction: whatever the kind, they are
+ * multiplied on the matrix cores from the packed codes, in an order of the sums that depends
+ * on the number of vectors.  The result of a vector may therefore differ in its last bits
+ * between batches of different sizes; the same call gives the same bits every time.
  */
 int rsr_matvec_ex(rsr_handle_t h, const void *v, int v_dtype, float scale, void *out,
                   int batch, int64_t ldv, int64_t ldo, void *stream);
@@ -165,7 +168,9 @@ int rsr_num_layers(rsr_handle_t h);       /* layers of a stacked handle; 0 other
  *                        every limit rsr_preprocess enforces and against the sizes it implies
  *                        (RSR_EINVAL otherwise); the stream contents are taken as they are, so
  *                        a damaged stream yields wrong products, never an out-of-range access
- *                        to device memory (stream entries only ever address LDS).
+ *                        to device memory (stream entries only ever address LDS).  The packed
+ *                        codes are not stored: they are rebuilt from the permutation and the
+ *                        boundaries, with every column and row checked.
  */
 int64_t rsr_serialized_size(rsr_handle_t h);
 int rsr_serialize(rsr_handle_t h, void *host_buf, int64_t capacity);
@@ -243,8 +248,8 @@ int64_t rsr_algorithmic_bytes(rsr_handle_t h, int v_dtype, int batch);
 /*
  * Measurement aids (the benchmark's reference legs; no part of the method).
  *
- *   rsr_launch_shape  launch geometry of the multiply kernel of an RSR handle for a vector
- *                     type: workgroups per vector, threads per workgroup, LDS bytes per
+ *   rsr_launch_shape  launch geometry of the kernel that multiplies one vector with an RSR
+ *                     handle, for a vector type: workgroups, threads per workgroup, LDS bytes per
  *                     workgroup (any of the three pointers may be NULL)
  *   rsr_probe_empty   launches a kernel that does nothing with the given geometry: what a
  *                     launch costs in a sequence before it moves a byte
@@ -261,8 +266,7 @@ int rsr_probe_read(const void *src, int64_t bytes, int workgroups, int threads, 
 
 /*
  * Name of the multiply kernel this handle launches for a vector type (the
- * symbol a profiler reports; the same for every batch size), or NULL on a bad
- * argument.  Static storage (per thread; the next call overwrites it).
+ * symbol a profiler reports for one vector), or NULL on a bad argument.  Static storage (per thread; the next call overwrites it).
  */
 const char *rsr_kernel_name(rsr_handle_t h, int v_dtype);
 

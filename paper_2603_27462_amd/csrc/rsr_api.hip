@@ -1,6 +1,7 @@
 // C ABI of librsr: argument checks, device-memory ownership, and the order of
 // the preprocessing launches.  All arithmetic of the method is in the kernels
 // (rsr_preprocess.hip, rsr_matvec.hip, rsr_dense.hip).
+#include <cstddef>
 #include <cstring>
 #include <new>
 #include <vector>
@@ -26,7 +27,7 @@ bool is_rsr_kind(int kind) {
 // the block patterns, which costs the same for every vector; three vectors on 1001 x 2999: 14 us
 // against 9).
 bool use_packed(const rsr_handle_s *h, int batch) {
-    return h->kind == RSR_DENSE_TERNARY_P2 || (h->packed && batch >= 2);
+    return h->kind == RSR_DENSE_TERNARY_P2 || (h->packed && (batch >= 2 || h->single_packed));
 }
 
 template <typename T>
@@ -170,7 +171,8 @@ int preprocess_dense(rsr_handle_s *h, const int8_t *M) {
     Temps t;
     const int64_t ntiles = (h->cols + rsr::kDenseTileCols - 1) / rsr::kDenseTileCols;
     h->row_bytes = ntiles * (rsr::kDenseTileCols / 4);
-    RSR_TRY(dev_alloc(&h->packed, (size_t)rsr::packed_bytes(h->rows, h->cols, h->code_bits)));
+    h->code_groups = rsr::row_groups(h->rows);
+    RSR_TRY(dev_alloc(&h->packed, (size_t)rsr::packed_bytes(h->code_groups, h->cols, h->code_bits)));
     RSR_TRY(dev_alloc(&t.flags, kFlagWords));
     rc = run_dense(h, M, t);
 done:
@@ -178,9 +180,9 @@ done:
     return rc;
 }
 
-// Stacked handles multiply one vector at a time through the general kernel: no packed codes and
-// no narrow layout.
-int preprocess_rsr(rsr_handle_s *h, const int8_t *M, bool stacked) {
+// codes: make the packed codes too.  Stacked handles have several output vectors, which the narrow
+// kernel does not know: they take the general layout.
+int preprocess_rsr(rsr_handle_s *h, const int8_t *M, bool stacked, bool codes) {
     int rc = RSR_OK;
     Temps t;
     const int64_t nb = h->nb, cols = h->cols, P = h->P;
@@ -188,7 +190,10 @@ int preprocess_rsr(rsr_handle_s *h, const int8_t *M, bool stacked) {
 
     RSR_TRY(dev_alloc(&t.code, (size_t)(nb * cols)));
     RSR_TRY(dev_alloc(&t.flags, kFlagWords));
-    if (!stacked) RSR_TRY(dev_alloc(&h->packed, (size_t)rsr::packed_bytes(h->rows, cols, h->code_bits)));
+    if (codes) {
+        h->code_groups = rsr::row_groups(h->rows);
+        RSR_TRY(dev_alloc(&h->packed, (size_t)rsr::packed_bytes(h->code_groups, cols, h->code_bits)));
+    }
     for (int ps = 0; ps < h->npass; ++ps) {
         RSR_TRY(dev_alloc(&h->pass[ps].pi, (size_t)(nb * cols)));
         RSR_TRY(dev_alloc(&h->pass[ps].off, (size_t)(nb * (P + 1))));
@@ -265,7 +270,7 @@ namespace {
 
 // Preprocessing with a given block height (k is ignored for the dense kind).
 rsr_handle_s *preprocess_with_k(const int8_t *M, int64_t rows, int64_t cols, int k, int kind,
-                                bool stacked = false) {
+                                bool stacked = false, bool codes = true) {
     rsr_handle_s *h = new (std::nothrow) rsr_handle_s();
     if (!h) { fail(RSR_ENOMEM); return nullptr; }
     h->magic = rsr::kMagic;
@@ -287,7 +292,7 @@ rsr_handle_s *preprocess_with_k(const int8_t *M, int64_t rows, int64_t cols, int
         if (k > kmax) { free_handle(h); fail(RSR_EUNSUPPORTED); return nullptr; }
         h->P = ipow(h->base, k);
         h->nb = (rows + k - 1) / k;
-        rc = preprocess_rsr(h, M, stacked);
+        rc = preprocess_rsr(h, M, stacked, codes);
     }
     if (rc == RSR_OK && hipDeviceSynchronize() != hipSuccess) rc = RSR_EHIP;
     if (rc != RSR_OK) {
@@ -301,7 +306,8 @@ rsr_handle_s *preprocess_with_k(const int8_t *M, int64_t rows, int64_t cols, int
 }
 
 hipError_t launch_any(rsr_handle_s *h, const void *v, int v_dtype, float *out) {
-    return h->narrow ? rsr::launch_narrow_matvec(h, v, v_dtype, 1.0f, out, 1, h->cols, h->rows, 0)
+    return h->single_packed ? rsr::launch_packed(h, v, v_dtype, 1.0f, out, 1, h->cols, h->rows, 0)
+           : h->narrow ? rsr::launch_narrow_matvec(h, v, v_dtype, 1.0f, out, 1, h->cols, h->rows, 0)
                      : rsr::launch_rsr_matvec(h, v, v_dtype, 1.0f, out, 1, h->cols, h->rows, 0);
 }
 
@@ -330,9 +336,12 @@ done:
 // device (paper, Demonstration Scenarios: the best-k comparison across shapes and devices,
 // and the k sweep of its interface), so it is chosen by measurement: preprocess with each
 // candidate height (make(k) returns the handle or null), time the multiply kernel, keep the
-// fastest handle.  padded_rows: an upper bound of the rows of any candidate handle.
-template <typename Make>
-rsr_handle_s *preprocess_auto_k(int kind, int64_t padded_rows, int64_t cols, Make make) {
+// fastest handle.  Then add_codes(handle) gives it its packed codes, and if a single vector is
+// multiplied faster from those, the handle does so (measured on MI355X: at every size tried;
+// 2560 x 2560 bf16 3.0 us against 4.6 with the best height, 4096 x 14336 5.4 against 6.3).
+// padded_rows: an upper bound of the rows of any candidate handle.
+template <typename Make, typename AddCodes>
+rsr_handle_s *preprocess_auto_k(int kind, int64_t padded_rows, int64_t cols, Make make, AddCodes add_codes) {
     static const int fused_k[] = {4, 5, 6, 7, 8};
     static const int binary_k[] = {4, 6, 8, 10, 12};
     const int *cand = (kind == RSR_TERNARY_FUSED) ? fused_k : binary_k;
@@ -362,12 +371,45 @@ rsr_handle_s *preprocess_auto_k(int kind, int64_t padded_rows, int64_t cols, Mak
             }
         }
         (void)hipDeviceSynchronize();
+        if (best) {
+            const int rc = add_codes(best);
+            if (rc == RSR_OK) {
+                best->single_packed = true;
+                const float us = time_matvec(best, v, out);
+                best->single_packed = us >= 0.0f && us < best_us;
+            } else {
+                free_handle(best);
+                best = nullptr;
+                last_err = rc;
+            }
+        }
     }
     if (v) (void)hipFree(v);
     if (out) (void)hipFree(out);
     if (!best) { fail(last_err); return nullptr; }
     g_last_error = RSR_OK;
     return best;
+}
+
+// Packed codes for a handle whose matrix (or layers, one after the other) has been checked.
+int add_codes(rsr_handle_s *h, const int8_t *const *Ms, const int64_t *rows, int n) {
+    int64_t first[rsr::kMaxLayers + 1];
+    first[0] = 0;
+    for (int i = 0; i < n; ++i) first[i + 1] = first[i] + rsr::row_groups(rows[i]);
+    int *flag = nullptr;
+    int rc = RSR_OK;
+    RSR_TRY(dev_alloc(&h->packed, (size_t)rsr::packed_bytes(first[n], h->cols, h->code_bits)));
+    RSR_TRY(dev_alloc(&flag, 1));
+    for (int i = 0; i < n; ++i)
+        RSR_TRY(rsr::launch_pack_codes(Ms[i], rows[i], h->cols, h->code_bits,
+                                       h->packed + rsr::packed_bytes(first[i], h->cols, h->code_bits), flag));
+    h->code_groups = first[n];
+    if (h->nlayers > 0)
+        for (int i = 0; i <= n; ++i) h->layer_code[i] = first[i];
+    RSR_TRY(hipDeviceSynchronize());
+done:
+    if (flag) (void)hipFree(flag);
+    return rc;
 }
 
 // Sibling layers stacked row-wise, every layer completed with zero rows to a whole number
@@ -394,7 +436,7 @@ rsr_handle_s *preprocess_stacked_with_k(const int8_t *const *Ms, const int64_t *
         (void)hipGetLastError();
         fail(RSR_EHIP);
     } else {
-        h = preprocess_with_k(T, padded, cols, k, kind, true);  // synchronises before returning
+        h = preprocess_with_k(T, padded, cols, k, kind, true, false);  // synchronises before returning
     }
     (void)hipFree(T);
     if (h) {
@@ -418,7 +460,8 @@ rsr_handle_t rsr_preprocess(const int8_t *M, int64_t rows, int64_t cols, int k, 
     if (cols > rsr::kMaxCols || rows > (int64_t)1 << 30) { fail(RSR_EUNSUPPORTED); return nullptr; }
     if (is_rsr_kind(kind) && k == 0)
         return preprocess_auto_k(kind, rows, cols,
-                                 [&](int kk) { return preprocess_with_k(M, rows, cols, kk, kind); });
+                                 [&](int kk) { return preprocess_with_k(M, rows, cols, kk, kind, false, false); },
+                                 [&](rsr_handle_s *h) { return add_codes(h, &M, &rows, 1); });
     return preprocess_with_k(M, rows, cols, k, kind);
 }
 
@@ -439,7 +482,7 @@ rsr_handle_t rsr_preprocess_stacked(const int8_t *const *Ms, const int64_t *rows
     if (is_rsr_kind(kind) && k == 0)
         return preprocess_auto_k(kind, total, cols, [&](int kk) {
             return preprocess_stacked_with_k(Ms, rows, n, cols, kk, kind);
-        });
+        }, [&](rsr_handle_s *h) { return add_codes(h, Ms, rows, n); });
     return preprocess_stacked_with_k(Ms, rows, n, cols, k, kind);
 }
 
@@ -462,10 +505,10 @@ int rsr_matvec_stacked(rsr_handle_t h, const void *v, int v_dtype, const float *
         lt.scale[i] = live ? (scales ? scales[i] : 1.0f) : 0.0f;
         lt.rows[i] = live ? (int)h->layer_rows[i] : 0;
     }
-    for (int i = 0; i <= rsr::kMaxLayers; ++i)
-        lt.first[i] = (int)h->layer_first[i <= h->nlayers ? i : h->nlayers];
+    const int64_t *first = (h->single_packed) ? h->layer_code : h->layer_first;
+    for (int i = 0; i <= rsr::kMaxLayers; ++i) lt.first[i] = (int)first[i <= h->nlayers ? i : h->nlayers];
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    const hipError_t e = (h->kind == RSR_DENSE_TERNARY_P2)
+    const hipError_t e = use_packed(h, 1)
                              ? rsr::launch_packed(h, v, v_dtype, 1.0f, nullptr, 1, h->cols, h->rows, s, &lt)
                              : rsr::launch_rsr_matvec(h, v, v_dtype, 1.0f, nullptr, 1, h->cols, h->rows, s, &lt);
     if (e != hipSuccess) return fail(hip_code(e));
@@ -592,7 +635,7 @@ int rsr_preprocess_into(rsr_handle_t h, const int8_t *M) {
 namespace {
 
 constexpr uint32_t kSerialMagic = 0x53525352u;  // "RSRS"
-constexpr uint32_t kSerialVersion = 2;
+constexpr uint32_t kSerialVersion = 3;  // 2: without single_packed, still read
 
 struct SerialHeader {
     uint32_t magic, version;
@@ -602,7 +645,9 @@ struct SerialHeader {
     int64_t slots;
     float sign[2];
     int64_t total_bytes;  // header + buffers
+    int64_t single_packed;
 };
+constexpr size_t kSerialHeader2 = offsetof(SerialHeader, single_packed);
 
 struct Piece {
     void **dev;      // the handle's device pointer
@@ -613,8 +658,8 @@ struct Piece {
 std::vector<Piece> pieces_of(rsr_handle_s *h) {
     std::vector<Piece> p;
     if (h->kind == RSR_DENSE_TERNARY_P2) {
-        const size_t groups = (size_t)((h->rows + rsr::kDenseRows - 1) / rsr::kDenseRows);
-        p.push_back({reinterpret_cast<void **>(&h->packed), groups * rsr::kDenseRows * (size_t)h->row_bytes});
+        p.push_back({reinterpret_cast<void **>(&h->packed),
+                     (size_t)rsr::packed_bytes(rsr::row_groups(h->rows), h->cols, h->code_bits)});
         return p;
     }
     for (int ps = 0; ps < h->npass; ++ps) {
@@ -649,7 +694,7 @@ int restore_codes(rsr_handle_s *h) {
     int8_t *M = nullptr;
     int *flag = nullptr;
     h->code_bits = (h->kind == RSR_BINARY) ? 1 : 2;
-    RSR_TRY(dev_alloc(&h->packed, (size_t)rsr::packed_bytes(h->rows, h->cols, h->code_bits)));
+    RSR_TRY(dev_alloc(&h->packed, (size_t)rsr::packed_bytes(h->code_groups, h->cols, h->code_bits)));
     RSR_TRY(dev_alloc(&M, (size_t)(h->rows * h->cols + 3) / 4 * 4));
     RSR_TRY(dev_alloc(&flag, 1));
     RSR_TRY(rsr::launch_fill_u32(reinterpret_cast<uint32_t *>(flag), 0u, 1));
@@ -692,6 +737,7 @@ int rsr_serialize(rsr_handle_t h, void *host_buf, int64_t capacity) {
     hd.rows = h->rows; hd.cols = h->cols; hd.nb = h->nb; hd.P = h->P; hd.row_bytes = h->row_bytes;
     for (int ps = 0; ps < 2; ++ps) { hd.S[ps] = h->pass[ps].S; hd.sign[ps] = h->pass[ps].sign; }
     hd.total_bytes = total;
+    hd.single_packed = h->single_packed ? 1 : 0;
     unsigned char *out = static_cast<unsigned char *>(host_buf);
     std::memcpy(out, &hd, sizeof(hd));
     size_t at = sizeof(hd);
@@ -710,7 +756,10 @@ rsr_handle_t rsr_deserialize(const void *host_buf, int64_t size) {
     if (!host_buf || size < (int64_t)sizeof(SerialHeader)) { fail(RSR_EINVAL); return nullptr; }
     SerialHeader hd;
     std::memcpy(&hd, host_buf, sizeof(hd));
-    if (hd.magic != kSerialMagic || hd.version != kSerialVersion || hd.total_bytes != size) {
+    const size_t header = hd.version == 2 ? kSerialHeader2 : sizeof(SerialHeader);
+    if (hd.version == 2) hd.single_packed = 0;
+    if (hd.magic != kSerialMagic || (hd.version != kSerialVersion && hd.version != 2) || hd.total_bytes != size ||
+        (hd.single_packed != 0 && hd.single_packed != 1)) {
         fail(RSR_EINVAL);
         return nullptr;
     }
@@ -758,18 +807,20 @@ rsr_handle_t rsr_deserialize(const void *host_buf, int64_t size) {
     int rc = RSR_OK;
     if (hipGetDevice(&h->device) != hipSuccess) rc = RSR_EHIP;
     const std::vector<Piece> pieces = pieces_of(h);
-    int64_t need = (int64_t)sizeof(SerialHeader);
+    int64_t need = (int64_t)header;
     for (const Piece &pc : pieces) need += (int64_t)pc.bytes;
     if (rc == RSR_OK && need != size) rc = RSR_EINVAL;
     const unsigned char *in = static_cast<const unsigned char *>(host_buf);
-    size_t at = sizeof(SerialHeader);
+    size_t at = header;
     for (size_t i = 0; rc == RSR_OK && i < pieces.size(); ++i) {
         hipError_t e = hipMalloc(pieces[i].dev, pieces[i].bytes ? pieces[i].bytes : 1);
         if (e == hipSuccess) e = hipMemcpy(*pieces[i].dev, in + at, pieces[i].bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) rc = hip_code(e);
         at += pieces[i].bytes;
     }
+    h->code_groups = rsr::row_groups(h->rows);
     if (rc == RSR_OK && !dense) rc = restore_codes(h);
+    h->single_packed = !dense && hd.single_packed;
     if (rc != RSR_OK) {
         (void)hipGetLastError();
         free_handle(h);
@@ -824,6 +875,14 @@ int rsr_probe_read(const void *src, int64_t bytes, int workgroups, int threads, 
 int rsr_launch_shape(rsr_handle_t h, int v_dtype, int *workgroups, int *threads, int *lds_bytes) {
     if (!good(h) || !is_rsr_kind(h->kind) || (v_dtype != RSR_F32 && v_dtype != RSR_BF16))
         return fail(RSR_EINVAL);
+    if (h->single_packed) {
+        int shape[3];
+        rsr::packed_launch_shape(h, v_dtype, &shape[0], &shape[1], &shape[2]);
+        if (workgroups) *workgroups = shape[0];
+        if (threads) *threads = shape[1];
+        if (lds_bytes) *lds_bytes = shape[2];
+        return RSR_OK;
+    }
     if (h->narrow) return fail(RSR_EUNSUPPORTED);
     if (workgroups) *workgroups = (int)h->nb;
     if (threads) *threads = h->W * 64;
@@ -918,7 +977,7 @@ int64_t rsr_algorithmic_bytes(rsr_handle_t h, int v_dtype, int batch) {
     const int64_t vb = (v_dtype == RSR_BF16) ? 2 : 4;
     int64_t weight_side;
     if (use_packed(h, batch)) {
-        weight_side = rsr::packed_bytes(h->rows, h->cols, h->code_bits);
+        weight_side = rsr::packed_bytes(h->code_groups, h->cols, h->code_bits);
     } else {
         weight_side = 0;
         for (int ps = 0; h->narrow && ps < h->npass; ++ps)
@@ -937,9 +996,10 @@ const char *rsr_kernel_name(rsr_handle_t h, int v_dtype) {
         fail(RSR_EINVAL);
         return nullptr;
     }
-    if (h->narrow) return v_dtype == RSR_BF16 ? "k_rsr_narrow<unsigned short>" : "k_rsr_narrow<float>";
     static thread_local char name[96];
-    if (h->kind == RSR_DENSE_TERNARY_P2)
+    if (h->narrow && !h->single_packed)
+        return v_dtype == RSR_BF16 ? "k_rsr_narrow<unsigned short>" : "k_rsr_narrow<float>";
+    if (use_packed(h, 1))
         rsr::packed_matvec_kernel_name(h, v_dtype, name, sizeof(name));
     else
         rsr::rsr_matvec_kernel_name(h, v_dtype, name, sizeof(name));

@@ -97,11 +97,14 @@ struct rsr_handle_s {
     int nlayers = 0;             // > 0: stacked handle (rows = the layers' rows padded to whole units)
     int64_t layer_rows[rsr::kMaxLayers] = {};
     int64_t layer_first[rsr::kMaxLayers + 1] = {};  // first unit (block / group of 16 rows) of a layer
+    int64_t layer_code[rsr::kMaxLayers + 1] = {};   // first row group of a layer in the packed codes
     bool stale = false;          // a failed rsr_preprocess_into left the buffers half-written
     // packed codes (rsr_packed.hip), [rows/16][tiles of 256 columns][64 lanes][8 * code_bits bytes]:
     // all a dense handle has; the other kinds multiply batches with them
     uint8_t *packed = nullptr;
     int code_bits = 2;           // bits per entry: 1 for the binary kind
+    int64_t code_groups = 0;     // row groups of 16; stacked handles: every layer starts a new one
+    bool single_packed = false;  // single vectors go through the packed codes too (k = 0, timed faster)
     int64_t row_bytes = 0;       // dense kind: 64 * tiles
 };
 
@@ -139,7 +142,8 @@ hipError_t launch_unsort(const uint16_t *pi, const uint32_t *off, int64_t rows, 
 hipError_t launch_transpose(const int8_t *M, int64_t rows, int64_t cols, int8_t *T);
 // Packed codes of the matrix (bits = 1 or 2 per entry), packed_bytes() of them; *err_flag |= 1
 // for an entry outside the alphabet.
-int64_t packed_bytes(int64_t rows, int64_t cols, int bits);
+int64_t packed_bytes(int64_t groups, int64_t cols, int bits);  // of `groups` row groups
+inline int64_t row_groups(int64_t rows) { return (rows + kDenseRows - 1) / kDenseRows; }
 hipError_t launch_pack_codes(const int8_t *M, int64_t rows, int64_t cols, int bits, void *packed,
                              int *err_flag);
 
@@ -155,6 +159,7 @@ hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, floa
                          const LayerTable *layers = nullptr);
 // Writes the name of the multiply kernel h launches for (v_dtype, batch) into buf.
 void rsr_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, char *buf, size_t len);
+void packed_launch_shape(const rsr_handle_s *h, int v_dtype, int *workgroups, int *threads, int *lds_bytes);
 void packed_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, char *buf, size_t len);
 
 // --- narrow matrices (cols <= kNarrowCols) ---------------------------------------------

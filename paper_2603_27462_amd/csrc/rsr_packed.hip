@@ -695,8 +695,8 @@ hipError_t launch(const Args &x) {
 
 }  // namespace
 
-int64_t packed_bytes(int64_t rows, int64_t cols, int bits) {
-    return (rows + kDenseRows - 1) / kDenseRows * ((cols + kTileCols - 1) / kTileCols) * 512 * bits;
+int64_t packed_bytes(int64_t groups, int64_t cols, int bits) {
+    return groups * ((cols + kTileCols - 1) / kTileCols) * 512 * bits;
 }
 
 hipError_t launch_pack_codes(const int8_t *M, int64_t rows, int64_t cols, int bits, void *packed, int *err_flag) {
@@ -718,7 +718,7 @@ hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, floa
     x.codes = reinterpret_cast<const uint32_t *>(h->packed);
     x.v = v;
     x.ntiles = (int)((h->cols + kTileCols - 1) / kTileCols);
-    x.ngroups = (int)((h->rows + kDenseRows - 1) / kDenseRows);
+    x.ngroups = (int)h->code_groups;
     x.n_in = (int)h->cols;
     x.n_out = (int)h->rows;
     x.batch = batch;
@@ -734,6 +734,14 @@ hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, floa
         x.layers.n = 0;
     if (h->code_bits == 1) return v_dtype == RSR_BF16 ? launch<uint16_t, 1>(x) : launch<float, 1>(x);
     return v_dtype == RSR_BF16 ? launch<uint16_t, 2>(x) : launch<float, 2>(x);
+}
+
+void packed_launch_shape(const rsr_handle_s *h, int v_dtype, int *workgroups, int *threads, int *lds_bytes) {
+    const int wk = few_wk((int)((h->cols + kTileCols - 1) / kTileCols)), waves = few_waves(wk), rows = waves / wk;
+    const int wave_bytes = v_dtype == RSR_BF16 ? Few<uint16_t, 1>::wave_bytes : Few<float, 1>::wave_bytes;
+    *workgroups = (int)((h->code_groups + rows - 1) / rows);
+    *threads = waves * 64;
+    *lds_bytes = waves * (wave_bytes + 64 * 4);
 }
 
 void packed_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, char *buf, size_t len) {

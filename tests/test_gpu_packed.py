@@ -90,3 +90,22 @@ def test_codes_after_loading_and_after_a_new_matrix(kind, rows, cols, k):
 def test_few_vectors(kind, rows, batch, bf16, pad, cols):
     M = _matrix(kind, rows, cols, 700 + rows + cols)
     _check(rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), 5, kind), M, batch, bf16, pad, rows)
+
+
+@pytest.mark.parametrize("kind,rows,cols", [(rsr.RSR_TERNARY_FUSED, 203, 1500), (rsr.RSR_BINARY, 5000, 130)])
+def test_library_chosen_height_after_loading(kind, rows, cols):
+    """k = 0: however the handle multiplies single vectors, its copy made from bytes does the same,
+    bit for bit; bytes without that field (written before it existed) are still read."""
+    M = _matrix(kind, rows, cols, 21)
+    h = rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), 0, kind)
+    blob = rsr.rsr_serialize(h)
+    h2 = rsr.rsr_deserialize(blob)
+    assert rsr.rsr_kernel_name(h2) == rsr.rsr_kernel_name(h)
+    v = torch.from_numpy(gen.normal_f32(cols, seed=8)).to(DEV)
+    assert torch.equal(rsr.rsr_matvec(h, v), rsr.rsr_matvec(h2, v))
+    old = np.concatenate([blob[:120], blob[128:]])      # the field is the header's last
+    old[4:8].view(np.int32)[0] = 2
+    old[112:120].view(np.int64)[0] -= 8
+    for handle in (h, h2, rsr.rsr_deserialize(old)):
+        for batch in (1, 3, 40):
+            _check(handle, M, batch, True, 1, 30 + batch)
