@@ -38,24 +38,42 @@ hipError_t dev_alloc(T **p, size_t count) {
 
 void free_handle(rsr_handle_s *h) {
     if (!h) return;
-    for (auto &ps : h->pass) {
-        if (ps.pi) (void)hipFree(ps.pi);
-        if (ps.off) (void)hipFree(ps.off);
-        if (ps.entries) (void)hipFree(ps.entries);
-        if (ps.start) (void)hipFree(ps.start);
-        if (ps.sgn) (void)hipFree(ps.sgn);
-        if (ps.gword) (void)hipFree(ps.gword);
-        if (ps.nent) (void)hipFree(ps.nent);
-        if (ps.nmeta) (void)hipFree(ps.nmeta);
-        if (ps.nsw) (void)hipFree(ps.nsw);
-        if (ps.gcount) (void)hipFree(ps.gcount);
-    }
-    if (h->fpack) (void)hipFree(h->fpack);
-    if (h->fshare) (void)hipFree(h->fshare);
-    if (h->packed) (void)hipFree(h->packed);
+    for (void *p : h->arena)
+        if (p) (void)hipFree(p);
     h->magic = 0;
     delete h;
 }
+
+// Device buffers that are allocated together: an allocation and a release cost about 15 and 20 us
+// each, whatever their size, and a handle has up to a dozen buffers.
+class Buffers {
+  public:
+    template <typename T>
+    void add(T **p, int64_t count) {
+        items_.push_back({reinterpret_cast<void **>(p), total_});
+        total_ += ((size_t)(count > 0 ? count : 1) * sizeof(T) + 255) & ~(size_t)255;
+    }
+    void add_bytes(void **p, int64_t bytes) { add(reinterpret_cast<unsigned char **>(p), bytes); }
+    hipError_t allocate(rsr_handle_s *h) {
+        int slot = 0;
+        while (slot < 4 && h->arena[slot]) ++slot;
+        if (slot == 4) return hipErrorInvalidValue;
+        if (hipError_t e = hipMalloc(&h->arena[slot], total_ ? total_ : 1)) {
+            h->arena[slot] = nullptr;
+            return e;
+        }
+        for (const Item &i : items_) *i.p = static_cast<unsigned char *>(h->arena[slot]) + i.at;
+        return hipSuccess;
+    }
+
+  private:
+    struct Item {
+        void **p;
+        size_t at;
+    };
+    std::vector<Item> items_;
+    size_t total_ = 0;
+};
 
 int64_t ipow(int64_t b, int e) {
     int64_t p = 1;
@@ -72,15 +90,12 @@ int hip_code(hipError_t e) { return e == hipErrorOutOfMemory ? RSR_ENOMEM : RSR_
         if (e_ != hipSuccess) { rc = hip_code(e_); goto done; } \
     } while (0)
 
-// Device memory a preprocessing run needs besides the handle's own buffers: the pattern
-// codes of every (block, column), the stream in logical order, the codes of the non-empty
-// groups (rank-indexed handles), and a few words of flags (kFlagErr: entry outside the
-// alphabet / self-check; kFlagStats + 3 * pass: the three maxima of launch_stream_stats).
+// Device memory a preprocessing run needs besides the handle's own buffers: a few words of flags
+// (kFlagErr: entry outside the alphabet / self-check; kFlagStats + 3 * pass: the three maxima of
+// launch_sort_columns), and for matrices too wide to be sorted as pairs the pattern codes.
 struct Temps {
-    uint16_t *code = nullptr;     // [nb][cols]
-    uint16_t *logical = nullptr;  // [nb][max over passes of S * 512]
-    uint16_t *gcode = nullptr;    // [nb][slots], rank-indexed handles only
-    int *flags = nullptr;         // [kFlagWords]
+    uint16_t *code = nullptr;  // [nb][cols] when sort_needs_codes(cols)
+    int *flags = nullptr;      // [kFlagWords]
 };
 constexpr int kFlagErr = 0, kFlagStats = 1, kFlagWords = 64;
 
@@ -104,7 +119,7 @@ int run_dense(rsr_handle_s *h, const int8_t *M, const Temps &t) {
     return host[kFlagErr] ? RSR_EVALUE : RSR_OK;
 }
 
-// encode -> counting sort -> stream statistics, per pass; and the packed codes, if the handle has
+// codes, counting sort and stream statistics, per pass; and the packed codes, if the handle has
 // room for them
 int run_sort_passes(rsr_handle_s *h, const int8_t *M, const Temps &t, StreamStats *st) {
     static const int modes[3][2] = {{rsr::MODE_BINARY, 0}, {rsr::MODE_POS, rsr::MODE_NEG},
@@ -115,12 +130,9 @@ int run_sort_passes(rsr_handle_s *h, const int8_t *M, const Temps &t, StreamStat
     for (int ps = 0; ps < h->npass; ++ps) {
         rsr::PassData &pd = h->pass[ps];
         pd.sign = (ps == 0) ? 1.0f : -1.0f;
-        if (rsr::launch_encode(M, h->rows, h->cols, h->k, modes[h->kind][ps], t.code,
-                               t.flags + kFlagErr) != hipSuccess ||
-            rsr::launch_sort(t.code, h->nb, h->cols, h->k, h->base, h->P, pd.pi, pd.off) != hipSuccess ||
-            rsr::launch_stream_stats(pd.off, h->nb, h->cols, h->P,
-                                     reinterpret_cast<uint32_t *>(t.flags + kFlagStats + 3 * ps)) !=
-                hipSuccess)
+        if (rsr::launch_sort_columns(M, h->rows, h->cols, h->k, h->base, modes[h->kind][ps], h->P, t.code, pd.pi,
+                                     pd.off, reinterpret_cast<uint32_t *>(t.flags + kFlagStats + 3 * ps),
+                                     t.flags + kFlagErr) != hipSuccess)
             return RSR_EHIP;
     }
     if (h->packed && rsr::launch_pack_codes(M, h->rows, h->cols, h->code_bits, h->packed,
@@ -154,7 +166,7 @@ int run_pack_passes(rsr_handle_s *h, const Temps &t) {
         rsr::launch_fold_tables(h->base, h->k, h->fold, h->W, h->fpack, h->fshare) != hipSuccess)
         return RSR_EHIP;
     for (int ps = 0; ps < h->npass; ++ps)
-        if (rsr::launch_pack_pass(h, ps, t.logical, t.gcode, t.flags + kFlagErr) != hipSuccess)
+        if (rsr::launch_pack_pass(h, ps, t.flags + kFlagErr) != hipSuccess)
             return RSR_EHIP;
     if (int rc = read_flags(t, host)) return rc;
     return host[kFlagErr] ? RSR_EINTERNAL : RSR_OK;
@@ -167,17 +179,38 @@ size_t sign_table_bytes(const rsr_handle_s *h) {
 }
 
 int preprocess_dense(rsr_handle_s *h, const int8_t *M) {
-    int rc = RSR_OK;
     Temps t;
-    const int64_t ntiles = (h->cols + rsr::kDenseTileCols - 1) / rsr::kDenseTileCols;
-    h->row_bytes = ntiles * (rsr::kDenseTileCols / 4);
+    Buffers own;
+    h->row_bytes = (h->cols + rsr::kDenseTileCols - 1) / rsr::kDenseTileCols * (rsr::kDenseTileCols / 4);
     h->code_groups = rsr::row_groups(h->rows);
-    RSR_TRY(dev_alloc(&h->packed, (size_t)rsr::packed_bytes(h->code_groups, h->cols, h->code_bits)));
-    RSR_TRY(dev_alloc(&t.flags, kFlagWords));
-    rc = run_dense(h, M, t);
-done:
-    if (t.flags) (void)hipFree(t.flags);
-    return rc;
+    own.add(&h->packed, rsr::packed_bytes(h->code_groups, h->cols, h->code_bits));
+    own.add(&t.flags, kFlagWords);
+    if (hipError_t e = own.allocate(h)) return hip_code(e);
+    return run_dense(h, M, t);
+}
+
+// The buffers a stream of the handle's layout needs.
+void add_stream_buffers(rsr_handle_s *h, Buffers *own) {
+    for (int ps = 0; ps < h->npass; ++ps) {
+        rsr::PassData &pd = h->pass[ps];
+        if (h->narrow) {
+            own->add(&pd.nent, h->nb * 64);
+            own->add(&pd.nmeta, h->nb * 64);
+            own->add_bytes(&pd.nsw, h->nb * h->slots * h->narrow_sw_bytes);
+            continue;
+        }
+        own->add(&pd.entries, h->nb * pd.S * rsr::kSlab);
+        own->add(&pd.start, h->nb * h->W * 64);
+        own->add_bytes(&pd.sgn, (int64_t)sign_table_bytes(h));
+        if (h->by_rank) {
+            own->add(&pd.gword, h->nb * h->slots);
+            own->add(&pd.gcount, h->nb);
+        }
+    }
+    if (!h->by_rank && !h->narrow) {
+        own->add(&h->fpack, (int64_t)h->k * h->fold.G * 64);
+        own->add(&h->fshare, h->W * 64);
+    }
 }
 
 // codes: make the packed codes too.  Stacked handles have several output vectors, which the narrow
@@ -185,41 +218,31 @@ done:
 int preprocess_rsr(rsr_handle_s *h, const int8_t *M, bool stacked, bool codes) {
     int rc = RSR_OK;
     Temps t;
+    Buffers own, stream;
     const int64_t nb = h->nb, cols = h->cols, P = h->P;
+    const int fw = h->base == 2 ? 1 : 2;
     StreamStats st;
 
-    RSR_TRY(dev_alloc(&t.code, (size_t)(nb * cols)));
-    RSR_TRY(dev_alloc(&t.flags, kFlagWords));
+    for (int ps = 0; ps < h->npass; ++ps) {
+        own.add(&h->pass[ps].pi, nb * cols);
+        own.add(&h->pass[ps].off, nb * (P + 1));
+    }
     if (codes) {
         h->code_groups = rsr::row_groups(h->rows);
-        RSR_TRY(dev_alloc(&h->packed, (size_t)rsr::packed_bytes(h->code_groups, cols, h->code_bits)));
+        own.add(&h->packed, rsr::packed_bytes(h->code_groups, cols, h->code_bits));
     }
-    for (int ps = 0; ps < h->npass; ++ps) {
-        RSR_TRY(dev_alloc(&h->pass[ps].pi, (size_t)(nb * cols)));
-        RSR_TRY(dev_alloc(&h->pass[ps].off, (size_t)(nb * (P + 1))));
-    }
+    own.add(&t.flags, kFlagWords);
+    RSR_TRY(own.allocate(h));
+    if (rsr::sort_needs_codes(cols)) RSR_TRY(dev_alloc(&t.code, (size_t)(nb * cols)));
     if ((rc = run_sort_passes(h, M, t, &st)) != RSR_OK) goto done;
-    {
+    if (!stacked && cols <= rsr::kNarrowCols && h->k * fw <= 32) {
         // narrow matrices: 8-bit entries, one wave per block
-        const int fw = h->base == 2 ? 1 : 2;
-        if (!stacked && cols <= rsr::kNarrowCols && h->k * fw <= 32) {
-            int64_t most = st.groups[0] > st.groups[1] ? st.groups[0] : st.groups[1];
-            h->narrow = 1;
-            h->narrow_fw = fw;
-            h->narrow_sw_bytes = h->k * fw <= 8 ? 1 : h->k * fw <= 16 ? 2 : 4;
-            h->slots = most < 4 ? 4 : (most + 3) / 4 * 4;
-            for (int ps = 0; ps < h->npass; ++ps) {
-                rsr::PassData &pd = h->pass[ps];
-                RSR_TRY(dev_alloc(&pd.nent, (size_t)nb * 64));
-                RSR_TRY(dev_alloc(&pd.nmeta, (size_t)nb * 64));
-                RSR_TRY(dev_alloc(reinterpret_cast<unsigned char **>(&pd.nsw),
-                                  (size_t)(nb * h->slots) * h->narrow_sw_bytes));
-            }
-            rc = run_pack_passes(h, t);
-            goto done;
-        }
-    }
-    {
+        const int64_t most = st.groups[0] > st.groups[1] ? st.groups[0] : st.groups[1];
+        h->narrow = 1;
+        h->narrow_fw = fw;
+        h->narrow_sw_bytes = h->k * fw <= 8 ? 1 : h->k * fw <= 16 ? 2 : 4;
+        h->slots = most < 4 ? 4 : (most + 3) / 4 * 4;
+    } else {
         const int ph = (h->npass == 2 && st.with_empty[1] > st.with_empty[0]) ? 1 : 0;  // the heavier pass
         h->by_rank = rsr::choose_by_rank(P, cols, st.with_empty[ph], st.real[ph], st.groups[ph]) ? 1 : 0;
         int64_t maxS = 0, most = 0;
@@ -236,31 +259,13 @@ int preprocess_rsr(rsr_handle_s *h, const int8_t *M, bool stacked, bool codes) {
             rc = RSR_EUNSUPPORTED;
             goto done;
         }
-        if (h->by_rank) {
-            RSR_TRY(dev_alloc(&t.gcode, (size_t)(nb * h->slots)));
-        } else {
-            rsr::make_fold_shape(h->base, h->k, P, h->W, &h->fold);
-            RSR_TRY(dev_alloc(&h->fpack, (size_t)h->k * h->fold.G * 64));
-            RSR_TRY(dev_alloc(&h->fshare, (size_t)h->W * 64));
-        }
-        RSR_TRY(dev_alloc(&t.logical, (size_t)(nb * maxS * rsr::kSlab)));
-        for (int ps = 0; ps < h->npass; ++ps) {
-            rsr::PassData &pd = h->pass[ps];
-            RSR_TRY(dev_alloc(&pd.entries, (size_t)(nb * pd.S * rsr::kSlab)));
-            RSR_TRY(dev_alloc(&pd.start, (size_t)(nb * h->W * 64)));
-            RSR_TRY(dev_alloc(reinterpret_cast<unsigned char **>(&pd.sgn), sign_table_bytes(h)));
-            if (h->by_rank) {
-                RSR_TRY(dev_alloc(&pd.gword, (size_t)(nb * h->slots)));
-                RSR_TRY(dev_alloc(&pd.gcount, (size_t)nb));
-            }
-        }
+        if (!h->by_rank) rsr::make_fold_shape(h->base, h->k, P, h->W, &h->fold);
     }
+    add_stream_buffers(h, &stream);
+    RSR_TRY(stream.allocate(h));
     rc = run_pack_passes(h, t);
 done:
     if (t.code) (void)hipFree(t.code);
-    if (t.logical) (void)hipFree(t.logical);
-    if (t.gcode) (void)hipFree(t.gcode);
-    if (t.flags) (void)hipFree(t.flags);
     return rc;
 }
 
@@ -397,19 +402,19 @@ int add_codes(rsr_handle_s *h, const int8_t *const *Ms, const int64_t *rows, int
     first[0] = 0;
     for (int i = 0; i < n; ++i) first[i + 1] = first[i] + rsr::row_groups(rows[i]);
     int *flag = nullptr;
-    int rc = RSR_OK;
-    RSR_TRY(dev_alloc(&h->packed, (size_t)rsr::packed_bytes(first[n], h->cols, h->code_bits)));
-    RSR_TRY(dev_alloc(&flag, 1));
+    Buffers own;
+    own.add(&h->packed, rsr::packed_bytes(first[n], h->cols, h->code_bits));
+    own.add(&flag, 1);
+    if (hipError_t e = own.allocate(h)) return hip_code(e);
     for (int i = 0; i < n; ++i)
-        RSR_TRY(rsr::launch_pack_codes(Ms[i], rows[i], h->cols, h->code_bits,
-                                       h->packed + rsr::packed_bytes(first[i], h->cols, h->code_bits), flag));
+        if (hipError_t e = rsr::launch_pack_codes(Ms[i], rows[i], h->cols, h->code_bits,
+                                                  h->packed + rsr::packed_bytes(first[i], h->cols, h->code_bits), flag))
+            return hip_code(e);
     h->code_groups = first[n];
     if (h->nlayers > 0)
         for (int i = 0; i <= n; ++i) h->layer_code[i] = first[i];
-    RSR_TRY(hipDeviceSynchronize());
-done:
-    if (flag) (void)hipFree(flag);
-    return rc;
+    const hipError_t e = hipDeviceSynchronize();
+    return e == hipSuccess ? RSR_OK : hip_code(e);
 }
 
 // Sibling layers stacked row-wise, every layer completed with zero rows to a whole number
@@ -592,19 +597,15 @@ int rsr_preprocess_into(rsr_handle_t h, const int8_t *M) {
         h->stale = true;
         rc = run_dense(h, M, t);
     } else {
+        // the documented limit counts the pattern codes, the stream in logical order and the
+        // codes of the groups, though most of it stays in LDS
         int64_t maxS = 0;
         for (int ps = 0; ps < h->npass; ++ps)
             if (h->pass[ps].S > maxS) maxS = h->pass[ps].S;
         t.code = reinterpret_cast<uint16_t *>(base + at);
         at += align256((size_t)(h->nb * h->cols) * sizeof(uint16_t));
-        if (!h->narrow) {
-            t.logical = reinterpret_cast<uint16_t *>(base + at);
-            at += align256((size_t)(h->nb * maxS * rsr::kSlab) * sizeof(uint16_t));
-        }
-        if (h->by_rank) {
-            t.gcode = reinterpret_cast<uint16_t *>(base + at);
-            at += align256((size_t)(h->nb * h->slots) * sizeof(uint16_t));
-        }
+        if (!h->narrow) at += align256((size_t)(h->nb * maxS * rsr::kSlab) * sizeof(uint16_t));
+        if (h->by_rank) at += align256((size_t)(h->nb * h->slots) * sizeof(uint16_t));
         if (at > kStaticScratchBytes) return fail(RSR_ESCRATCH);
         h->stale = true;  // from here on the handle's buffers are being rewritten
         StreamStats st;
@@ -693,10 +694,12 @@ int restore_codes(rsr_handle_s *h) {
     int rc = RSR_OK, err = 0;
     int8_t *M = nullptr;
     int *flag = nullptr;
+    Buffers own;
     h->code_bits = (h->kind == RSR_BINARY) ? 1 : 2;
-    RSR_TRY(dev_alloc(&h->packed, (size_t)rsr::packed_bytes(h->code_groups, h->cols, h->code_bits)));
+    own.add(&h->packed, rsr::packed_bytes(h->code_groups, h->cols, h->code_bits));
+    own.add(&flag, 1);
+    RSR_TRY(own.allocate(h));
     RSR_TRY(dev_alloc(&M, (size_t)(h->rows * h->cols + 3) / 4 * 4));
-    RSR_TRY(dev_alloc(&flag, 1));
     RSR_TRY(rsr::launch_fill_u32(reinterpret_cast<uint32_t *>(flag), 0u, 1));
     RSR_TRY(rsr::launch_fill_u32(reinterpret_cast<uint32_t *>(M), 0u, (h->rows * h->cols + 3) / 4));
     for (int ps = 0; ps < h->npass; ++ps)
@@ -707,7 +710,6 @@ int restore_codes(rsr_handle_s *h) {
     if (err) rc = RSR_EINVAL;
 done:
     if (M) (void)hipFree(M);
-    if (flag) (void)hipFree(flag);
     return rc;
 }
 
@@ -807,14 +809,19 @@ rsr_handle_t rsr_deserialize(const void *host_buf, int64_t size) {
     int rc = RSR_OK;
     if (hipGetDevice(&h->device) != hipSuccess) rc = RSR_EHIP;
     const std::vector<Piece> pieces = pieces_of(h);
+    Buffers own;
+    for (const Piece &pc : pieces) own.add_bytes(pc.dev, (int64_t)pc.bytes);
     int64_t need = (int64_t)header;
     for (const Piece &pc : pieces) need += (int64_t)pc.bytes;
     if (rc == RSR_OK && need != size) rc = RSR_EINVAL;
+    if (rc == RSR_OK) {
+        const hipError_t e = own.allocate(h);
+        if (e != hipSuccess) rc = hip_code(e);
+    }
     const unsigned char *in = static_cast<const unsigned char *>(host_buf);
     size_t at = header;
     for (size_t i = 0; rc == RSR_OK && i < pieces.size(); ++i) {
-        hipError_t e = hipMalloc(pieces[i].dev, pieces[i].bytes ? pieces[i].bytes : 1);
-        if (e == hipSuccess) e = hipMemcpy(*pieces[i].dev, in + at, pieces[i].bytes, hipMemcpyHostToDevice);
+        const hipError_t e = hipMemcpy(*pieces[i].dev, in + at, pieces[i].bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) rc = hip_code(e);
         at += pieces[i].bytes;
     }

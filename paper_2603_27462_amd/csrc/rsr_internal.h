@@ -82,6 +82,7 @@ struct FoldShape {
 
 struct rsr_handle_s {
     uint32_t magic = 0;
+    void *arena[4] = {};  // device allocations; every other device pointer of the handle is inside one
     int kind = 0, k = 0, base = 0, npass = 0, device = 0;
     int W = 0;        // waves per workgroup of the multiply kernel
     int enc = 0;      // entry encoding: kEncSmall or kEncBig
@@ -122,19 +123,17 @@ enum { MODE_BINARY = 0, MODE_POS = 1, MODE_NEG = 2, MODE_FUSED3 = 3 };
 
 // --- preprocessing launches (null stream) ------------------------------------
 hipError_t launch_fill_u32(uint32_t *p, uint32_t value, int64_t count);
-hipError_t launch_encode(const int8_t *M, int64_t rows, int64_t cols, int k, int mode,
-                         uint16_t *code, int *err_flag);
-hipError_t launch_sort(const uint16_t *code, int64_t nb, int64_t cols, int k, int base, int64_t P,
-                       uint16_t *pi, uint32_t *off);
+// Pattern codes, stable sort and boundaries of every block in one pass over the matrix.
 // stats[0..2] = max over blocks of: columns outside group 0; the same plus the empty groups
-// among codes 1..P-1; the non-empty groups among codes 1..P-1 (the caller zeroes them)
-hipError_t launch_stream_stats(const uint32_t *off, int64_t nb, int64_t cols, int64_t P,
-                               uint32_t *stats);
-// Everything the multiply kernel reads of one pass, from the canonical pi / off:
-// `logical` is scratch of nb * S * kSlab entries, `gcode` scratch of nb * slots entries
-// (by rank only).  *err_flag |= 2 when a block does not hold the expected number of tails.
-hipError_t launch_pack_pass(const rsr_handle_s *h, int pass, uint16_t *logical, uint16_t *gcode,
-                            int *err_flag);
+// among codes 1..P-1; the non-empty groups among codes 1..P-1 (the caller zeroes them).
+// `codes` is scratch of nb * cols words, used when sort_needs_codes(cols); *err_flag |= 1 for an
+// entry outside the alphabet.
+bool sort_needs_codes(int64_t cols);
+hipError_t launch_sort_columns(const int8_t *M, int64_t rows, int64_t cols, int k, int base, int mode, int64_t P,
+                               uint16_t *codes, uint16_t *pi, uint32_t *off, uint32_t *stats, int *err_flag);
+// Everything the multiply kernel reads of one pass, from the canonical pi / off.  *err_flag |= 2
+// when a block does not hold the expected number of tails.
+hipError_t launch_pack_pass(const rsr_handle_s *h, int pass, int *err_flag);
 // Entries of the matrix from the canonical pi / off of one pass: M (zeroed by the caller) gets
 // the digits that are not zero, 2 as -1, times sign.
 hipError_t launch_unsort(const uint16_t *pi, const uint32_t *off, int64_t rows, int64_t cols, int k, int base,

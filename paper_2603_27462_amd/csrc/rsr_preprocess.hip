@@ -1,57 +1,25 @@
 // One-time preprocessing kernels of librsr (paper, System Overview, "Algorithm
-// overview", and Kernels Implementation):
-//   encode       pattern code of every (block, column)
-//   sort         per block, stable counting sort of the columns by code, done
-//                digit group by digit group (each pass is a counting sort over
-//                4 or 9 buckets: count, scan, stable placement), then the group
-//                boundaries over all P codes
-//   stream_len / pack_stream / finalize_stream
-//                the compact stream the multiply kernel reads: 16-bit entries,
-//                zero-contribution group dropped, one tail flag per group,
-//                laid out for coalesced per-lane strips
+// overview", and Kernels Implementation), one workgroup per block of k rows:
+//   k_sort_columns  pattern codes of the block's columns, a stable counting sort of the
+//                   columns by code, the group boundaries over all P codes, and what the
+//                   host needs to choose the layout of the stream
+//   k_build_stream  the compact stream the multiply kernel reads: 16-bit entries,
+//                   zero-contribution group dropped, one tail flag per group, columns of a
+//                   group in an order that suits the LDS banks, laid out for coalesced
+//                   per-lane strips; and the small tables of the multiply kernel
+// Everything between the matrix and these results stays in LDS.  Both are bound by the latency
+// and the instruction count of their LDS steps, not by memory (4096 x 4096, fused, k = 8: 48 and
+// 95 us, 70 of them for spreading the columns over the banks; as seven kernels with their
+// intermediates in memory and the placement of whole runs 430 us).
+#include <type_traits>
+
 #include "rsr_internal.h"
 
 namespace rsr {
 
 namespace {
 
-constexpr int kThreads = 256;  // workgroup size of every preprocessing kernel
-constexpr int kWaves = kThreads / 64;
-
-__device__ __forceinline__ int digit_of(int m, int mode) {
-    switch (mode) {
-        case MODE_BINARY: return (m == 0) ? 0 : (m == 1) ? 1 : -1;
-        case MODE_POS: return (m == 1) ? 1 : (m == 0 || m == -1) ? 0 : -1;
-        case MODE_NEG: return (m == -1) ? 1 : (m == 0 || m == 1) ? 0 : -1;
-        default: return (m == 0) ? 0 : (m == 1) ? 1 : (m == -1) ? 2 : -1;
-    }
-}
-
-// code[b][j] = sum_r digit(M[b*k+r][j]) * base^r; rows past the end are zero.
-__global__ __launch_bounds__(kThreads) void k_encode(const int8_t *__restrict__ M, int64_t rows,
-                                                     int64_t cols, int k, int mode, int64_t nb,
-                                                     uint16_t *__restrict__ code,
-                                                     int *__restrict__ err_flag) {
-    const int64_t cols_pad = (cols + kThreads - 1) / kThreads * kThreads;
-    const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const int64_t b = gid / cols_pad;
-    const int64_t j = gid % cols_pad;
-    if (b >= nb || j >= cols) return;
-    const uint32_t base = (mode == MODE_FUSED3) ? 3u : 2u;
-    uint32_t c = 0, weight = 1;
-    bool bad = false;
-    for (int r = 0; r < k; ++r) {
-        const int64_t i = b * k + r;
-        if (i < rows) {
-            int d = digit_of(M[i * cols + j], mode);
-            if (d < 0) { bad = true; d = 0; }
-            c += (uint32_t)d * weight;
-        }
-        weight *= base;
-    }
-    if (bad) atomicOr(err_flag, 1);
-    code[b * cols + j] = (uint16_t)c;
-}
+constexpr int kThreads = 256;  // workgroup size of the element-wise kernels
 
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
     const int lane = threadIdx.x & 63;
@@ -64,15 +32,14 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
 }
 
 // Exclusive scan of one value per thread over the workgroup; *total gets the sum.
-// wsum: kWaves words of LDS.  Contains two barriers.
-__device__ __forceinline__ uint32_t wg_exclusive_scan(uint32_t x, uint32_t *wsum, uint32_t *total) {
+// wsum: one word of LDS per wave.  Contains two barriers.
+__device__ __forceinline__ uint32_t wg_exclusive_scan(uint32_t x, uint32_t *wsum, int waves, uint32_t *total) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint32_t incl = wave_inclusive_scan(x);
     if (lane == 63) wsum[w] = incl;
     __syncthreads();
     uint32_t before = 0, all = 0;
-#pragma unroll
-    for (int i = 0; i < kWaves; ++i) {
+    for (int i = 0; i < waves; ++i) {
         const uint32_t t = wsum[i];
         if (i < w) before += t;
         all += t;
@@ -82,73 +49,175 @@ __device__ __forceinline__ uint32_t wg_exclusive_scan(uint32_t x, uint32_t *wsum
     return before + incl - x;
 }
 
-// Stable sort of the columns of each block by pattern code.  R = buckets per
-// digit pass (4 = two binary digits, 9 = two ternary digits).  Each thread
-// owns a contiguous strip of positions, so placing strip after strip in
-// thread order keeps equal keys in their previous order.
-template <int R>
-__global__ __launch_bounds__(kThreads) void k_sort(const uint16_t *__restrict__ code, int64_t nb,
-                                                   int n, int passes, int64_t P,
-                                                   uint16_t *__restrict__ pi,
-                                                   uint32_t *__restrict__ off) {
-    extern __shared__ unsigned char smem[];
+// ---- codes, sort, boundaries -----------------------------------------------------------------
+typedef uint32_t u32_any __attribute__((aligned(1)));
+
+// Digits of four entries (one per byte) for an encode mode, one per byte; bad != 0: an entry
+// outside the alphabet.
+__device__ __forceinline__ uint32_t digits4(uint32_t x, int mode, uint32_t *bad) {
+    const uint32_t one = x & 0x01010101u, neg = (x >> 7) & 0x01010101u;
+    if (mode == MODE_BINARY) {
+        *bad |= x & 0xfefefefeu;
+        return one;
+    }
+    // 0, 1 and 255: all bits alike but for the lowest, and that one set where the others are
+    *bad |= ((x ^ (neg * 255u)) & 0xfefefefeu) | (neg & ~one);
+    if (mode == MODE_POS) return one & ~neg;
+    if (mode == MODE_NEG) return neg;
+    return one + neg;
+}
+
+constexpr int kDigitBits = 5;  // most bits of the code one sorting step looks at
+
+// Stable sort of the columns of each block by pattern code: digit by digit of the code's bits,
+// every step a counting sort over at most 32 buckets.  A wave owns a contiguous run of positions and
+// takes it 64 at a time; lanes with equal digits find each other with one ballot per bit, so
+// their ranks keep the order.  WIDE: more columns than LDS holds as (code, column) pairs: only
+// the columns are moved and the codes are looked up in `codes`, [nb][n].
+// stats[0] = max over blocks of the columns outside group 0; stats[1] = the same plus one
+// placeholder per empty group among codes 1..P-1; stats[2] = most non-empty groups among
+// codes 1..P-1.  The caller zeroes stats.
+template <int NT, bool WIDE>
+__global__ __launch_bounds__(NT) void k_sort_columns(const int8_t *__restrict__ M, int64_t rows, int n, int k,
+                                                     int base, int mode, int64_t nb, int64_t P, int bits,
+                                                     uint16_t *__restrict__ codes, uint16_t *__restrict__ pi,
+                                                     uint32_t *__restrict__ off, uint32_t *__restrict__ stats,
+                                                     int *__restrict__ err_flag) {
+    constexpr int W = NT / 64;
+    typedef typename std::conditional<WIDE, uint16_t, uint32_t>::type Item;  // column, or code << 16 | column
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int npad = (n + 7) & ~7;
-    uint16_t *A = reinterpret_cast<uint16_t *>(smem);
-    uint16_t *B = A + npad;
-    uint32_t *cnt = reinterpret_cast<uint32_t *>(B + npad);  // [R][kThreads]
-    uint32_t *wsum = cnt + R * kThreads;                      // [kWaves]
-    const int tid = threadIdx.x;
-    const int L = (n + kThreads - 1) / kThreads;
-    const int lo = min(n, tid * L), hi = min(n, lo + L);
+    Item *A = reinterpret_cast<Item *>(smem), *B = A + npad;
+    uint32_t *cnt = reinterpret_cast<uint32_t *>(B + npad);  // [digit][wave]
+    uint32_t *sums = cnt + (W << kDigitBits);                 // groups, columns outside group 0
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int seg = (n + NT - 1) / NT * 64;
+    const int lo = min(n, w * seg), hi = min(n, lo + seg);
+    const int steps = (bits + kDigitBits - 1) / kDigitBits, step_bits = (bits + steps - 1) / steps;
 
     for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
-        const uint16_t *cb = code + b * n;
-        for (int t = tid; t < n; t += kThreads) A[t] = (uint16_t)t;
-        __syncthreads();
-        uint32_t div = 1;
-        for (int pass = 0; pass < passes; ++pass) {
+        uint16_t *cb = WIDE ? codes + b * n : nullptr;
+        if (tid < 2) sums[tid] = 0;
+        // codes of four columns at a time, two per register: c = c * base + digit, last row first
+        uint32_t bad = 0;
+        for (int j = 4 * tid; j < n; j += 4 * NT) {
+            uint32_t even = 0, odd = 0;
+            const int valid = (int)min((int64_t)k, rows - b * k);
+            const int8_t *col = M + b * k * n + j;
+            for (int r0 = (valid - 1) & ~3; r0 >= 0; r0 -= 4) {
+                uint32_t x[4];
 #pragma unroll
-            for (int d = 0; d < R; ++d) cnt[d * kThreads + tid] = 0;
-            for (int t = lo; t < hi; ++t) {                      // count
-                const uint32_t d = ((uint32_t)cb[A[t]] / div) % R;
-                cnt[d * kThreads + tid] += 1;
+                for (int i = 0; i < 4; ++i) {
+                    x[i] = 0;
+                    if (r0 + i >= valid) continue;
+                    const int8_t *at = col + (int64_t)(r0 + i) * n;
+                    if (j + 4 <= n) {
+                        x[i] = *reinterpret_cast<const u32_any *>(at);
+                    } else {
+                        for (int e = 0; j + e < n; ++e) x[i] |= (uint32_t)(uint8_t)at[e] << (8 * e);
+                    }
+                }
+#pragma unroll
+                for (int i = 3; i >= 0; --i) {
+                    const uint32_t d = digits4(x[i], mode, &bad);
+                    even = even * base + (d & 0x00ff00ffu);
+                    odd = odd * base + ((d >> 8) & 0x00ff00ffu);
+                }
+            }
+            const uint32_t c[4] = {even & 0xffffu, odd & 0xffffu, even >> 16, odd >> 16};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (j + e < n) {
+                    if (WIDE) {
+                        cb[j + e] = (uint16_t)c[e];
+                        A[j + e] = (Item)(j + e);
+                    } else {
+                        A[j + e] = (Item)(c[e] << 16 | (uint32_t)(j + e));
+                    }
+                }
+        }
+        if (bad) atomicOr(err_flag, 1);
+        auto code_of = [&](Item x) -> uint32_t { return WIDE ? (uint32_t)cb[x] : (uint32_t)x >> 16; };
+        for (int shift = 0; shift < bits; shift += step_bits) {
+            const int nbits = min(step_bits, bits - shift);
+            for (int i = tid; i < (W << nbits); i += NT) cnt[i] = 0;
+            __syncthreads();
+            // lanes of the wave with the same digit
+            auto peers = [&](uint32_t digit, bool valid) {
+                uint64_t m = __ballot(valid);
+                for (int i = 0; i < nbits; ++i) {
+                    const bool set = (digit >> i) & 1u;
+                    const uint64_t ones = __ballot(set);
+                    m &= set ? ones : ~ones;
+                }
+                return m;
+            };
+            const uint32_t mask = (1u << nbits) - 1u;
+            for (int t = lo + lane; t < hi; t += 64)  // count
+                atomicAdd(&cnt[((code_of(A[t]) >> shift) & mask) * W + w], 1u);
+            __syncthreads();
+            if (w == 0) {  // exclusive scan over [digit][wave]
+                const int each = ((W << nbits) + 63) / 64;
+                uint32_t sum = 0;
+                for (int i = 0; i < each; ++i)
+                    if (lane * each + i < (W << nbits)) sum += cnt[lane * each + i];
+                uint32_t run = wave_inclusive_scan(sum) - sum;
+                for (int i = 0; i < each; ++i)
+                    if (lane * each + i < (W << nbits)) {
+                        const uint32_t x = cnt[lane * each + i];
+                        cnt[lane * each + i] = run;
+                        run += x;
+                    }
             }
             __syncthreads();
-            // exclusive scan over the bucket-major array cnt[R*kThreads]
-            uint32_t local[R], sum = 0;
-#pragma unroll
-            for (int i = 0; i < R; ++i) { local[i] = cnt[tid * R + i]; sum += local[i]; }
-            uint32_t total;
-            uint32_t run = wg_exclusive_scan(sum, wsum, &total);
-#pragma unroll
-            for (int i = 0; i < R; ++i) { cnt[tid * R + i] = run; run += local[i]; }
-            __syncthreads();
-            for (int t = lo; t < hi; ++t) {                      // stable placement
-                const uint16_t j = A[t];
-                const uint32_t d = ((uint32_t)cb[j] / div) % R;
-                const uint32_t dst = cnt[d * kThreads + tid]++;
-                B[dst] = j;
+            for (int t0 = lo; t0 < hi; t0 += 64) {  // stable placement
+                const int t = t0 + lane;
+                const bool valid = t < hi;
+                const Item x = valid ? A[t] : Item(0);
+                const uint32_t digit = valid ? (code_of(x) >> shift) & mask : 0u;
+                const uint64_t m = peers(digit, valid);
+                const uint32_t rank =
+                    __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                if (valid) {
+                    const uint32_t first = cnt[digit * W + w];
+                    B[first + rank] = x;
+                    // (the wave's LDS operations execute in order: everybody has read it)
+                    if (rank == 0) cnt[digit * W + w] = first + (uint32_t)__popcll(m);
+                }
             }
             __syncthreads();
-            uint16_t *tmp = A; A = B; B = tmp;
-            div *= R;
+            Item *tmp = A; A = B; B = tmp;
         }
         // A is pi_b.  Group boundaries: off[c] = first position whose code >= c.
         uint16_t *pib = pi + b * n;
         uint32_t *ob = off + b * (P + 1);
-        for (int t = tid; t < n; t += kThreads) {
-            const uint16_t j = A[t];
-            pib[t] = j;
-            const int64_t ccur = cb[j];
-            const int64_t cprev = t ? (int64_t)cb[A[t - 1]] : -1;
-            for (int64_t c = cprev + 1; c <= ccur; ++c) ob[c] = (uint32_t)t;
+        uint32_t groups = 0;
+        for (int t = tid; t < n; t += NT) {
+            const Item x = A[t];
+            pib[t] = (uint16_t)x;
+            const int64_t cur = code_of(x), prev = t ? (int64_t)code_of(A[t - 1]) : -1;
+            for (int64_t c = prev + 1; c <= cur; ++c) ob[c] = (uint32_t)t;
             if (t == n - 1)
-                for (int64_t c = ccur + 1; c <= P; ++c) ob[c] = (uint32_t)n;
+                for (int64_t c = cur + 1; c <= P; ++c) ob[c] = (uint32_t)n;
+            if (cur != prev && cur > 0) {
+                ++groups;
+                if (prev <= 0) sums[1] = (uint32_t)(n - t);
+            }
+        }
+        if (groups) atomicAdd(&sums[0], groups);
+        __syncthreads();
+        if (tid == 0) {
+            const uint32_t some = sums[0], real = sums[1];
+            const uint32_t mine[3] = {real, real + (uint32_t)(P - 1) - some, some};
+            for (int i = 0; i < 3; ++i)
+                if (mine[i] > __hip_atomic_load(&stats[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                    atomicMax(&stats[i], mine[i]);
         }
         __syncthreads();
     }
 }
 
+// ---- the stream of the multiply kernel -------------------------------------------------------
 // Slabs wave w owns when S slabs are dealt to W waves, the longer shares first.
 __device__ __forceinline__ void wave_share(int S, int W, int w, int *first, int *count) {
     const int per = S / W, rem = S - per * W;
@@ -156,294 +225,290 @@ __device__ __forceinline__ void wave_share(int S, int W, int w, int *first, int 
     *count = per + (w < rem ? 1 : 0);
 }
 
-// stats[0] = max over blocks of the columns outside group 0; stats[1] = the same plus one
-// placeholder per empty group among codes 1..P-1; stats[2] = most non-empty groups among
-// codes 1..P-1.  The caller zeroes stats.
-__global__ __launch_bounds__(kThreads) void k_stream_stats(const uint32_t *__restrict__ off,
-                                                           int64_t nb, int64_t n, int64_t P,
-                                                           uint32_t *__restrict__ stats) {
-    __shared__ uint32_t empties;
-    for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
-        const uint32_t *ob = off + b * (P + 1);
-        if (threadIdx.x == 0) empties = 0;
-        __syncthreads();
-        uint32_t mine = 0;
-        for (int64_t c = 1 + threadIdx.x; c < P; c += kThreads) mine += (ob[c + 1] == ob[c]);
-        if (mine) atomicAdd(&empties, mine);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const uint32_t real = (uint32_t)(n - ob[1]);
-            atomicMax(&stats[0], real);
-            atomicMax(&stats[1], real + empties);
-            atomicMax(&stats[2], (uint32_t)(P - 1) - empties);
-        }
-        __syncthreads();
-    }
-}
-
-// Logical stream of block b (L entries): for code c = 1..P-1 in order, the columns of
-// group c in ascending order (entry = column<<1, last one |1).  Indexed by code: an empty
-// group contributes one placeholder entry (zero slot = index n, tail bit set), so that
-// every code owns exactly one tail.  Indexed by rank: empty groups contribute nothing and
-// gcode[b][rank] records the code of every non-empty group (rank 1.., gcode[b][0] = 0,
-// zeros behind the last one), gcount[b] their number.  Filler entries (zero slot, no tail)
-// up to L.
-__global__ __launch_bounds__(kThreads) void k_pack_stream(const uint16_t *__restrict__ pi,
-                                                          const uint32_t *__restrict__ off,
-                                                          int64_t nb, int n, int64_t P, int64_t L,
-                                                          int by_rank, int64_t slots,
-                                                          uint16_t *__restrict__ stream,
-                                                          uint16_t *__restrict__ gcode,
-                                                          uint32_t *__restrict__ gcount) {
-    __shared__ uint32_t wsum[kWaves];
-    const uint16_t zero_entry = (uint16_t)(n << 1);
-    for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
-        const uint16_t *pib = pi + b * n;
-        const uint32_t *ob = off + b * (P + 1);
-        uint16_t *sb = stream + b * L;
-        uint16_t *gb = by_rank ? gcode + b * slots : nullptr;
-        const uint32_t off1 = ob[1];
-        uint32_t carry = 0;  // empty groups among the codes before the current batch
-        for (int64_t c0 = 1; c0 < P; c0 += kThreads) {
-            const int64_t c = c0 + threadIdx.x;
-            const bool valid = c < P;
-            const uint32_t s = valid ? ob[c] : 0, e = valid ? ob[c + 1] : 0;
-            const uint32_t empty = (valid && s == e) ? 1u : 0u;
-            uint32_t total;
-            const uint32_t eb = carry + wg_exclusive_scan(empty, wsum, &total);
-            if (valid) {
-                if (empty) {
-                    if (!by_rank) sb[s - off1 + eb] = zero_entry | 1;
-                } else {
-                    const uint32_t dst = s - off1 + (by_rank ? 0u : eb);
-                    for (uint32_t t = s; t < e; ++t)
-                        sb[dst + (t - s)] = (uint16_t)((pib[t] << 1) | (t + 1 == e ? 1 : 0));
-                    if (by_rank) gb[c - eb] = (uint16_t)c;
-                }
-            }
-            carry += total;
-        }
-        const int64_t len = (int64_t)(n - off1) + (by_rank ? 0 : carry);
-        for (int64_t t = len + threadIdx.x; t < L; t += kThreads) sb[t] = zero_entry;
-        if (by_rank) {
-            const int64_t count = P - 1 - carry;
-            if (threadIdx.x == 0) { gcount[b] = (uint32_t)count; gb[0] = 0; }
-            for (int64_t r = count + 1 + threadIdx.x; r < slots; r += kThreads) gb[r] = 0;
-        }
-        __syncthreads();
-    }
-}
-
-// Reorders the logical stream inside its groups so that the LDS gathers of the multiply
-// kernel collide less.  Gather instruction i of a wave reads entry i of all 64 strips of
-// the wave; the LDS serves the two half-waves side by side and needs one cycle per
-// distinct dword that falls on the same of its 32 banks.  The order of the columns inside
-// a group is free for the kernel (sums commute up to rounding; the canonical pi is not
-// touched), so for every run of entries of one group inside a strip, each slot takes the
-// remaining column whose banks are least loaded so far in that slot of the half-wave --
-// counted for both vector types the kernel serves: bank (col / 2) mod 32 for 2-byte
-// elements and col mod 32 for 4-byte elements; two more sweeps re-place every strip
-// against all the others.  One wave per (block, wave of the multiply kernel): thread =
-// (half-wave, slot), strips in order; the first slot of a run places the run.  Strips of
-// more than 32 entries are left as they are.
-constexpr int kSpreadSweeps = 3;
-constexpr int kSpreadMaxRun = 8;
-
-__global__ __launch_bounds__(64) void k_spread_banks(uint16_t *__restrict__ logical, int64_t nb,
-                                                     int S, int W) {
-    __shared__ uint8_t load2[2][32][33];  // [half][slot][bank of a 2-byte element], padded
-    __shared__ uint8_t load4[2][32][33];  // [half][slot][bank of a 4-byte element]
-    __shared__ uint16_t strip[64][33];    // the wave's part: [strip][slot], padded
-    const int half = threadIdx.x >> 5, slot = threadIdx.x & 31;
-    for (int64_t unit = blockIdx.x; unit < nb * W; unit += gridDim.x) {
-        const int64_t b = unit / W;
-        int first, count;
-        wave_share(S, W, (int)(unit - b * W), &first, &count);
-        const int epl = 8 * count;
-        if (epl == 0 || epl > 32) continue;
-        const bool live = slot < epl;
-        uint16_t *cb = logical + (b * S + first) * kSlab;
-        for (int i = threadIdx.x; i < 64 * epl; i += 64) strip[i / epl][i % epl] = cb[i];
-        for (int k = 0; k < 33; ++k) { load2[half][slot][k] = 0; load4[half][slot][k] = 0; }
-        __syncthreads();
-        for (int sweep = 0; sweep < kSpreadSweeps; ++sweep) {
-            for (int l = 0; l < 32; ++l) {
-                uint16_t *st = strip[32 * half + l];
-                // slots past the strip count as tails, so that no run reaches into them
-                const uint32_t entry = live ? st[slot] : 1u;
-                const uint32_t tail = entry & 1u;
-                const uint64_t ball = __ballot(tail != 0);
-                const uint32_t tails = (uint32_t)(ball >> (32 * half));
-                if (live) {
-                    st[slot] = (uint16_t)(entry >> 1);  // columns only while the strip is placed
-                    if (sweep > 0) {
-                        --load2[half][slot][(entry >> 2) & 31];
-                        --load4[half][slot][(entry >> 1) & 31];
-                    }
-                }
-                __syncthreads();
-                const bool start = live && (slot == 0 || ((tails >> (slot - 1)) & 1u));
-                if (start) {
-                    const uint32_t rest = tails >> slot;
-                    int e = rest ? slot + __builtin_ctz(rest) : epl - 1;
-                    if (e > epl - 1) e = epl - 1;
-                    // (long runs -- filler behind the last group, or one very common pattern --
-                    // are counted as they stand: placing them would cost run^2 steps)
-                    const bool place = e - slot < kSpreadMaxRun;
-                    for (int sl = slot; sl <= e; ++sl) {
-                        int best = sl;
-                        int bl = load2[half][sl][(st[sl] >> 1) & 31] + load4[half][sl][st[sl] & 31];
-                        for (int t = sl + 1; place && t <= e; ++t) {
-                            const int x = load2[half][sl][(st[t] >> 1) & 31] + load4[half][sl][st[t] & 31];
-                            if (x < bl) { bl = x; best = t; }
-                        }
-                        const uint16_t c = st[best];
-                        st[best] = st[sl];
-                        st[sl] = c;
-                        ++load2[half][sl][(c >> 1) & 31];
-                        ++load4[half][sl][c & 31];
-                    }
-                }
-                __syncthreads();
-                if (live) st[slot] = (uint16_t)((st[slot] << 1) | tail);
-            }
-        }
-        __syncthreads();
-        for (int i = threadIdx.x; i < 64 * epl; i += 64) cb[i] = strip[i / epl][i % epl];
-        __syncthreads();
-    }
-}
-
-// Final layout of the stream (see PassData): re-encodes the entries, moves them to the
-// slabs, and records for every strip the slot of the first tail at or after its start
-// (1 + tails before it).  Also checks that the block holds the expected number of tails:
-// P - 1 (indexed by code) or gcount[b] (indexed by rank).
-__global__ __launch_bounds__(kThreads) void k_finalize_stream(
-    const uint16_t *__restrict__ logical, int64_t nb, int64_t P, int S, int W, int enc,
-    const uint32_t *__restrict__ gcount, uint16_t *__restrict__ entries,
-    uint16_t *__restrict__ start, int *__restrict__ err_flag) {
-    __shared__ uint32_t wsum[kWaves];
-    const int strips = W * 64;
-    for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
-        const uint16_t *lb = logical + b * S * kSlab;
-        uint32_t carry = 1;
-        for (int g0 = 0; g0 < strips; g0 += kThreads) {
-            const int g = g0 + threadIdx.x;
-            const int w = g >> 6, lane = g & 63;
-            int first = 0, count = 0;
-            if (g < strips) wave_share(S, W, w, &first, &count);
-            const int epl = 8 * count;
-            const uint16_t *sp = lb + (int64_t)first * kSlab + (int64_t)lane * epl;
-            uint32_t cnt = 0;
-            for (int i = 0; i < epl; ++i) cnt += sp[i] & 1u;
-            uint32_t total;
-            const uint32_t ex = wg_exclusive_scan(cnt, wsum, &total);
-            if (g < strips) {
-                start[(b * W + w) * 64 + lane] = (uint16_t)(carry + ex);
-                for (int i = 0; i < epl; ++i) {
-                    const uint32_t e = sp[i];
-                    const uint32_t out = (enc == kEncSmall) ? (((e & 1u) << 15) | (e & 0xfffeu)) : e;
-                    entries[(((b * S + first + (i >> 3)) * 64) + lane) * 8 + (i & 7)] = (uint16_t)out;
-                }
-            }
-            carry += total;
-        }
-        const int64_t expect = gcount ? (int64_t)gcount[b] : P - 1;
-        if (threadIdx.x == 0 && (int64_t)carry != expect + 1) atomicOr(err_flag, 2);
-        __syncthreads();
-    }
-}
-
 // Sign of digit r of code c as a 2-bit two's complement field (00: 0, 01: +1, 11: -1).
-__device__ __forceinline__ uint32_t sign2_of(uint32_t c, int r, int base) {
-    for (int i = 0; i < r; ++i) c /= (uint32_t)base;
-    const uint32_t d = c % (uint32_t)base;
+template <int BASE>
+__device__ __forceinline__ uint32_t sign2_of(uint32_t c, int r) {
+    for (int i = 0; i < r; ++i) c /= (uint32_t)BASE;
+    const uint32_t d = c % (uint32_t)BASE;
     return d == 0 ? 0u : d == 1 ? 1u : 3u;
 }
-__device__ __forceinline__ int sign_of(uint32_t c, int r, int base) {
-    const uint32_t s = sign2_of(c, r, base);
+template <int BASE>
+__device__ __forceinline__ int sign_of(uint32_t c, int r) {
+    const uint32_t s = sign2_of<BASE>(c, r);
     return s == 3u ? -1 : (int)s;
 }
 
-// Code of the first group closed at or after the start of the strip that follows strip g of
-// block b; false when there is none (last strip, or no tail from there on).
-__device__ __forceinline__ bool next_strip_code(const uint16_t *__restrict__ start, int64_t b, int g,
-                                                int strips, int64_t P,
-                                                const uint16_t *__restrict__ gcode,
-                                                const uint32_t *__restrict__ gcount, int64_t slots,
-                                                uint32_t *code) {
-    if (g + 1 >= strips) return false;
-    const uint32_t slot = start[b * strips + g + 1];
-    if (gcode) {
-        if (slot > gcount[b]) return false;
-        *code = gcode[b * slots + slot];
-        return true;
-    }
-    if ((int64_t)slot >= P) return false;
-    *code = slot;
-    return true;
-}
+// Reorders the stream inside its groups so that the LDS gathers of the multiply kernel collide
+// less.  Gather instruction i of a wave reads entry i of all 64 strips of the wave; the LDS serves
+// the two half-waves side by side and needs one cycle per distinct dword that falls on the same
+// of its 32 banks.  The order of the columns inside a group is free for the kernel (sums commute
+// up to rounding; the canonical pi is not touched), so for every run of entries of one group
+// inside a strip, each slot takes the remaining column whose banks are least loaded so far in
+// that slot of the half-wave -- counted for both vector types the kernel serves: bank
+// (col / 2) mod 32 for 2-byte elements and col mod 32 for 4-byte elements; a second sweep
+// re-places every strip against all the others.  (Left as sorted, the product of
+// the metric workload takes 3.5 % longer than with three sweeps of whole runs; with two of pieces 0.7 %.)
+// One wave per wave of the
+// multiply kernel: lane = (half-wave, slot), strips in order.  Runs are placed in pieces of four,
+// each by the lane of its first slot, with the reads of a piece independent of each other: placing
+// whole runs of up to eight took four times as long.  Strips of more than 32 entries are left as
+// they are.
+constexpr int kSpreadSweeps = 2;
+constexpr int kSpreadRun = 4;
+constexpr int kSpreadPad = 33;                                  // bytes per (slot, banks)
+constexpr int kSpreadWaveBytes = 2 * 2 * 32 * kSpreadPad;       // [half][bank kind][slot][bank]
 
-// Strip signs, indexed by code: word (b, r, l) holds, at bits 2w, the sign of digit r of the
-// code that follows strip (w, l).  16-bit words when W <= 8.
-__global__ __launch_bounds__(kThreads) void k_strip_signs_rows(const uint16_t *__restrict__ start,
-                                                               int64_t nb, int W, int k, int base,
-                                                               int64_t P, void *__restrict__ sgn) {
-    const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (gid >= nb * k * 64) return;
-    const int lane = (int)(gid & 63);
-    const int r = (int)((gid >> 6) % k);
-    const int64_t b = (gid >> 6) / k;
-    uint32_t word = 0;
-    for (int w = 0; w < W; ++w) {
-        uint32_t c;
-        if (next_strip_code(start, b, w * 64 + lane, W * 64, P, nullptr, nullptr, 0, &c))
-            word |= sign2_of(c, r, base) << (2 * w);
-    }
-    if (W <= 8)
-        static_cast<uint16_t *>(sgn)[gid] = (uint16_t)word;
-    else
-        static_cast<uint32_t *>(sgn)[gid] = word;
-}
-
-// Strip signs, indexed by rank: word (b, w, l) holds, at bits 2r, the sign of digit r of
-// the code that follows strip (w, l).
-__global__ __launch_bounds__(kThreads) void k_strip_signs_strips(
-    const uint16_t *__restrict__ start, int64_t nb, int W, int k, int base, int64_t P,
-    const uint16_t *__restrict__ gcode, const uint32_t *__restrict__ gcount, int64_t slots,
-    uint32_t *__restrict__ sgn) {
-    const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (gid >= nb * W * 64) return;
-    const int g = (int)(gid % (W * 64));
-    const int64_t b = gid / (W * 64);
-    uint32_t word = 0, c;
-    if (next_strip_code(start, b, g, W * 64, P, gcode, gcount, slots, &c))
-        for (int r = 0; r < k; ++r) word |= sign2_of(c, r, base) << (2 * r);
-    sgn[gid] = word;
-}
-
-// Weights of the slots of a rank-indexed E: field r of gword[b][s] (fw bits, two's
-// complement) = sgn_r(code of rank s) - sgn_r(code of rank s+1), the second term 0 behind
-// the last group; 0 for s = 0 and behind the last group.
-__global__ __launch_bounds__(kThreads) void k_group_words(const uint16_t *__restrict__ gcode,
-                                                          const uint32_t *__restrict__ gcount,
-                                                          int64_t nb, int64_t slots, int k, int base,
-                                                          int fw, uint32_t *__restrict__ gword) {
-    const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (gid >= nb * slots) return;
-    const int64_t b = gid / slots, s = gid - b * slots;
-    const int64_t count = gcount[b];
-    uint32_t word = 0;
-    if (s >= 1 && s <= count) {
-        const uint32_t c = gcode[gid];
-        const bool has_next = s < count;
-        const uint32_t cn = has_next ? gcode[gid + 1] : 0u;
-        for (int r = 0; r < k; ++r) {
-            const int wgt = sign_of(c, r, base) - (has_next ? sign_of(cn, r, base) : 0);
-            word |= ((uint32_t)wgt & ((1u << fw) - 1u)) << (fw * r);
+__device__ __forceinline__ void spread_banks(uint16_t *part, int epl, uint8_t *loads) {
+    const int lane = threadIdx.x & 63, half = lane >> 5, slot = lane & 31;
+    uint8_t *load2 = loads + half * 2 * 32 * kSpreadPad + slot * kSpreadPad;  // [bank of a 2-byte element]
+    uint8_t *load4 = load2 + 32 * kSpreadPad;                                 // [bank of a 4-byte element]
+    for (int i = 0; i < kSpreadPad; ++i) load2[i] = load4[i] = 0;
+    const bool live = slot < epl;
+    for (int sweep = 0; sweep < kSpreadSweeps; ++sweep) {
+        for (int l = 0; l < 32; ++l) {
+            uint16_t *st = part + (32 * half + l) * epl + slot;
+            // slots past the strip count as tails, so that no run reaches into them
+            const uint32_t entry = live ? *st : 1u;
+            const uint32_t tails = (uint32_t)(__ballot(entry & 1u) >> (32 * half));
+            if (live && sweep > 0) {
+                --load2[(entry >> 2) & 31];
+                --load4[(entry >> 1) & 31];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const uint32_t behind = tails & ((1u << slot) - 1u), rest = tails >> slot;
+            const int run = behind ? 32 - __builtin_clz(behind) : 0;  // first slot of the run
+            const int last = min(rest ? slot + __builtin_ctz(rest) : epl - 1, epl - 1);
+            if (live && ((slot - run) & (kSpreadRun - 1)) == 0) {
+                const int len = min(last - slot + 1, kSpreadRun);
+                const uint32_t flag = (rest >> (len - 1)) & 1u;  // the piece's last entry is a tail
+                uint32_t x[kSpreadRun];
+#pragma unroll
+                for (int i = 0; i < kSpreadRun; ++i) x[i] = i < len ? (uint32_t)st[i] >> 1 : 0u;
+#pragma unroll
+                for (int i = 0; i < kSpreadRun; ++i) {
+                    if (i >= len) break;
+                    uint8_t *l2 = load2 + i * kSpreadPad, *l4 = load4 + i * kSpreadPad;
+                    uint32_t c2[kSpreadRun], c4[kSpreadRun];
+#pragma unroll
+                    for (int t = i; t < kSpreadRun; ++t) {
+                        c2[t] = l2[(x[t] >> 1) & 31];
+                        c4[t] = l4[x[t] & 31];
+                    }
+                    uint32_t best = x[i], b2 = c2[i], b4 = c4[i];
+#pragma unroll
+                    for (int t = i + 1; t < kSpreadRun; ++t)
+                        if (t < len && c2[t] + c4[t] < b2 + b4) {
+                            b2 = c2[t];
+                            b4 = c4[t];
+                            const uint32_t y = x[t];
+                            x[t] = best;  // (the column it replaces stays among the remaining ones)
+                            best = y;
+                        }
+                    l2[(best >> 1) & 31] = (uint8_t)(b2 + 1);
+                    l4[best & 31] = (uint8_t)(b4 + 1);
+                    st[i] = (uint16_t)(best << 1 | (i == len - 1 ? flag : 0u));
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
         }
     }
-    gword[gid] = word;
+}
+
+struct StreamArgs {
+    const uint16_t *pi;
+    const uint32_t *off;
+    int64_t nb, P, slots;
+    int n, S, W, k, enc, by_rank, fw, spread;  // spread: the strips are short enough to be spread
+    uint16_t *entries, *start;
+    void *sgn;
+    uint32_t *gword, *gcount;
+    int *err_flag;
+};
+
+constexpr int kLongGroup = 64;  // groups from here on are copied by the whole workgroup
+
+// LDS of k_build_stream, byte offsets.
+struct StreamLds {
+    int gcode, start, loads, longs, wsum, holes, total;
+};
+inline __host__ __device__ StreamLds stream_lds(int n, int64_t P, int S, int W, int64_t slots, int by_rank,
+                                              int spread) {
+    StreamLds o;
+    o.gcode = S * kSlab * 2;                                              // the stream comes first
+    o.start = o.gcode + (by_rank ? (int)((slots * 2 + 15) & ~(int64_t)15) : 0);
+    o.loads = o.start + ((W * 64 + 1) * 2 + 15) / 16 * 16;
+    o.longs = o.loads + (spread ? W * kSpreadWaveBytes : 0);
+    o.wsum = o.longs + (n / kLongGroup + 2) * 12;
+    o.holes = o.wsum + 16 * 4;
+    o.total = o.holes + (int)(P / 64 + 16) * 4;
+    return o;
+}
+
+// Stream of block b (L = 512 S entries): for code c = 1..P-1 in order, the columns of group c
+// (entry = column<<1, last one |1).  Indexed by code: an empty group contributes one placeholder
+// entry (zero slot = index n, tail bit set), so that every code owns exactly one tail.  Indexed by
+// rank: empty groups contribute nothing and gcode[rank] records the code of every non-empty group
+// (rank 1.., gcode[0] = 0), gcount[b] their number.  Filler entries (zero slot, no tail) up to L.
+// Then the columns are spread over the banks, every strip gets the slot of the first tail at or
+// after its start (1 + tails before it), the entries go to their slabs (see PassData), and the signs
+// of the strips and the weights of the slots follow from the codes.
+template <int BASE>
+__global__ __launch_bounds__(1024) void k_build_stream(const StreamArgs a) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const StreamLds at = stream_lds(a.n, a.P, a.S, a.W, a.slots, a.by_rank, a.spread);
+    uint16_t *stream = reinterpret_cast<uint16_t *>(smem);
+    uint16_t *gcode = reinterpret_cast<uint16_t *>(smem + at.gcode);
+    uint16_t *first_slot = reinterpret_cast<uint16_t *>(smem + at.start);
+    uint32_t *longs = reinterpret_cast<uint32_t *>(smem + at.longs);  // count, -, -, then {from, to, length}
+    uint32_t *wsum = reinterpret_cast<uint32_t *>(smem + at.wsum);
+    uint32_t *holes = reinterpret_cast<uint32_t *>(smem + at.holes);  // [round][wave]
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, NT = blockDim.x, waves = NT >> 6;
+    const int L = a.S * kSlab, strips = a.W * 64;
+    const uint16_t zero_entry = (uint16_t)(a.n << 1);
+    const int64_t b = blockIdx.x;
+    const uint16_t *pib = a.pi + b * a.n;
+    const uint32_t *ob = a.off + b * (a.P + 1);
+    const uint32_t off1 = ob[1];
+    if (tid == 0) longs[0] = 0;
+
+    // ---- logical order: rounds of NT codes; empty groups are counted per (round, wave) first ------
+    const int rounds = (int)((a.P - 1 + NT - 1) / NT);
+#pragma unroll 4
+    for (int r = 0; r < rounds; ++r) {
+        const int64_t c = 1 + (int64_t)r * NT + tid;
+        const uint64_t none = __ballot(c < a.P && ob[min(c, a.P - 1)] == ob[min(c + 1, a.P)]);
+        if (lane == 0) holes[r * waves + w] = (uint32_t)__popcll(none);
+    }
+    __syncthreads();
+    uint32_t empties = 0;
+    for (int i0 = 0; i0 < rounds * waves; i0 += NT) {
+        const uint32_t x = i0 + tid < rounds * waves ? holes[i0 + tid] : 0u;
+        uint32_t sum;
+        const uint32_t ex = empties + wg_exclusive_scan(x, wsum, waves, &sum);
+        if (i0 + tid < rounds * waves) holes[i0 + tid] = ex;
+        empties += sum;
+    }
+    __syncthreads();
+    for (int r = 0; r < rounds; ++r) {
+        const int64_t c = 1 + (int64_t)r * NT + tid;
+        const uint32_t s = ob[min(c, a.P - 1)], e = ob[min(c + 1, a.P)];
+        const uint64_t none = __ballot(c < a.P && s == e);
+        const uint32_t eb = holes[r * waves + w] +  // empty groups before code c
+            __builtin_amdgcn_mbcnt_hi((uint32_t)(none >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)none, 0u));
+        if (c >= a.P) continue;
+        const uint32_t to = s - off1 + (a.by_rank ? 0u : eb);
+        if (s == e) {
+            if (!a.by_rank) stream[to] = zero_entry | 1;
+            continue;
+        }
+        if (a.by_rank) gcode[c - eb] = (uint16_t)c;
+        if (e - s >= kLongGroup) {
+            uint32_t *l = longs + 3 + 3 * atomicAdd(&longs[0], 1u);
+            l[0] = s; l[1] = to; l[2] = e - s;
+        } else {
+            for (uint32_t t = s; t < e; t += 4) {  // four columns in flight
+                uint32_t col[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) col[i] = pib[min(t + i, e - 1)];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (t + i < e) stream[to + (t + i - s)] = (uint16_t)(col[i] << 1 | (t + i + 1 == e ? 1u : 0u));
+            }
+        }
+    }
+    const int len = (int)(a.n - off1) + (a.by_rank ? 0 : (int)empties);
+    for (int t = len + tid; t < L; t += NT) stream[t] = zero_entry;
+    const int64_t count = a.P - 1 - empties;
+    if (a.by_rank && tid == 0) { a.gcount[b] = (uint32_t)count; gcode[0] = 0; }
+    __syncthreads();
+    for (uint32_t i = 0; i < longs[0]; ++i) {
+        const uint32_t s = longs[3 + 3 * i], to = longs[4 + 3 * i], m = longs[5 + 3 * i];
+        for (uint32_t t = tid; t < m; t += NT) stream[to + t] = (uint16_t)((pib[s + t] << 1) | (t + 1 == m ? 1 : 0));
+    }
+    __syncthreads();
+
+    // ---- banks ---------------------------------------------------------------------------------
+    int first = 0, slabs = 0;  // of this wave
+    if (w < a.W) wave_share(a.S, a.W, w, &first, &slabs);
+    const int epl = 8 * slabs;
+    if (a.spread && w < a.W && epl > 0 && epl <= 32)
+        spread_banks(stream + first * kSlab, epl, smem + at.loads + w * kSpreadWaveBytes);
+    __syncthreads();
+
+    // ---- strips --------------------------------------------------------------------------------
+    const uint4 *strip = reinterpret_cast<const uint4 *>(stream + first * kSlab + lane * epl);
+    uint32_t tails = 0;
+    for (int h = 0; h < slabs; ++h) {
+        const uint4 d = strip[h];
+        tails += __popc(d.x & 0x00010001u) + __popc(d.y & 0x00010001u) + __popc(d.z & 0x00010001u) +
+                 __popc(d.w & 0x00010001u);
+    }
+    uint32_t total;
+    const uint32_t slot = 1 + wg_exclusive_scan(tails, wsum, waves, &total);
+    if (w < a.W) {
+        a.start[(b * a.W + w) * 64 + lane] = (uint16_t)slot;
+        first_slot[w * 64 + lane] = (uint16_t)slot;
+        uint4 *to = reinterpret_cast<uint4 *>(a.entries) + (b * a.S + first) * 64 + lane;
+        for (int h = 0; h < slabs; ++h) {
+            uint4 d = strip[h];
+            if (a.enc == kEncSmall) {
+                d.x = ((d.x & 0x00010001u) << 15) | (d.x & 0xfffefffeu);
+                d.y = ((d.y & 0x00010001u) << 15) | (d.y & 0xfffefffeu);
+                d.z = ((d.z & 0x00010001u) << 15) | (d.z & 0xfffefffeu);
+                d.w = ((d.w & 0x00010001u) << 15) | (d.w & 0xfffefffeu);
+            }
+            to[h * 64] = d;
+        }
+    }
+    // every block holds exactly P - 1 (by code) or `count` (by rank) tails
+    if (tid == 0 && (int64_t)total != (a.by_rank ? count : a.P - 1)) atomicOr(a.err_flag, 2);
+    __syncthreads();
+
+    // ---- signs of the strips: digits of the first group closed at or after the start of the next
+    // strip, if there is one -----------------------------------------------------------------------
+    if (!a.by_rank) {
+        // word (b, r, l): row r at bits 2w for strip (w, l); 16-bit words when W <= 8
+        for (int i = tid; i < a.k * 64; i += NT) {
+            const int r = i >> 6, l = i & 63;
+            uint32_t word = 0;
+            for (int v = 0; v < a.W; ++v) {
+                const int g = v * 64 + l + 1;
+                const uint32_t c = g < strips ? first_slot[g] : 0xffffffffu;
+                if (c < a.P) word |= sign2_of<BASE>(c, r) << (2 * v);
+            }
+            const int64_t to = (b * a.k) * 64 + i;
+            if (a.W <= 8)
+                static_cast<uint16_t *>(a.sgn)[to] = (uint16_t)word;
+            else
+                static_cast<uint32_t *>(a.sgn)[to] = word;
+        }
+        return;
+    }
+    // word (b, w, l): strip (w, l), row r at bits 2r
+    for (int g = tid; g < strips; g += NT) {
+        uint32_t word = 0;
+        const uint32_t next = g + 1 < strips ? first_slot[g + 1] : 0xffffffffu;
+        if (next <= count) {
+            const uint32_t c = gcode[next];
+            for (int r = 0; r < a.k; ++r) word |= sign2_of<BASE>(c, r) << (2 * r);
+        }
+        static_cast<uint32_t *>(a.sgn)[b * strips + g] = word;
+    }
+    // weights of the slots: field r (fw bits, two's complement) = sgn_r(code of rank s) -
+    // sgn_r(code of rank s+1), the second term 0 behind the last group; 0 for s = 0 and behind it
+    for (int64_t s = tid; s < a.slots; s += NT) {
+        uint32_t word = 0;
+        if (s >= 1 && s <= count) {
+            const uint32_t c = gcode[s], next = s < count ? gcode[s + 1] : 0u;
+            for (int r = 0; r < a.k; ++r) {
+                const int wgt = sign_of<BASE>(c, r) - sign_of<BASE>(next, r);
+                word |= ((uint32_t)wgt & ((1u << a.fw) - 1u)) << (a.fw * r);
+            }
+        }
+        a.gword[b * a.slots + s] = word;
+    }
 }
 
 // Plain fill (used instead of a memset node so that callers may capture the sequence).
@@ -477,8 +542,6 @@ __global__ __launch_bounds__(kThreads) void k_unsort(const uint16_t *__restrict_
     }
 }
 
-int grid_for_blocks(int64_t nb) { return (int)(nb < 4096 ? nb : 4096); }
-
 // T[j][i] = M[i][j] through 64 x 64 tiles in LDS (coalesced on both sides).
 __global__ __launch_bounds__(256) void k_transpose_i8(const int8_t *__restrict__ M, int64_t rows,
                                                       int64_t cols, int8_t *__restrict__ T) {
@@ -497,40 +560,48 @@ __global__ __launch_bounds__(256) void k_transpose_i8(const int8_t *__restrict__
     }
 }
 
-}  // namespace
+// Columns a block can have if it is sorted as (code, column) pairs.
+constexpr int kPairColumns = 18 * 1024;
 
-hipError_t launch_encode(const int8_t *M, int64_t rows, int64_t cols, int k, int mode,
-                         uint16_t *code, int *err_flag) {
+template <int NT, bool WIDE>
+hipError_t launch_sort(const int8_t *M, int64_t rows, int64_t cols, int k, int base, int mode, int64_t P,
+                       uint16_t *codes, uint16_t *pi, uint32_t *off, uint32_t *stats, int *err_flag) {
+    static std::atomic<size_t> enabled[kMaxDevices];
     const int64_t nb = (rows + k - 1) / k;
-    const int64_t cols_pad = (cols + kThreads - 1) / kThreads * kThreads;
-    const int64_t groups = nb * cols_pad / kThreads;
-    hipLaunchKernelGGL(k_encode, dim3((unsigned)groups), dim3(kThreads), 0, 0, M, rows, cols, k,
-                       mode, nb, code, err_flag);
+    const int64_t npad = (cols + 7) & ~(int64_t)7;
+    const size_t lds = (size_t)npad * (WIDE ? 4 : 8) + (((NT / 64) << kDigitBits) + 2) * 4;
+    int bits = 1, device = 0;
+    while (((int64_t)1 << bits) < P) ++bits;
+    if (hipError_t e = hipGetDevice(&device)) return e;
+    auto kern = k_sort_columns<NT, WIDE>;
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, device, enabled)) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(nb < 65536 ? nb : 65536)), dim3(NT), lds, 0, M, rows, (int)cols, k, base,
+                       mode, nb, P, bits, codes, pi, off, stats, err_flag);
     return hipGetLastError();
 }
 
-hipError_t launch_sort(const uint16_t *code, int64_t nb, int64_t cols, int k, int base, int64_t P,
-                       uint16_t *pi, uint32_t *off) {
-    const int n = (int)cols;
-    const int npad = (n + 7) & ~7;
-    const int passes = (k + 1) / 2;
-    const int R = (base == 2) ? 4 : 9;
-    const size_t lds = (size_t)npad * 4 + (size_t)(R * kThreads + kWaves) * 4;
-    hipError_t e;
-    if (base == 2) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_sort<4>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_sort<4>, dim3(grid_for_blocks(nb)), dim3(kThreads), lds, 0, code, nb,
-                           n, passes, P, pi, off);
-    } else {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_sort<9>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_sort<9>, dim3(grid_for_blocks(nb)), dim3(kThreads), lds, 0, code, nb,
-                           n, passes, P, pi, off);
-    }
+template <int BASE>
+hipError_t launch_stream(const StreamArgs &a, int threads, size_t lds) {
+    static std::atomic<size_t> enabled[kMaxDevices];
+    int device = 0;
+    if (hipError_t e = hipGetDevice(&device)) return e;
+    auto kern = k_build_stream<BASE>;
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, device, enabled)) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)a.nb), dim3(threads), lds, 0, a);
     return hipGetLastError();
+}
+
+}  // namespace
+
+bool sort_needs_codes(int64_t cols) { return cols > kPairColumns; }
+
+hipError_t launch_sort_columns(const int8_t *M, int64_t rows, int64_t cols, int k, int base, int mode, int64_t P,
+                               uint16_t *codes, uint16_t *pi, uint32_t *off, uint32_t *stats, int *err_flag) {
+    if (sort_needs_codes(cols))
+        return launch_sort<512, true>(M, rows, cols, k, base, mode, P, codes, pi, off, stats, err_flag);
+    // (workgroups of 1024 threads do not share a CU: 4096 columns sort 2.3 times slower with them)
+    return cols > 512 ? launch_sort<512, false>(M, rows, cols, k, base, mode, P, codes, pi, off, stats, err_flag)
+                      : launch_sort<256, false>(M, rows, cols, k, base, mode, P, codes, pi, off, stats, err_flag);
 }
 
 hipError_t launch_unsort(const uint16_t *pi, const uint32_t *off, int64_t rows, int64_t cols, int k, int base,
@@ -547,49 +618,39 @@ hipError_t launch_transpose(const int8_t *M, int64_t rows, int64_t cols, int8_t 
     return hipGetLastError();
 }
 
-hipError_t launch_stream_stats(const uint32_t *off, int64_t nb, int64_t cols, int64_t P,
-                               uint32_t *stats) {
-    hipLaunchKernelGGL(k_stream_stats, dim3(grid_for_blocks(nb)), dim3(kThreads), 0, 0, off, nb,
-                       cols, P, stats);
-    return hipGetLastError();
-}
-
 hipError_t launch_fill_u32(uint32_t *p, uint32_t value, int64_t count) {
     hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)((count + kThreads - 1) / kThreads)), dim3(kThreads),
                        0, 0, p, value, count);
     return hipGetLastError();
 }
 
-hipError_t launch_pack_pass(const rsr_handle_s *h, int pass, uint16_t *logical, uint16_t *gcode,
-                            int *err_flag) {
+hipError_t launch_pack_pass(const rsr_handle_s *h, int pass, int *err_flag) {
     const PassData &pd = h->pass[pass];
-    const int64_t nb = h->nb, P = h->P;
-    const int S = (int)pd.S, W = h->W;
-    const int by_rank = h->by_rank;
-    auto blocks_for = [](int64_t threads) { return dim3((unsigned)((threads + kThreads - 1) / kThreads)); };
-    hipLaunchKernelGGL(k_pack_stream, dim3(grid_for_blocks(nb)), dim3(kThreads), 0, 0, pd.pi, pd.off,
-                       nb, (int)h->cols, P, (int64_t)S * kSlab, by_rank, h->slots, logical, gcode,
-                       pd.gcount);
-    if (hipError_t e = hipGetLastError()) return e;
-    const int64_t units = nb * W;
-    hipLaunchKernelGGL(k_spread_banks, dim3((unsigned)(units < 65536 ? units : 65536)), dim3(64), 0, 0,
-                       logical, nb, S, W);
-    if (hipError_t e = hipGetLastError()) return e;
-    hipLaunchKernelGGL(k_finalize_stream, dim3(grid_for_blocks(nb)), dim3(kThreads), 0, 0, logical, nb,
-                       P, S, W, h->enc, by_rank ? pd.gcount : nullptr, pd.entries, pd.start, err_flag);
-    if (hipError_t e = hipGetLastError()) return e;
-    if (by_rank) {
-        hipLaunchKernelGGL(k_strip_signs_strips, blocks_for(nb * W * 64), dim3(kThreads), 0, 0, pd.start,
-                           nb, W, h->k, h->base, P, gcode, pd.gcount, h->slots,
-                           static_cast<uint32_t *>(pd.sgn));
-        if (hipError_t e = hipGetLastError()) return e;
-        hipLaunchKernelGGL(k_group_words, blocks_for(nb * h->slots), dim3(kThreads), 0, 0, gcode,
-                           pd.gcount, nb, h->slots, h->k, h->base, gword_field_bits(h->base), pd.gword);
-    } else {
-        hipLaunchKernelGGL(k_strip_signs_rows, blocks_for(nb * h->k * 64), dim3(kThreads), 0, 0, pd.start,
-                           nb, W, h->k, h->base, P, pd.sgn);
-    }
-    return hipGetLastError();
+    StreamArgs a;
+    a.pi = pd.pi;
+    a.off = pd.off;
+    a.nb = h->nb;
+    a.P = h->P;
+    a.slots = h->slots;
+    a.n = (int)h->cols;
+    a.S = (int)pd.S;
+    a.W = h->W;
+    a.k = h->k;
+    a.enc = h->enc;
+    a.by_rank = h->by_rank;
+    a.fw = gword_field_bits(h->base);
+    a.spread = a.S / a.W <= 4;
+    a.entries = pd.entries;
+    a.start = pd.start;
+    a.sgn = pd.sgn;
+    a.gword = pd.gword;
+    a.gcount = pd.gcount;
+    a.err_flag = err_flag;
+    const StreamLds lds = stream_lds(a.n, a.P, a.S, a.W, a.slots, a.by_rank, a.spread);
+    if (lds.total > kLdsBytes) return hipErrorInvalidValue;
+    const int threads = a.W * 64 > 512 ? a.W * 64 : 512;
+    return h->base == 2 ? launch_stream<2>(a, threads, (size_t)lds.total)
+                        : launch_stream<3>(a, threads, (size_t)lds.total);
 }
 
 }  // namespace rsr

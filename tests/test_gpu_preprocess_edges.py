@@ -1,0 +1,53 @@
+"""Preprocessing at the edges of its kernels: columns around a wave, a workgroup and the widest
+matrix that is sorted as (code, column) pairs; block heights around the sorting steps of five bits;
+groups around the length that the whole workgroup copies.  The artifacts must be the oracle's bit
+for bit, and an integer-valued vector must come out exact."""
+import numpy as np
+import pytest
+
+import oracle
+import rsr_inputs as gen
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+rsr = pytest.importorskip("paper_2603_27462_amd")
+DEV = "cuda:0"
+KINDS = {rsr.RSR_BINARY: oracle.BINARY, rsr.RSR_TERNARY_2PASS: oracle.TERNARY_2PASS,
+         rsr.RSR_TERNARY_FUSED: oracle.TERNARY_FUSED}
+
+
+def _check(M, k, kind):
+    h = rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), k, kind)
+    for n, p in enumerate(oracle.preprocess(M, k, KINDS[kind]).passes):
+        assert np.array_equal(rsr.rsr_get_perm(h, n), p.pi)
+        assert np.array_equal(rsr.rsr_get_offsets(h, n), p.off)
+    vi = gen.integer_f32(M.shape[1], seed=3)
+    got = rsr.rsr_matvec(h, torch.from_numpy(vi).to(DEV)).cpu().numpy()
+    assert np.array_equal(got.astype(np.float64), oracle.dense_matvec(M, vi.astype(np.float64)))
+
+
+@pytest.mark.parametrize("cols", [3, 63, 65, 257, 511, 513, 4097, 18432, 18433])
+@pytest.mark.parametrize("kind,k", [(rsr.RSR_BINARY, 5), (rsr.RSR_TERNARY_FUSED, 7)])
+def test_column_counts(kind, k, cols):
+    M = gen.binary_matrix(2 * k + 1, cols, 0.4, cols) if kind == rsr.RSR_BINARY else \
+        gen.ternary_matrix(2 * k + 1, cols, 0.4, cols)
+    _check(M, k, kind)
+
+
+@pytest.mark.parametrize("kind,k", [(rsr.RSR_BINARY, 1), (rsr.RSR_BINARY, 6), (rsr.RSR_BINARY, 11),
+                                    (rsr.RSR_TERNARY_2PASS, 10), (rsr.RSR_TERNARY_FUSED, 1),
+                                    (rsr.RSR_TERNARY_FUSED, 3), (rsr.RSR_TERNARY_FUSED, 4),
+                                    (rsr.RSR_TERNARY_FUSED, 10)])
+def test_block_heights(kind, k):
+    M = gen.binary_matrix(3 * k, 1000, 0.5, k) if kind == rsr.RSR_BINARY else gen.ternary_matrix(3 * k, 1000, 0.4, k)
+    _check(M, k, kind)
+
+
+@pytest.mark.parametrize("length", [63, 64, 65, 700])
+def test_long_groups(length):
+    """Every pattern group of a block has about `length` columns."""
+    for kind, k in ((rsr.RSR_BINARY, 4), (rsr.RSR_TERNARY_FUSED, 8)):
+        base = gen.binary_matrix(k, 9, 0.5, 5) if kind == rsr.RSR_BINARY else gen.ternary_matrix(k, 9, 0.3, 5)
+        M = np.ascontiguousarray(np.repeat(base, length, axis=1)[:, np.random.default_rng(1).permutation(9 * length)])
+        _check(M, k, kind)
