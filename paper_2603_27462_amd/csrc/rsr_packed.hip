@@ -5,7 +5,7 @@
 // the kind of the handle; the redundancy a block of rows has is worth less there than the
 // vectors that share one decoded weight.  The dense kind, the comparison point without any
 // preprocessing beyond packing (the role the paper gives its low-bit multiplier baseline in
-// Benchmarking Results), multiplies a single vector this way too.  Three kernels:
+// Benchmarking Results), multiplies a single vector this way too.  Kernels:
 //   few    16 rows x up to 4 vectors per wave, for 1 to 4 vectors
 //   split  32 rows x 32 vectors per workgroup, the columns dealt to its eight waves; bound by the
 //          latency of its loads (4096 x 14336, 16 bf16 vectors: 14.4 us; as 16 products of one
@@ -13,7 +13,8 @@
 //   tile   128 rows x 128 vectors per workgroup, a 64 x 64 quarter per wave; bound by the matrix
 //          cores (4096 x 14336, 2048 bf16 vectors: 211 us = 1.14 PFLOP/s, 8.2 ms as single
 //          products; a library product of 8192^3 reaches 1.21 PFLOP/s on the same card)
-// The last two use v_mfma_f32_32x32x16_bf16 (measured 15.1 ns per instruction and SIMD against
+//   table  up to 256 columns and many rows: v stays in registers or LDS, waves go through the rows
+// Split and tile use v_mfma_f32_32x32x16_bf16 (measured 15.1 ns per instruction and SIMD against
 // 12.7 for v_mfma_f32_16x16x32_bf16, which does half the work), the first the smaller one.
 //
 // Layout: [row group of 16][tile of 256 columns][lane][2 * BITS dwords], one load of 16
@@ -599,6 +600,207 @@ __global__ __launch_bounds__(256, 2) void k_packed_tile(
     }
 }
 
+// ---- tables: up to 256 columns -----------------------------------------------------------------
+// One tile of columns: all of a vector fits the registers (or the LDS) of a wave, so it is brought
+// into operand order once and the wave then works through many row groups, with nothing but their
+// codes to wait for.  1048576 x 256 binary, float32 vectors, before (a wave stages v for every 512
+// bytes of codes; tiles of 128 vectors) and now: 1 vector 24.7 -> 14.5 us (2.6 TB/s, bound by
+// decoding and MFMAs about alike), 16 vectors 171 -> 32, 64 vectors 201 -> 100 (3.0 TB/s, of which
+// the 268 MB of results take two thirds).
+
+// table_few: up to 16 vectors.  The operands of the eight 32-column steps stay in registers; for up
+// to four vectors the float32 planes are rows of the MFMA as in k_packed_few, beyond that every
+// plane is an MFMA of its own.
+constexpr int kTableWaves = 4;
+template <typename VT, int NV>
+struct TableFew {
+    static constexpr int planes = sizeof(VT) == 4 ? 3 : 1;
+    static constexpr int operands = NV == 16 ? planes : 1;
+    static constexpr int occupancy = operands == 3 ? 2 : 4;  // waves per SIMD
+    static constexpr int stride = kTileCols * 2 + 16;  // bytes between slots: an odd number of 16-byte units
+};
+
+template <typename VT, int BITS, int NV>
+__global__ __launch_bounds__(kTableWaves * 64, (TableFew<VT, NV>::occupancy)) void k_table_few(
+    const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ngroups, int per, int n_in, int n_out,
+    long long ldv, int nv, float scale, float *__restrict__ out, long long ldo, const LayerTable layers) {
+    using S = TableFew<VT, NV>;
+    constexpr int U = 8 / BITS;  // row groups at a time: 4 KiB of codes
+    const int lane = threadIdx.x & 63, m = lane & 15, q = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    __shared__ __attribute__((aligned(16))) unsigned char smem[NV * S::planes * S::stride];
+    const int g0 = (int)min((long long)ngroups, ((long long)blockIdx.x * kTableWaves + w) * per);
+    const int g1 = (int)min((long long)ngroups, (long long)g0 + per);
+
+    const uint32_t *c0 = codes + lane * (2 * BITS);
+    uint32_t c[U][2 * BITS];
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+        if (g0 + i < g1) load_codes<BITS>(c0 + (long long)(g0 + i) * 128 * BITS, c[i]);
+    constexpr int pieces = kTileCols / 8;
+    for (int i = threadIdx.x; i < NV * pieces; i += kTableWaves * 64) {
+        const int n = i / pieces, col = 8 * (i % pieces);
+        const VT *row = v + min(n, nv - 1) * ldv;
+        Piece<VT> p = load_piece<VT>(row, col, n_in);
+        if (n_in & 7) finish_piece<VT>(p, row, col, n_in);
+        store_piece(smem + n * S::planes * S::stride + col * 2, S::stride, p);
+    }
+    __syncthreads();
+    bf16x8 op[S::operands][kTileSteps];
+    {
+        const int n = NV == 1 ? 0 : NV == 4 ? m >> 2 : m;
+        const int plane = NV < 16 && S::planes == 3 ? min(m & 3, 2) : 0;
+#pragma unroll
+        for (int o = 0; o < S::operands; ++o)
+#pragma unroll
+            for (int st = 0; st < kTileSteps; ++st)
+                op[o][st] = lds_operand(smem + (n * S::planes + plane + o) * S::stride + 64 * st + 16 * q);
+    }
+    for (int g = g0; g < g1; g += U) {
+        uint32_t next[U][2 * BITS];
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+            if (g + U + i < g1) load_codes<BITS>(c0 + (long long)(g + U + i) * 128 * BITS, next[i]);
+        f32x4 acc[U] = {};
+#pragma unroll
+        for (int i0 = 0; i0 < U; i0 += 2) {
+            if (g + i0 >= g1) break;
+#pragma unroll
+            for (int st = 0; st < kTileSteps; ++st)
+#pragma unroll
+                for (int i = i0; i < i0 + 2; ++i) {
+                    const bf16x8 x = decode<BITS>(c[i], st);
+#pragma unroll
+                    for (int o = 0; o < S::operands; ++o)
+                        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(op[o][st], x, acc[i], 0, 0, 0);
+                }
+        }
+        if (NV == 16) {
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                const long long row = (long long)(g + i) * kDenseRows + m;
+                if (g + i >= g1 || row >= n_out) continue;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (4 * q + e < nv) out[(4 * q + e) * ldo + row] = scale * acc[i][e];
+            }
+        } else {
+            float sum[U];
+#pragma unroll
+            for (int i = 0; i < U; ++i) sum[i] = S::planes == 3 ? acc[i].x + (acc[i].y + acc[i].z) : acc[i].x;
+            if (layers.n) {
+#pragma unroll
+                for (int i = 0; i < U; ++i) {
+                    if (q || g + i >= g1) continue;
+                    int s = 0;
+#pragma unroll
+                    for (int l = 1; l < kMaxLayers; ++l)
+                        if (l < layers.n && g + i >= layers.first[l]) s = l;
+                    const int local = (g + i - layers.first[s]) * kDenseRows + m;
+                    if (local < layers.rows[s]) layers.out[s][local] = layers.scale[s] * sum[i];
+                }
+            } else if (NV == 1) {
+                // all rows of the MFMA are the one vector: lane quarter q stores the q-th of four groups
+#pragma unroll
+                for (int i = 0; i < U; i += 4) {
+                    const float x = q == 0 ? sum[i] : q == 1 ? sum[i + 1] : q == 2 ? sum[i + 2] : sum[i + 3];
+                    const long long row = (long long)(g + i) * kDenseRows + lane;
+                    if (g + i + q < g1 && row < n_out) out[row] = scale * x;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < U; ++i) {
+                    const long long row = (long long)(g + i) * kDenseRows + m;
+                    if (g + i < g1 && row < n_out && q < nv) out[q * ldo + row] = scale * sum[i];
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+#pragma unroll
+            for (int d = 0; d < 2 * BITS; ++d) c[i][d] = next[i][d];
+    }
+}
+
+// table_many: 32 NT vectors per workgroup, in LDS in operand order with all planes; a wave takes
+// 64 rows at a time, so an operand read from LDS serves two MFMAs.
+constexpr int kManyWaves = 8;
+constexpr int kManyStride = kTileCols * 2 + 16;  // bytes between vectors: an odd number of 16-byte units
+template <typename VT, int NT>
+struct TableMany {
+    static constexpr int planes = sizeof(VT) == 4 ? 3 : 1;
+    static constexpr int plane = 32 * NT * kManyStride;
+    static constexpr int lds = planes * plane;
+};
+
+template <typename VT, int BITS, int NT>
+__global__ __launch_bounds__(kManyWaves * 64, (NT == 1 ? 4 : 2)) void k_table_many(
+    const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ngroups, int n_in, int n_out, long long ldv,
+    int batch, float scale, float *__restrict__ out, long long ldo) {
+    using S = TableMany<VT, NT>;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int vec0 = blockIdx.y * 32 * NT;
+    const int sets = (ngroups + 3) / 4, stride = gridDim.x * kManyWaves;
+    const uint32_t *c0 = codes + lane * (2 * BITS);
+    uint32_t c[4][2 * BITS];
+    int set = blockIdx.x * kManyWaves + w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_codes<BITS>(c0 + (long long)min(set * 4 + i, ngroups - 1) * 128 * BITS, c[i]);
+    for (int i = tid; i < 32 * NT * (kTileCols / 8); i += kManyWaves * 64) {
+        const int n = i / (kTileCols / 8), col = 8 * (i % (kTileCols / 8));
+        const VT *row = v + (long long)min(vec0 + n, batch - 1) * ldv;
+        Piece<VT> p = load_piece<VT>(row, col, n_in);
+        if (n_in & 7) finish_piece<VT>(p, row, col, n_in);
+        store_piece(smem + n * kManyStride + col * 2, S::plane, p);
+    }
+    __syncthreads();
+    const unsigned char *x = smem + (lane & 31) * kManyStride + 32 * half;
+    for (; set < sets; set += stride) {
+        uint32_t next[4][2 * BITS];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            load_codes<BITS>(c0 + (long long)min((set + stride) * 4LL + i, ngroups - 1LL) * 128 * BITS, next[i]);
+        pair_groups(c[0], c[1]);
+        pair_groups(c[2], c[3]);
+        f32x16 acc[2][NT] = {};
+#pragma unroll
+        for (int st = 0; st < kTileSteps; ++st) {
+            if (32 * st >= n_in) break;
+#pragma unroll
+            for (int xy = 0; xy < 2; ++xy) {
+                const bf16x8 w0 = decode<BITS>(c[xy], st), w1 = decode<BITS>(c[2 + xy], st);
+#pragma unroll
+                for (int pl = 0; pl < S::planes; ++pl)
+#pragma unroll
+                    for (int ng = 0; ng < NT; ++ng) {
+                        const bf16x8 o =
+                            lds_operand(x + pl * S::plane + ng * 32 * kManyStride + 64 * st + 16 * xy);
+                        acc[0][ng] = mfma32(o, w0, acc[0][ng]);
+                        acc[1][ng] = mfma32(o, w1, acc[1][ng]);
+                    }
+            }
+        }
+#pragma unroll
+        for (int ng = 0; ng < NT; ++ng)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int n = vec0 + ng * 32 + acc_vector(i, half);
+#pragma unroll
+                for (int rg = 0; rg < 2; ++rg) {
+                    const long long r = (long long)set * 64 + rg * 32 + (lane & 31);
+                    if (n < batch && r < n_out)
+                        out[(long long)n * ldo + r] = scale * acc[rg][ng][i];
+                }
+            }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int d = 0; d < 2 * BITS; ++d) c[i][d] = next[i][d];
+    }
+}
+
 struct Args {
     const uint32_t *codes;
     const void *v;
@@ -646,6 +848,43 @@ hipError_t launch_few(const Args &x) {
     }
 }
 
+constexpr int kCUs = 256;
+
+// Consecutive row groups every wave gets: so many that `waves` waves, which just fill the chip, do
+// them all.
+int table_groups_per_wave(int64_t groups, int waves) {
+    const int64_t per = (groups + waves - 1) / waves;
+    return (int)(per > 4 ? (per + 3) / 4 * 4 : per);
+}
+
+template <typename VT, int BITS, int NV>
+hipError_t launch_table_few(const Args &x) {
+    constexpr int waves = kCUs * 4 * TableFew<VT, NV>::occupancy;
+    const int per = table_groups_per_wave(x.ngroups, waves);
+    const unsigned grid = (unsigned)((x.ngroups + (long long)per * kTableWaves - 1) / ((long long)per * kTableWaves));
+    hipLaunchKernelGGL((k_table_few<VT, BITS, NV>), dim3(grid), dim3(kTableWaves * 64), 0, x.stream, x.codes,
+                       static_cast<const VT *>(x.v), x.ngroups, per, x.n_in, x.n_out, x.ldv, x.batch, x.scale, x.out,
+                       x.ldo, x.layers);
+    return hipGetLastError();
+}
+
+template <typename VT, int BITS, int NT>
+hipError_t launch_table_many(const Args &x) {
+    static std::atomic<size_t> enabled[kMaxDevices];
+    auto kern = k_table_many<VT, BITS, NT>;
+    constexpr size_t lds = TableMany<VT, NT>::lds;
+    static_assert(lds <= (size_t)kLdsBytes, "all vectors of a workgroup are staged at once");
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, x.device, enabled)) return e;
+    const int sets = (x.ngroups + 3) / 4, chunks = (x.batch + 32 * NT - 1) / (32 * NT);
+    int grid = (sets + kManyWaves - 1) / kManyWaves;
+    const int room = kCUs * (NT == 1 ? 2 : 1) / chunks;  // of the workgroups that the chip holds
+    if (grid > room) grid = room;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid, (unsigned)chunks), dim3(kManyWaves * 64), lds, x.stream, x.codes,
+                       static_cast<const VT *>(x.v), x.ngroups, x.n_in, x.n_out, x.ldv, x.batch, x.scale, x.out,
+                       x.ldo);
+    return hipGetLastError();
+}
+
 template <typename VT, int BITS>
 hipError_t launch_split(const Args &x) {
     static std::atomic<size_t> enabled[kMaxDevices];
@@ -686,8 +925,36 @@ bool use_tile(const Args &x) {
     return workgroups >= 160 && (x.batch > 32 || x.ntiles < 4);
 }
 
+// Up to 256 columns: vectors per workgroup of the table kernels, 0 where the others are faster.
+// Waves that work through many row groups pay for bringing v into registers first and win only
+// when there are rows enough, measured (table kernel / other, 200 ternary columns):
+//   1 float32 vector   100000 rows 4.3 / 4.5 us (binary 5.1 / 4.4), 200000 5.3 / 6.7
+//   1 bf16 vector      400000 rows 8.2 / 8.1 (binary 7.9 / 7.6), 700000 11.8 / 12.5
+//   4 bf16 vectors     20000 rows 3.3 / 3.1, 100000 4.1 / 5.0
+//   5 to 16            500 rows 3.3 / 3.6 (bf16), 20000 rows 4.6 / 14.7 (float32): always
+//   up to 64, float32  3000 rows 10.9 / 6.0, 12000 11.7 / 15.1
+//   up to 64, bf16     12000 rows 7.4 / 6.3, 20000 7.7 / 8.8
+// From more than 128 vectors on the tile kernel has little padding left (100000 rows, 200 float32
+// vectors: 49.9 / 53.5; 20000 rows, 512 bf16 vectors 18.4 / 13.7).
+int table_vectors(int ntiles, int64_t rows, int batch, bool wide) {
+    if (ntiles != 1) return 0;
+    if (batch == 1) return rows >= (wide ? 160000 : 500000) ? 1 : 0;
+    if (batch <= 4) return rows >= 65536 ? 4 : 0;
+    if (batch <= 16) return 16;
+    if (batch > 128 || rows < (wide ? 10000 : 16384)) return 0;
+    return batch <= 32 ? 32 : 64;
+}
+
 template <typename VT, int BITS>
 hipError_t launch(const Args &x) {
+    switch (table_vectors(x.ntiles, x.n_out, x.batch, sizeof(VT) == 4)) {
+        case 1: return launch_table_few<VT, BITS, 1>(x);
+        case 4: return launch_table_few<VT, BITS, 4>(x);
+        case 16: return launch_table_few<VT, BITS, 16>(x);
+        case 32: return launch_table_many<VT, BITS, 1>(x);
+        case 64: return launch_table_many<VT, BITS, 2>(x);
+        default: break;
+    }
     if (x.batch == 1) return launch_few<VT, BITS, 1>(x);
     if (x.batch <= 4) return launch_few<VT, BITS, 4>(x);
     return use_tile(x) ? launch_tile<VT, BITS>(x) : launch_split<VT, BITS>(x);
@@ -737,8 +1004,17 @@ hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, floa
 }
 
 void packed_launch_shape(const rsr_handle_s *h, int v_dtype, int *workgroups, int *threads, int *lds_bytes) {
-    const int wk = few_wk((int)((h->cols + kTileCols - 1) / kTileCols)), waves = few_waves(wk), rows = waves / wk;
-    const int wave_bytes = v_dtype == RSR_BF16 ? Few<uint16_t, 1>::wave_bytes : Few<float, 1>::wave_bytes;
+    const int ntiles = (int)((h->cols + kTileCols - 1) / kTileCols);
+    const bool wide = v_dtype != RSR_BF16;
+    if (table_vectors(ntiles, h->rows, 1, wide)) {
+        const int64_t per = kTableWaves * (int64_t)table_groups_per_wave(h->code_groups, kCUs * 4 * 4);
+        *workgroups = (int)((h->code_groups + per - 1) / per);
+        *threads = kTableWaves * 64;
+        *lds_bytes = (wide ? 3 : 1) * TableFew<float, 1>::stride;
+        return;
+    }
+    const int wk = few_wk(ntiles), waves = few_waves(wk), rows = waves / wk;
+    const int wave_bytes = wide ? Few<float, 1>::wave_bytes : Few<uint16_t, 1>::wave_bytes;
     *workgroups = (int)((h->code_groups + rows - 1) / rows);
     *threads = waves * 64;
     *lds_bytes = waves * (wave_bytes + 64 * 4);
@@ -746,8 +1022,12 @@ void packed_launch_shape(const rsr_handle_s *h, int v_dtype, int *workgroups, in
 
 void packed_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, char *buf, size_t len) {
     // the instantiation a single vector launches, as a profiler prints it
-    std::snprintf(buf, len, "k_packed_few<%s, %d, 1, %d>", v_dtype == RSR_BF16 ? "unsigned short" : "float",
-                  h->code_bits, few_wk((int)((h->cols + kTileCols - 1) / kTileCols)));
+    const int ntiles = (int)((h->cols + kTileCols - 1) / kTileCols);
+    const char *type = v_dtype == RSR_BF16 ? "unsigned short" : "float";
+    if (table_vectors(ntiles, h->rows, 1, v_dtype != RSR_BF16))
+        std::snprintf(buf, len, "k_table_few<%s, %d, 1>", type, h->code_bits);
+    else
+        std::snprintf(buf, len, "k_packed_few<%s, %d, 1, %d>", type, h->code_bits, few_wk(ntiles));
 }
 
 }  // namespace rsr

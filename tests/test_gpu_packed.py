@@ -92,6 +92,32 @@ def test_few_vectors(kind, rows, batch, bf16, pad, cols):
     _check(rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), 5, kind), M, batch, bf16, pad, rows)
 
 
+# up to 256 columns and many rows: waves go through several row groups (the last one short), and
+# 32 or 64 vectors share a workgroup; sizes on both sides of where these kernels start
+@pytest.mark.parametrize("kind,rows,cols,batch,bf16,pad", [
+    (rsr.RSR_DENSE_TERNARY_P2, 159999, 9, 1, False, 0), (rsr.RSR_DENSE_TERNARY_P2, 160001, 256, 1, False, 0),
+    (rsr.RSR_DENSE_TERNARY_P2, 500007, 30, 1, True, 0), (rsr.RSR_BINARY, 65537, 251, 3, False, 1),
+    (rsr.RSR_BINARY, 140001, 64, 4, True, 3), (rsr.RSR_TERNARY_2PASS, 65536, 17, 2, True, 0),
+    (rsr.RSR_TERNARY_FUSED, 5, 1, 5, False, 1), (rsr.RSR_BINARY, 70001, 255, 16, False, 0),
+    (rsr.RSR_BINARY, 1047, 200, 9, True, 1), (rsr.RSR_TERNARY_2PASS, 33001, 100, 13, False, 2),
+    (rsr.RSR_TERNARY_FUSED, 10001, 256, 17, False, 1), (rsr.RSR_BINARY, 16384, 33, 32, True, 0),
+    (rsr.RSR_BINARY, 70003, 129, 65, False, 1), (rsr.RSR_DENSE_TERNARY_P2, 40000, 7, 128, True, 0),
+    (rsr.RSR_BINARY, 16385, 255, 33, True, 3)])
+def test_tables(kind, rows, cols, batch, bf16, pad):
+    M = _matrix(kind, rows, cols, 900 + cols)
+    _check(rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), 8, kind), M, batch, bf16, pad, cols, distinct=5)
+
+
+def test_stacked_table():
+    """Sibling tables in one launch; every layer starts a new row group."""
+    Ms = [_matrix(rsr.RSR_DENSE_TERNARY_P2, r, 40, 60 + r) for r in (100001, 17, 99999)]
+    h = rsr.rsr_preprocess_stacked([torch.from_numpy(M).to(DEV) for M in Ms], 0, rsr.RSR_DENSE_TERNARY_P2)
+    v = gen.integer_f32(40, seed=3)
+    outs = rsr.rsr_matvec_stacked(h, torch.from_numpy(v).to(DEV), [1.0, -2.0, 0.5])
+    for M, out, scale in zip(Ms, outs, (1.0, -2.0, 0.5)):
+        assert np.array_equal(out.cpu().numpy().astype(np.float64), oracle.dense_matvec(M, v.astype(np.float64), scale))
+
+
 @pytest.mark.parametrize("kind,rows,cols", [(rsr.RSR_TERNARY_FUSED, 203, 1500), (rsr.RSR_BINARY, 5000, 130)])
 def test_library_chosen_height_after_loading(kind, rows, cols):
     """k = 0: however the handle multiplies single vectors, its copy made from bytes does the same,
