@@ -7,15 +7,15 @@
 // preprocessing beyond packing (the role the paper gives its low-bit multiplier baseline in
 // Benchmarking Results), multiplies a single vector this way too.  Kernels:
 //   few    16 rows x up to 4 vectors per wave, for 1 to 4 vectors
-//   split  32 rows x 32 vectors per workgroup, the columns dealt to its eight waves; bound by the
-//          latency of its loads (4096 x 14336, 16 bf16 vectors: 14.4 us; as 16 products of one
-//          vector 78 us)
+//   split  16 to 64 rows x 16 or 32 vectors per workgroup, the columns dealt to its eight waves; bound
+//          by the latency of its loads (4096 x 14336, 16 bf16 vectors: 10.3 us; as 16 products of one
+//          vector 78 us; with 32 vectors per workgroup, half of them padding, 14.4)
 //   tile   128 rows x 128 vectors per workgroup, a 64 x 64 quarter per wave; bound by the matrix
 //          cores (4096 x 14336, 2048 bf16 vectors: 211 us = 1.14 PFLOP/s, 8.2 ms as single
 //          products; a library product of 8192^3 reaches 1.21 PFLOP/s on the same card)
 //   table  up to 256 columns and many rows: v stays in registers or LDS, waves go through the rows
-// Split and tile use v_mfma_f32_32x32x16_bf16 (measured 15.1 ns per instruction and SIMD against
-// 12.7 for v_mfma_f32_16x16x32_bf16, which does half the work), the first the smaller one.
+// Tiles and workgroups of 32 vectors use v_mfma_f32_32x32x16_bf16 (measured 15.1 ns per instruction and SIMD against
+// 12.7 for v_mfma_f32_16x16x32_bf16, which does half the work), the others the smaller one.
 //
 // Layout: [row group of 16][tile of 256 columns][lane][2 * BITS dwords], one load of 16
 // (8) bytes per lane and tile.  Lane l holds row l%16 and the column slices 8*(l/16).. of the
@@ -55,6 +55,7 @@ typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
 
 constexpr int kTileCols = kDenseTileCols;  // 256: eight 32-column steps
 constexpr int kTileSteps = kTileCols / 32;
+constexpr int kCUs = 256;
 
 // ---- packing ---------------------------------------------------------------------------------
 // One thread per (row group, tile, lane): eight loads of eight entries each.
@@ -389,67 +390,79 @@ __global__ __launch_bounds__(few_waves(WK) * 64) void k_packed_few(
     }
 }
 
-// ---- split: 32 rows x 32 vectors, the columns dealt to eight waves ---------------------------
-// For batches too small to fill the chip with tiles of 128 x 128.  Every wave works through
-// its own share of the tiles and stages its own columns of the 32 vectors in LDS of its own:
-// nothing in the loop waits for another wave, the partial results are added at the end.
-template <typename VT>
+// ---- split: 16 to 64 rows x 16 or 32 vectors, the columns dealt to the waves -------------------
+// For batches too small to fill the chip with tiles of 128 x 128.  2^wk_log2 of the eight waves of a
+// workgroup share the columns of 16 G rows (ROWS: fewer than all eight).  Every wave works through its own share of the tiles and
+// stages its own columns of the 16 NT vectors in LDS of its own: nothing in the loop waits for
+// another wave, the partial results are added at the end.
+template <typename VT, int NT>
 struct Split {
     static constexpr int planes = sizeof(VT) == 4 ? 3 : 1;
+    static constexpr int vectors = 16 * NT;
     static constexpr int cols = sizeof(VT) == 4 ? 64 : 128;  // columns staged at a time
     static constexpr int pieces = cols / 8;
+    static constexpr int loads = vectors * pieces / 64;
     static constexpr int stride = cols * 2 + 16;  // bytes between vectors: an odd number of 16-byte units
-    static constexpr int plane = 32 * stride;
+    static constexpr int plane = vectors * stride;
     static constexpr int wave_bytes = planes * plane;
     static constexpr int stages = kTileCols / cols;
 };
 constexpr int kSplitWaves = 8;
 
-template <typename VT, int BITS>
+template <typename VT, int BITS, int NT, int G, bool ROWS>
 __global__ __launch_bounds__(kSplitWaves * 64) void k_packed_split(
     const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ntiles, int ngroups, int n_in, int n_out,
-    long long ldv, int batch, float *__restrict__ out, long long ldo, float scale) {
-    using S = Split<VT>;
+    long long ldv, int batch, float *__restrict__ out, long long ldo, float scale, int wk_log2_rows) {
+    using S = Split<VT, NT>;
+    const int wk_log2 = ROWS ? wk_log2_rows : 3;  // (shifts that are known: 0.3 us less for the smallest products)
+    constexpr bool kPairs = NT == 2;              // 32 x 32 MFMAs over two row groups
+    constexpr int kAcc = G * NT * 4;              // result registers of a lane
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int vec0 = blockIdx.y * 32;
-    const int g0 = blockIdx.x * 2, g1 = min(g0 + 1, ngroups - 1);
-    const int t0 = ntiles * w / kSplitWaves, t1 = ntiles * (w + 1) / kSplitWaves;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wr = w >> wk_log2, kpart = w - (wr << wk_log2);
+    const int vec0 = blockIdx.y * S::vectors;
+    const int row_sets = kSplitWaves >> wk_log2;  // of 16 G rows
+    const int group0 = ((int)blockIdx.x * row_sets + wr) * G;
+    const int t0 = ntiles * kpart >> wk_log2, t1 = ntiles * (kpart + 1) >> wk_log2;
     unsigned char *mine = smem + w * S::wave_bytes;
-    constexpr int kLoads = 32 * S::pieces / 64;
 
-    const VT *row[kLoads];
-    int at[kLoads];
+    const VT *row[S::loads];
+    int at[S::loads];
 #pragma unroll
-    for (int j = 0; j < kLoads; ++j) {
+    for (int j = 0; j < S::loads; ++j) {
         const int n = (j * 64 + lane) / S::pieces;
         row[j] = v + (long long)min(vec0 + n, batch - 1) * ldv;
         at[j] = n * S::stride;
     }
     const int piece_col = 8 * (lane % S::pieces);
-    const uint32_t *c0 = codes + ((long long)g0 * ntiles * 64 + lane) * (2 * BITS);
-    const uint32_t *c1 = codes + ((long long)g1 * ntiles * 64 + lane) * (2 * BITS);
+    const uint32_t *code[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+        code[g] = codes + ((long long)min(group0 + g, ngroups - 1) * ntiles * 64 + lane) * (2 * BITS);
 
-    Piece<VT> p[kLoads];
+    Piece<VT> p[S::loads];
     auto request = [&](int col0) { load_pieces<VT>(p, row, col0, S::cols, piece_col, n_in); };
-    f32x16 acc = {};
-    uint32_t a[2 * BITS], b[2 * BITS];
+    f32x4 acc[kPairs ? 1 : G] = {};
+    f32x16 pair_acc[kPairs ? G / 2 : 1] = {};
+    uint32_t c[G][2 * BITS];
     if (t0 < t1) {
-        load_codes<BITS>(c0 + (long long)t0 * 128 * BITS, a);
-        load_codes<BITS>(c1 + (long long)t0 * 128 * BITS, b);
+#pragma unroll
+        for (int g = 0; g < G; ++g) load_codes<BITS>(code[g] + (long long)t0 * 128 * BITS, c[g]);
         request(t0 * kTileCols);
     }
     for (int t = t0; t < t1; ++t) {
-        uint32_t an[2 * BITS], bn[2 * BITS];
+        uint32_t cn[G][2 * BITS];
         const long long next = (long long)min(t + 1, t1 - 1) * 128 * BITS;
-        load_codes<BITS>(c0 + next, an);
-        load_codes<BITS>(c1 + next, bn);
-        pair_groups(a, b);
+#pragma unroll
+        for (int g = 0; g < G; ++g) load_codes<BITS>(code[g] + next, cn[g]);
+        if constexpr (kPairs) {
+#pragma unroll
+            for (int g = 0; g < G; g += 2) pair_groups(c[g], c[g + 1]);
+        }
 #pragma unroll
         for (int s = 0; s < S::stages; ++s) {
 #pragma unroll
-            for (int j = 0; j < kLoads; ++j) store_piece(mine + at[j] + piece_col * 2, S::plane, p[j]);
+            for (int j = 0; j < S::loads; ++j) store_piece(mine + at[j] + piece_col * 2, S::plane, p[j]);
             const int ahead = t * kTileCols + (s + 1) * S::cols;
             if (ahead < t1 * kTileCols) request(ahead);
             // the wave's LDS operations execute in order: no barrier inside a wave
@@ -458,32 +471,61 @@ __global__ __launch_bounds__(kSplitWaves * 64) void k_packed_split(
 #pragma unroll
             for (int k = 0; k < S::cols / 32; ++k) {
                 const int st = s * (S::cols / 32) + k;
-                const bf16x8 w0 = decode<BITS>(a, st), w1 = decode<BITS>(b, st);
-                const unsigned char *x = mine + (lane & 31) * S::stride + (4 * k + 2 * half) * 16;
+                if constexpr (kPairs) {
+                    const unsigned char *x = mine + (lane & 31) * S::stride + (4 * k + 2 * half) * 16;
 #pragma unroll
-                for (int pl = 0; pl < S::planes; ++pl) {
-                    acc = mfma32(lds_operand(x + pl * S::plane), w0, acc);
-                    acc = mfma32(lds_operand(x + pl * S::plane + 16), w1, acc);
+                    for (int xy = 0; xy < 2; ++xy) {
+                        bf16x8 o[S::planes];
+#pragma unroll
+                        for (int pl = 0; pl < S::planes; ++pl) o[pl] = lds_operand(x + pl * S::plane + 16 * xy);
+#pragma unroll
+                        for (int g = 0; g < G; g += 2) {
+                            const bf16x8 y = decode<BITS>(c[g + xy], st);
+#pragma unroll
+                            for (int pl = 0; pl < S::planes; ++pl) pair_acc[g / 2] = mfma32(o[pl], y, pair_acc[g / 2]);
+                        }
+                    }
+                } else {
+                    const unsigned char *x = mine + (lane & 15) * S::stride + (4 * k + (lane >> 4)) * 16;
+                    bf16x8 o[S::planes];
+#pragma unroll
+                    for (int pl = 0; pl < S::planes; ++pl) o[pl] = lds_operand(x + pl * S::plane);
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        const bf16x8 y = decode<BITS>(c[g], st);
+#pragma unroll
+                        for (int pl = 0; pl < S::planes; ++pl)
+                            acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o[pl], y, acc[g], 0, 0, 0);
+                    }
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
 #pragma unroll
-        for (int d = 0; d < 2 * BITS; ++d) { a[d] = an[d]; b[d] = bn[d]; }
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int d = 0; d < 2 * BITS; ++d) c[g][d] = cn[g][d];
     }
     __syncthreads();  // the staging areas become the partial results [wave][register][lane]
     float *red = reinterpret_cast<float *>(smem);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) red[(w * 16 + i) * 64 + lane] = acc[i];
+    for (int i = 0; i < kAcc; ++i) red[(w * kAcc + i) * 64 + lane] = kPairs ? pair_acc[i >> 4][i & 15] : acc[i >> 2][i & 3];
     __syncthreads();
-    for (int e = tid; e < 1024; e += kSplitWaves * 64) {
+    for (int e = tid; e < row_sets * kAcc * 64; e += kSplitWaves * 64) {
+        const int i = (e >> 6) % kAcc, r = (e >> 6) / kAcc;
+        const float *part = red + ((r << wk_log2) * kAcc + i) * 64 + lane;
         float sum = 0.0f;
+        if (!ROWS) {
 #pragma unroll
-        for (int i = 0; i < kSplitWaves; ++i) sum += red[i * 1024 + e];
-        const int n = vec0 + acc_vector(e >> 6, half);
-        const int r = blockIdx.x * 32 + (e & 31);
-        if (n < batch && r < n_out) out[(long long)n * ldo + r] = scale * sum;
+            for (int k = 0; k < kSplitWaves; ++k) sum += part[k * kAcc * 64];
+        } else {
+            for (int k = 0; k < 1 << wk_log2; ++k) sum += part[k * kAcc * 64];
+        }
+        const long long first = (long long)(((int)blockIdx.x * row_sets + r) * G) * kDenseRows;
+        const long long rr = first + (kPairs ? 32 * (i >> 4) + (lane & 31) : 16 * (i >> 2) + (lane & 15));
+        const int n = vec0 + (kPairs ? acc_vector(i & 15, half) : 4 * (lane >> 4) + (i & 3));
+        if (n < batch && rr < n_out) out[(long long)n * ldo + rr] = scale * sum;
     }
 }
 
@@ -848,8 +890,6 @@ hipError_t launch_few(const Args &x) {
     }
 }
 
-constexpr int kCUs = 256;
-
 // Consecutive row groups every wave gets: so many that `waves` waves, which just fill the chip, do
 // them all.
 int table_groups_per_wave(int64_t groups, int waves) {
@@ -885,17 +925,64 @@ hipError_t launch_table_many(const Args &x) {
     return hipGetLastError();
 }
 
+// Shape of the split kernel: vectors (16 NT) and row groups (G) of a workgroup, waves that share a row
+// group's columns.  Up to 16 vectors take the 16 x 16 MFMA and no padding.  More rows per workgroup
+// read v less often, fewer give more workgroups: measured with 1 / 2 / 4 row groups, 16 float32
+// vectors: 4096 rows (x 14336) 22.8 / 23.4 / 28.7 us, 6912 (x 2560) 10.0 / 8.3 / 9.7, 14336 (x 4096)
+// 20.9 / 13.8 / 11.8.  32 vectors with 2 / 4: a workgroup of four row groups takes about 1.3 times as
+// long (24 float32 vectors, 6912 x 2560: 12.4 / 15.0), so four pay where they save a round of
+// workgroups (14336 x 4096: 24.0 / 16.8), for bf16 where they fit in one round (4096 x 14336, 100
+// vectors: 30.4 / 21.5; 6912 x 2560, 432 workgroups: 13.7 / 14.5).  Waves without columns take
+// other rows where there are workgroups enough (60000 x 300, 24 float32 vectors: 31 / 19 / 13.5 us
+// with 4 / 2 / 2 waves on a row group and 2 / 2 / 4 row groups).
+struct SplitShape {
+    int NT, G, wk_log2;
+};
+SplitShape split_shape(int ntiles, int ngroups, int batch, bool wide) {
+    SplitShape s = {batch <= 16 ? 1 : 2, 1, 3};
+    const long long units = (long long)ngroups * ((batch + 16 * s.NT - 1) / (16 * s.NT));
+    if (s.NT == 1) {
+        s.G = units > 640 ? 4 : units > 320 ? 2 : 1;
+    } else {
+        const long long two = (units / 2 + kCUs - 1) / kCUs, four = (units / 4 + kCUs - 1) / kCUs;  // rounds
+        s.G = 13 * four < 10 * two && (wide || four <= 1) ? 4 : 2;
+    }
+    const long long room = s.NT == 2 && !wide ? 2 * kCUs : kCUs;
+    while (s.wk_log2 > 0 && 1 << s.wk_log2 > ntiles && (units / s.G << s.wk_log2) / kSplitWaves > room) --s.wk_log2;
+    return s;
+}
+
+template <typename VT, int BITS, int NT, int G, bool ROWS>
+hipError_t launch_split_rows(const Args &x, int wk_log2) {
+    static std::atomic<size_t> enabled[kMaxDevices];
+    auto kern = k_packed_split<VT, BITS, NT, G, ROWS>;
+    constexpr size_t lds = (size_t)kSplitWaves * Split<VT, NT>::wave_bytes;
+    static_assert(lds >= (size_t)kSplitWaves * G * NT * 1024 && lds <= (size_t)kLdsBytes,
+                  "partial results share the staging area");
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, x.device, enabled)) return e;
+    const int groups = (kSplitWaves >> wk_log2) * G;  // of a workgroup
+    const dim3 grid((unsigned)((x.ngroups + groups - 1) / groups), (unsigned)((x.batch + 16 * NT - 1) / (16 * NT)));
+    hipLaunchKernelGGL(kern, grid, dim3(kSplitWaves * 64), lds, x.stream, x.codes, static_cast<const VT *>(x.v),
+                       x.ntiles, x.ngroups, x.n_in, x.n_out, x.ldv, x.batch, x.out, x.ldo, x.scale, wk_log2);
+    return hipGetLastError();
+}
+
+template <typename VT, int BITS, int NT, int G>
+hipError_t launch_split_g(const Args &x, int wk_log2) {
+    return wk_log2 == 3 ? launch_split_rows<VT, BITS, NT, G, false>(x, 3)
+                        : launch_split_rows<VT, BITS, NT, G, true>(x, wk_log2);
+}
+
 template <typename VT, int BITS>
 hipError_t launch_split(const Args &x) {
-    static std::atomic<size_t> enabled[kMaxDevices];
-    auto kern = k_packed_split<VT, BITS>;
-    constexpr size_t lds = (size_t)kSplitWaves * Split<VT>::wave_bytes;
-    static_assert(lds >= (size_t)kSplitWaves * 1024 * 4 && lds <= (size_t)kLdsBytes, "partial results share the staging area");
-    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, x.device, enabled)) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((x.n_out + 31) / 32), (unsigned)((x.batch + 31) / 32)),
-                       dim3(kSplitWaves * 64), lds, x.stream, x.codes, static_cast<const VT *>(x.v), x.ntiles,
-                       x.ngroups, x.n_in, x.n_out, x.ldv, x.batch, x.out, x.ldo, x.scale);
-    return hipGetLastError();
+    const SplitShape sh = split_shape(x.ntiles, x.ngroups, x.batch, sizeof(VT) == 4);
+    switch (sh.NT * 10 + sh.G) {
+        case 24: return launch_split_g<VT, BITS, 2, 4>(x, sh.wk_log2);
+        case 22: return launch_split_g<VT, BITS, 2, 2>(x, sh.wk_log2);
+        case 14: return launch_split_g<VT, BITS, 1, 4>(x, sh.wk_log2);
+        case 12: return launch_split_g<VT, BITS, 1, 2>(x, sh.wk_log2);
+        default: return launch_split_g<VT, BITS, 1, 1>(x, sh.wk_log2);
+    }
 }
 
 template <typename VT, int BITS>
@@ -914,15 +1001,14 @@ hipError_t launch_tile(const Args &x) {
 
 // Tiles of 128 x 128 need about 160 workgroups to be worth their size: 4096 x 4096 x 512 bf16
 // vectors (128 workgroups) 38.8 us against 37.9 with the columns split over waves, 6912 x 2560 x
-// 512 (216) 29 against 48, 14336 x 4096 x 192 (224) 40.5 against 45.2.  Up to 32 vectors one
-// workgroup of the split kernel holds them all, and only matrices that leave most of its waves
-// without a tile of columns are better off with tiles (100000 x 256, 16 vectors: 13.5 against 17.5).
+// 512 (216) 29 against 48, 14336 x 4096 x 192 (224) 40.5 against 45.2.  Up to 32 vectors a tile is
+// mostly padding (60000 x 300, 24 float32 vectors: 24.3 against 13.5).
 bool use_tile(const Args &x) {
 #ifdef RSR_TUNING
     if (const char *s = std::getenv("RSR_TILE")) return std::atoi(s) != 0;
 #endif
     const long long workgroups = (long long)((x.n_out + 127) / 128) * ((x.batch + 127) / 128);
-    return workgroups >= 160 && (x.batch > 32 || x.ntiles < 4);
+    return workgroups >= 160 && x.batch > 32;
 }
 
 // Up to 256 columns: vectors per workgroup of the table kernels, 0 where the others are faster.

@@ -51,6 +51,20 @@ def test_columns_split_over_waves(kind, rows, cols, k, batch, bf16, pad):
     _check(rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), k, kind), M, batch, bf16, pad, rows)
 
 
+# 16 vectors or 32 per workgroup, one to four row groups, and waves that share rows instead of columns
+# when there are few tiles of columns: sizes on both sides of every choice
+@pytest.mark.parametrize("kind,rows,cols,k,batch,bf16,pad", [
+    (rsr.RSR_DENSE_TERNARY_P2, 320 * 16, 300, 0, 5, True, 0), (rsr.RSR_BINARY, 320 * 16 + 1, 520, 8, 16, False, 1),
+    (rsr.RSR_DENSE_TERNARY_P2, 640 * 16 + 1, 1025, 0, 16, True, 3), (rsr.RSR_BINARY, 640 * 16 - 15, 257, 6, 7, False, 0),
+    (rsr.RSR_TERNARY_FUSED, 60001, 299, 6, 6, True, 1), (rsr.RSR_BINARY, 33333, 700, 8, 13, False, 0),
+    (rsr.RSR_DENSE_TERNARY_P2, 8209, 1100, 0, 17, False, 1), (rsr.RSR_BINARY, 16400, 260, 8, 32, True, 0),
+    (rsr.RSR_TERNARY_2PASS, 30011, 303, 8, 25, False, 3), (rsr.RSR_DENSE_TERNARY_P2, 4097, 2100, 0, 97, True, 0),
+    (rsr.RSR_BINARY, 1500, 1999, 8, 300, False, 1), (rsr.RSR_DENSE_TERNARY_P2, 40001, 513, 0, 18, True, 1)])
+def test_split_shapes(kind, rows, cols, k, batch, bf16, pad):
+    M = _matrix(kind, rows, cols, 1100 + cols)
+    _check(rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), k, kind), M, batch, bf16, pad, cols, distinct=4)
+
+
 # one workgroup holds 128 rows x 128 vectors
 @pytest.mark.parametrize("kind,rows,cols,k,batch,bf16,pad", [
     (rsr.RSR_TERNARY_FUSED, 128 * 24, 256, 4, 128 * 8, True, 0),
