@@ -10,8 +10,8 @@
 //   split  16 to 64 rows x 16 or 32 vectors per workgroup, the columns dealt to its eight waves; bound
 //          by the latency of its loads (4096 x 14336, 16 bf16 vectors: 10.3 us; as 16 products of one
 //          vector 78 us; with 32 vectors per workgroup, half of them padding, 14.4)
-//   tile   128 rows x 128 vectors per workgroup, a 64 x 64 quarter per wave; bound by the matrix
-//          cores (4096 x 14336, 2048 bf16 vectors: 211 us = 1.14 PFLOP/s, 8.2 ms as single
+//   tile   128 rows x 128 vectors per workgroup of four or eight waves; bound by the matrix cores and
+//          the decoding (4096 x 14336, 2048 bf16 vectors: 211 us = 1.14 PFLOP/s, 8.2 ms as single
 //          products; a library product of 8192^3 reaches 1.21 PFLOP/s on the same card)
 //   table  up to 256 columns and many rows: v stays in registers or LDS, waves go through the rows
 // Tiles and workgroups of 32 vectors use v_mfma_f32_32x32x16_bf16 (measured 15.1 ns per instruction and SIMD against
@@ -529,11 +529,13 @@ __global__ __launch_bounds__(kSplitWaves * 64) void k_packed_split(
     }
 }
 
-// ---- tile: 128 rows x 128 vectors, four waves ------------------------------------------------
-// Wave (wr, wn) owns rows 64 wr.. and vectors 64 wn.. of the tile: two weight operands and two
-// vector operands make four MFMAs, so a decoded weight is used twice and an LDS read twice.
-// The vectors are staged in LDS, double buffered, one barrier per stage; the codes come
-// straight from memory, every wave those of its own rows.
+// ---- tile: 128 rows x 128 vectors, four or eight waves ------------------------------------------
+// A wave owns RB x VB blocks of 32 rows x 32 vectors: 64 x 64 or 32 x 128.  KW = 2: two sets of four
+// waves, one multiplies the even 16-column operands and one the odd ones; they add up at the end.
+// The vectors are staged in LDS, double buffered, one barrier per stage, float32 four stages ahead
+// (14336 x 4096, 700 vectors: 262 -> 240 us; bf16, with a quarter of the load instructions per MFMA,
+// gains nothing from more than one); the codes come straight from memory, every wave those of its
+// own rows.
 template <typename VT>
 struct Tile {
     static constexpr int planes = sizeof(VT) == 4 ? 3 : 1;
@@ -543,16 +545,21 @@ struct Tile {
     static constexpr int plane = 128 * stride;
     static constexpr int buffer = planes * plane;
     static constexpr int stages = kTileCols / cols;
+    static constexpr int ahead = sizeof(VT) == 4 ? 4 : 1;  // stages of v in registers, on their way
+    static_assert(stages % ahead == 0, "a stage's registers are known when the code is compiled");
 };
 
-template <typename VT, int BITS>
-__global__ __launch_bounds__(256, 2) void k_packed_tile(
+template <typename VT, int BITS, int KW, int RB>
+__global__ __launch_bounds__(256 * KW, 2) void k_packed_tile(
     const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ntiles, int ngroups, int n_in, int n_out,
     long long ldv, int batch, float *__restrict__ out, long long ldo, float scale, int row_tiles, int vec_tiles) {
     using S = Tile<VT>;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wr = w & 1, wn = w >> 1;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), kw = w >> 2;
+    constexpr int NT = 256 * KW;
+    constexpr int VB = 4 / RB, RW = 4 / RB;       // blocks of 32 vectors of a wave; waves beside each other in rows
+    const int wr = w & (RW - 1), wn = (w & 3) / RW;
     // consecutive workgroups go to the eight XCDs in turn: each XCD gets a contiguous run of
     // tiles, eight row tiles for every vector tile, so that its L2 sees the same vectors again
     const int all = row_tiles * vec_tiles, per = (all + 7) / 8;
@@ -562,82 +569,110 @@ __global__ __launch_bounds__(256, 2) void k_packed_tile(
     const int band_rows = min(8, row_tiles - band * 8);
     const int rt = band * 8 + in_band % band_rows, vt = in_band / band_rows;
     const int vec0 = vt * 128;
-    constexpr int kLoads = 128 * S::pieces / 256;
+    constexpr int kLoads = 128 * S::pieces / NT;
 
     const VT *row[kLoads];
 #pragma unroll
     for (int j = 0; j < kLoads; ++j)
-        row[j] = v + (long long)min(vec0 + (j * 256 + tid) / S::pieces, batch - 1) * ldv;
+        row[j] = v + (long long)min(vec0 + (j * NT + tid) / S::pieces, batch - 1) * ldv;
     const int piece_col = 8 * (tid % S::pieces);
     unsigned char *put = smem + (tid / S::pieces) * S::stride + piece_col * 2;
-    const uint32_t *code[4];
+    const uint32_t *code[2 * RB];
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
-        code[g] = codes + ((long long)min(rt * 8 + wr * 4 + g, ngroups - 1) * ntiles * 64 + lane) * (2 * BITS);
+    for (int g = 0; g < 2 * RB; ++g)
+        code[g] = codes + ((long long)min(rt * 8 + wr * 2 * RB + g, ngroups - 1) * ntiles * 64 + lane) * (2 * BITS);
 
-    Piece<VT> p[kLoads];
-    auto request = [&](int col0) { load_pieces<VT>(p, row, col0, S::cols, piece_col, n_in); };
-    auto stage = [&](int buf) {
+    Piece<VT> p[S::ahead][kLoads];  // stage s of a tile in p[s % ahead]
+    auto request = [&](int slot, int col0) { load_pieces<VT>(p[slot], row, col0, S::cols, piece_col, n_in); };
+    auto stage = [&](int buf, int slot) {
 #pragma unroll
         for (int j = 0; j < kLoads; ++j)
-            store_piece(put + buf * S::buffer + j * (256 / S::pieces) * S::stride, S::plane, p[j]);
+            store_piece(put + buf * S::buffer + j * (NT / S::pieces) * S::stride, S::plane, p[slot][j]);
     };
-    f32x16 acc[2][2] = {};
-    uint32_t c[4][2 * BITS];
+    f32x16 acc[RB][VB] = {};
+    uint32_t c[2 * RB][2 * BITS];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) load_codes<BITS>(code[g], c[g]);
-    request(0);
-    stage(0);
+    for (int g = 0; g < 2 * RB; ++g) load_codes<BITS>(code[g], c[g]);
+#pragma unroll
+    for (int s = 0; s < S::ahead; ++s) request(s, s * S::cols);
+    stage(0, 0);
     const int end = ntiles * kTileCols;
-    request(S::cols);
+    if (S::ahead * S::cols < end) request(0, S::ahead * S::cols);
     __syncthreads();
     for (int t = 0; t < ntiles; ++t) {
-        uint32_t cn[4][2 * BITS];
+        uint32_t cn[2 * RB][2 * BITS];
         const long long next = (long long)min(t + 1, ntiles - 1) * 128 * BITS;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) load_codes<BITS>(code[g] + next, cn[g]);
-        pair_groups(c[0], c[1]);
-        pair_groups(c[2], c[3]);
+        for (int g = 0; g < 2 * RB; ++g) load_codes<BITS>(code[g] + next, cn[g]);
+#pragma unroll
+        for (int r = 0; r < RB; ++r) pair_groups(c[2 * r], c[2 * r + 1]);
+        if (KW == 2 && kw == 1) {  // this wave multiplies the odd 16-column operands
+#pragma unroll
+            for (int d = 0; d < 2 * BITS; ++d)
+#pragma unroll
+                for (int r = 0; r < RB; ++r) c[2 * r][d] = c[2 * r + 1][d];
+        }
 #pragma unroll
         for (int s = 0; s < S::stages; ++s) {
-            const unsigned char *buf = smem + (s & 1) * S::buffer + (wn * 64 + (lane & 31)) * S::stride + 32 * half;
+            const unsigned char *buf = smem + (s & 1) * S::buffer + (wn * 32 * VB + (lane & 31)) * S::stride + 32 * half;
 #pragma unroll
             for (int k = 0; k < S::cols / 32; ++k) {
                 const int st = s * (S::cols / 32) + k;
 #pragma unroll
-                for (int xy = 0; xy < 2; ++xy) {
-                    const bf16x8 w0 = decode<BITS>(c[xy], st), w1 = decode<BITS>(c[2 + xy], st);
+                for (int half_step = 0; half_step < 2 / KW; ++half_step) {
+                    const int xy = KW == 2 ? kw : half_step;
+                    bf16x8 x[RB];
 #pragma unroll
-                    for (int pl = 0; pl < S::planes; ++pl) {
-                        const unsigned char *x = buf + pl * S::plane + 64 * k + 16 * xy;
-                        const bf16x8 v0 = lds_operand(x), v1 = lds_operand(x + 32 * S::stride);
-                        acc[0][0] = mfma32(v0, w0, acc[0][0]);
-                        acc[0][1] = mfma32(v1, w0, acc[0][1]);
-                        acc[1][0] = mfma32(v0, w1, acc[1][0]);
-                        acc[1][1] = mfma32(v1, w1, acc[1][1]);
-                    }
+                    for (int r = 0; r < RB; ++r) x[r] = decode<BITS>(c[2 * r + (KW == 2 ? 0 : xy)], st);
+#pragma unroll
+                    for (int pl = 0; pl < S::planes; ++pl)
+#pragma unroll
+                        for (int n = 0; n < VB; ++n) {
+                            const bf16x8 o = lds_operand(buf + pl * S::plane + 64 * k + 16 * xy + n * 32 * S::stride);
+#pragma unroll
+                            for (int r = 0; r < RB; ++r) acc[r][n] = mfma32(o, x[r], acc[r][n]);
+                        }
                 }
             }
             // the next stage goes to the other buffer, which nobody reads any more
-            stage((s + 1) & 1);
-            const int ahead = t * kTileCols + (s + 2) * S::cols;
-            if (ahead < end) request(ahead);
+            stage((s + 1) & 1, (s + 1) % S::ahead);
+            const int ahead = t * kTileCols + (s + 1 + S::ahead) * S::cols;
+            if (ahead < end) request((s + 1) % S::ahead, ahead);
             __syncthreads();
         }
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+        for (int g = 0; g < 2 * RB; ++g)
 #pragma unroll
             for (int d = 0; d < 2 * BITS; ++d) c[g][d] = cn[g][d];
     }
+    if constexpr (KW == 2) {
+        // the second four waves hand over their sums, half of them at a time (the last stage's barrier
+        // is behind every read of the buffers)
+        float *red = reinterpret_cast<float *>(smem) + (w & 3) * 2048 + lane;
 #pragma unroll
-    for (int rg = 0; rg < 2; ++rg) {
-        const int r = rt * 128 + wr * 64 + rg * 32 + (lane & 31);
+        for (int part = 0; part < 2; ++part) {
+            if (kw == 1) {
 #pragma unroll
-        for (int ng = 0; ng < 2; ++ng)
+                for (int i = 0; i < 32; ++i) red[i * 64] = acc[(2 * part + i / 16) / VB][(2 * part + i / 16) % VB][i & 15];
+            }
+            __syncthreads();
+            if (kw == 0) {
+#pragma unroll
+                for (int i = 0; i < 32; ++i) acc[(2 * part + i / 16) / VB][(2 * part + i / 16) % VB][i & 15] += red[i * 64];
+            }
+            __syncthreads();
+        }
+        if (kw == 1) return;
+    }
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+        const int row_out = rt * 128 + (wr * RB + r) * 32 + (lane & 31);
+#pragma unroll
+        for (int b = 0; b < VB; ++b)
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int n = vec0 + wn * 64 + ng * 32 + acc_vector(i, half);
-                if (n < batch && r < n_out) out[(long long)n * ldo + r] = scale * acc[rg][ng][i];
+                const int n = vec0 + (wn * VB + b) * 32 + acc_vector(i, half);
+                if (n < batch && row_out < n_out) out[(long long)n * ldo + row_out] = scale * acc[r][b][i];
             }
     }
 }
@@ -985,30 +1020,43 @@ hipError_t launch_split(const Args &x) {
     }
 }
 
-template <typename VT, int BITS>
-hipError_t launch_tile(const Args &x) {
+template <typename VT, int BITS, int KW, int RB>
+hipError_t launch_tile_kw(const Args &x) {
     static std::atomic<size_t> enabled[kMaxDevices];
-    auto kern = k_packed_tile<VT, BITS>;
+    auto kern = k_packed_tile<VT, BITS, KW, RB>;
     constexpr size_t lds = 2 * (size_t)Tile<VT>::buffer;
+    static_assert(lds >= 4 * 2048 * sizeof(float), "partial results share the staging buffers");
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, x.device, enabled)) return e;
     const int row_tiles = (x.n_out + 127) / 128, vec_tiles = (x.batch + 127) / 128;
     const int per = (row_tiles * vec_tiles + 7) / 8;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(per * 8)), dim3(256), lds, x.stream, x.codes,
+    hipLaunchKernelGGL(kern, dim3((unsigned)(per * 8)), dim3(256 * KW), lds, x.stream, x.codes,
                        static_cast<const VT *>(x.v), x.ntiles, x.ngroups, x.n_in, x.n_out, x.ldv, x.batch, x.out,
                        x.ldo, x.scale, row_tiles, vec_tiles);
     return hipGetLastError();
 }
 
-// Tiles of 128 x 128 need about 160 workgroups to be worth their size: 4096 x 4096 x 512 bf16
-// vectors (128 workgroups) 38.8 us against 37.9 with the columns split over waves, 6912 x 2560 x
-// 512 (216) 29 against 48, 14336 x 4096 x 192 (224) 40.5 against 45.2.  Up to 32 vectors a tile is
-// mostly padding (60000 x 300, 24 float32 vectors: 24.3 against 13.5).
-bool use_tile(const Args &x) {
+// Up to 256 workgroups a CU has one, and eight waves do better than four: 4096 x 14336 x 512 bf16
+// vectors 125 -> 105 us, 6912 x 2560 x 300 float32 75 -> 57; beyond, two workgroups share a CU and
+// four waves each are faster (14336 x 4096 x 2048 bf16: 207 against 221).  With eight waves bf16 is
+// bound by decoding, so a wave takes 32 rows and all vectors (every code decoded by two waves
+// instead of four: 120 -> 105); float32 reads its three planes of v too often then (252 -> 259).
+template <typename VT, int BITS>
+hipError_t launch_tile(const Args &x) {
+    if ((long long)((x.n_out + 127) / 128) * ((x.batch + 127) / 128) > kCUs) return launch_tile_kw<VT, BITS, 1, 2>(x);
+    return launch_tile_kw<VT, BITS, 2, sizeof(VT) == 4 ? 2 : 1>(x);
+}
+
+// Tiles of 128 x 128 need enough workgroups to be worth their size, tiles / columns split over waves:
+// bf16 4096 x 4096 x 512 vectors (128 workgroups) 34.7 / 36.8 us, 4096 x 14336 x 512 105 / 117,
+// 14336 x 4096 x 100 (112) 28.7 / 27.4; float32 14336 x 4096 x 100 (112) 79 / 64, 6912 x 2560 x 300
+// (162) 57 / 73.  Up to 32 vectors a tile is mostly padding (60000 x 300, 24 float32 vectors:
+// 24.3 / 13.5).
+bool use_tile(const Args &x, bool wide) {
 #ifdef RSR_TUNING
     if (const char *s = std::getenv("RSR_TILE")) return std::atoi(s) != 0;
 #endif
     const long long workgroups = (long long)((x.n_out + 127) / 128) * ((x.batch + 127) / 128);
-    return workgroups >= 160 && x.batch > 32;
+    return workgroups >= (wide ? 160 : 128) && x.batch > 32;
 }
 
 // Up to 256 columns: vectors per workgroup of the table kernels, 0 where the others are faster.
@@ -1043,7 +1091,7 @@ hipError_t launch(const Args &x) {
     }
     if (x.batch == 1) return launch_few<VT, BITS, 1>(x);
     if (x.batch <= 4) return launch_few<VT, BITS, 4>(x);
-    return use_tile(x) ? launch_tile<VT, BITS>(x) : launch_split<VT, BITS>(x);
+    return use_tile(x, sizeof(VT) == 4) ? launch_tile<VT, BITS>(x) : launch_split<VT, BITS>(x);
 }
 
 }  // namespace

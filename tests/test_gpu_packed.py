@@ -71,7 +71,11 @@ def test_split_shapes(kind, rows, cols, k, batch, bf16, pad):
     (rsr.RSR_BINARY, 128 * 24 + 1, 255, 8, 128 * 8 + 1, False, 1),
     (rsr.RSR_DENSE_TERNARY_P2, 128 * 33 - 17, 777, 0, 128 * 7 - 1, True, 1),
     (rsr.RSR_TERNARY_2PASS, 128 * 100 - 1, 33, 6, 129, False, 0),
-    (rsr.RSR_BINARY, 128 * 193, 40, 8, 65, True, 5)])
+    (rsr.RSR_BINARY, 128 * 193, 40, 8, 65, True, 5),
+    # eight waves up to 256 workgroups, four beyond
+    (rsr.RSR_DENSE_TERNARY_P2, 128 * 128 - 5, 513, 0, 33, True, 1), (rsr.RSR_BINARY, 128 * 160 - 1, 767, 8, 120, False, 1),
+    (rsr.RSR_TERNARY_FUSED, 128 * 64, 1024, 8, 512, True, 0), (rsr.RSR_DENSE_TERNARY_P2, 128 * 85, 290, 0, 300, False, 3),
+    (rsr.RSR_BINARY, 128 * 86, 300, 8, 300, False, 0)])
 def test_tiles_of_rows_and_vectors(kind, rows, cols, k, batch, bf16, pad):
     M = _matrix(kind, rows, cols, 500 + cols)
     _check(rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), k, kind), M, batch, bf16, pad, cols, distinct=40)
