@@ -1,6 +1,6 @@
 // C ABI of librsr: argument checks, device-memory ownership, and the order of
 // the preprocessing launches.  All arithmetic of the method is in the kernels
-// (rsr_preprocess.hip, rsr_matvec.hip, rsr_dense.hip).
+// (rsr_preprocess.hip, rsr_matvec.hip, rsr_narrow.hip, rsr_packed.hip).
 #include <cstddef>
 #include <cstring>
 #include <new>
@@ -22,7 +22,7 @@ bool is_rsr_kind(int kind) {
     return kind == RSR_BINARY || kind == RSR_TERNARY_2PASS || kind == RSR_TERNARY_FUSED;
 }
 
-// Whether a batch is multiplied on the matrix cores.  From four vectors on that is faster for
+// Whether a batch is multiplied on the matrix cores.  From two vectors on that is faster for
 // every kind and size measured (8B layers, 4 vectors: 10 us a launch against 22 for the stream of
 // the block patterns, which costs the same for every vector; three vectors on 1001 x 2999: 14 us
 // against 9).

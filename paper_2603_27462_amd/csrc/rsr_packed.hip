@@ -32,7 +32,9 @@
 // float32 vectors are split exactly into three bf16 planes (top, middle and bottom 8
 // significant bits) that take one MFMA each, so integer-valued inputs stay exact and nothing
 // is lost against float32 inputs.  Accumulation is float32 throughout and the order of the
-// sums is fixed.
+// sums is fixed.  The top plane has sums of its own: its products have few bits, so they add up
+// almost exactly, and the other planes' rounding is 2^-8 of what it would be on top of them
+// (14336 x 4096, 700 vectors, relative error against float64 with all planes in one sum 5.6e-7).
 #include <cstdio>
 #ifdef RSR_TUNING
 #include <cstdlib>
@@ -442,8 +444,9 @@ __global__ __launch_bounds__(kSplitWaves * 64) void k_packed_split(
 
     Piece<VT> p[S::loads];
     auto request = [&](int col0) { load_pieces<VT>(p, row, col0, S::cols, piece_col, n_in); };
-    f32x4 acc[kPairs ? 1 : G] = {};
-    f32x16 pair_acc[kPairs ? G / 2 : 1] = {};
+    constexpr int kSums = S::planes == 3 ? 2 : 1;  // the top plane, and the others
+    f32x4 acc[kSums][kPairs ? 1 : G] = {};
+    f32x16 pair_acc[kSums][kPairs ? G / 2 : 1] = {};
     uint32_t c[G][2 * BITS];
     if (t0 < t1) {
 #pragma unroll
@@ -482,7 +485,10 @@ __global__ __launch_bounds__(kSplitWaves * 64) void k_packed_split(
                         for (int g = 0; g < G; g += 2) {
                             const bf16x8 y = decode<BITS>(c[g + xy], st);
 #pragma unroll
-                            for (int pl = 0; pl < S::planes; ++pl) pair_acc[g / 2] = mfma32(o[pl], y, pair_acc[g / 2]);
+                            for (int pl = 0; pl < S::planes; ++pl) {
+                                f32x16 &to = pair_acc[pl ? kSums - 1 : 0][g / 2];
+                                to = mfma32(o[pl], y, to);
+                            }
                         }
                     }
                 } else {
@@ -494,8 +500,10 @@ __global__ __launch_bounds__(kSplitWaves * 64) void k_packed_split(
                     for (int g = 0; g < G; ++g) {
                         const bf16x8 y = decode<BITS>(c[g], st);
 #pragma unroll
-                        for (int pl = 0; pl < S::planes; ++pl)
-                            acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o[pl], y, acc[g], 0, 0, 0);
+                        for (int pl = 0; pl < S::planes; ++pl) {
+                            f32x4 &to = acc[pl ? kSums - 1 : 0][g];
+                            to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o[pl], y, to, 0, 0, 0);
+                        }
                     }
                 }
             }
@@ -510,7 +518,11 @@ __global__ __launch_bounds__(kSplitWaves * 64) void k_packed_split(
     __syncthreads();  // the staging areas become the partial results [wave][register][lane]
     float *red = reinterpret_cast<float *>(smem);
 #pragma unroll
-    for (int i = 0; i < kAcc; ++i) red[(w * kAcc + i) * 64 + lane] = kPairs ? pair_acc[i >> 4][i & 15] : acc[i >> 2][i & 3];
+    for (int i = 0; i < kAcc; ++i) {
+        float sum = kPairs ? pair_acc[0][i >> 4][i & 15] : acc[0][i >> 2][i & 3];
+        if (kSums == 2) sum += kPairs ? pair_acc[1][i >> 4][i & 15] : acc[1][i >> 2][i & 3];
+        red[(w * kAcc + i) * 64 + lane] = sum;
+    }
     __syncthreads();
     for (int e = tid; e < row_sets * kAcc * 64; e += kSplitWaves * 64) {
         const int i = (e >> 6) % kAcc, r = (e >> 6) / kAcc;
@@ -532,9 +544,9 @@ __global__ __launch_bounds__(kSplitWaves * 64) void k_packed_split(
 // ---- tile: 128 rows x 128 vectors, four or eight waves ------------------------------------------
 // A wave owns RB x VB blocks of 32 rows x 32 vectors: 64 x 64 or 32 x 128.  KW = 2: two sets of four
 // waves, one multiplies the even 16-column operands and one the odd ones; they add up at the end.
-// The vectors are staged in LDS, double buffered, one barrier per stage, float32 four stages ahead
-// (14336 x 4096, 700 vectors: 262 -> 240 us; bf16, with a quarter of the load instructions per MFMA,
-// gains nothing from more than one); the codes come straight from memory, every wave those of its
+// The vectors are staged in LDS, double buffered, one barrier per stage, float32 two (four with
+// eight waves) stages ahead, as far as the registers reach; bf16, with a quarter of the load
+// instructions per MFMA, gains nothing from more than one; the codes come straight from memory, every wave those of its
 // own rows.
 template <typename VT>
 struct Tile {
@@ -545,8 +557,7 @@ struct Tile {
     static constexpr int plane = 128 * stride;
     static constexpr int buffer = planes * plane;
     static constexpr int stages = kTileCols / cols;
-    static constexpr int ahead = sizeof(VT) == 4 ? 4 : 1;  // stages of v in registers, on their way
-    static_assert(stages % ahead == 0, "a stage's registers are known when the code is compiled");
+    static constexpr int ahead = sizeof(VT) == 4 ? 2 : 1;  // stages of v in registers, on their way (KW = 1)
 };
 
 template <typename VT, int BITS, int KW, int RB>
@@ -582,22 +593,26 @@ __global__ __launch_bounds__(256 * KW, 2) void k_packed_tile(
     for (int g = 0; g < 2 * RB; ++g)
         code[g] = codes + ((long long)min(rt * 8 + wr * 2 * RB + g, ngroups - 1) * ntiles * 64 + lane) * (2 * BITS);
 
-    Piece<VT> p[S::ahead][kLoads];  // stage s of a tile in p[s % ahead]
+    constexpr int kAhead = S::planes == 3 ? S::ahead * KW : S::ahead;
+    static_assert(S::stages % kAhead == 0, "a stage's registers are known when the code is compiled");
+    Piece<VT> p[kAhead][kLoads];  // stage s of a tile in p[s % ahead]
     auto request = [&](int slot, int col0) { load_pieces<VT>(p[slot], row, col0, S::cols, piece_col, n_in); };
     auto stage = [&](int buf, int slot) {
 #pragma unroll
         for (int j = 0; j < kLoads; ++j)
             store_piece(put + buf * S::buffer + j * (NT / S::pieces) * S::stride, S::plane, p[slot][j]);
     };
-    f32x16 acc[RB][VB] = {};
+    constexpr int kSums = S::planes == 3 ? 2 : 1;  // the top plane, and the others
+    f32x16 sums[kSums][RB][VB] = {};
+    auto &acc = sums[0];
     uint32_t c[2 * RB][2 * BITS];
 #pragma unroll
     for (int g = 0; g < 2 * RB; ++g) load_codes<BITS>(code[g], c[g]);
 #pragma unroll
-    for (int s = 0; s < S::ahead; ++s) request(s, s * S::cols);
+    for (int s = 0; s < kAhead; ++s) request(s, s * S::cols);
     stage(0, 0);
     const int end = ntiles * kTileCols;
-    if (S::ahead * S::cols < end) request(0, S::ahead * S::cols);
+    if (kAhead * S::cols < end) request(0, kAhead * S::cols);
     __syncthreads();
     for (int t = 0; t < ntiles; ++t) {
         uint32_t cn[2 * RB][2 * BITS];
@@ -630,20 +645,29 @@ __global__ __launch_bounds__(256 * KW, 2) void k_packed_tile(
                         for (int n = 0; n < VB; ++n) {
                             const bf16x8 o = lds_operand(buf + pl * S::plane + 64 * k + 16 * xy + n * 32 * S::stride);
 #pragma unroll
-                            for (int r = 0; r < RB; ++r) acc[r][n] = mfma32(o, x[r], acc[r][n]);
+                            for (int r = 0; r < RB; ++r) {
+                                f32x16 &to = sums[pl ? kSums - 1 : 0][r][n];
+                                to = mfma32(o, x[r], to);
+                            }
                         }
                 }
             }
             // the next stage goes to the other buffer, which nobody reads any more
-            stage((s + 1) & 1, (s + 1) % S::ahead);
-            const int ahead = t * kTileCols + (s + 1 + S::ahead) * S::cols;
-            if (ahead < end) request((s + 1) % S::ahead, ahead);
+            stage((s + 1) & 1, (s + 1) % kAhead);
+            const int ahead = t * kTileCols + (s + 1 + kAhead) * S::cols;
+            if (ahead < end) request((s + 1) % kAhead, ahead);
             __syncthreads();
         }
 #pragma unroll
         for (int g = 0; g < 2 * RB; ++g)
 #pragma unroll
             for (int d = 0; d < 2 * BITS; ++d) c[g][d] = cn[g][d];
+    }
+    if constexpr (kSums == 2) {
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int n = 0; n < VB; ++n) acc[r][n] += sums[1][r][n];
     }
     if constexpr (KW == 2) {
         // the second four waves hand over their sums, half of them at a time (the last stage's barrier
