@@ -181,9 +181,14 @@ __global__ __launch_bounds__(NT) void k_sort_columns(const int8_t *__restrict__ 
                 if (valid) {
                     const uint32_t first = cnt[digit * W + w];
                     B[first + rank] = x;
-                    // (the wave's LDS operations execute in order: everybody has read it)
+                    // the wave's LDS operations execute in order: everybody has read it, and the next
+                    // 64 positions read it after this
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
                     if (rank == 0) cnt[digit * W + w] = first + (uint32_t)__popcll(m);
                 }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
             }
             __syncthreads();
             Item *tmp = A; A = B; B = tmp;

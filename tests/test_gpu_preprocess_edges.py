@@ -51,3 +51,14 @@ def test_long_groups(length):
         base = gen.binary_matrix(k, 9, 0.5, 5) if kind == rsr.RSR_BINARY else gen.ternary_matrix(k, 9, 0.3, 5)
         M = np.ascontiguousarray(np.repeat(base, length, axis=1)[:, np.random.default_rng(1).permutation(9 * length)])
         _check(M, k, kind)
+
+
+@pytest.mark.parametrize("cols", [64, 129, 4100, 18433])
+@pytest.mark.parametrize("patterns", [1, 2, 5])
+def test_positions_of_a_wave_that_share_a_digit(patterns, cols):
+    """Few distinct columns: in every sorting step a wave takes many positions of one digit one 64
+    after the other, each 64 counting on from where the last ones ended."""
+    k = 7
+    base = gen.ternary_matrix(k, patterns, 0.3, patterns)
+    M = np.ascontiguousarray(base[:, np.random.default_rng(cols).integers(0, patterns, cols)])
+    _check(M, k, rsr.RSR_TERNARY_FUSED)
