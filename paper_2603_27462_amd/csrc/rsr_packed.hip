@@ -1126,15 +1126,21 @@ int64_t packed_bytes(int64_t groups, int64_t cols, int bits) {
 
 hipError_t launch_pack_codes(const int8_t *M, int64_t rows, int64_t cols, int bits, void *packed, int *err_flag) {
     const int64_t ntiles = (cols + kTileCols - 1) / kTileCols;
-    const int64_t total = (rows + kDenseRows - 1) / kDenseRows * ntiles * 64;
-    const dim3 grid((unsigned)((total + 255) / 256));
-    if (bits == 1)
-        hipLaunchKernelGGL(k_pack_codes<1>, grid, dim3(256), 0, 0, M, rows, cols, ntiles,
-                           static_cast<uint32_t *>(packed), err_flag);
-    else
-        hipLaunchKernelGGL(k_pack_codes<2>, grid, dim3(256), 0, 0, M, rows, cols, ntiles,
-                           static_cast<uint32_t *>(packed), err_flag);
-    return hipGetLastError();
+    // (a launch holds fewer than 2^32 threads: so many row groups at a time)
+    const int64_t band = (((int64_t)1 << 31) / (64 * ntiles)) * kDenseRows;
+    uint32_t *to = static_cast<uint32_t *>(packed);
+    for (int64_t r = 0; r < rows; r += band) {
+        const int64_t n = rows - r < band ? rows - r : band;
+        const int64_t total = row_groups(n) * ntiles * 64;
+        const dim3 grid((unsigned)((total + 255) / 256));
+        if (bits == 1)
+            hipLaunchKernelGGL(k_pack_codes<1>, grid, dim3(256), 0, 0, M + r * cols, n, cols, ntiles, to, err_flag);
+        else
+            hipLaunchKernelGGL(k_pack_codes<2>, grid, dim3(256), 0, 0, M + r * cols, n, cols, ntiles, to, err_flag);
+        if (hipError_t e = hipGetLastError()) return e;
+        to += total * 2 * bits;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, float scale, float *out, int batch,

@@ -324,6 +324,7 @@ __device__ __forceinline__ void spread_banks(uint16_t *part, int epl, uint8_t *l
 struct StreamArgs {
     const uint16_t *pi;
     const uint32_t *off;
+    int64_t block0;  // of workgroup 0
     int64_t nb, P, slots;
     int n, S, W, k, enc, by_rank, fw, spread;  // spread: the strips are short enough to be spread
     uint16_t *entries, *start;
@@ -372,7 +373,7 @@ __global__ __launch_bounds__(1024) void k_build_stream(const StreamArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, NT = blockDim.x, waves = NT >> 6;
     const int L = a.S * kSlab, strips = a.W * 64;
     const uint16_t zero_entry = (uint16_t)(a.n << 1);
-    const int64_t b = blockIdx.x;
+    const int64_t b = a.block0 + blockIdx.x;
     const uint16_t *pib = a.pi + b * a.n;
     const uint32_t *ob = a.off + b * (a.P + 1);
     const uint32_t off1 = ob[1];
@@ -585,15 +586,24 @@ hipError_t launch_sort(const int8_t *M, int64_t rows, int64_t cols, int k, int b
     return hipGetLastError();
 }
 
+// A launch holds fewer than 2^32 threads; the runtime takes a larger grid without an error and runs
+// a part of it.  More blocks than kLaunchBlocks (of up to 1024 threads) take several launches.
+constexpr int64_t kLaunchBlocks = (int64_t)1 << 21;
+
 template <int BASE>
-hipError_t launch_stream(const StreamArgs &a, int threads, size_t lds) {
+hipError_t launch_stream(StreamArgs a, int threads, size_t lds) {
     static std::atomic<size_t> enabled[kMaxDevices];
     int device = 0;
     if (hipError_t e = hipGetDevice(&device)) return e;
     auto kern = k_build_stream<BASE>;
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, device, enabled)) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)a.nb), dim3(threads), lds, 0, a);
-    return hipGetLastError();
+    for (a.block0 = 0; a.block0 < a.nb; a.block0 += kLaunchBlocks) {
+        const int64_t left = a.nb - a.block0;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(left < kLaunchBlocks ? left : kLaunchBlocks)), dim3(threads), lds, 0,
+                           a);
+        if (hipError_t e = hipGetLastError()) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace

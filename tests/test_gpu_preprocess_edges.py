@@ -62,3 +62,15 @@ def test_positions_of_a_wave_that_share_a_digit(patterns, cols):
     base = gen.ternary_matrix(k, patterns, 0.3, patterns)
     M = np.ascontiguousarray(base[:, np.random.default_rng(cols).integers(0, patterns, cols)])
     _check(M, k, rsr.RSR_TERNARY_FUSED)
+
+
+def test_more_blocks_than_one_launch_holds():
+    """8388700 blocks of one row: 512 threads each are more than the 2^32 a launch can have.  (Stacked,
+    because a matrix of four columns alone takes the narrow layout.)"""
+    rows = (1 << 32) // 512 + 92
+    M = (torch.rand((rows, 4), device=DEV) < 0.5).to(torch.int8)
+    v = torch.tensor([1.0, 2.0, 4.0, 8.0], device=DEV)
+    h = rsr.rsr_preprocess_stacked([M], 1, rsr.RSR_BINARY)
+    out, = rsr.rsr_matvec_stacked(h, v)
+    assert torch.equal(out, M.float() @ v)
+    rsr.rsr_destroy(h)
