@@ -3,8 +3,9 @@
 // (rsr_preprocess.hip, rsr_matvec.hip, rsr_narrow.hip, rsr_packed.hip).
 #include <cstddef>
 #include <cstring>
+#include <memory>
 #include <new>
-#include <vector>
+#include <type_traits>
 
 #include "rsr_internal.h"
 
@@ -45,24 +46,26 @@ void free_handle(rsr_handle_s *h) {
 }
 
 // Device buffers that are allocated together: an allocation and a release cost about 15 and 20 us
-// each, whatever their size, and a handle has up to a dozen buffers.
+// each, whatever their size, and a handle has up to a dozen buffers.  (No container: nothing may
+// throw through the C entries.)
 class Buffers {
   public:
     template <typename T>
     void add(T **p, int64_t count) {
-        items_.push_back({reinterpret_cast<void **>(p), total_});
+        if (n_ < kMost) items_[n_] = {reinterpret_cast<void **>(p), total_};
+        ++n_;
         total_ += ((size_t)(count > 0 ? count : 1) * sizeof(T) + 255) & ~(size_t)255;
     }
     void add_bytes(void **p, int64_t bytes) { add(reinterpret_cast<unsigned char **>(p), bytes); }
     hipError_t allocate(rsr_handle_s *h) {
         int slot = 0;
         while (slot < 4 && h->arena[slot]) ++slot;
-        if (slot == 4) return hipErrorInvalidValue;
+        if (slot == 4 || n_ > kMost) return hipErrorInvalidValue;
         if (hipError_t e = hipMalloc(&h->arena[slot], total_ ? total_ : 1)) {
             h->arena[slot] = nullptr;
             return e;
         }
-        for (const Item &i : items_) *i.p = static_cast<unsigned char *>(h->arena[slot]) + i.at;
+        for (int i = 0; i < n_; ++i) *items_[i].p = static_cast<unsigned char *>(h->arena[slot]) + items_[i].at;
         return hipSuccess;
     }
 
@@ -71,9 +74,12 @@ class Buffers {
         void **p;
         size_t at;
     };
-    std::vector<Item> items_;
+    static constexpr int kMost = 16;  // two passes of seven buffers, and two more
+    Item items_[kMost];
+    int n_ = 0;
     size_t total_ = 0;
 };
+static_assert(std::is_trivially_destructible<Buffers>::value, "allocates nothing on the host, so it cannot throw");
 
 int64_t ipow(int64_t b, int e) {
     int64_t p = 1;
@@ -655,9 +661,17 @@ struct Piece {
     size_t bytes;
 };
 
+struct Pieces {
+    Piece piece[16];  // two passes of at most seven
+    int n = 0;
+    void push_back(const Piece &x) { piece[n++] = x; }
+    const Piece *begin() const { return piece; }
+    const Piece *end() const { return piece + n; }
+};
+
 // The device buffers of a handle in file order, with the sizes its geometry dictates.
-std::vector<Piece> pieces_of(rsr_handle_s *h) {
-    std::vector<Piece> p;
+Pieces pieces_of(rsr_handle_s *h) {
+    Pieces p;
     if (h->kind == RSR_DENSE_TERNARY_P2) {
         p.push_back({reinterpret_cast<void **>(&h->packed),
                      (size_t)rsr::packed_bytes(rsr::row_groups(h->rows), h->cols, h->code_bits)});
@@ -808,7 +822,7 @@ rsr_handle_t rsr_deserialize(const void *host_buf, int64_t size) {
     if (!dense && !h->by_rank && !h->narrow) rsr::make_fold_shape(h->base, h->k, h->P, h->W, &h->fold);
     int rc = RSR_OK;
     if (hipGetDevice(&h->device) != hipSuccess) rc = RSR_EHIP;
-    const std::vector<Piece> pieces = pieces_of(h);
+    const Pieces pieces = pieces_of(h);
     Buffers own;
     for (const Piece &pc : pieces) own.add_bytes(pc.dev, (int64_t)pc.bytes);
     int64_t need = (int64_t)header;
@@ -820,10 +834,11 @@ rsr_handle_t rsr_deserialize(const void *host_buf, int64_t size) {
     }
     const unsigned char *in = static_cast<const unsigned char *>(host_buf);
     size_t at = header;
-    for (size_t i = 0; rc == RSR_OK && i < pieces.size(); ++i) {
-        const hipError_t e = hipMemcpy(*pieces[i].dev, in + at, pieces[i].bytes, hipMemcpyHostToDevice);
+    for (const Piece &pc : pieces) {
+        if (rc != RSR_OK) break;
+        const hipError_t e = hipMemcpy(*pc.dev, in + at, pc.bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) rc = hip_code(e);
-        at += pieces[i].bytes;
+        at += pc.bytes;
     }
     h->code_groups = rsr::row_groups(h->rows);
     if (rc == RSR_OK && !dense) rc = restore_codes(h);
@@ -928,8 +943,9 @@ int rsr_get_perm(rsr_handle_t h, int pass, uint32_t *host_pi) {
     if (!good(h) || !host_pi || !is_rsr_kind(h->kind) || pass < 0 || pass >= h->npass)
         return fail(RSR_EINVAL);
     const size_t n = (size_t)(h->nb * h->cols);
-    std::vector<uint16_t> tmp(n);
-    if (hipMemcpy(tmp.data(), h->pass[pass].pi, n * sizeof(uint16_t), hipMemcpyDeviceToHost) !=
+    const std::unique_ptr<uint16_t[]> tmp(new (std::nothrow) uint16_t[n]);
+    if (!tmp) return fail(RSR_ENOMEM);
+    if (hipMemcpy(tmp.get(), h->pass[pass].pi, n * sizeof(uint16_t), hipMemcpyDeviceToHost) !=
         hipSuccess)
         return fail(RSR_EHIP);
     for (size_t i = 0; i < n; ++i) host_pi[i] = tmp[i];
@@ -951,8 +967,9 @@ int rsr_get_packed(rsr_handle_t h, uint8_t *host_packed) {
     const int64_t ntiles = h->row_bytes / (rsr::kDenseTileCols / 4);
     const int64_t ngroups = (h->rows + rsr::kDenseRows - 1) / rsr::kDenseRows;
     const size_t words = (size_t)(ngroups * ntiles * 256);
-    std::vector<uint32_t> tiled(words);
-    if (hipMemcpy(tiled.data(), h->packed, words * 4, hipMemcpyDeviceToHost) != hipSuccess)
+    const std::unique_ptr<uint32_t[]> tiled(new (std::nothrow) uint32_t[words]);
+    if (!tiled) return fail(RSR_ENOMEM);
+    if (hipMemcpy(tiled.get(), h->packed, words * 4, hipMemcpyDeviceToHost) != hipSuccess)
         return fail(RSR_EHIP);
     // undo the kernel tiling: pure data movement of 2-bit fields
     const int64_t rb = (h->cols + 3) / 4;

@@ -49,3 +49,12 @@ def test_no_oracle_in_product():
             if f.endswith((".py", ".hip", ".h")):
                 src = open(os.path.join(root, f)).read()
                 assert "import oracle" not in src and "rsr_oracle" not in src, f
+
+
+def test_nothing_in_the_c_interface_throws():
+    """No function throws (include/rsr.h): on the host the interface allocates with nothrow new only, and
+    neither containers nor strings, whose allocations throw."""
+    src = open(os.path.join(os.path.dirname(rsr.__file__), "csrc", "rsr_api.hip")).read()
+    code = re.sub(r"//[^\n]*", "", src)
+    assert not re.search(r"std::(vector|string|map|deque|list|function|make_unique|make_shared)\b", code)
+    assert not re.search(r"\bnew\b(?!\s*\(std::nothrow\))(?!>)", code)
