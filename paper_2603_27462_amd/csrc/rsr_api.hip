@@ -702,31 +702,6 @@ Pieces pieces_of(rsr_handle_s *h) {
     return p;
 }
 
-// The packed codes are not in the byte string: they are rebuilt from the permutation and the
-// boundaries.  RSR_EINVAL when those are not what a matrix gives.
-int restore_codes(rsr_handle_s *h) {
-    int rc = RSR_OK, err = 0;
-    int8_t *M = nullptr;
-    int *flag = nullptr;
-    Buffers own;
-    h->code_bits = (h->kind == RSR_BINARY) ? 1 : 2;
-    own.add(&h->packed, rsr::packed_bytes(h->code_groups, h->cols, h->code_bits));
-    own.add(&flag, 1);
-    RSR_TRY(own.allocate(h));
-    RSR_TRY(dev_alloc(&M, (size_t)(h->rows * h->cols + 3) / 4 * 4));
-    RSR_TRY(rsr::launch_fill_u32(reinterpret_cast<uint32_t *>(flag), 0u, 1));
-    RSR_TRY(rsr::launch_fill_u32(reinterpret_cast<uint32_t *>(M), 0u, (h->rows * h->cols + 3) / 4));
-    for (int ps = 0; ps < h->npass; ++ps)
-        RSR_TRY(rsr::launch_unsort(h->pass[ps].pi, h->pass[ps].off, h->rows, h->cols, h->k, h->base, h->P,
-                                   ps == 0 ? 1 : -1, M));
-    RSR_TRY(rsr::launch_pack_codes(M, h->rows, h->cols, h->code_bits, h->packed, flag));
-    RSR_TRY(hipMemcpy(&err, flag, sizeof(err), hipMemcpyDeviceToHost));
-    if (err) rc = RSR_EINVAL;
-done:
-    if (M) (void)hipFree(M);
-    return rc;
-}
-
 }  // namespace
 
 extern "C" {
@@ -825,6 +800,11 @@ rsr_handle_t rsr_deserialize(const void *host_buf, int64_t size) {
     const Pieces pieces = pieces_of(h);
     Buffers own;
     for (const Piece &pc : pieces) own.add_bytes(pc.dev, (int64_t)pc.bytes);
+    h->code_groups = rsr::row_groups(h->rows);
+    if (!dense) {  // the packed codes are not in the byte string: they follow from the artifacts
+        h->code_bits = (h->kind == RSR_BINARY) ? 1 : 2;
+        own.add(&h->packed, rsr::packed_bytes(h->code_groups, h->cols, h->code_bits));
+    }
     int64_t need = (int64_t)header;
     for (const Piece &pc : pieces) need += (int64_t)pc.bytes;
     if (rc == RSR_OK && need != size) rc = RSR_EINVAL;
@@ -840,8 +820,8 @@ rsr_handle_t rsr_deserialize(const void *host_buf, int64_t size) {
         if (e != hipSuccess) rc = hip_code(e);
         at += pc.bytes;
     }
-    h->code_groups = rsr::row_groups(h->rows);
-    if (rc == RSR_OK && !dense) rc = restore_codes(h);
+    if (rc == RSR_OK && !dense && rsr::launch_restore_codes(h) != hipSuccess) rc = RSR_EHIP;
+    if (rc == RSR_OK && hipDeviceSynchronize() != hipSuccess) rc = RSR_EHIP;
     h->single_packed = !dense && hd.single_packed;
     if (rc != RSR_OK) {
         (void)hipGetLastError();

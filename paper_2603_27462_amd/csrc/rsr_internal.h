@@ -134,10 +134,6 @@ hipError_t launch_sort_columns(const int8_t *M, int64_t rows, int64_t cols, int 
 // Everything the multiply kernel reads of one pass, from the canonical pi / off.  *err_flag |= 2
 // when a block does not hold the expected number of tails.
 hipError_t launch_pack_pass(const rsr_handle_s *h, int pass, int *err_flag);
-// Entries of the matrix from the canonical pi / off of one pass: M (zeroed by the caller) gets
-// the digits that are not zero, 2 as -1, times sign.
-hipError_t launch_unsort(const uint16_t *pi, const uint32_t *off, int64_t rows, int64_t cols, int k, int base,
-                         int64_t P, int sign, int8_t *M);
 hipError_t launch_transpose(const int8_t *M, int64_t rows, int64_t cols, int8_t *T);
 // Packed codes of the matrix (bits = 1 or 2 per entry), packed_bytes() of them; *err_flag |= 1
 // for an entry outside the alphabet.
@@ -145,6 +141,8 @@ int64_t packed_bytes(int64_t groups, int64_t cols, int bits);  // of `groups` ro
 inline int64_t row_groups(int64_t rows) { return (rows + kDenseRows - 1) / kDenseRows; }
 hipError_t launch_pack_codes(const int8_t *M, int64_t rows, int64_t cols, int bits, void *packed,
                              int *err_flag);
+// The packed codes of h from its canonical pi / off.
+hipError_t launch_restore_codes(const rsr_handle_s *h);
 
 // --- multiply launches ---------------------------------------------------------
 // `layers` (may be null): per-layer outputs and scales of a stacked handle; then out, scale

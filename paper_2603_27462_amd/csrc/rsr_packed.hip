@@ -60,6 +60,19 @@ constexpr int kTileSteps = kTileCols / 32;
 constexpr int kCUs = 256;
 
 // ---- packing ---------------------------------------------------------------------------------
+// Puts the code of column e (0..7) of a lane's slice in 32-column step st into the lane's dwords.
+template <int BITS>
+__device__ __forceinline__ void put_code(uint32_t (&word)[2 * BITS], int st, int e, uint32_t code) {
+    if (BITS == 2) {
+        const int p = 4 * (st & 1) + (e >> 1);
+        word[st >> 1] |= code << ((e & 1 ? 30 : 14) - 2 * p);
+    } else {
+        constexpr int bit_of[4] = {2, 1, 0, 3};
+        const int nibble = e < 4 ? 2 * e + 1 : 2 * (e - 4);
+        word[st >> 2] |= code << (4 * nibble + bit_of[st & 3]);
+    }
+}
+
 // One thread per (row group, tile, lane): eight loads of eight entries each.
 template <int BITS>
 __global__ __launch_bounds__(256) void k_pack_codes(const int8_t *__restrict__ M, int64_t rows, int64_t cols,
@@ -98,21 +111,142 @@ __global__ __launch_bounds__(256) void k_pack_codes(const int8_t *__restrict__ M
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const uint32_t code = (x[e >> 2] >> (8 * (e & 3))) & (BITS == 2 ? 3u : 1u);
-                if (BITS == 2) {
-                    const int p = 4 * (st & 1) + (e >> 1);
-                    word[st >> 1] |= code << ((e & 1 ? 30 : 14) - 2 * p);
-                } else {
-                    constexpr int bit_of[4] = {2, 1, 0, 3};
-                    const int nibble = e < 4 ? 2 * e + 1 : 2 * (e - 4);
-                    word[st >> 2] |= code << (4 * nibble + bit_of[st & 3]);
-                }
+                put_code<BITS>(word, st, e, (x[e >> 2] >> (8 * (e & 3))) & (BITS == 2 ? 3u : 1u));
             }
         }
     }
     if (bad) atomicOr(err_flag, 1);
 #pragma unroll
     for (int d = 0; d < 2 * BITS; ++d) tiled[gid * 2 * BITS + d] = word[d];
+}
+
+// The same codes from the canonical artifacts (a handle made from bytes has no matrix), one workgroup
+// per row group: LDS holds one word per column, the codes of the group's 16 rows, and every block that
+// has rows in the group puts its digits there, a thread per pattern code.  The matrix itself is never
+// formed: its rows x cols bytes can be more than all else that loading allocates.  (Loading 1024 x 1024
+// binary 130 us, 4096 x 14336 fused k = 8 1.6 ms, with the matrix formed, packed and freed 180 us and
+// 2.0 ms; few row groups of a wide matrix are bound by the latency of their chains: 40 x 32000 192 us.)
+constexpr uint32_t kLongColumns = 128, kPieceColumns = 512;  // longer groups are cut up and dealt to the waves
+constexpr __host__ __device__ int long_pieces(int cols) { return cols / (int)kLongColumns + 1; }  // the most there are
+
+// Codes of the rows that digits [lo, hi) of pattern code c stand for, the first of them row `at` of the
+// group.  Digits 0, 1, 2 are 0, +1, -1; pass 1 is M-.
+template <int BITS>
+__device__ __forceinline__ uint32_t row_bits(uint32_t c, int base, int pass, int lo, int hi, int at) {
+    uint32_t bits = 0;
+    if (base == 2) {
+        c = (c >> lo) & ((1u << (hi - lo)) - 1u);
+        if (BITS == 1) return c << at;
+        c = (c | c << 8) & 0x00ff00ffu;
+        c = (c | c << 4) & 0x0f0f0f0fu;
+        c = (c | c << 2) & 0x33333333u;
+        c = (c | c << 1) & 0x55555555u;
+        return (pass ? 3u * c : c) << (2 * at);
+    }
+    for (int r = 0; r < hi; ++r, c /= 3u) {
+        const uint32_t d = c % 3u;
+        if (r >= lo && d) bits |= (d == 1 ? 1u : 3u) << (2 * (at + r - lo));
+    }
+    return bits;
+}
+
+struct RestorePass {
+    const uint16_t *pi;
+    const uint32_t *off;
+};
+
+template <int BITS>
+__global__ __launch_bounds__(1024) void k_restore_codes(const RestorePass p0, const RestorePass p1, int npass,
+                                                        int64_t rows, int cols, int k, int base, int64_t P,
+                                                        int64_t ngroups, uint32_t *__restrict__ tiled) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    uint32_t *column = reinterpret_cast<uint32_t *>(smem);
+    uint32_t *longs = column + cols;  // count, then {first position, length, codes} of the pieces of long groups
+    const int tid = threadIdx.x, NT = blockDim.x;
+    const int ntiles = (cols + kTileCols - 1) / kTileCols;
+    for (int64_t G = blockIdx.x; G < ngroups; G += gridDim.x) {
+        for (int j = tid; j < cols; j += NT) column[j] = 0;
+        const int64_t r0 = G * kDenseRows, r1 = min(r0 + kDenseRows, rows);
+        for (int64_t b = r0 / k; b * k < r1; ++b) {
+            const int lo = (int)max((int64_t)0, r0 - b * k), hi = (int)min((int64_t)k, r1 - b * k);
+            const int at = (int)(b * k + lo - r0);  // row of the group that digit `lo` belongs to
+            for (int ps = 0; ps < npass; ++ps) {
+                const uint16_t *pib = (ps ? p1.pi : p0.pi) + b * cols;
+                const uint32_t *ob = (ps ? p1.off : p0.off) + b * (P + 1);
+                __syncthreads();
+                if (tid == 0) longs[0] = 0;
+                __syncthreads();
+                auto put = [&](int j, uint32_t bits) {
+                    if (j < cols) atomicOr(&column[j], bits);
+                };
+                for (int64_t c0 = 1 + tid; c0 < P; c0 += 4 * NT) {
+                    uint32_t first[4], end[4];  // four codes in flight, and the first column of each
+                    int column0[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int64_t c = min(c0 + i * NT, P - 1);
+                        // (pi and the boundaries may come from anywhere: positions stay inside the block)
+                        first[i] = ob[c];
+                        end[i] = c0 + i * NT < P ? min(ob[c + 1], (uint32_t)cols) : 0u;
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) column0[i] = pib[min(first[i], (uint32_t)cols - 1u)];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint32_t s = first[i], e = end[i];
+                        if (s >= e) continue;
+                        const uint32_t bits = row_bits<BITS>((uint32_t)(c0 + i * NT), base, ps, lo, hi, at);
+                        if (e - s >= kLongColumns) {
+                            const uint32_t pieces = (e - s + kPieceColumns - 1) / kPieceColumns;
+                            const uint32_t n = atomicAdd(&longs[0], pieces);
+                            for (uint32_t q = 0; q < pieces; ++q) {
+                                // (there is room, unless the boundaries are damaged)
+                                if (n + q >= (uint32_t)long_pieces(cols)) break;
+                                uint32_t *l = longs + 1 + 3 * (n + q);
+                                l[0] = s + q * kPieceColumns;
+                                l[1] = min((q + 1) * kPieceColumns, e - s) - q * kPieceColumns;
+                                l[2] = bits;
+                            }
+                            continue;
+                        }
+                        put(column0[i], bits);
+                        for (uint32_t t = s + 1; t < e; t += 4) {
+                            int col[4];
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) col[q] = pib[min(t + q, e - 1)];
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) put(col[q], bits);  // (the last one again, past the end)
+                        }
+                    }
+                }
+                __syncthreads();
+                const uint32_t n = min(longs[0], (uint32_t)long_pieces(cols));
+                for (uint32_t i = tid >> 6; i < n; i += NT >> 6) {  // a wave per piece
+                    const uint32_t *l = longs + 1 + 3 * i;
+                    for (uint32_t t = tid & 63; t < l[1]; t += 64) put(pib[l[0] + t], l[2]);
+                }
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < ntiles * 64; i += NT) {
+            const int lane = i & 63, j0 = (i >> 6) * kTileCols + 8 * (lane >> 4);
+            uint32_t word[2 * BITS];
+#pragma unroll
+            for (int d = 0; d < 2 * BITS; ++d) word[d] = 0;
+#pragma unroll
+            for (int st = 0; st < kTileSteps; ++st)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int j = j0 + 32 * st + e;
+                    const uint32_t x = j < cols ? column[j] : 0u;
+                    put_code<BITS>(word, st, e, (x >> (BITS * (lane & 15))) & (BITS == 2 ? 3u : 1u));
+                }
+            uint32_t *to = tiled + (G * ntiles * 64 + i) * (2 * BITS);
+#pragma unroll
+            for (int d = 0; d < 2 * BITS; ++d) to[d] = word[d];
+        }
+        __syncthreads();
+    }
 }
 
 // ---- decoding --------------------------------------------------------------------------------
@@ -1141,6 +1275,34 @@ hipError_t launch_pack_codes(const int8_t *M, int64_t rows, int64_t cols, int bi
         to += total * 2 * bits;
     }
     return hipSuccess;
+}
+
+namespace {
+
+template <int BITS>
+hipError_t launch_restore(const rsr_handle_s *h) {
+    static std::atomic<size_t> enabled[kMaxDevices];
+    auto kern = k_restore_codes<BITS>;
+    const size_t lds = ((size_t)h->cols + 1 + 3 * long_pieces((int)h->cols)) * 4;
+    static_assert((kMaxCols + 1 + 3 * long_pieces(kMaxCols)) * 4 <= kLdsBytes, "a word per column, three per piece");
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, h->device, enabled)) return e;
+    RestorePass p[2];
+    for (int i = 0; i < 2; ++i) {
+        const PassData &pd = h->pass[i < h->npass ? i : 0];
+        p[i] = {pd.pi, pd.off};
+    }
+    const int64_t grid = h->code_groups < 65536 ? h->code_groups : 65536;
+    const int64_t wide = h->cols > h->P ? h->cols : h->P;
+    const int threads = wide <= 1024 ? 256 : wide <= 8192 ? 512 : 1024;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), lds, 0, p[0], p[1], h->npass, h->rows, (int)h->cols,
+                       h->k, h->base, h->P, h->code_groups, reinterpret_cast<uint32_t *>(h->packed));
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_restore_codes(const rsr_handle_s *h) {
+    return h->code_bits == 1 ? launch_restore<1>(h) : launch_restore<2>(h);
 }
 
 hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, float scale, float *out, int batch,

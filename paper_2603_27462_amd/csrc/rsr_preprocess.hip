@@ -524,30 +524,6 @@ __global__ __launch_bounds__(kThreads) void k_fill_u32(uint32_t *__restrict__ p,
     if (i < count) p[i] = value;
 }
 
-// One thread per (block, position): the code of the position is the last one whose boundary is
-// not behind it.  Columns and rows are checked: pi and off may come from a file.
-__global__ __launch_bounds__(kThreads) void k_unsort(const uint16_t *__restrict__ pi,
-                                                     const uint32_t *__restrict__ off, int64_t nb, int64_t rows,
-                                                     int64_t cols, int k, int base, int64_t P, int sign,
-                                                     int8_t *__restrict__ M) {
-    const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (gid >= nb * cols) return;
-    const int64_t b = gid / cols, t = gid - b * cols;
-    const uint32_t *ob = off + b * (P + 1);
-    int64_t lo = 0, hi = P;  // ob[lo] <= t < ob[hi]
-    while (hi - lo > 1) {
-        const int64_t mid = (lo + hi) / 2;
-        if ((int64_t)ob[mid] <= t) lo = mid; else hi = mid;
-    }
-    const int64_t j = pi[gid];
-    if (j >= cols) return;
-    uint32_t c = (uint32_t)lo;
-    for (int r = 0; r < k && b * k + r < rows; ++r, c /= (uint32_t)base) {
-        const uint32_t d = c % (uint32_t)base;
-        if (d) M[(b * k + r) * cols + j] = (int8_t)(d == 1 ? sign : -sign);
-    }
-}
-
 // T[j][i] = M[i][j] through 64 x 64 tiles in LDS (coalesced on both sides).
 __global__ __launch_bounds__(256) void k_transpose_i8(const int8_t *__restrict__ M, int64_t rows,
                                                       int64_t cols, int8_t *__restrict__ T) {
@@ -617,14 +593,6 @@ hipError_t launch_sort_columns(const int8_t *M, int64_t rows, int64_t cols, int 
     // (workgroups of 1024 threads do not share a CU: 4096 columns sort 2.3 times slower with them)
     return cols > 512 ? launch_sort<512, false>(M, rows, cols, k, base, mode, P, codes, pi, off, stats, err_flag)
                       : launch_sort<256, false>(M, rows, cols, k, base, mode, P, codes, pi, off, stats, err_flag);
-}
-
-hipError_t launch_unsort(const uint16_t *pi, const uint32_t *off, int64_t rows, int64_t cols, int k, int base,
-                         int64_t P, int sign, int8_t *M) {
-    const int64_t nb = (rows + k - 1) / k;
-    hipLaunchKernelGGL(k_unsort, dim3((unsigned)((nb * cols + kThreads - 1) / kThreads)), dim3(kThreads), 0, 0, pi,
-                       off, nb, rows, cols, k, base, P, sign, M);
-    return hipGetLastError();
 }
 
 hipError_t launch_transpose(const int8_t *M, int64_t rows, int64_t cols, int8_t *T) {

@@ -153,3 +153,43 @@ def test_library_chosen_height_after_loading(kind, rows, cols):
     for handle in (h, h2, rsr.rsr_deserialize(old)):
         for batch in (1, 3, 40):
             _check(handle, M, batch, True, 1, 30 + batch)
+
+
+@pytest.mark.parametrize("kind,rows,cols,k", [(rsr.RSR_BINARY, 1, 1, 1), (rsr.RSR_BINARY, 33, 257, 1), (rsr.RSR_BINARY, 100, 70, 15),
+                                              (rsr.RSR_TERNARY_2PASS, 47, 1030, 5), (rsr.RSR_TERNARY_2PASS, 31, 9000, 12),
+                                              (rsr.RSR_TERNARY_FUSED, 90, 600, 10), (rsr.RSR_TERNARY_FUSED, 35, 20000, 3),
+                                              (rsr.RSR_TERNARY_2PASS, 18, 32766, 7)])
+def test_codes_rebuilt_from_the_artifacts(kind, rows, cols, k):
+    """Blocks that straddle row groups, several per group, one longer than all rows; one word per column
+    from one column to the widest; sparse and crowded pattern spaces."""
+    for M in (_matrix(kind, rows, cols, 31), np.zeros((rows, cols), np.int8)):
+        h = rsr.rsr_deserialize(rsr.rsr_serialize(rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), k, kind)))
+        _check(h, M, 600 if rows < 20 else 90, False, 0, 3, distinct=4)
+
+
+def test_loading_needs_no_room_for_the_matrix():
+    """A table of a GiB of entries is loaded with half a GiB to spare beyond the handle's own buffers
+    (1.1 GiB)."""
+    rows, cols = 1 << 22, 256
+    M = torch.empty((rows, cols), dtype=torch.int8, device=DEV)
+    for at in range(0, rows, 1 << 20):
+        M[at:at + (1 << 20)] = torch.rand((1 << 20, cols), device=DEV) < 0.4
+    h = rsr.rsr_preprocess(M, 8, rsr.RSR_BINARY)
+    del M
+    v = torch.randint(-8, 9, (20, cols), device=DEV).float()
+    want = rsr.rsr_matvec_ex(h, v)
+    blob = rsr.rsr_serialize(h)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    before = torch.cuda.mem_get_info()[0]
+    rsr.rsr_destroy(h)
+    own = torch.cuda.mem_get_info()[0] - before
+    assert own > 1 << 30
+    hog = torch.empty(torch.cuda.mem_get_info()[0] - own - (1 << 29), dtype=torch.uint8, device=DEV)
+    try:
+        h = rsr.rsr_deserialize(blob)
+    finally:
+        del hog
+        torch.cuda.empty_cache()
+    assert torch.equal(rsr.rsr_matvec_ex(h, v), want)
+    rsr.rsr_destroy(h)
