@@ -170,7 +170,10 @@ int rsr_num_layers(rsr_handle_t h);       /* layers of a stacked handle; 0 other
  *                        a damaged stream yields wrong products, never an out-of-range access
  *                        to device memory (stream entries only ever address LDS).  The packed
  *                        codes are not stored: they are rebuilt from the permutation and the
- *                        boundaries.  Allocates the handle's own buffers and nothing else.
+ *                        boundaries, which have to be those of a matrix (RSR_EINVAL otherwise: a
+ *                        column missing or twice in a block, boundaries that do not rise from 0
+ *                        to cols, entries in rows behind the last one, or in M+ and M- both).
+ *                        Allocates the handle's own buffers and nothing else.
  */
 int64_t rsr_serialized_size(rsr_handle_t h);
 int rsr_serialize(rsr_handle_t h, void *host_buf, int64_t capacity);

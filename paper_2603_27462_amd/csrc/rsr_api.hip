@@ -799,11 +799,13 @@ rsr_handle_t rsr_deserialize(const void *host_buf, int64_t size) {
     if (hipGetDevice(&h->device) != hipSuccess) rc = RSR_EHIP;
     const Pieces pieces = pieces_of(h);
     Buffers own;
+    int *flag = nullptr, err = 0;
     for (const Piece &pc : pieces) own.add_bytes(pc.dev, (int64_t)pc.bytes);
     h->code_groups = rsr::row_groups(h->rows);
     if (!dense) {  // the packed codes are not in the byte string: they follow from the artifacts
         h->code_bits = (h->kind == RSR_BINARY) ? 1 : 2;
         own.add(&h->packed, rsr::packed_bytes(h->code_groups, h->cols, h->code_bits));
+        own.add(&flag, 1);
     }
     int64_t need = (int64_t)header;
     for (const Piece &pc : pieces) need += (int64_t)pc.bytes;
@@ -820,8 +822,14 @@ rsr_handle_t rsr_deserialize(const void *host_buf, int64_t size) {
         if (e != hipSuccess) rc = hip_code(e);
         at += pc.bytes;
     }
-    if (rc == RSR_OK && !dense && rsr::launch_restore_codes(h) != hipSuccess) rc = RSR_EHIP;
-    if (rc == RSR_OK && hipDeviceSynchronize() != hipSuccess) rc = RSR_EHIP;
+    if (rc == RSR_OK && !dense) {
+        if (rsr::launch_fill_u32(reinterpret_cast<uint32_t *>(flag), 0u, 1) != hipSuccess ||
+            rsr::launch_restore_codes(h, flag) != hipSuccess ||
+            hipMemcpy(&err, flag, sizeof(err), hipMemcpyDeviceToHost) != hipSuccess)
+            rc = RSR_EHIP;
+        else if (err)
+            rc = RSR_EINVAL;  // a permutation and boundaries that no matrix gives
+    }
     h->single_packed = !dense && hd.single_packed;
     if (rc != RSR_OK) {
         (void)hipGetLastError();

@@ -141,8 +141,8 @@ int64_t packed_bytes(int64_t groups, int64_t cols, int bits);  // of `groups` ro
 inline int64_t row_groups(int64_t rows) { return (rows + kDenseRows - 1) / kDenseRows; }
 hipError_t launch_pack_codes(const int8_t *M, int64_t rows, int64_t cols, int bits, void *packed,
                              int *err_flag);
-// The packed codes of h from its canonical pi / off.
-hipError_t launch_restore_codes(const rsr_handle_s *h);
+// The packed codes of h from its canonical pi / off; *err_flag |= 4 when those are not what a matrix gives.
+hipError_t launch_restore_codes(const rsr_handle_s *h, int *err_flag);
 
 // --- multiply launches ---------------------------------------------------------
 // `layers` (may be null): per-layer outputs and scales of a stacked handle; then out, scale

@@ -122,7 +122,10 @@ __global__ __launch_bounds__(256) void k_pack_codes(const int8_t *__restrict__ M
 
 // The same codes from the canonical artifacts (a handle made from bytes has no matrix), one workgroup
 // per row group: LDS holds one word per column, the codes of the group's 16 rows, and every block that
-// has rows in the group puts its digits there, a thread per pattern code.  The matrix itself is never
+// has rows in the group puts its digits there, a thread per pattern code.  The artifacts may be damaged:
+// whatever they hold, no access leaves the block or LDS, and *err_flag |= 4 unless every pi is a
+// permutation, the boundaries rise from 0 to the number of columns, no code has digits in rows that
+// do not exist and no entry is in M+ and M- both.  The matrix itself is never
 // formed: its rows x cols bytes can be more than all else that loading allocates.  (Loading 1024 x 1024
 // binary 130 us, 4096 x 14336 fused k = 8 1.6 ms, with the matrix formed, packed and freed 180 us and
 // 2.0 ms; few row groups of a wide matrix are bound by the latency of their chains: 40 x 32000 192 us.)
@@ -158,12 +161,15 @@ struct RestorePass {
 template <int BITS>
 __global__ __launch_bounds__(1024) void k_restore_codes(const RestorePass p0, const RestorePass p1, int npass,
                                                         int64_t rows, int cols, int k, int base, int64_t P,
-                                                        int64_t ngroups, uint32_t *__restrict__ tiled) {
+                                                        int64_t ngroups, uint32_t *__restrict__ tiled,
+                                                        int *__restrict__ err_flag) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     uint32_t *column = reinterpret_cast<uint32_t *>(smem);
     uint32_t *longs = column + cols;  // count, then {first position, length, codes} of the pieces of long groups
     const int tid = threadIdx.x, NT = blockDim.x;
+    uint32_t *seen = longs + 1 + 3 * long_pieces(cols);  // a bit per column
     const int ntiles = (cols + kTileCols - 1) / kTileCols;
+    bool bad = false;
     for (int64_t G = blockIdx.x; G < ngroups; G += gridDim.x) {
         for (int j = tid; j < cols; j += NT) column[j] = 0;
         const int64_t r0 = G * kDenseRows, r1 = min(r0 + kDenseRows, rows);
@@ -175,26 +181,41 @@ __global__ __launch_bounds__(1024) void k_restore_codes(const RestorePass p0, co
                 const uint32_t *ob = (ps ? p1.off : p0.off) + b * (P + 1);
                 __syncthreads();
                 if (tid == 0) longs[0] = 0;
+                if (b * k >= r0)
+                    for (int i = tid; i < (cols + 31) / 32; i += NT) seen[i] = 0;
                 __syncthreads();
+                if (b * k >= r0) {  // checked by the group its first row is in: a permutation, and all of it
+                    for (int t = tid; t < cols; t += NT) {
+                        const uint32_t j = pib[t], bit = 1u << (j & 31);
+                        if (j >= (uint32_t)cols || (atomicOr(&seen[j >> 5], bit) & bit)) bad = true;
+                    }
+                    if (tid == 0 && (ob[0] != 0 || ob[1] > (uint32_t)cols || ob[P] != (uint32_t)cols)) bad = true;
+                }
                 auto put = [&](int j, uint32_t bits) {
-                    if (j < cols) atomicOr(&column[j], bits);
+                    // (a row of the column that M+ has set already cannot be in M- too)
+                    if (j < cols && (atomicOr(&column[j], bits) & bits & (BITS == 1 ? 0xffffu : 0x55555555u))) bad = true;
                 };
+                // codes from here on have digits in rows behind the last one
+                uint32_t code_end = 1;
+                for (int64_t r = b * k; r < min((b + 1) * k, rows); ++r) code_end *= (uint32_t)base;
                 for (int64_t c0 = 1 + tid; c0 < P; c0 += 4 * NT) {
                     uint32_t first[4], end[4];  // four codes in flight, and the first column of each
                     int column0[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const int64_t c = min(c0 + i * NT, P - 1);
-                        // (pi and the boundaries may come from anywhere: positions stay inside the block)
                         first[i] = ob[c];
-                        end[i] = c0 + i * NT < P ? min(ob[c + 1], (uint32_t)cols) : 0u;
+                        end[i] = ob[c + 1];
                     }
 #pragma unroll
                     for (int i = 0; i < 4; ++i) column0[i] = pib[min(first[i], (uint32_t)cols - 1u)];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const uint32_t s = first[i], e = end[i];
+                        if (c0 + i * NT >= P) continue;
+                        const uint32_t s = first[i], e = min(end[i], (uint32_t)cols);
+                        if (end[i] < s || end[i] > (uint32_t)cols) bad = true;
                         if (s >= e) continue;
+                        if (c0 + i * NT >= code_end) bad = true;
                         const uint32_t bits = row_bits<BITS>((uint32_t)(c0 + i * NT), base, ps, lo, hi, at);
                         if (e - s >= kLongColumns) {
                             const uint32_t pieces = (e - s + kPieceColumns - 1) / kPieceColumns;
@@ -215,7 +236,8 @@ __global__ __launch_bounds__(1024) void k_restore_codes(const RestorePass p0, co
 #pragma unroll
                             for (int q = 0; q < 4; ++q) col[q] = pib[min(t + q, e - 1)];
 #pragma unroll
-                            for (int q = 0; q < 4; ++q) put(col[q], bits);  // (the last one again, past the end)
+                            for (int q = 0; q < 4; ++q)
+                                if (t + q < e) put(col[q], bits);
                         }
                     }
                 }
@@ -247,6 +269,7 @@ __global__ __launch_bounds__(1024) void k_restore_codes(const RestorePass p0, co
         }
         __syncthreads();
     }
+    if (bad) atomicOr(err_flag, 4);
 }
 
 // ---- decoding --------------------------------------------------------------------------------
@@ -1280,11 +1303,12 @@ hipError_t launch_pack_codes(const int8_t *M, int64_t rows, int64_t cols, int bi
 namespace {
 
 template <int BITS>
-hipError_t launch_restore(const rsr_handle_s *h) {
+hipError_t launch_restore(const rsr_handle_s *h, int *err_flag) {
     static std::atomic<size_t> enabled[kMaxDevices];
     auto kern = k_restore_codes<BITS>;
-    const size_t lds = ((size_t)h->cols + 1 + 3 * long_pieces((int)h->cols)) * 4;
-    static_assert((kMaxCols + 1 + 3 * long_pieces(kMaxCols)) * 4 <= kLdsBytes, "a word per column, three per piece");
+    const size_t lds = ((size_t)h->cols + 1 + 3 * long_pieces((int)h->cols) + (h->cols + 31) / 32) * 4;
+    static_assert((kMaxCols + 1 + 3 * long_pieces(kMaxCols) + (kMaxCols + 31) / 32) * 4 <= kLdsBytes,
+                  "a word and a bit per column, three words per piece");
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, h->device, enabled)) return e;
     RestorePass p[2];
     for (int i = 0; i < 2; ++i) {
@@ -1295,14 +1319,14 @@ hipError_t launch_restore(const rsr_handle_s *h) {
     const int64_t wide = h->cols > h->P ? h->cols : h->P;
     const int threads = wide <= 1024 ? 256 : wide <= 8192 ? 512 : 1024;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), lds, 0, p[0], p[1], h->npass, h->rows, (int)h->cols,
-                       h->k, h->base, h->P, h->code_groups, reinterpret_cast<uint32_t *>(h->packed));
+                       h->k, h->base, h->P, h->code_groups, reinterpret_cast<uint32_t *>(h->packed), err_flag);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_restore_codes(const rsr_handle_s *h) {
-    return h->code_bits == 1 ? launch_restore<1>(h) : launch_restore<2>(h);
+hipError_t launch_restore_codes(const rsr_handle_s *h, int *err_flag) {
+    return h->code_bits == 1 ? launch_restore<1>(h, err_flag) : launch_restore<2>(h, err_flag);
 }
 
 hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, float scale, float *out, int batch,

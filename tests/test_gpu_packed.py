@@ -193,3 +193,48 @@ def test_loading_needs_no_room_for_the_matrix():
         torch.cuda.empty_cache()
     assert torch.equal(rsr.rsr_matvec_ex(h, v), want)
     rsr.rsr_destroy(h)
+
+
+@pytest.mark.parametrize("kind,rows,cols,k", [(rsr.RSR_BINARY, 50, 300, 6), (rsr.RSR_BINARY, 40, 90, 8),
+                                              (rsr.RSR_TERNARY_2PASS, 45, 513, 7), (rsr.RSR_TERNARY_FUSED, 203, 700, 5)])
+def test_artifacts_of_no_matrix_are_refused(kind, rows, cols, k):
+    """A byte string whose permutation or boundaries are damaged: RSR_EINVAL, not a handle whose single
+    vectors and batches are products of different matrices."""
+    M = _matrix(kind, rows, cols, 12)
+    blob = rsr.rsr_serialize(rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), k, kind))
+    nb, P = -(-rows // k), (3 if kind == rsr.RSR_TERNARY_FUSED else 2) ** k
+    pi_at, off_at = 128, 128 + 2 * nb * cols
+
+    def damaged(change):
+        bad = blob.copy()
+        change(bad[pi_at:off_at].view(np.uint16).reshape(nb, cols),
+               bad[off_at:off_at + 4 * nb * (P + 1)].view(np.uint32).reshape(nb, P + 1))
+        assert not np.array_equal(bad, blob)
+        with pytest.raises(rsr.RsrError) as e:
+            rsr.rsr_deserialize(bad)
+        assert e.value.code == 1
+
+    def twice(pi, off): pi[nb - 1, cols // 2] = pi[nb - 1, cols // 2 - 1]
+    def too_wide(pi, off): pi[nb // 2, 3] = cols
+    def far_too_wide(pi, off): pi[nb // 2, 3] = 65535
+    def first_boundary(pi, off): off[0, 0] = 1
+    def last_boundary(pi, off): off[nb - 1, P] = cols - 1
+    def falling(pi, off): off[nb // 2, P // 2] = off[nb // 2, P // 2 + 1] + 1
+    def beyond(pi, off): off[1, P // 2:P] = 0xfffffff0
+    def absent_rows(pi, off): off[nb - 1, :P] = 0       # every column has the last code: all digits set
+    changes = [twice, too_wide, far_too_wide, first_boundary, last_boundary, falling, beyond]
+    if rows % k:
+        changes.append(absent_rows)
+    for change in changes:
+        damaged(change)
+    if kind == rsr.RSR_TERNARY_2PASS:                   # M+ as M- too: entries in both
+        bad = blob.copy()
+        h = rsr.rsr_deserialize(blob)
+        one = [np.concatenate([rsr.rsr_get_perm(h, p).astype(np.uint16).view(np.uint8).ravel(),
+                               rsr.rsr_get_offsets(h, p).view(np.uint8).ravel()]) for p in (0, 1)]
+        at = blob.tobytes().index(one[1].tobytes())
+        bad[at:at + one[0].size] = one[0]
+        with pytest.raises(rsr.RsrError) as e:
+            rsr.rsr_deserialize(bad)
+        assert e.value.code == 1
+    _check(rsr.rsr_deserialize(blob), M, 90, True, 0, 7, distinct=4)
