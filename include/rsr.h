@@ -114,10 +114,14 @@ int rsr_matvec(rsr_handle_t h, const void *v, void *out, void *stream);
  *   batch   number of vectors (>= 1); vector i starts at v + i*ldv elements,
  *           its result at out + i*ldo elements (ldv >= cols, ldo >= rows)
  *
- * A batch is one launch.  Several vectors are a contraction: whatever the kind, they are
- * multiplied on the matrix cores from the packed codes, in an order of the sums that depends
- * on the number of vectors.  The result of a vector may therefore differ in its last bits
- * between batches of different sizes; the same call gives the same bits every time.
+ * A batch is one launch.  Several vectors are a contraction and are multiplied on the matrix
+ * cores from the packed codes, whatever the kind; where a matrix has too few rows to fill the
+ * chip that way (about 1000 and fewer, less the more vectors there are), the RSR kinds give
+ * every vector workgroups of its own over the block patterns.  The order of the sums therefore
+ * depends on the number of vectors: the result of a vector may differ in its last bits between
+ * batches of different sizes (integer-valued vectors are exact in any order).  The same call
+ * gives the same bits every time.  A caller whose results must not depend on the batch that a
+ * vector happens to be in makes one call per vector.
  */
 int rsr_matvec_ex(rsr_handle_t h, const void *v, int v_dtype, float scale, void *out,
                   int batch, int64_t ldv, int64_t ldo, void *stream);

@@ -23,12 +23,32 @@ bool is_rsr_kind(int kind) {
     return kind == RSR_BINARY || kind == RSR_TERNARY_2PASS || kind == RSR_TERNARY_FUSED;
 }
 
-// Whether a batch is multiplied on the matrix cores.  From two vectors on that is faster for
-// every kind and size measured (8B layers, 4 vectors: 10 us a launch against 22 for the stream of
-// the block patterns, which costs the same for every vector; three vectors on 1001 x 2999: 14 us
-// against 9).
-bool use_packed(const rsr_handle_s *h, int batch) {
-    return h->kind == RSR_DENSE_TERNARY_P2 || (h->packed && (batch >= 2 || h->single_packed));
+// Whether `batch` vectors are multiplied on the matrix cores.  One vector: where k = 0 timed that to
+// be faster.  Several vectors are a contraction, and on tall matrices the matrix cores win for every kind
+// (4096 x 14336 fused k = 8, 4 vectors: 7.6 us against 32).  But their workgroups share the columns of
+// at least 16 rows, so a matrix of few rows leaves most of the chip idle, while the block patterns
+// have a workgroup per block and vector: 512 x 14336 fused k = 8, float32, 8 vectors 17.6 against 9.2 us,
+// 64 x 14336, 32 vectors 31 against 5.5.  So both are estimated; the estimates differ from 23000
+// measured products (binary k = 2..12, fused 2..10, two passes 4..12, 1..10000 rows, 257..32766 columns,
+// 2..300 vectors, both types) by 15 % in the mean, and by more for blocks of more than eight rows, hence
+// the 0.85 and the 1.35: with them the block patterns are taken wrongly, by more than 4 %, in 16 of
+// 4650 cases.
+bool use_packed(const rsr_handle_s *h, int v_dtype, int batch, bool aligned) {
+    if (h->kind == RSR_DENSE_TERNARY_P2) return true;
+    if (!h->packed) return false;
+    if (batch == 1) return h->single_packed;
+    const bool wide = v_dtype != RSR_BF16;
+    // up to 256 columns a wave has a block of its own: faster for one block and float32 vectors that
+    // do not fit one workgroup's 16 (8 x 200, 64 vectors: 5.0 against 6.1 us)
+    if (h->narrow) return !(h->nb == 1 && h->npass == 1 && wide && batch > 16);
+    if (h->nb * batch > 4096) return true;
+    const float blocks = rsr::rsr_matvec_us(h, wide ? 4 : 2, batch, aligned) * (h->k > 8 ? 1.35f : 1.0f);
+    return blocks > 0.85f * rsr::packed_few_rows_us(h, wide, batch);
+}
+
+// Whether every vector starts on a 16-byte boundary.
+bool vectors_aligned(const void *v, int v_dtype, int64_t ldv) {
+    return ((reinterpret_cast<uintptr_t>(v) | (uint64_t)(ldv * (v_dtype == RSR_BF16 ? 2 : 4))) & 15) == 0;
 }
 
 template <typename T>
@@ -519,7 +539,7 @@ int rsr_matvec_stacked(rsr_handle_t h, const void *v, int v_dtype, const float *
     const int64_t *first = (h->single_packed) ? h->layer_code : h->layer_first;
     for (int i = 0; i <= rsr::kMaxLayers; ++i) lt.first[i] = (int)first[i <= h->nlayers ? i : h->nlayers];
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    const hipError_t e = use_packed(h, 1)
+    const hipError_t e = use_packed(h, v_dtype, 1, true)
                              ? rsr::launch_packed(h, v, v_dtype, 1.0f, nullptr, 1, h->cols, h->rows, s, &lt)
                              : rsr::launch_rsr_matvec(h, v, v_dtype, 1.0f, nullptr, 1, h->cols, h->rows, s, &lt);
     if (e != hipSuccess) return fail(hip_code(e));
@@ -853,8 +873,7 @@ int rsr_matvec_ex(rsr_handle_t h, const void *v, int v_dtype, float scale, void 
     if (hipGetDevice(&device) != hipSuccess) return fail(RSR_EHIP);
     if (device != h->device) return fail(RSR_EINVAL);  // the handle's buffers live on another GPU
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    // several vectors: a contraction, on the matrix cores, whatever the kind
-    hipError_t e = use_packed(h, batch)
+    hipError_t e = use_packed(h, v_dtype, batch, vectors_aligned(v, v_dtype, ldv))
                        ? rsr::launch_packed(h, v, v_dtype, scale, static_cast<float *>(out), batch, ldv, ldo, s)
                    : h->narrow
                        ? rsr::launch_narrow_matvec(h, v, v_dtype, scale, static_cast<float *>(out), batch, ldv,
@@ -988,7 +1007,7 @@ int64_t rsr_algorithmic_bytes(rsr_handle_t h, int v_dtype, int batch) {
     }
     const int64_t vb = (v_dtype == RSR_BF16) ? 2 : 4;
     int64_t weight_side;
-    if (use_packed(h, batch)) {
+    if (use_packed(h, v_dtype, batch, h->cols * vb % 16 == 0)) {
         weight_side = rsr::packed_bytes(h->code_groups, h->cols, h->code_bits);
     } else {
         weight_side = 0;
@@ -1011,7 +1030,7 @@ const char *rsr_kernel_name(rsr_handle_t h, int v_dtype) {
     static thread_local char name[96];
     if (h->narrow && !h->single_packed)
         return v_dtype == RSR_BF16 ? "k_rsr_narrow<unsigned short>" : "k_rsr_narrow<float>";
-    if (use_packed(h, 1))
+    if (use_packed(h, v_dtype, 1, true))
         rsr::packed_matvec_kernel_name(h, v_dtype, name, sizeof(name));
     else
         rsr::rsr_matvec_kernel_name(h, v_dtype, name, sizeof(name));

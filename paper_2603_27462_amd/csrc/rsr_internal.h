@@ -150,6 +150,11 @@ hipError_t launch_restore_codes(const rsr_handle_s *h, int *err_flag);
 hipError_t launch_rsr_matvec(const rsr_handle_s *h, const void *v, int v_dtype, float scale,
                              float *out, int batch, int64_t ldv, int64_t ldo, hipStream_t stream,
                              const LayerTable *layers = nullptr);
+// Estimates in microseconds of a batch on a matrix of few rows: with the block patterns (v_bytes: of an
+// element of v; aligned: every vector starts on a 16-byte boundary), and on the matrix cores while
+// their workgroups do not fill the chip.
+float rsr_matvec_us(const rsr_handle_s *h, int v_bytes, int batch, bool aligned);
+float packed_few_rows_us(const rsr_handle_s *h, bool wide, int batch);
 // Product on the matrix cores, from the packed codes of any kind.
 hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, float scale, float *out,
                          int batch, int64_t ldv, int64_t ldo, hipStream_t stream,

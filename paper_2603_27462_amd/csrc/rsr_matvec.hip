@@ -790,6 +790,26 @@ hipError_t launch_rsr_matvec(const rsr_handle_s *h, const void *v, int v_dtype, 
                                : launch_nr<float, kEncBig>(x, h->npass, r);
 }
 
+// A launch, a chain of staging, slabs and the two levels (or the words) of the scatter phase, and from 256
+// workgroups on the work of the ones that share a CU.  Beyond 80 KiB of LDS a CU holds one workgroup
+// at a time.  Vectors off the 16-byte boundaries are staged element by element.  Coefficients: least
+// squares over the products described at use_packed.
+float rsr_matvec_us(const rsr_handle_s *h, int v_bytes, int batch, bool aligned) {
+    const float n = (float)(h->nb * batch), np = (float)h->npass;
+    const float slabs = np * (float)(h->pass[0].S > h->pass[h->npass - 1].S ? h->pass[0].S : h->pass[h->npass - 1].S);
+    const float v = (float)h->cols * v_bytes * 1e-4f;
+    const float words = h->by_rank ? np * h->slots * h->k : 0.0f, codes = h->by_rank ? 0.0f : np * h->slots;
+    const float stage = aligned ? 0.0f : 0.12f * h->cols / (h->W * 64);
+    if (matvec_lds_bytes(h->slots, h->cols, v_bytes, h->W, h->by_rank != 0) > kLdsBytes / 2) {
+        const float x = n <= 256 ? 1.0f : h->by_rank ? (float)((h->nb * batch + 255) / 256) : n / 256;
+        return 2.5f * np - 0.5f + stage * (0.5f + 0.5f * x) + x * (0.075f * slabs + 0.26f * v + 2e-5f * words);
+    }
+    const float x = n <= 256 ? 0.0f : (n - 256) / 256;
+    return 2.1f + stage + 1.5f * np + 0.042f * slabs + 0.15f * v + 8.4e-5f * codes + 3.6e-5f * words +
+           (h->by_rank ? 0.4f * np : 0.0f) +
+           x * (0.031f * slabs + 0.06f * np * h->W + 0.106f * v + 6.5e-5f * codes + 1.4e-5f * words + 0.5f * stage);
+}
+
 void rsr_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, char *buf, size_t len) {
     // as a profiler prints the instantiation
     const bool common = !h->by_rank && h->npass == 1 && h->fold.Tc == kCommonClasses;

@@ -238,3 +238,22 @@ def test_artifacts_of_no_matrix_are_refused(kind, rows, cols, k):
             rsr.rsr_deserialize(bad)
         assert e.value.code == 1
     _check(rsr.rsr_deserialize(blob), M, 90, True, 0, 7, distinct=4)
+
+
+# few rows: every vector has workgroups of its own and the sums of a single product, bit for bit
+@pytest.mark.parametrize("kind,rows,cols,k,batch,bf16,pad", [
+    (rsr.RSR_TERNARY_FUSED, 64, 14336, 8, 32, False, 0), (rsr.RSR_TERNARY_FUSED, 64, 14336, 8, 30, False, 1),
+    (rsr.RSR_BINARY, 200, 9000, 8, 8, False, 8), (rsr.RSR_TERNARY_2PASS, 99, 20000, 8, 20, True, 0),
+    (rsr.RSR_TERNARY_2PASS, 99, 20000, 8, 20, True, 3), (rsr.RSR_TERNARY_FUSED, 40, 7001, 10, 18, False, 0),
+    (rsr.RSR_BINARY, 10, 32766, 8, 300, False, 0), (rsr.RSR_BINARY, 300, 14336, 5, 2, False, 0),
+    (rsr.RSR_BINARY, 8, 200, 8, 40, False, 1), (rsr.RSR_TERNARY_FUSED, 3, 17, 4, 17, False, 0)])
+def test_batches_of_few_rows(kind, rows, cols, k, batch, bf16, pad):
+    M = _matrix(kind, rows, cols, 1300 + cols)
+    h = rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), k, kind)
+    _check(h, M, batch, bf16, pad, cols, distinct=6)
+    v = torch.zeros((batch, cols + pad), device=DEV)
+    v[:, :cols] = torch.from_numpy(np.stack([gen.normal_f32(cols, seed=i) for i in range(batch)])).to(DEV)
+    v = v.to(torch.bfloat16 if bf16 else torch.float32)[:, :cols]
+    got = rsr.rsr_matvec_ex(h, v, scale=0.5)
+    for i in range(batch):
+        assert torch.equal(got[i], rsr.rsr_matvec_ex(h, v[i], scale=0.5)), i
