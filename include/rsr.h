@@ -122,6 +122,12 @@ int rsr_matvec(rsr_handle_t h, const void *v, void *out, void *stream);
  * batches of different sizes (integer-valued vectors are exact in any order).  The same call
  * gives the same bits every time.  A caller whose results must not depend on the batch that a
  * vector happens to be in makes one call per vector.
+ *
+ * An infinite or NaN element of a vector reaches the rows whose entry in its column is not zero; with
+ * the block patterns (one vector, and batches on few rows) it may reach the other rows of their blocks
+ * too, as sums of several groups are subtracted there.  The dense kind multiplies every entry, so
+ * all rows of the vector are NaN.  Other vectors of a batch are never touched.  On the matrix cores a
+ * float32 element below 2^-109 loses its bits below 2^-133.
  */
 int rsr_matvec_ex(rsr_handle_t h, const void *v, int v_dtype, float scale, void *out,
                   int batch, int64_t ldv, int64_t ldo, void *stream);

@@ -430,6 +430,69 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 v, bf16x8 w, f32x16 acc) {
 // Vector (row of the MFMA result) of accumulator register i in lane half h.
 __device__ __forceinline__ int acc_vector(int i, int h) { return 8 * (i >> 2) + 4 * h + (i & 3); }
 
+// ---- infinities and NaN ------------------------------------------------------------------------
+// 0 x inf is NaN, so one infinite or NaN element of v makes all rows of its vector NaN on the matrix
+// cores, and the float32 planes of an infinity (inf, then inf - inf) do the same to the rows that it is in.
+// The block patterns leave columns without a row out, and so do the products here (`skip_zeros`: the
+// kinds that have block patterns; the dense kind multiplies every entry): a result that is not
+// finite is summed again over the entries that are not zero.  A finite one says that all its elements
+// were, so nothing is looked at before.
+__device__ __forceinline__ bool finite(float x) { return __builtin_fabsf(x) <= 3.402823466e38f; }
+__device__ __forceinline__ float widen(float x) { return x; }
+__device__ __forceinline__ float widen(uint16_t x) { return __uint_as_float((uint32_t)x << 16); }
+
+// (Functions of their own, called where nothing else is left to do: inlined, they changed the order of
+// the instructions of the kernels around them, 2 % for 1 to 16 vectors and 15 % for bf16 tiles.)
+// row: of the codes; n: vector.
+template <typename VT, int BITS>
+__device__ __forceinline__ float nonzeros(const uint32_t *codes, int ntiles, const VT *v, long long ldv, long long row,
+                                          int n) {
+    const uint32_t *group = codes + (row / kDenseRows) * ntiles * 128 * BITS;
+    const int r = (int)(row % kDenseRows);
+    const VT *x = v + n * ldv;
+    float sum = 0.0f;
+#pragma unroll 1
+    for (int i = 0; i < ntiles * 4 * kTileSteps; ++i) {  // (tile, step, slice)
+        const int t = i >> 5, st = (i >> 2) & 7, slice = i & 3;
+        const uint32_t *lane = group + ((long long)t * 64 + 16 * slice + r) * (2 * BITS);
+        const uint32_t word = lane[BITS == 2 ? st >> 1 : st >> 2];
+        const VT *at = x + t * kTileCols + 32 * st + 8 * slice;
+#pragma unroll 1
+        for (int e = 0; e < 8; ++e) {
+            int shift;
+            if (BITS == 2) {
+                shift = (e & 1 ? 30 : 14) - 2 * (4 * (st & 1) + (e >> 1));
+            } else {
+                const int j = st & 3;
+                shift = 4 * (e < 4 ? 2 * e + 1 : 2 * (e - 4)) + (j == 3 ? 3 : 2 - j);
+            }
+            const uint32_t code = (word >> shift) & (BITS == 2 ? 3u : 1u);
+            if (code) sum += code & 2u ? -widen(at[e]) : widen(at[e]);  // (columns past the end have code 0)
+        }
+    }
+    return sum;
+}
+
+template <typename VT, int BITS>
+__device__ __attribute__((noinline)) float sum_of_nonzeros(const uint32_t *codes, int ntiles, const VT *v,
+                                                           long long ldv, long long row, int n) {
+    return nonzeros<VT, BITS>(codes, ntiles, v, ldv, row, n);
+}
+
+// A wave's results of `vectors` x `rows`, which it has stored: out is the first, of row `row` of the codes and
+// of the vector at v.
+template <typename VT, int BITS>
+__device__ __attribute__((noinline)) void sum_again(const uint32_t *codes, int ntiles, const VT *v, long long ldv,
+                                                    long long row, float *out, long long ldo, int rows, int vectors,
+                                                    float scale) {
+    __threadfence();
+    for (int n = 0; n < vectors; ++n)
+        for (int i = threadIdx.x & 63; i < rows; i += 64) {
+            float *at = out + n * ldo + i;
+            if (!finite(*at)) *at = scale * nonzeros<VT, BITS>(codes, ntiles, v, ldv, row + i, n);
+        }
+}
+
 // ---- few: up to four vectors -----------------------------------------------------------------
 // A wave takes 16 rows and a share of the columns; `wk` waves of a workgroup share the columns of
 // a row group and add their partial results at the end, the only place where waves wait for each
@@ -453,7 +516,8 @@ struct Few {
 template <typename VT, int BITS, int NV, int WK>
 __global__ __launch_bounds__(few_waves(WK) * 64) void k_packed_few(
     const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ntiles, int ngroups, int n_in, int n_out,
-    long long ldv, int nv, float scale, float *__restrict__ out, long long ldo, const LayerTable layers) {
+    long long ldv, int nv, float scale, float *__restrict__ out, long long ldo, int skip_zeros,
+    const LayerTable layers) {
     using S = Few<VT, NV>;
     constexpr int WR = few_waves(WK) / WK;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -536,16 +600,23 @@ __global__ __launch_bounds__(few_waves(WK) * 64) void k_packed_few(
     }
     const int q = lane >> 4;
     const long long row = (long long)group * kDenseRows + m;
-    if (layers.n == 0) {
-        if (q < nv && row < n_out) out[q * ldo + row] = scale * sum;
-    } else if (q == 0 && group < ngroups) {
-        // stacked handle: the group belongs to one layer (layers start on group boundaries)
-        int s = 0;
+    auto store = [&](float x) {
+        if (layers.n == 0) {
+            if (q < nv && row < n_out) out[q * ldo + row] = scale * x;
+        } else if (q == 0 && group < ngroups) {
+            // stacked handle: the group belongs to one layer (layers start on group boundaries)
+            int s = 0;
 #pragma unroll
-        for (int i = 1; i < kMaxLayers; ++i)
-            if (i < layers.n && group >= layers.first[i]) s = i;
-        const int local = (group - layers.first[s]) * kDenseRows + m;
-        if (local < layers.rows[s]) layers.out[s][local] = layers.scale[s] * sum;
+            for (int i = 1; i < kMaxLayers; ++i)
+                if (i < layers.n && group >= layers.first[i]) s = i;
+            const int local = (group - layers.first[s]) * kDenseRows + m;
+            if (local < layers.rows[s]) layers.out[s][local] = layers.scale[s] * x;
+        }
+    };
+    store(sum);
+    if (__builtin_expect(!finite(sum), 0)) {
+        if (skip_zeros && q < nv && group < ngroups)
+            store(sum_of_nonzeros<VT, BITS>(codes, ntiles, v, ldv, row, q));
     }
 }
 
@@ -571,7 +642,7 @@ constexpr int kSplitWaves = 8;
 template <typename VT, int BITS, int NT, int G, bool ROWS>
 __global__ __launch_bounds__(kSplitWaves * 64) void k_packed_split(
     const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ntiles, int ngroups, int n_in, int n_out,
-    long long ldv, int batch, float *__restrict__ out, long long ldo, float scale, int wk_log2_rows) {
+    long long ldv, int batch, float *__restrict__ out, long long ldo, float scale, int wk_log2_rows, int skip_zeros) {
     using S = Split<VT, NT>;
     const int wk_log2 = ROWS ? wk_log2_rows : 3;  // (shifts that are known: 0.3 us less for the smallest products)
     constexpr bool kPairs = NT == 2;              // 32 x 32 MFMAs over two row groups
@@ -694,7 +765,13 @@ __global__ __launch_bounds__(kSplitWaves * 64) void k_packed_split(
         const long long first = (long long)(((int)blockIdx.x * row_sets + r) * G) * kDenseRows;
         const long long rr = first + (kPairs ? 32 * (i >> 4) + (lane & 31) : 16 * (i >> 2) + (lane & 15));
         const int n = vec0 + (kPairs ? acc_vector(i & 15, half) : 4 * (lane >> 4) + (i & 3));
-        if (n < batch && rr < n_out) out[(long long)n * ldo + rr] = scale * sum;
+        if (n < batch && rr < n_out) {
+            out[(long long)n * ldo + rr] = scale * sum;
+            if (__builtin_expect(!finite(sum), 0)) {
+                if (skip_zeros)
+                    out[(long long)n * ldo + rr] = scale * sum_of_nonzeros<VT, BITS>(codes, ntiles, v, ldv, rr, n);
+            }
+        }
     }
 }
 
@@ -720,7 +797,8 @@ struct Tile {
 template <typename VT, int BITS, int KW, int RB>
 __global__ __launch_bounds__(256 * KW, 2) void k_packed_tile(
     const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ntiles, int ngroups, int n_in, int n_out,
-    long long ldv, int batch, float *__restrict__ out, long long ldo, float scale, int row_tiles, int vec_tiles) {
+    long long ldv, int batch, float *__restrict__ out, long long ldo, float scale, int row_tiles, int vec_tiles,
+    int skip_zeros) {
     using S = Tile<VT>;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
@@ -820,6 +898,10 @@ __global__ __launch_bounds__(256 * KW, 2) void k_packed_tile(
 #pragma unroll
             for (int d = 0; d < 2 * BITS; ++d) c[g][d] = cn[g][d];
     }
+    // The codes requested last are not used.  They are waited for here (vmcnt = 0): if one of their
+    // registers comes to hold an address or a result below, every store gets a wait for all that is on its
+    // way, the stores before it among them (6912 x 2560 x 512 bf16 vectors: 30.0 instead of 25.3 us).
+    __builtin_amdgcn_s_waitcnt(0x0f70);
     if constexpr (kSums == 2) {
 #pragma unroll
         for (int r = 0; r < RB; ++r)
@@ -845,6 +927,14 @@ __global__ __launch_bounds__(256 * KW, 2) void k_packed_tile(
         }
         if (kw == 1) return;
     }
+    float check = 0.0f;  // NaN if a result is not finite
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int b = 0; b < VB; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) check += 0.0f * acc[r][b][i];
+    const bool again = __ballot(check != check) != 0;
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
         const int row_out = rt * 128 + (wr * RB + r) * 32 + (lane & 31);
@@ -855,6 +945,12 @@ __global__ __launch_bounds__(256 * KW, 2) void k_packed_tile(
                 const int n = vec0 + (wn * VB + b) * 32 + acc_vector(i, half);
                 if (n < batch && row_out < n_out) out[(long long)n * ldo + row_out] = scale * acc[r][b][i];
             }
+    }
+    if (__builtin_expect(again, 0)) {
+        const int row0 = rt * 128 + wr * RB * 32, n0 = vec0 + wn * VB * 32;
+        if (skip_zeros && row0 < n_out && n0 < batch)
+            sum_again<VT, BITS>(codes, ntiles, v + n0 * ldv, ldv, row0, out + n0 * ldo + row0, ldo,
+                                min(RB * 32, n_out - row0), min(VB * 32, batch - n0), scale);
     }
 }
 
@@ -881,7 +977,8 @@ struct TableFew {
 template <typename VT, int BITS, int NV>
 __global__ __launch_bounds__(kTableWaves * 64, (TableFew<VT, NV>::occupancy)) void k_table_few(
     const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ngroups, int per, int n_in, int n_out,
-    long long ldv, int nv, float scale, float *__restrict__ out, long long ldo, const LayerTable layers) {
+    long long ldv, int nv, float scale, float *__restrict__ out, long long ldo, int skip_zeros,
+    const LayerTable layers) {
     using S = TableFew<VT, NV>;
     constexpr int U = 8 / BITS;  // row groups at a time: 4 KiB of codes
     const int lane = threadIdx.x & 63, m = lane & 15, q = lane >> 4;
@@ -914,6 +1011,7 @@ __global__ __launch_bounds__(kTableWaves * 64, (TableFew<VT, NV>::occupancy)) vo
             for (int st = 0; st < kTileSteps; ++st)
                 op[o][st] = lds_operand(smem + (n * S::planes + plane + o) * S::stride + 64 * st + 16 * q);
     }
+    uint64_t again = 0;  // lanes with results that are not finite
     for (int g = g0; g < g1; g += U) {
         uint32_t next[U][2 * BITS];
 #pragma unroll
@@ -933,19 +1031,25 @@ __global__ __launch_bounds__(kTableWaves * 64, (TableFew<VT, NV>::occupancy)) vo
                         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(op[o][st], x, acc[i], 0, 0, 0);
                 }
         }
+        float check = 0.0f;  // NaN if one of them is not finite
         if (NV == 16) {
 #pragma unroll
             for (int i = 0; i < U; ++i) {
                 const long long row = (long long)(g + i) * kDenseRows + m;
                 if (g + i >= g1 || row >= n_out) continue;
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
+                for (int e = 0; e < 4; ++e) {
                     if (4 * q + e < nv) out[(4 * q + e) * ldo + row] = scale * acc[i][e];
+                    check += 0.0f * acc[i][e];
+                }
             }
         } else {
             float sum[U];
 #pragma unroll
-            for (int i = 0; i < U; ++i) sum[i] = S::planes == 3 ? acc[i].x + (acc[i].y + acc[i].z) : acc[i].x;
+            for (int i = 0; i < U; ++i) {
+                sum[i] = S::planes == 3 ? acc[i].x + (acc[i].y + acc[i].z) : acc[i].x;
+                if (g + i < g1) check += 0.0f * sum[i];
+            }
             if (layers.n) {
 #pragma unroll
                 for (int i = 0; i < U; ++i) {
@@ -973,10 +1077,28 @@ __global__ __launch_bounds__(kTableWaves * 64, (TableFew<VT, NV>::occupancy)) vo
                 }
             }
         }
+        again |= __ballot(check != check);
 #pragma unroll
         for (int i = 0; i < U; ++i)
 #pragma unroll
             for (int d = 0; d < 2 * BITS; ++d) c[i][d] = next[i][d];
+    }
+    if (__builtin_expect(again != 0, 0)) {
+        if (!skip_zeros) return;
+        const long long row0 = (long long)g0 * kDenseRows;
+        const int rows = (int)min((long long)(g1 - g0) * kDenseRows, (long long)n_out - row0);
+        if (layers.n == 0) {
+            sum_again<VT, BITS>(codes, 1, v, ldv, row0, out + row0, ldo, rows, nv, scale);
+            return;
+        }
+        for (int s = 0; s < layers.n; ++s) {  // the part of the wave's rows that is in layer s
+            const long long start = (long long)layers.first[s] * kDenseRows;
+            const long long from = max(row0, start);
+            const long long to = min((long long)g1 * kDenseRows, start + layers.rows[s]);
+            if (from < to)
+                sum_again<VT, BITS>(codes, 1, v, 0, from, layers.out[s] + (from - start), 0, (int)(to - from), 1,
+                                    layers.scale[s]);
+        }
     }
 }
 
@@ -994,7 +1116,7 @@ struct TableMany {
 template <typename VT, int BITS, int NT>
 __global__ __launch_bounds__(kManyWaves * 64, (NT == 1 ? 4 : 2)) void k_table_many(
     const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ngroups, int n_in, int n_out, long long ldv,
-    int batch, float scale, float *__restrict__ out, long long ldo) {
+    int batch, float scale, float *__restrict__ out, long long ldo, int skip_zeros) {
     using S = TableMany<VT, NT>;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
@@ -1015,6 +1137,7 @@ __global__ __launch_bounds__(kManyWaves * 64, (NT == 1 ? 4 : 2)) void k_table_ma
     }
     __syncthreads();
     const unsigned char *x = smem + (lane & 31) * kManyStride + 32 * half;
+    uint64_t again = 0;  // lanes with results that are not finite
     for (; set < sets; set += stride) {
         uint32_t next[4][2 * BITS];
 #pragma unroll
@@ -1040,6 +1163,7 @@ __global__ __launch_bounds__(kManyWaves * 64, (NT == 1 ? 4 : 2)) void k_table_ma
                     }
             }
         }
+        float check = 0.0f;  // NaN if one of them is not finite
 #pragma unroll
         for (int ng = 0; ng < NT; ++ng)
 #pragma unroll
@@ -1050,19 +1174,29 @@ __global__ __launch_bounds__(kManyWaves * 64, (NT == 1 ? 4 : 2)) void k_table_ma
                     const long long r = (long long)set * 64 + rg * 32 + (lane & 31);
                     if (n < batch && r < n_out)
                         out[(long long)n * ldo + r] = scale * acc[rg][ng][i];
+                    check += 0.0f * acc[rg][ng][i];
                 }
             }
+        again |= __ballot(check != check);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int d = 0; d < 2 * BITS; ++d) c[i][d] = next[i][d];
+    }
+    if (__builtin_expect(again != 0, 0)) {
+        if (!skip_zeros || vec0 >= batch) return;
+        for (set = blockIdx.x * kManyWaves + w; set < sets; set += stride) {
+            const long long row0 = (long long)set * 64;
+            sum_again<VT, BITS>(codes, 1, v + vec0 * ldv, ldv, row0, out + vec0 * ldo + row0, ldo,
+                                (int)min(64LL, n_out - row0), min(32 * NT, batch - vec0), scale);
+        }
     }
 }
 
 struct Args {
     const uint32_t *codes;
     const void *v;
-    int ntiles, ngroups, n_in, n_out, batch, device;
+    int ntiles, ngroups, n_in, n_out, batch, device, skip_zeros;
     long long ldv, ldo;
     float *out;
     float scale;
@@ -1079,7 +1213,7 @@ hipError_t launch_few_wk(const Args &x) {
     constexpr int WR = few_waves(WK) / WK;
     hipLaunchKernelGGL(kern, dim3((unsigned)((x.ngroups + WR - 1) / WR)), dim3(few_waves(WK) * 64), lds, x.stream,
                        x.codes, static_cast<const VT *>(x.v), x.ntiles, x.ngroups, x.n_in, x.n_out, x.ldv, x.batch,
-                       x.scale, x.out, x.ldo, x.layers);
+                       x.scale, x.out, x.ldo, x.skip_zeros, x.layers);
     return hipGetLastError();
 }
 
@@ -1120,7 +1254,7 @@ hipError_t launch_table_few(const Args &x) {
     const unsigned grid = (unsigned)((x.ngroups + (long long)per * kTableWaves - 1) / ((long long)per * kTableWaves));
     hipLaunchKernelGGL((k_table_few<VT, BITS, NV>), dim3(grid), dim3(kTableWaves * 64), 0, x.stream, x.codes,
                        static_cast<const VT *>(x.v), x.ngroups, per, x.n_in, x.n_out, x.ldv, x.batch, x.scale, x.out,
-                       x.ldo, x.layers);
+                       x.ldo, x.skip_zeros, x.layers);
     return hipGetLastError();
 }
 
@@ -1137,7 +1271,7 @@ hipError_t launch_table_many(const Args &x) {
     if (grid > room) grid = room;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid, (unsigned)chunks), dim3(kManyWaves * 64), lds, x.stream, x.codes,
                        static_cast<const VT *>(x.v), x.ngroups, x.n_in, x.n_out, x.ldv, x.batch, x.scale, x.out,
-                       x.ldo);
+                       x.ldo, x.skip_zeros);
     return hipGetLastError();
 }
 
@@ -1179,7 +1313,8 @@ hipError_t launch_split_rows(const Args &x, int wk_log2) {
     const int groups = (kSplitWaves >> wk_log2) * G;  // of a workgroup
     const dim3 grid((unsigned)((x.ngroups + groups - 1) / groups), (unsigned)((x.batch + 16 * NT - 1) / (16 * NT)));
     hipLaunchKernelGGL(kern, grid, dim3(kSplitWaves * 64), lds, x.stream, x.codes, static_cast<const VT *>(x.v),
-                       x.ntiles, x.ngroups, x.n_in, x.n_out, x.ldv, x.batch, x.out, x.ldo, x.scale, wk_log2);
+                       x.ntiles, x.ngroups, x.n_in, x.n_out, x.ldv, x.batch, x.out, x.ldo, x.scale, wk_log2,
+                       x.skip_zeros);
     return hipGetLastError();
 }
 
@@ -1212,7 +1347,7 @@ hipError_t launch_tile_kw(const Args &x) {
     const int per = (row_tiles * vec_tiles + 7) / 8;
     hipLaunchKernelGGL(kern, dim3((unsigned)(per * 8)), dim3(256 * KW), lds, x.stream, x.codes,
                        static_cast<const VT *>(x.v), x.ntiles, x.ngroups, x.n_in, x.n_out, x.ldv, x.batch, x.out,
-                       x.ldo, x.scale, row_tiles, vec_tiles);
+                       x.ldo, x.scale, row_tiles, vec_tiles, x.skip_zeros);
     return hipGetLastError();
 }
 
@@ -1340,6 +1475,7 @@ hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, floa
     x.n_out = (int)h->rows;
     x.batch = batch;
     x.device = h->device;
+    x.skip_zeros = h->kind != RSR_DENSE_TERNARY_P2;
     x.ldv = ldv;
     x.ldo = ldo;
     x.out = out;

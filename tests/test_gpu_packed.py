@@ -257,3 +257,44 @@ def test_batches_of_few_rows(kind, rows, cols, k, batch, bf16, pad):
     got = rsr.rsr_matvec_ex(h, v, scale=0.5)
     for i in range(batch):
         assert torch.equal(got[i], rsr.rsr_matvec_ex(h, v[i], scale=0.5)), i
+
+
+def _from_codes(h):
+    """The same handle with its single vectors multiplied from the packed codes, as k = 0 may choose
+    by timing (the last field of the header of its bytes)."""
+    blob = rsr.rsr_serialize(h)
+    blob[120:128].view(np.int64)[0] = 1
+    return rsr.rsr_deserialize(blob)
+
+
+# one of the vectors has infinite or NaN elements: every kernel of the matrix cores
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("kind,rows,cols,batch", [
+    (rsr.RSR_TERNARY_FUSED, 1200, 1500, 1), (rsr.RSR_BINARY, 170000, 30, 1), (rsr.RSR_TERNARY_2PASS, 500100, 9, 1),
+    (rsr.RSR_TERNARY_FUSED, 3001, 700, 3), (rsr.RSR_TERNARY_2PASS, 1200, 300, 9), (rsr.RSR_BINARY, 601, 520, 20),
+    (rsr.RSR_TERNARY_FUSED, 12790, 300, 180), (rsr.RSR_BINARY, 12800, 290, 290),
+    (rsr.RSR_BINARY, 65540, 100, 3), (rsr.RSR_TERNARY_2PASS, 3000, 201, 11),
+    (rsr.RSR_TERNARY_FUSED, 17000, 256, 25), (rsr.RSR_BINARY, 17001, 63, 60)])
+def test_infinities_and_nan(kind, rows, cols, batch, bf16):
+    """Rows with no entry in those columns keep their values, and so do the other vectors."""
+    M = _matrix(kind, rows, cols, 17)
+    h = rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), 2, kind)
+    if batch == 1:
+        h = _from_codes(h)
+        assert "few" in rsr.rsr_kernel_name(h, int(bf16))
+    v = np.stack([gen.integer_f32(cols, seed=40 + i) for i in range(min(batch, 5))])[np.arange(batch) % min(batch, 5)]
+    want = np.stack([oracle.dense_matvec(M, x.astype(np.float64), 0.5) for x in v[:5]])[np.arange(batch) % min(batch, 5)]
+    hit = batch // 2
+    for columns in ({1: np.inf}, {0: -np.inf, cols - 1: np.inf}, {cols // 2: np.nan}):
+        x = v.copy()
+        x[hit, list(columns)] = 0.0
+        y = want.copy()
+        y[hit] = oracle.dense_matvec(M, x[hit].astype(np.float64), 0.5)
+        for j, bad in columns.items():
+            x[hit, j] = bad
+            with np.errstate(invalid="ignore"):
+                y[hit] = np.where(M[:, j] != 0, y[hit] + M[:, j] * np.float64(bad), y[hit])
+        xd = torch.from_numpy(x).to(DEV).to(torch.bfloat16 if bf16 else torch.float32)
+        got = rsr.rsr_matvec_ex(h, xd if batch > 1 else xd[0], scale=0.5).cpu().numpy().reshape(batch, rows)
+        assert np.array_equal(got.astype(np.float64), y, equal_nan=True), columns
+        assert np.isfinite(got[hit]).any() or not (M[:, list(columns)] == 0).all(axis=1).any()
