@@ -278,9 +278,11 @@ int rsr_probe_empty(int workgroups, int threads, int lds_bytes, void *stream);
 int rsr_probe_read(const void *src, int64_t bytes, int workgroups, int threads, void *sink, void *stream);
 
 /*
- * Name of the multiply kernel this handle launches for a vector type (the
- * symbol a profiler reports for one vector), or NULL on a bad argument.  Static storage (per thread; the next call overwrites it).
+ * Name of the kernel that multiplies one vector, or `batch` vectors that follow each other without
+ * gaps from a 16-byte boundary on (the symbol a profiler reports), or NULL on a bad argument.  Static
+ * storage (per thread; the next call overwrites it).
  */
+const char *rsr_batch_kernel_name(rsr_handle_t h, int v_dtype, int batch);
 const char *rsr_kernel_name(rsr_handle_t h, int v_dtype);
 
 #ifdef __cplusplus

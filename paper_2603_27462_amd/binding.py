@@ -25,7 +25,7 @@ exported_symbols = [
     "rsr_num_blocks", "rsr_block_height", "rsr_num_patterns", "rsr_num_passes",
     "rsr_algorithmic_bytes",
     "rsr_kernel_name", "rsr_preprocess_into", "rsr_launch_shape", "rsr_probe_empty", "rsr_probe_read",
-    "rsr_preprocess_stacked", "rsr_matvec_stacked", "rsr_num_layers",
+    "rsr_preprocess_stacked", "rsr_matvec_stacked", "rsr_num_layers", "rsr_batch_kernel_name",
 ]
 
 
@@ -106,6 +106,8 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.rsr_algorithmic_bytes.argtypes = [vp, ci, ci]
     lib.rsr_kernel_name.restype = ctypes.c_char_p
     lib.rsr_kernel_name.argtypes = [vp, ci]
+    lib.rsr_batch_kernel_name.restype = ctypes.c_char_p
+    lib.rsr_batch_kernel_name.argtypes = [vp, ci, ci]
     _lib = lib
     return lib
 
@@ -396,4 +398,11 @@ def rsr_kernel_name(h: Handle, v_dtype: int = RSR_F32) -> str:
     s = load_library().rsr_kernel_name(h.ptr, v_dtype)
     if s is None:
         raise RsrError(rsr_last_error(), "rsr_kernel_name")
+    return s.decode()
+
+
+def rsr_batch_kernel_name(h: Handle, v_dtype: int = RSR_F32, batch: int = 1) -> str:
+    s = load_library().rsr_batch_kernel_name(h.ptr, v_dtype, int(batch))
+    if s is None:
+        raise RsrError(rsr_last_error(), "rsr_batch_kernel_name")
     return s.decode()

@@ -1022,19 +1022,21 @@ int64_t rsr_algorithmic_bytes(rsr_handle_t h, int v_dtype, int batch) {
     return weight_side + (int64_t)batch * (h->cols * vb + h->rows * 4);
 }
 
-const char *rsr_kernel_name(rsr_handle_t h, int v_dtype) {
-    if (!good(h) || (v_dtype != RSR_F32 && v_dtype != RSR_BF16)) {
+const char *rsr_batch_kernel_name(rsr_handle_t h, int v_dtype, int batch) {
+    if (!good(h) || (v_dtype != RSR_F32 && v_dtype != RSR_BF16) || batch < 1) {
         fail(RSR_EINVAL);
         return nullptr;
     }
     static thread_local char name[96];
-    if (h->narrow && !h->single_packed)
+    if (use_packed(h, v_dtype, batch, h->cols * (v_dtype == RSR_BF16 ? 2 : 4) % 16 == 0))
+        rsr::packed_kernel_name(h, v_dtype, batch, name, sizeof(name));
+    else if (h->narrow)
         return v_dtype == RSR_BF16 ? "k_rsr_narrow<unsigned short>" : "k_rsr_narrow<float>";
-    if (use_packed(h, v_dtype, 1, true))
-        rsr::packed_matvec_kernel_name(h, v_dtype, name, sizeof(name));
     else
         rsr::rsr_matvec_kernel_name(h, v_dtype, name, sizeof(name));
     return name;
 }
+
+const char *rsr_kernel_name(rsr_handle_t h, int v_dtype) { return rsr_batch_kernel_name(h, v_dtype, 1); }
 
 }  // extern "C"

@@ -159,10 +159,10 @@ float packed_few_rows_us(const rsr_handle_s *h, bool wide, int batch);
 hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, float scale, float *out,
                          int batch, int64_t ldv, int64_t ldo, hipStream_t stream,
                          const LayerTable *layers = nullptr);
-// Writes the name of the multiply kernel h launches for (v_dtype, batch) into buf.
+// Writes the name of the kernel that multiplies into buf, as a profiler prints it.
 void rsr_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, char *buf, size_t len);
 void packed_launch_shape(const rsr_handle_s *h, int v_dtype, int *workgroups, int *threads, int *lds_bytes);
-void packed_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, char *buf, size_t len);
+void packed_kernel_name(const rsr_handle_s *h, int v_dtype, int batch, char *buf, size_t len);
 
 // --- narrow matrices (cols <= kNarrowCols) ---------------------------------------------
 constexpr int kNarrowCols = 256;

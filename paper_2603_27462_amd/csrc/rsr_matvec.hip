@@ -34,9 +34,6 @@
 // LDS addresses are raw integers: this kernel owns the whole LDS allocation
 // (it declares no static __shared__), so dynamic LDS starts at address 0.
 #include <cstdio>
-#ifdef RSR_TUNING
-#include <cstdlib>
-#endif
 
 #include "rsr_device.h"
 #include "rsr_internal.h"
@@ -678,21 +675,12 @@ int choose_waves(int64_t slabs, int64_t nb, int k, bool by_rank) {
         w = (int)(waves < 1 ? 1 : waves <= kMaxWaves ? waves : 8);
         if (!by_rank && w < 8 && 2 * w < k) w = (k + 1) / 2 < 8 ? (k + 1) / 2 : 8;
     }
-#ifdef RSR_TUNING
-    if (const char *s = std::getenv("RSR_W")) {
-        const int x = std::atoi(s);
-        if (x >= 1 && x <= kMaxWaves) w = x;
-    }
-#endif
     return w;
 }
 
 bool choose_by_rank(int64_t P, int64_t cols, int64_t longest_by_code, int64_t longest_by_rank,
                     int64_t most_groups) {
     if (matvec_lds_bytes(P, cols, 4, kMaxWaves, false) > kLdsBytes) return true;
-#ifdef RSR_TUNING
-    if (const char *s = std::getenv("RSR_BY_RANK")) return std::atoi(s) != 0;
-#endif
     // bytes per block beside the real entries: 2 per placeholder against 4 per group; the
     // rank-indexed scatter phase costs about k multiply-adds per group more, so it has to
     // win clearly

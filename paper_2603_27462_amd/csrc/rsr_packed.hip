@@ -36,9 +36,6 @@
 // almost exactly, and the other planes' rounding is 2^-8 of what it would be on top of them
 // (14336 x 4096, 700 vectors, relative error against float64 with all planes in one sum 5.6e-7).
 #include <cstdio>
-#ifdef RSR_TUNING
-#include <cstdlib>
-#endif
 
 #include "rsr_internal.h"
 
@@ -1202,10 +1199,21 @@ struct Args {
     float scale;
     hipStream_t stream;
     LayerTable layers;
+    char *name;  // not null: write the name of the kernel there instead of launching it
+    size_t name_len;
 };
+
+// The instantiation as a profiler prints it.
+template <typename VT, typename... Number>
+hipError_t put_name(const Args &x, const char *kernel, const char *numbers, Number... n) {
+    const int at = std::snprintf(x.name, x.name_len, "%s<%s, ", kernel, sizeof(VT) == 4 ? "float" : "unsigned short");
+    if (at > 0 && (size_t)at < x.name_len) std::snprintf(x.name + at, x.name_len - at, numbers, n...);
+    return hipSuccess;
+}
 
 template <typename VT, int BITS, int NV, int WK>
 hipError_t launch_few_wk(const Args &x) {
+    if (x.name) return put_name<VT>(x, "k_packed_few", "%d, %d, %d>", BITS, NV, WK);
     static std::atomic<size_t> enabled[kMaxDevices];
     auto kern = k_packed_few<VT, BITS, NV, WK>;
     constexpr size_t lds = (size_t)few_waves(WK) * (Few<VT, NV>::wave_bytes + 64 * 4);
@@ -1223,9 +1231,6 @@ hipError_t launch_few_wk(const Args &x) {
 // 5.9 / 5.4 us, 2560 x 6912 (27) 4.6 / 3.7 / 3.6, 4096 x 4096 (16) 3.3 / 3.0 / 3.2, 14336 x 4096
 // 5.3 / 4.9 / 6.1; 100000 x 256 (one tile) 3.3 with one wave, 4.3 with two.
 int few_wk(int ntiles) {
-#ifdef RSR_TUNING
-    if (const char *s = std::getenv("RSR_WK")) return std::atoi(s);
-#endif
     return ntiles >= 24 ? 16 : ntiles >= 8 ? 8 : ntiles >= 4 ? 4 : ntiles >= 2 ? 2 : 1;
 }
 
@@ -1249,6 +1254,7 @@ int table_groups_per_wave(int64_t groups, int waves) {
 
 template <typename VT, int BITS, int NV>
 hipError_t launch_table_few(const Args &x) {
+    if (x.name) return put_name<VT>(x, "k_table_few", "%d, %d>", BITS, NV);
     constexpr int waves = kCUs * 4 * TableFew<VT, NV>::occupancy;
     const int per = table_groups_per_wave(x.ngroups, waves);
     const unsigned grid = (unsigned)((x.ngroups + (long long)per * kTableWaves - 1) / ((long long)per * kTableWaves));
@@ -1260,6 +1266,7 @@ hipError_t launch_table_few(const Args &x) {
 
 template <typename VT, int BITS, int NT>
 hipError_t launch_table_many(const Args &x) {
+    if (x.name) return put_name<VT>(x, "k_table_many", "%d, %d>", BITS, NT);
     static std::atomic<size_t> enabled[kMaxDevices];
     auto kern = k_table_many<VT, BITS, NT>;
     constexpr size_t lds = TableMany<VT, NT>::lds;
@@ -1304,6 +1311,7 @@ SplitShape split_shape(int ntiles, int ngroups, int batch, bool wide) {
 
 template <typename VT, int BITS, int NT, int G, bool ROWS>
 hipError_t launch_split_rows(const Args &x, int wk_log2) {
+    if (x.name) return put_name<VT>(x, "k_packed_split", "%d, %d, %d, %s>", BITS, NT, G, ROWS ? "true" : "false");
     static std::atomic<size_t> enabled[kMaxDevices];
     auto kern = k_packed_split<VT, BITS, NT, G, ROWS>;
     constexpr size_t lds = (size_t)kSplitWaves * Split<VT, NT>::wave_bytes;
@@ -1338,6 +1346,7 @@ hipError_t launch_split(const Args &x) {
 
 template <typename VT, int BITS, int KW, int RB>
 hipError_t launch_tile_kw(const Args &x) {
+    if (x.name) return put_name<VT>(x, "k_packed_tile", "%d, %d, %d>", BITS, KW, RB);
     static std::atomic<size_t> enabled[kMaxDevices];
     auto kern = k_packed_tile<VT, BITS, KW, RB>;
     constexpr size_t lds = 2 * (size_t)Tile<VT>::buffer;
@@ -1368,9 +1377,6 @@ hipError_t launch_tile(const Args &x) {
 // (162) 57 / 73.  Up to 32 vectors a tile is mostly padding (60000 x 300, 24 float32 vectors:
 // 24.3 / 13.5).
 bool use_tile(const Args &x, bool wide) {
-#ifdef RSR_TUNING
-    if (const char *s = std::getenv("RSR_TILE")) return std::atoi(s) != 0;
-#endif
     const long long workgroups = (long long)((x.n_out + 127) / 128) * ((x.batch + 127) / 128);
     return workgroups >= (wide ? 160 : 128) && x.batch > 32;
 }
@@ -1464,18 +1470,31 @@ hipError_t launch_restore_codes(const rsr_handle_s *h, int *err_flag) {
     return h->code_bits == 1 ? launch_restore<1>(h, err_flag) : launch_restore<2>(h, err_flag);
 }
 
+namespace {
+
+void set_sizes(const rsr_handle_s *h, int batch, Args *x) {
+    x->codes = reinterpret_cast<const uint32_t *>(h->packed);
+    x->ntiles = (int)((h->cols + kTileCols - 1) / kTileCols);
+    x->ngroups = (int)h->code_groups;
+    x->n_in = (int)h->cols;
+    x->n_out = (int)h->rows;
+    x->batch = batch;
+    x->device = h->device;
+    x->skip_zeros = h->kind != RSR_DENSE_TERNARY_P2;
+}
+
+hipError_t launch_any(const rsr_handle_s *h, int v_dtype, const Args &x) {
+    if (h->code_bits == 1) return v_dtype == RSR_BF16 ? launch<uint16_t, 1>(x) : launch<float, 1>(x);
+    return v_dtype == RSR_BF16 ? launch<uint16_t, 2>(x) : launch<float, 2>(x);
+}
+
+}  // namespace
+
 hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, float scale, float *out, int batch,
                          int64_t ldv, int64_t ldo, hipStream_t stream, const LayerTable *layers) {
     Args x;
-    x.codes = reinterpret_cast<const uint32_t *>(h->packed);
+    set_sizes(h, batch, &x);
     x.v = v;
-    x.ntiles = (int)((h->cols + kTileCols - 1) / kTileCols);
-    x.ngroups = (int)h->code_groups;
-    x.n_in = (int)h->cols;
-    x.n_out = (int)h->rows;
-    x.batch = batch;
-    x.device = h->device;
-    x.skip_zeros = h->kind != RSR_DENSE_TERNARY_P2;
     x.ldv = ldv;
     x.ldo = ldo;
     x.out = out;
@@ -1485,8 +1504,16 @@ hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, floa
         x.layers = *layers;
     else
         x.layers.n = 0;
-    if (h->code_bits == 1) return v_dtype == RSR_BF16 ? launch<uint16_t, 1>(x) : launch<float, 1>(x);
-    return v_dtype == RSR_BF16 ? launch<uint16_t, 2>(x) : launch<float, 2>(x);
+    x.name = nullptr;
+    return launch_any(h, v_dtype, x);
+}
+
+void packed_kernel_name(const rsr_handle_s *h, int v_dtype, int batch, char *buf, size_t len) {
+    Args x = {};
+    set_sizes(h, batch, &x);
+    x.name = buf;
+    x.name_len = len;
+    (void)launch_any(h, v_dtype, x);
 }
 
 // Flat in the number of rows as long as every CU has at most one workgroup, linear in the column tiles
@@ -1513,16 +1540,6 @@ void packed_launch_shape(const rsr_handle_s *h, int v_dtype, int *workgroups, in
     *workgroups = (int)((h->code_groups + rows - 1) / rows);
     *threads = waves * 64;
     *lds_bytes = waves * (wave_bytes + 64 * 4);
-}
-
-void packed_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, char *buf, size_t len) {
-    // the instantiation a single vector launches, as a profiler prints it
-    const int ntiles = (int)((h->cols + kTileCols - 1) / kTileCols);
-    const char *type = v_dtype == RSR_BF16 ? "unsigned short" : "float";
-    if (table_vectors(ntiles, h->rows, 1, v_dtype != RSR_BF16))
-        std::snprintf(buf, len, "k_table_few<%s, %d, 1>", type, h->code_bits);
-    else
-        std::snprintf(buf, len, "k_packed_few<%s, %d, 1, %d>", type, h->code_bits, few_wk(ntiles));
 }
 
 }  // namespace rsr
