@@ -10,7 +10,9 @@ from . import binding as _b
 
 class RsrLinear(torch.nn.Module):
     """y = scale * W x for a fixed int8 weight W [out_features][in_features] in {-1,0,+1}
-    ({0,1} for the binary kind).  k = 0 lets the library choose the block height."""
+    ({0,1} for the binary kind).  k = 0 lets the library choose the block height.  All tokens of a call
+    are one batch, and the order of the sums depends on its size: a token's outputs may differ in their
+    last bits between a call for it alone, a small batch and a prompt (see rsr_matvec_ex)."""
 
     def __init__(self, weight: torch.Tensor, scale: float = 1.0, k: int = 0,
                  kind: int = _b.RSR_TERNARY_FUSED):

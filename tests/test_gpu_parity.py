@@ -197,8 +197,9 @@ def test_batch_and_strides():
     (rsr.RSR_DENSE_TERNARY_P2, True, 5, 19), (rsr.RSR_DENSE_TERNARY_P2, False, 2, 6)])
 def test_batch_many_blocks(kind, bf16, pad, batch):
     """Many blocks and several vectors in one call; aligned and unaligned vector strides;
-    integer-valued vectors, so every output is exact.  264 columns take the general kernel,
-    200 columns the one for narrow matrices."""
+    integer-valued vectors, so every output is exact.  Batches on that many rows run on the matrix cores;
+    each vector alone takes the general kernel of the block patterns with 264 columns, the one for
+    narrow matrices with 200."""
     for cols in (264, 200):
         _batch_many_blocks(kind, bf16, pad, batch, cols)
 
@@ -217,6 +218,8 @@ def _batch_many_blocks(kind, bf16, pad, batch, cols):
     for i in range(batch):
         want = oracle.dense_matvec(M, vi[i].astype(np.float64), 3.0)
         assert np.array_equal(got[i, :rows].astype(np.float64), want), "vector %d" % i
+        alone = rsr.rsr_matvec_ex(h, vbuf[i, :cols], scale=3.0).cpu().numpy()
+        assert np.array_equal(alone.astype(np.float64), want), "vector %d alone" % i
 
 
 @pytest.mark.parametrize("kind,rows,cols,k,batch,bf16,pad", [
@@ -227,8 +230,9 @@ def _batch_many_blocks(kind, bf16, pad, batch, cols):
     (rsr.RSR_TERNARY_FUSED, 4096, 1000, 8, 4, True, 4),     # the common class count, short stream
     (rsr.RSR_BINARY, 3100, 2000, 2, 5, True, 0)])           # four waves per block
 def test_batch_shapes(kind, rows, cols, k, batch, bf16, pad):
-    """Batches over the launch shapes of the multiply kernel: integer-valued vectors, so
-    every output of every vector is exact; rows past the matrix stay untouched."""
+    """The launch shapes of the block patterns' kernel, one vector at a time, and the same vectors as a
+    batch, whichever kernel takes it: integer-valued vectors, so every output is exact in any order of
+    the sums; rows past the matrix stay untouched."""
     if cols >= 30000:
         M = gen.dictionary_binary_matrix(rows, cols, k, 1000, 5)   # 30000 entries + 3100 placeholders
     else:
@@ -244,9 +248,29 @@ def test_batch_shapes(kind, rows, cols, k, batch, bf16, pad):
     for i in range(batch):
         want = oracle.dense_matvec(M, vi[i].astype(np.float64), -2.0)
         assert np.array_equal(got[i, :rows].astype(np.float64), want), "vector %d" % i
-    # and one vector alone gives the same bits as it did inside the batch
-    alone = rsr.rsr_matvec_ex(h, vbuf[1, :cols], scale=-2.0).cpu().numpy()
-    assert np.array_equal(alone, got[1, :rows])
+        alone = rsr.rsr_matvec_ex(h, vbuf[i, :cols], scale=-2.0).cpu().numpy()
+        assert np.array_equal(alone.astype(np.float64), want), "vector %d alone" % i
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("kind,k", [(rsr.RSR_TERNARY_FUSED, 6), (rsr.RSR_BINARY, 8), (rsr.RSR_DENSE_TERNARY_P2, 0)])
+def test_a_vector_in_batches_of_every_size(kind, k, bf16):
+    """The order of the sums depends on the number of vectors, so a vector's result may differ between
+    batches, but by rounding only: two float32 sums of n terms, in whatever order, are within
+    2 n 2^-24 sum |v| of each other.  The same call gives the same bits, and a vector that is multiplied
+    alone always does."""
+    rows, cols = 3000, 1500
+    M = _matrix(kind, rows, cols, 5)
+    h = rsr.rsr_preprocess(_dev(M), k, kind)
+    v = torch.from_numpy(np.stack([gen.normal_f32(cols, seed=60 + i) for i in range(700)])).to(DEV)
+    v = v.to(torch.bfloat16 if bf16 else torch.float32)
+    alone = rsr.rsr_matvec_ex(h, v[3])
+    bound = 2 * cols * 2.0 ** -24 * float(v[3].double().abs().sum())
+    for batch in (4, 9, 16, 31, 100, 700):
+        got = rsr.rsr_matvec_ex(h, v[:batch])
+        assert float((got[3] - alone).abs().max()) <= bound
+        assert torch.equal(got, rsr.rsr_matvec_ex(h, v[:batch]))
+    assert torch.equal(alone, rsr.rsr_matvec_ex(h, v[3]))
 
 
 @pytest.mark.parametrize("kind,k", [(rsr.RSR_TERNARY_FUSED, 6), (rsr.RSR_TERNARY_2PASS, 5),
