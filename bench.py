@@ -267,7 +267,7 @@ def run_configs(args):
                         "v_dtype": "bf16" if bf16 else "f32", "launches": len(sets[0]),
                         "weight_sets": nsets, "algorithmic_MB": nbytes / 1e6,
                         "cold_us": tc, "warm_us": tw, "cold_GBs": nbytes / tc / 1e3,
-                        "kernel": rsr.rsr_kernel_name(sets[0][0], vt)})
+                        "kernel": rsr.rsr_batch_kernel_name(sets[0][0], vt, batch)})
         print("  %-44s %-13s k=%2d batch=%d: cold %8.2f us  warm %8.2f us  %6.1f MB  %5.0f GB/s  k used %s"
               % (name, kind_name[kind], k, batch, tc, tw, nbytes / 1e6, nbytes / tc / 1e3,
                  sorted(set(h.k for h in sets[0]))),

@@ -368,8 +368,9 @@ done:
 // and the k sweep of its interface), so it is chosen by measurement: preprocess with each
 // candidate height (make(k) returns the handle or null), time the multiply kernel, keep the
 // fastest handle.  Then add_codes(handle) gives it its packed codes, and if a single vector is
-// multiplied faster from those, the handle does so (measured on MI355X: at every size tried;
-// 2560 x 2560 bf16 3.0 us against 4.6 with the best height, 4096 x 14336 5.4 against 6.3).
+// multiplied faster from those, the handle does so (measured on MI355X: wherever there are rows for
+// the chip, 2560 x 2560 bf16 3.0 us against 4.6 with the best height, 4096 x 14336 5.4 against 6.3;
+// not with few rows, 512 x 14336 float32 7.2 against 5.1).
 // padded_rows: an upper bound of the rows of any candidate handle.
 template <typename Make, typename AddCodes>
 rsr_handle_s *preprocess_auto_k(int kind, int64_t padded_rows, int64_t cols, Make make, AddCodes add_codes) {

@@ -2,8 +2,8 @@
 //
 // A batch of vectors turns the product into a contraction, so it runs on the matrix cores
 // straight from the matrix entries, packed to 2 bits (ternary) or 1 bit (binary), whatever
-// the kind of the handle; the redundancy a block of rows has is worth less there than the
-// vectors that share one decoded weight.  The dense kind, the comparison point without any
+// the kind of the handle (but for matrices of few rows, see use_packed); the redundancy a block of
+// rows has is worth less there than the vectors that share one decoded weight.  The dense kind, the comparison point without any
 // preprocessing beyond packing (the role the paper gives its low-bit multiplier baseline in
 // Benchmarking Results), multiplies a single vector this way too.  Kernels:
 //   few    16 rows x up to 4 vectors per wave, for 1 to 4 vectors
@@ -31,10 +31,13 @@
 //
 // float32 vectors are split exactly into three bf16 planes (top, middle and bottom 8
 // significant bits) that take one MFMA each, so integer-valued inputs stay exact and nothing
-// is lost against float32 inputs.  Accumulation is float32 throughout and the order of the
-// sums is fixed.  The top plane has sums of its own: its products have few bits, so they add up
-// almost exactly, and the other planes' rounding is 2^-8 of what it would be on top of them
-// (14336 x 4096, 700 vectors, relative error against float64 with all planes in one sum 5.6e-7).
+// is lost against float32 inputs (elements below 2^-109 excepted, whose last bits a bf16 cannot
+// hold).  Accumulation is float32 throughout and the order of the sums is fixed.  In split and tile,
+// and up to four vectors, where every plane is a row of its own, the top plane has sums of its
+// own: its products have few bits, so they add up almost exactly, and the other planes' rounding is
+// 2^-8 of what it would be on top of them (14336 x 4096, 700 vectors, relative error against float64
+// 4.6e-8, with all planes in one sum 5.6e-7).  The tables of up to 256 columns with more vectors add all
+// planes into one: sums that short do not need it (at most 1.6e-7; the block patterns 1.6e-7 and more).
 #include <cstdio>
 
 #include "rsr_internal.h"
@@ -1361,10 +1364,12 @@ hipError_t launch_tile_kw(const Args &x) {
 }
 
 // Up to 256 workgroups a CU has one, and eight waves do better than four: 4096 x 14336 x 512 bf16
-// vectors 125 -> 105 us, 6912 x 2560 x 300 float32 75 -> 57; beyond, two workgroups share a CU and
-// four waves each are faster (14336 x 4096 x 2048 bf16: 207 against 221).  With eight waves bf16 is
-// bound by decoding, so a wave takes 32 rows and all vectors (every code decoded by two waves
-// instead of four: 120 -> 105); float32 reads its three planes of v too often then (252 -> 259).
+// vectors 118 -> 108 us, 6912 x 2560 x 300 float32 71 -> 53; beyond, two workgroups share a CU and four
+// waves each are faster (6912 x 2560 x 700: bf16 37.8 against 38.8, float32 95 against 106), until, from
+// 500 workgroups on, the two meet (4096 x 4096 x 2048 float32 172 / 175; 14336 x 4096 x 700 260 / 244).
+// With eight waves bf16 is bound by decoding, so a wave takes 32 rows and all vectors (every code
+// decoded by one wave instead of two: 120 -> 105); float32 reads its three planes of v too often then
+// (252 -> 259).
 template <typename VT, int BITS>
 hipError_t launch_tile(const Args &x) {
     if ((long long)((x.n_out + 127) / 128) * ((x.batch + 127) / 128) > kCUs) return launch_tile_kw<VT, BITS, 1, 2>(x);
@@ -1372,9 +1377,9 @@ hipError_t launch_tile(const Args &x) {
 }
 
 // Tiles of 128 x 128 need enough workgroups to be worth their size, tiles / columns split over waves:
-// bf16 4096 x 4096 x 512 vectors (128 workgroups) 34.7 / 36.8 us, 4096 x 14336 x 512 105 / 117,
-// 14336 x 4096 x 100 (112) 28.7 / 27.4; float32 14336 x 4096 x 100 (112) 79 / 64, 6912 x 2560 x 300
-// (162) 57 / 73.  Up to 32 vectors a tile is mostly padding (60000 x 300, 24 float32 vectors:
+// bf16 4096 x 4096 x 512 vectors (128 workgroups) 33.7 / 36.2 us, 4096 x 14336 x 512 108 / 119,
+// 14336 x 4096 x 100 (112) 31.6 / 27.3; float32 14336 x 4096 x 100 (112) 76 / 60, 4096 x 4096 x 512 (128)
+// 80 / 64, x 600 (160) 82 / 78, 6912 x 2560 x 300 (162) 53 / 69.  Up to 32 vectors a tile is mostly padding (60000 x 300, 24 float32 vectors:
 // 24.3 / 13.5).
 bool use_tile(const Args &x, bool wide) {
     const long long workgroups = (long long)((x.n_out + 127) / 128) * ((x.batch + 127) / 128);
