@@ -80,7 +80,10 @@ enum {
  * group (8-bit entries, tail bits and one sign word per existing group when cols <= 256);
  * the per-group prefix array of the kernel is indexed by pattern code, or by the rank of the
  * group among the existing ones when P is much larger than cols.  It also keeps the entries
- * packed to 2 bits (1 bit for RSR_BINARY), from which batches are multiplied.
+ * packed to 2 bits (1 bit for RSR_BINARY), from which batches are multiplied: ceil(rows/16) *
+ * ceil(cols/256) KiB (half of that), about as much as the stream.  A handle made with k = 0 that
+ * multiplies single vectors from them keeps its stream all the same (getters, byte strings, batches on
+ * few rows).
  *
  * Runs on the current HIP device, on the null stream, and synchronises
  * before returning.  Returns NULL on failure (see rsr_last_error()).
