@@ -298,3 +298,29 @@ def test_infinities_and_nan(kind, rows, cols, batch, bf16):
         got = rsr.rsr_matvec_ex(h, xd if batch > 1 else xd[0], scale=0.5).cpu().numpy().reshape(batch, rows)
         assert np.array_equal(got.astype(np.float64), y, equal_nan=True), columns
         assert np.isfinite(got[hit]).any() or not (M[:, list(columns)] == 0).all(axis=1).any()
+
+
+@pytest.mark.parametrize("kind,rows,cols,k,batch", [
+    (rsr.RSR_TERNARY_FUSED, 64, 14336, 8, 20),      # few rows: block patterns
+    (rsr.RSR_TERNARY_FUSED, 5000, 700, 8, 4), (rsr.RSR_BINARY, 5000, 700, 8, 20),
+    (rsr.RSR_BINARY, 17000, 100, 8, 60), (rsr.RSR_DENSE_TERNARY_P2, 25700, 300, 0, 300)])
+def test_batches_in_a_graph(kind, rows, cols, k, batch):
+    """Captured and replayed several times, with new vectors in the same buffer and other work between."""
+    M = _matrix(kind, rows, cols, 3)
+    h = rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), k, kind)
+    v = torch.zeros((batch, cols), device=DEV)
+    out = torch.zeros((batch, rows), device=DEV)
+    rsr.rsr_matvec_ex(h, v, out=out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rsr.rsr_matvec_ex(h, v, out=out)
+    for i in range(4):
+        v.copy_(torch.randint(-8, 9, (batch, cols), device=DEV))
+        want = rsr.rsr_matvec_ex(h, v)
+        out.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), i
+    assert np.array_equal(want[1].cpu().numpy().astype(np.float64),
+                          oracle.dense_matvec(M, v[1].cpu().numpy().astype(np.float64)))
