@@ -1048,7 +1048,7 @@ __global__ __launch_bounds__(kTableWaves * 64, (TableFew<VT, NV>::occupancy)) vo
 #pragma unroll
             for (int i = 0; i < U; ++i) {
                 sum[i] = S::planes == 3 ? acc[i].x + (acc[i].y + acc[i].z) : acc[i].x;
-                if (g + i < g1) check += 0.0f * sum[i];
+                check += 0.0f * sum[i];  // (behind g1: some finite weights, whatever the registers hold)
             }
             if (layers.n) {
 #pragma unroll
