@@ -43,7 +43,11 @@ bool use_packed(const rsr_handle_s *h, int v_dtype, int batch, bool aligned) {
     if (h->narrow) return !(h->nb == 1 && h->npass == 1 && wide && batch > 16);
     if (h->nb * batch > 4096) return true;
     const float blocks = rsr::rsr_matvec_us(h, wide ? 4 : 2, batch, aligned) * (h->k > 8 ? 1.35f : 1.0f);
-    return blocks > 0.85f * rsr::packed_few_rows_us(h, wide, batch);
+    // 0.85 keeps wrong picks out over all shapes. With a workgroup per CU at most, ordinary heights and long aligned
+    // vectors the estimate is closer: 0.95 takes 202 more of the products it was fitted on to the block patterns, each
+    // at 0.91 of the time or less (mean 1/1.26); at 1.0 it would be 280 with 9 wrong, the worst 1.13 times slower
+    const bool sure = h->nb * batch <= 256 && batch <= 16 && h->k >= 4 && h->k <= 8 && aligned && h->cols >= 8000;
+    return blocks > (sure ? 0.95f : 0.85f) * rsr::packed_few_rows_us(h, wide, batch);
 }
 
 // Whether every vector starts on a 16-byte boundary.

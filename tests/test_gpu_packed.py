@@ -246,6 +246,7 @@ def test_artifacts_of_no_matrix_are_refused(kind, rows, cols, k):
     (rsr.RSR_BINARY, 200, 9000, 8, 8, False, 8), (rsr.RSR_TERNARY_2PASS, 99, 20000, 8, 20, True, 0),
     (rsr.RSR_TERNARY_2PASS, 99, 20000, 8, 20, True, 3), (rsr.RSR_TERNARY_FUSED, 40, 7001, 10, 18, False, 0),
     (rsr.RSR_BINARY, 10, 32766, 8, 300, False, 0), (rsr.RSR_BINARY, 300, 14336, 5, 2, False, 0),
+    (rsr.RSR_BINARY, 512, 14336, 8, 2, True, 0), (rsr.RSR_BINARY, 512, 14336, 8, 4, True, 8),
     (rsr.RSR_BINARY, 8, 200, 8, 40, False, 1), (rsr.RSR_TERNARY_FUSED, 3, 17, 4, 17, False, 0)])
 def test_batches_of_few_rows(kind, rows, cols, k, batch, bf16, pad):
     M = _matrix(kind, rows, cols, 1300 + cols)
