@@ -28,11 +28,11 @@ bool is_rsr_kind(int kind) {
 // (4096 x 14336 fused k = 8, 4 vectors: 7.6 us against 32).  But their workgroups share the columns of
 // at least 16 rows, so a matrix of few rows leaves most of the chip idle, while the block patterns
 // have a workgroup per block and vector: 512 x 14336 fused k = 8, float32, 8 vectors 17.6 against 9.2 us,
-// 64 x 14336, 32 vectors 31 against 5.5.  So both are estimated; the estimates differ from 23000
-// measured products (binary k = 2..12, fused 2..10, two passes 4..12, 1..10000 rows, 257..32766 columns,
-// 2..300 vectors, both types) by 15 % in the mean, and by more for blocks of more than eight rows, hence
-// the 0.85 and the 1.35: with them the block patterns are taken wrongly, by more than 4 %, in 16 of
-// 4650 cases.
+// 64 x 14336, 32 vectors 31 against 5.5.  So both are estimated; the estimates differ from the 17528
+// measured products that they are fitted to (binary k = 2..12, fused 2..10, two passes 4..12, 1..10000
+// rows, 300..32766 columns, 2..300 vectors, both types) by 12 % in the mean for the block patterns and 7 %
+// for the codes, hence the 0.85; the 1.35 keeps blocks of more than eight rows on the safe side.  With them
+// the block patterns are taken wrongly, by more than 4 %, in 16 of 4692 cases.
 bool use_packed(const rsr_handle_s *h, int v_dtype, int batch, bool aligned) {
     if (h->kind == RSR_DENSE_TERNARY_P2) return true;
     if (!h->packed) return false;
