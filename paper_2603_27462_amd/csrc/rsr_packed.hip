@@ -958,13 +958,13 @@ __global__ __launch_bounds__(256 * KW, 2) void k_packed_tile(
 // One tile of columns: all of a vector fits the registers (or the LDS) of a wave, so it is brought
 // into operand order once and the wave then works through many row groups, with nothing but their
 // codes to wait for.  1048576 x 256 binary, float32 vectors, before (a wave stages v for every 512
-// bytes of codes; tiles of 128 vectors) and now: 1 vector 24.7 -> 14.5 us (2.6 TB/s, bound by
-// decoding and MFMAs about alike), 16 vectors 171 -> 32, 64 vectors 201 -> 100 (3.0 TB/s, of which
+// bytes of codes; tiles of 128 vectors) and now: 1 vector 24.7 -> 14.5 us with bf16 operands, 8.4 with digits (4.5 TB/s; a
+// plain read of the codes takes 6.6), 16 vectors 171 -> 32, 64 vectors 201 -> 100 (3.0 TB/s, of which
 // the 268 MB of results take two thirds).
 
 // table_few: up to 16 vectors.  The operands of the eight 32-column steps stay in registers; for up
 // to four vectors the float32 planes are rows of the MFMA as in k_packed_few, beyond that every
-// plane is an MFMA of its own.
+// plane is an MFMA of its own.  One vector: digits, below.
 constexpr int kTableWaves = 4;
 template <typename VT, int NV>
 struct TableFew {
@@ -973,6 +973,163 @@ struct TableFew {
     static constexpr int occupancy = operands == 3 ? 2 : 4;  // waves per SIMD
     static constexpr int stride = kTileCols * 2 + 16;  // bytes between slots: an odd number of 16-byte units
 };
+
+// One vector: the 16 rows of the MFMA are free for its digits.  With 2^E <= max |v| < 2^(E+1) an element
+// is the sum of d_p 2^(E-3-5p), p = 0..15, d_p whole numbers from -16 to 16.  Those are exact in the 8-bit float
+// format, and the nibbles of the codes are 4-bit floats as they are, so v_mfma_scale_f32_16x16x128_f8f6f4
+// takes both: per row group 2 MFMAs of 14.6 ns where the bf16 operands took 8 of 7.7, and one AND for eight
+// entries where they took an AND and four conversions.  Every row of the result is a sum of whole
+// numbers below 2^13 in units of its own plane, which is exact (the instruction cuts off what lies 2^-15
+// and more below its largest term: 14 binades in one sum were measured to be wrong by 4e-5 of it), so
+// the only roundings are those of the final sum over the planes.  Not taken, by the whole
+// workgroup, where an element reaches below the last digit (nonzero and smaller than 2^(E-55)) or is not finite.
+constexpr int kDigits = 16;
+constexpr int kDigitStride = kTileCols + 16;  // bytes between planes
+constexpr int kDigitExponents = 55;
+constexpr int kTableOneLds = kDigits * kDigitStride + 2 * kTableWaves * 4;  // digits; two floats per wave
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+
+// Where the digit of a column stands among the 256 of its plane, [half][lane quarter][dword][nibble] of the weights'
+// operand; `weight`: what an entry of 1 is as a 4-bit float there.
+template <int BITS>
+__device__ __forceinline__ int digit_place(int col, float *weight) {
+    const int st = col >> 5, q = (col >> 3) & 3, e = col & 7;
+    if (BITS == 1) {
+        const int j = st & 3;
+        *weight = j == 1 ? 1.0f : j == 2 ? 0.5f : 2.0f;
+        return 128 * (st >> 2) + 32 * q + 8 * j + (e < 4 ? 2 * e + 1 : 2 * (e - 4));
+    }
+    const int bit = (e & 1 ? 30 : 14) - 2 * (4 * (st & 1) + (e >> 1));
+    *weight = 2.0f;
+    return 128 * (st >> 2) + 32 * q + 16 * ((st >> 1) & 1) + (bit & 2 ? 0 : 8) + (bit >> 2);
+}
+
+// The weights' operand of half h of the columns.
+template <int BITS>
+__device__ __forceinline__ i32x8 nibbles(const uint32_t (&w)[2 * BITS], int h) {
+    i32x4 x;
+    if (BITS == 1) {
+        x = i32x4{(int)(w[h] & 0x44444444u), (int)(w[h] & 0x22222222u), (int)(w[h] & 0x11111111u),
+                  (int)((w[h] >> 1) & 0x44444444u)};
+    } else {
+        const uint32_t a = w[2 * h * (BITS - 1)], b = w[2 * h * (BITS - 1) + 1];
+        x = i32x4{(int)(a & 0xccccccccu), (int)((a << 2) & 0xccccccccu), (int)(b & 0xccccccccu),
+                  (int)((b << 2) & 0xccccccccu)};
+    }
+    return __builtin_shufflevector(x, x, 0, 1, 2, 3, -1, -1, -1, -1);
+}
+
+// The largest of the wave's values, none of them negative, in lane 63.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_max(float x) {
+    return __builtin_fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROW_MASK, 0xf, false)));
+}
+__device__ __forceinline__ float wave_max(float x) {
+    x = dpp_max<0x111, 0xf>(x);  // row_shr:1, 2, 4, 8
+    x = dpp_max<0x112, 0xf>(x);
+    x = dpp_max<0x114, 0xf>(x);
+    x = dpp_max<0x118, 0xf>(x);
+    x = dpp_max<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+    return dpp_max<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
+}
+
+// Writes the digits of v to LDS, a thread per column; false (for the whole workgroup) if they do not hold it.
+// *exponent: of the unit of plane 0.  `most`: two floats per wave.
+template <typename VT, int BITS>
+__device__ __forceinline__ bool table_digits(const VT *__restrict__ v, int n_in, unsigned char *digits, float *most,
+                                             int *exponent) {
+    const int col = threadIdx.x;
+    const float x = col < n_in ? widen(v[col]) : 0.0f;
+    float top = wave_max(__builtin_fabsf(x));  // (a NaN is lost by the maximum and found below)
+    if ((col & 63) == 63) most[col >> 6] = top;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kTableWaves; ++i) top = __builtin_fmaxf(top, most[i]);
+    const int E = top > 0.0f ? (int)__builtin_amdgcn_frexp_expf(top) - 1 : 0;
+    const bool bad = !finite(x) || (x != 0.0f && (int)__builtin_amdgcn_frexp_expf(x) - 1 < E - kDigitExponents);
+    float weight;
+    unsigned char *at = digits + digit_place<BITS>(col, &weight);
+    const float unit = 1.0f / weight;
+    float rest = __builtin_amdgcn_ldexpf(x, 3 - E);
+#pragma unroll
+    for (int p = 0; p < kDigits; p += 2) {
+        const float d0 = __builtin_rintf(rest);
+        rest = (rest - d0) * 32.0f;
+        const float d1 = __builtin_rintf(rest);
+        rest = (rest - d1) * 32.0f;
+        const int two = __builtin_amdgcn_cvt_pk_fp8_f32(d0 * unit, d1 * unit, 0, false);
+        at[p * kDigitStride] = (unsigned char)two;
+        at[(p + 1) * kDigitStride] = (unsigned char)(two >> 8);
+    }
+    *exponent = E - 3;
+    const uint64_t lanes = __ballot(bad);
+    if ((col & 63) == 0) most[kTableWaves + (col >> 6)] = lanes ? 1.0f : 0.0f;
+    __syncthreads();
+    float any = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kTableWaves; ++i) any += most[kTableWaves + i];
+    return any == 0.0f;
+}
+
+// The row groups [g0, g1) of a wave with the digits in LDS; c: the codes of the first ones.
+template <int BITS, int U>
+__device__ __forceinline__ void table_by_digits(const uint32_t *__restrict__ c0, uint32_t (&c)[U][2 * BITS],
+                                                const unsigned char *digits, int exponent, int g0, int g1, int n_out,
+                                                float scale, float *__restrict__ out, const LayerTable &layers) {
+    const int lane = threadIdx.x & 63, m = lane & 15, q = lane >> 4;
+    i32x8 op[2];  // row m: plane m; bytes 0..15 and 16..31: columns 16 q and 64 + 16 q of a half
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const i32x4 lo = *reinterpret_cast<const i32x4 *>(digits + m * kDigitStride + 128 * h + 16 * q);
+        const i32x4 hi = *reinterpret_cast<const i32x4 *>(digits + m * kDigitStride + 128 * h + 64 + 16 * q);
+        op[h] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+    const int plane_scale = 127 - 5 * m;  // a power of two, biased by 127
+    for (int g = g0; g < g1; g += U) {
+        uint32_t next[U][2 * BITS];
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+            if (g + U + i < g1) load_codes<BITS>(c0 + (long long)(g + U + i) * 128 * BITS, next[i]);
+        f32x4 acc[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+            acc[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(op[0], nibbles<BITS>(c[i], 0), f32x4{}, 0, 4, 0,
+                                                                      plane_scale, 0, 127);
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+            acc[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(op[1], nibbles<BITS>(c[i], 1), acc[i], 0, 4, 0,
+                                                                      plane_scale, 0, 127);
+        float sum[U];  // lane quarter q: planes 4 q .. 4 q + 3
+#pragma unroll
+        for (int i = 0; i < U; ++i) sum[i] = ((acc[i].w + acc[i].z) + acc[i].y) + acc[i].x;
+#pragma unroll
+        for (int i = 0; i < U; i += 4) {
+            // sums over the four lane quarters; quarter q gets that of the q-th of four row groups
+            auto add = [](auto r) { return __uint_as_float(r[0]) + __uint_as_float(r[1]); };
+            const float a = add(__builtin_amdgcn_permlane32_swap(__float_as_uint(sum[i]), __float_as_uint(sum[i + 2]), false, false));
+            const float b = add(__builtin_amdgcn_permlane32_swap(__float_as_uint(sum[i + 1]), __float_as_uint(sum[i + 3]), false, false));
+            const float x = __builtin_amdgcn_ldexpf(
+                add(__builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false)), exponent);
+            if (g + i + q >= g1) continue;
+            if (layers.n == 0) {
+                const long long row = (long long)(g + i) * kDenseRows + lane;
+                if (row < n_out) out[row] = scale * x;
+            } else {
+                int s = 0;
+#pragma unroll
+                for (int l = 1; l < kMaxLayers; ++l)
+                    if (l < layers.n && g + i + q >= layers.first[l]) s = l;
+                const int local = (g + i + q - layers.first[s]) * kDenseRows + m;
+                if (local < layers.rows[s]) layers.out[s][local] = layers.scale[s] * x;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+#pragma unroll
+            for (int d = 0; d < 2 * BITS; ++d) c[i][d] = next[i][d];
+    }
+}
 
 template <typename VT, int BITS, int NV>
 __global__ __launch_bounds__(kTableWaves * 64, (TableFew<VT, NV>::occupancy)) void k_table_few(
@@ -983,7 +1140,8 @@ __global__ __launch_bounds__(kTableWaves * 64, (TableFew<VT, NV>::occupancy)) vo
     constexpr int U = 8 / BITS;  // row groups at a time: 4 KiB of codes
     const int lane = threadIdx.x & 63, m = lane & 15, q = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    __shared__ __attribute__((aligned(16))) unsigned char smem[NV * S::planes * S::stride];
+    constexpr int kBytes = NV * S::planes * S::stride;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[NV == 1 ? kTableOneLds : kBytes];
     const int g0 = (int)min((long long)ngroups, ((long long)blockIdx.x * kTableWaves + w) * per);
     const int g1 = (int)min((long long)ngroups, (long long)g0 + per);
 
@@ -992,6 +1150,15 @@ __global__ __launch_bounds__(kTableWaves * 64, (TableFew<VT, NV>::occupancy)) vo
 #pragma unroll
     for (int i = 0; i < U; ++i)
         if (g0 + i < g1) load_codes<BITS>(c0 + (long long)(g0 + i) * 128 * BITS, c[i]);
+    if constexpr (NV == 1) {
+        static_assert(kTableWaves * 64 == kTileCols && kBytes <= kDigits * kDigitStride, "a thread per column");
+        int exponent;
+        if (table_digits<VT, BITS>(v, n_in, smem, reinterpret_cast<float *>(smem + kDigits * kDigitStride), &exponent)) {
+            table_by_digits<BITS, U>(c0, c, smem, exponent, g0, g1, n_out, scale, out, layers);
+            return;
+        }
+        __syncthreads();  // (the flags have been read)
+    }
     constexpr int pieces = kTileCols / 8;
     for (int i = threadIdx.x; i < NV * pieces; i += kTableWaves * 64) {
         const int n = i / pieces, col = 8 * (i % pieces);
@@ -1389,8 +1556,8 @@ bool use_tile(const Args &x, bool wide) {
 // Up to 256 columns: vectors per workgroup of the table kernels, 0 where the others are faster.
 // Waves that work through many row groups pay for bringing v into registers first and win only
 // when there are rows enough, measured (table kernel / other, 200 ternary columns):
-//   1 float32 vector   100000 rows 4.3 / 4.5 us (binary 5.1 / 4.4), 200000 5.3 / 6.7
-//   1 bf16 vector      400000 rows 8.2 / 8.1 (binary 7.9 / 7.6), 700000 11.8 / 12.5
+//   1 float32 vector   120000 rows 4.7 / 4.9 us (binary 5.3 / 4.8), 160000 4.9 / 5.8 (binary 5.3 / 5.7)
+//   1 bf16 vector      160000 rows 4.9 / 4.7 (binary 5.3 / 4.6), 240000 5.3 / 5.8 (binary 5.6 / 5.7)
 //   4 bf16 vectors     20000 rows 3.3 / 3.1, 100000 4.1 / 5.0
 //   5 to 16            500 rows 3.3 / 3.6 (bf16), 20000 rows 4.6 / 14.7 (float32): always
 //   up to 64, float32  3000 rows 10.9 / 6.0, 12000 11.7 / 15.1
@@ -1399,7 +1566,7 @@ bool use_tile(const Args &x, bool wide) {
 // vectors: 49.9 / 53.5; 20000 rows, 512 bf16 vectors 18.4 / 13.7).
 int table_vectors(int ntiles, int64_t rows, int batch, bool wide) {
     if (ntiles != 1) return 0;
-    if (batch == 1) return rows >= (wide ? 160000 : 500000) ? 1 : 0;
+    if (batch == 1) return rows >= (wide ? 140000 : 240000) ? 1 : 0;
     if (batch <= 4) return rows >= 65536 ? 4 : 0;
     if (batch <= 16) return 16;
     if (batch > 128 || rows < (wide ? 10000 : 16384)) return 0;
@@ -1537,7 +1704,7 @@ void packed_launch_shape(const rsr_handle_s *h, int v_dtype, int *workgroups, in
         const int64_t per = kTableWaves * (int64_t)table_groups_per_wave(h->code_groups, kCUs * 4 * 4);
         *workgroups = (int)((h->code_groups + per - 1) / per);
         *threads = kTableWaves * 64;
-        *lds_bytes = (wide ? 3 : 1) * TableFew<float, 1>::stride;
+        *lds_bytes = kTableOneLds;
         return;
     }
     const int wk = few_wk(ntiles), waves = few_waves(wk), rows = waves / wk;
