@@ -8,8 +8,8 @@
 //                   group in an order that suits the LDS banks, laid out for coalesced
 //                   per-lane strips; and the small tables of the multiply kernel
 // Everything between the matrix and these results stays in LDS.  Both are bound by the latency
-// and the instruction count of their LDS steps, not by memory (4096 x 4096, fused, k = 8: 48 and
-// 95 us, 70 of them for spreading the columns over the banks; as seven kernels with their
+// and the instruction count of their LDS steps, not by memory (4096 x 4096, fused, k = 8: 40 and
+// 46 us, 15 of them for spreading the columns over the banks; as seven kernels with their
 // intermediates in memory and the placement of whole runs 430 us).
 #include <type_traits>
 
@@ -68,6 +68,10 @@ __device__ __forceinline__ uint32_t digits4(uint32_t x, int mode, uint32_t *bad)
 }
 
 constexpr int kDigitBits = 5;  // most bits of the code one sorting step looks at
+// Codes without columns whose boundaries the next column's thread writes by itself; of more in a row it is the
+// wave (4096 x 4096 binary, k = 12, where the codes of a random matrix crowd together: 140 -> 36 us; where gaps are
+// short nothing changes, while a search per code takes 45 -> 50 us for fused, k = 8).
+constexpr int kShortGap = 8;
 
 // Stable sort of the columns of each block by pattern code: digit by digit of the code's bits,
 // every step a counting sort over at most 32 buckets.  A wave owns a contiguous run of positions and
@@ -197,26 +201,36 @@ __global__ __launch_bounds__(NT) void k_sort_columns(const int8_t *__restrict__ 
         uint16_t *pib = pi + b * n;
         uint32_t *ob = off + b * (P + 1);
         uint32_t groups = 0;
-        for (int t = tid; t < n; t += NT) {
-            const Item x = A[t];
-            pib[t] = (uint16_t)x;
-            const int64_t cur = code_of(x), prev = t ? (int64_t)code_of(A[t - 1]) : -1;
-            for (int64_t c = prev + 1; c <= cur; ++c) ob[c] = (uint32_t)t;
-            if (t == n - 1)
-                for (int64_t c = cur + 1; c <= P; ++c) ob[c] = (uint32_t)n;
-            if (cur != prev && cur > 0) {
-                ++groups;
-                if (prev <= 0) sums[1] = (uint32_t)(n - t);
+        for (int t0 = 64 * w; t0 < n; t0 += NT) {
+            const int t = t0 + lane;
+            int cur = 0, prev = 0;
+            if (t < n) {
+                const Item x = A[t];
+                pib[t] = (uint16_t)x;
+                cur = (int)code_of(x);
+                prev = t ? (int)code_of(A[t - 1]) : -1;
+                for (int c = prev + 1; c <= min(cur, prev + kShortGap); ++c) ob[c] = (uint32_t)t;
+                if (cur != prev && cur > 0) {
+                    ++groups;
+                    if (prev <= 0) sums[1] = (uint32_t)(n - t);
+                }
+            }
+            // many empty groups in a row: the wave writes them together
+            for (uint64_t wide = __ballot(cur - prev > kShortGap); wide; wide &= wide - 1) {
+                const int l = __builtin_ctzll(wide);
+                const int to = __builtin_amdgcn_readlane(cur, l);
+                for (int c = __builtin_amdgcn_readlane(prev, l) + 1 + kShortGap + lane; c <= to; c += 64)
+                    ob[c] = (uint32_t)(t0 + l);
             }
         }
+        for (int c = (int)code_of(A[n - 1]) + 1 + tid; c <= (int)P; c += NT) ob[c] = (uint32_t)n;
         if (groups) atomicAdd(&sums[0], groups);
         __syncthreads();
-        if (tid == 0) {
+        if (tid < 3) {  // (one thread for all three took three times the latency, 4 us of a block's 45)
             const uint32_t some = sums[0], real = sums[1];
-            const uint32_t mine[3] = {real, real + (uint32_t)(P - 1) - some, some};
-            for (int i = 0; i < 3; ++i)
-                if (mine[i] > __hip_atomic_load(&stats[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                    atomicMax(&stats[i], mine[i]);
+            const uint32_t mine = tid == 0 ? real : tid == 1 ? real + (uint32_t)(P - 1) - some : some;
+            if (mine > __hip_atomic_load(&stats[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                atomicMax(&stats[tid], mine);
         }
         __syncthreads();
     }
@@ -247,73 +261,76 @@ __device__ __forceinline__ int sign_of(uint32_t c, int r) {
 // less.  Gather instruction i of a wave reads entry i of all 64 strips of the wave; the LDS serves
 // the two half-waves side by side and needs one cycle per distinct dword that falls on the same
 // of its 32 banks.  The order of the columns inside a group is free for the kernel (sums commute
-// up to rounding; the canonical pi is not touched), so for every run of entries of one group
-// inside a strip, each slot takes the remaining column whose banks are least loaded so far in
-// that slot of the half-wave -- counted for both vector types the kernel serves: bank
-// (col / 2) mod 32 for 2-byte elements and col mod 32 for 4-byte elements; a second sweep
-// re-places every strip against all the others.  (Left as sorted, the product of
-// the metric workload takes 3.5 % longer than with three sweeps of whole runs; with two of
-// pieces 0.9 %, 6.80 against 6.74 us; a third sweep of pieces, 35 us more, gets 0.2 % back.)
-// One wave per wave of the
-// multiply kernel: lane = (half-wave, slot), strips in order.  Runs are placed in pieces of four,
-// each by the lane of its first slot, with the reads of a piece independent of each other: placing
-// whole runs of up to eight took four times as long.  Strips of more than 32 entries are left as
-// they are.
+// up to rounding; the canonical pi is not touched), so neighbours of one group inside a strip change places
+// where that lowers the loads of their banks, the other entries of the two slots of the half-wave being what they
+// are -- counted for both vector types the kernel serves: bank
+// (col / 2) mod 32 for 2-byte elements and col mod 32 for 4-byte elements.  One wave per wave of the
+// multiply kernel, or per two of them if their strips have at most 16 entries: lane = (wave, half-wave, slot).
+// A sweep looks at the even or at the odd pairs of slots, in turn, so that columns move along
+// their group; neighbouring lanes are a pair, so an element's partner and its share of the gain come through DPP, a lane
+// needs the loads of its own slot only, and writes are rare.  Four strips at a time, which do not see
+// each other's changes.  Bound by vector instructions, 30 per strip and sweep; one lane placing up to four
+// columns at a time took 220 (4096 x 4096, fused, k = 8: the whole kernel 112 -> 46 us; the product is the same,
+// 7.35 -> 7.31 us for the metric workload, and 3 % slower with the streams left as sorted.  Four sweeps give another
+// 0.5 % and cost 17 us).  Strips of more than 32 entries are left as they are.
 constexpr int kSpreadSweeps = 2;
-constexpr int kSpreadRun = 4;
-constexpr int kSpreadPad = 33;                                  // bytes per (slot, banks)
-constexpr int kSpreadWaveBytes = 2 * 2 * 32 * kSpreadPad;       // [half][bank kind][slot][bank]
+constexpr int kSpreadTogether = 4;                     // strips
+constexpr int kSpreadRow = 2 * 32 + 4;                 // loads of a slot: a byte per bank of either kind; padding
+constexpr int kSpreadWaveBytes = 64 * kSpreadRow;
 
-__device__ __forceinline__ void spread_banks(uint16_t *part, int epl, uint8_t *loads) {
-    const int lane = threadIdx.x & 63, half = lane >> 5, slot = lane & 31;
-    uint8_t *load2 = loads + half * 2 * 32 * kSpreadPad + slot * kSpreadPad;  // [bank of a 2-byte element]
-    uint8_t *load4 = load2 + 32 * kSpreadPad;                                 // [bank of a 4-byte element]
-    for (int i = 0; i < kSpreadPad; ++i) load2[i] = load4[i] = 0;
-    const bool live = slot < epl;
-    for (int sweep = 0; sweep < kSpreadSweeps; ++sweep) {
+// x of the other lane of the pair (2 i, 2 i + 1)
+__device__ __forceinline__ int pair_lane(int x) {
+    return __builtin_amdgcn_mov_dpp(x, 0xb1, 0xf, 0xf, true);  // quad_perm: 1, 0, 3, 2
+}
+
+// part: of the stream, 64 strips of epl entries; lane0: of the part's first slot, `slots` (16 or 32) per half.
+__device__ __forceinline__ void spread_banks(uint16_t *part, int epl, int slots, uint8_t *loads) {
+    const int lane = threadIdx.x & 63, half = slots == 16 ? (lane >> 4) & 1 : lane >> 5, own = lane & (slots - 1);
+    uint32_t *words = reinterpret_cast<uint32_t *>(loads + lane * kSpreadRow);
+    for (int i = 0; i < kSpreadRow / 4; ++i) words[i] = 0;
+    if (own < epl) {
+        const uint16_t *at = part + 32 * half * epl + own;
+#pragma unroll 8
         for (int l = 0; l < 32; ++l) {
-            uint16_t *st = part + (32 * half + l) * epl + slot;
-            // slots past the strip count as tails, so that no run reaches into them
-            const uint32_t entry = live ? *st : 1u;
-            const uint32_t tails = (uint32_t)(__ballot(entry & 1u) >> (32 * half));
-            if (live && sweep > 0) {
-                --load2[(entry >> 2) & 31];
-                --load4[(entry >> 1) & 31];
+            const uint32_t x = at[l * epl] >> 1;
+            atomicAdd(&words[(x >> 3) & 7], 1u << (8 * ((x >> 1) & 3)));
+            atomicAdd(&words[8 + ((x >> 2) & 7)], 1u << (8 * (x & 3)));
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int sweep = 0; sweep < kSpreadSweeps; ++sweep) {
+        const int odd = sweep & 1, upper = lane & 1, slot = own + odd;  // pairs (0, 1), (2, 3), .. or (1, 2), ..
+        const bool pair = slot - upper + 1 < epl;
+        uint8_t *load2 = loads + (pair ? lane + odd : lane) * kSpreadRow, *load4 = load2 + 32;
+        words = reinterpret_cast<uint32_t *>(load2);
+        uint16_t *first = part + 32 * half * epl + (pair ? slot : 0);
+        for (int l0 = 0; l0 < 32; l0 += kSpreadTogether) {
+            uint16_t *at = first + l0 * epl;
+            uint32_t entry[kSpreadTogether], other[kSpreadTogether];
+            int gain[kSpreadTogether];
+#pragma unroll
+            for (int l = 0; l < kSpreadTogether; ++l) entry[l] = at[l * epl];
+#pragma unroll
+            for (int l = 0; l < kSpreadTogether; ++l) {
+                other[l] = (uint32_t)pair_lane((int)entry[l]);
+                const uint32_t b2 = (entry[l] >> 2) & 31, b4 = (entry[l] >> 1) & 31;
+                const uint32_t o2 = (other[l] >> 2) & 31, o4 = (other[l] >> 1) & 31;
+                // what changes in this slot: the partner's column joins its banks, this one has left
+                gain[l] = (b2 == o2 ? 0 : (int)load2[o2] - (int)load2[b2] + 1) +
+                          (b4 == o4 ? 0 : (int)load4[o4] - (int)load4[b4] + 1);
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const uint32_t behind = tails & ((1u << slot) - 1u), rest = tails >> slot;
-            const int run = behind ? 32 - __builtin_clz(behind) : 0;  // first slot of the run
-            const int last = min(rest ? slot + __builtin_ctz(rest) : epl - 1, epl - 1);
-            if (live && ((slot - run) & (kSpreadRun - 1)) == 0) {
-                const int len = min(last - slot + 1, kSpreadRun);
-                const uint32_t flag = (rest >> (len - 1)) & 1u;  // the piece's last entry is a tail
-                uint32_t x[kSpreadRun];
 #pragma unroll
-                for (int i = 0; i < kSpreadRun; ++i) x[i] = i < len ? (uint32_t)st[i] >> 1 : 0u;
-#pragma unroll
-                for (int i = 0; i < kSpreadRun; ++i) {
-                    if (i >= len) break;
-                    uint8_t *l2 = load2 + i * kSpreadPad, *l4 = load4 + i * kSpreadPad;
-                    uint32_t c2[kSpreadRun], c4[kSpreadRun];
-#pragma unroll
-                    for (int t = i; t < kSpreadRun; ++t) {
-                        c2[t] = l2[(x[t] >> 1) & 31];
-                        c4[t] = l4[x[t] & 31];
-                    }
-                    uint32_t best = x[i], b2 = c2[i], b4 = c4[i];
-#pragma unroll
-                    for (int t = i + 1; t < kSpreadRun; ++t)
-                        if (t < len && c2[t] + c4[t] < b2 + b4) {
-                            b2 = c2[t];
-                            b4 = c4[t];
-                            const uint32_t y = x[t];
-                            x[t] = best;  // (the column it replaces stays among the remaining ones)
-                            best = y;
-                        }
-                    l2[(best >> 1) & 31] = (uint8_t)(b2 + 1);
-                    l4[best & 31] = (uint8_t)(b4 + 1);
-                    st[i] = (uint16_t)(best << 1 | (i == len - 1 ? flag : 0u));
+            for (int l = 0; l < kSpreadTogether; ++l) {
+                // (columns may pass each other unless a group ends between them)
+                const bool open = pair && !((upper ? other[l] : entry[l]) & 1u);
+                if (open && gain[l] + pair_lane(gain[l]) < 0) {
+                    const uint32_t x = entry[l] >> 1, y = other[l] >> 1;
+                    atomicSub(&words[(x >> 3) & 7], 1u << (8 * ((x >> 1) & 3)));
+                    atomicAdd(&words[(y >> 3) & 7], 1u << (8 * ((y >> 1) & 3)));
+                    atomicSub(&words[8 + ((x >> 2) & 7)], 1u << (8 * (x & 3)));
+                    atomicAdd(&words[8 + ((y >> 2) & 7)], 1u << (8 * (y & 3)));
+                    at[l * epl] = (uint16_t)((other[l] & ~1u) | (entry[l] & 1u));
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -382,7 +399,7 @@ __global__ __launch_bounds__(1024) void k_build_stream(const StreamArgs a) {
 
     // ---- logical order: rounds of NT codes; empty groups are counted per (round, wave) first ------
     const int rounds = (int)((a.P - 1 + NT - 1) / NT);
-#pragma unroll 4
+#pragma unroll 8
     for (int r = 0; r < rounds; ++r) {
         const int64_t c = 1 + (int64_t)r * NT + tid;
         const uint64_t none = __ballot(c < a.P && ob[min(c, a.P - 1)] == ob[min(c + 1, a.P)]);
@@ -398,32 +415,56 @@ __global__ __launch_bounds__(1024) void k_build_stream(const StreamArgs a) {
         empties += sum;
     }
     __syncthreads();
+    // (two rounds ahead the boundaries, one round ahead the first four columns of the groups are on their way:
+    // 4096 x 4096 fused, k = 8: 55 -> 52 us)
+    auto bounds = [&](int r, uint32_t *from, uint32_t *to) {
+        const int64_t c = 1 + (int64_t)r * NT + tid;
+        *from = ob[min(c, a.P - 1)];
+        *to = ob[min(c + 1, a.P)];
+    };
+    auto columns = [&](uint32_t from, uint32_t to, uint32_t (&col)[4]) {
+        const uint32_t last = min(max(to, from + 1) - 1, (uint32_t)a.n - 1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) col[i] = pib[min(from + i, last)];
+    };
+    uint32_t s, e, s1, e1, col[4];
+    bounds(0, &s, &e);
+    bounds(1, &s1, &e1);
+    columns(s, e, col);
     for (int r = 0; r < rounds; ++r) {
         const int64_t c = 1 + (int64_t)r * NT + tid;
-        const uint32_t s = ob[min(c, a.P - 1)], e = ob[min(c + 1, a.P)];
+        uint32_t s2, e2, next[4];
+        bounds(r + 2, &s2, &e2);
+        columns(s1, e1, next);
         const uint64_t none = __ballot(c < a.P && s == e);
         const uint32_t eb = holes[r * waves + w] +  // empty groups before code c
             __builtin_amdgcn_mbcnt_hi((uint32_t)(none >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)none, 0u));
-        if (c >= a.P) continue;
         const uint32_t to = s - off1 + (a.by_rank ? 0u : eb);
-        if (s == e) {
+        if (c >= a.P) {
+        } else if (s == e) {
             if (!a.by_rank) stream[to] = zero_entry | 1;
-            continue;
-        }
-        if (a.by_rank) gcode[c - eb] = (uint16_t)c;
-        if (e - s >= kLongGroup) {
-            uint32_t *l = longs + 3 + 3 * atomicAdd(&longs[0], 1u);
-            l[0] = s; l[1] = to; l[2] = e - s;
         } else {
-            for (uint32_t t = s; t < e; t += 4) {  // four columns in flight
-                uint32_t col[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) col[i] = pib[min(t + i, e - 1)];
+            if (a.by_rank) gcode[c - eb] = (uint16_t)c;
+            if (e - s >= kLongGroup) {
+                uint32_t *l = longs + 3 + 3 * atomicAdd(&longs[0], 1u);
+                l[0] = s; l[1] = to; l[2] = e - s;
+            } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (t + i < e) stream[to + (t + i - s)] = (uint16_t)(col[i] << 1 | (t + i + 1 == e ? 1u : 0u));
+                    if (s + i < e) stream[to + i] = (uint16_t)(col[i] << 1 | (s + i + 1 == e ? 1u : 0u));
+                for (uint32_t t = s + 4; t < e; t += 4) {  // four columns in flight
+                    uint32_t more[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) more[i] = pib[min(t + i, e - 1)];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (t + i < e) stream[to + (t + i - s)] = (uint16_t)(more[i] << 1 | (t + i + 1 == e ? 1u : 0u));
+                }
             }
         }
+        s = s1; e = e1; s1 = s2; e1 = e2;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) col[i] = next[i];
     }
     const int len = (int)(a.n - off1) + (a.by_rank ? 0 : (int)empties);
     for (int t = len + tid; t < L; t += NT) stream[t] = zero_entry;
@@ -440,8 +481,16 @@ __global__ __launch_bounds__(1024) void k_build_stream(const StreamArgs a) {
     int first = 0, slabs = 0;  // of this wave
     if (w < a.W) wave_share(a.S, a.W, w, &first, &slabs);
     const int epl = 8 * slabs;
-    if (a.spread && w < a.W && epl > 0 && epl <= 32)
-        spread_banks(stream + first * kSlab, epl, smem + at.loads + w * kSpreadWaveBytes);
+    if (a.spread) {
+        // (the first wave's strips are the longest)
+        const bool two = 8 * ((a.S + a.W - 1) / a.W) <= 16;
+        const int v = two ? 2 * w + (lane >> 5) : w;
+        int from, count;
+        wave_share(a.S, a.W, min(v, a.W - 1), &from, &count);
+        if (v >= a.W) count = 0;
+        if (two ? 2 * w < a.W : w < a.W && 8 * count <= 32)
+            spread_banks(stream + from * kSlab, 8 * count, two ? 16 : 32, smem + at.loads + w * kSpreadWaveBytes);
+    }
     __syncthreads();
 
     // ---- strips --------------------------------------------------------------------------------
@@ -630,6 +679,7 @@ hipError_t launch_pack_pass(const rsr_handle_s *h, int pass, int *err_flag) {
     a.gword = pd.gword;
     a.gcount = pd.gcount;
     a.err_flag = err_flag;
+    // (what the multiply kernel's LDS holds, 4 (columns + slots) bytes and more, bounds this to 156 KiB)
     const StreamLds lds = stream_lds(a.n, a.P, a.S, a.W, a.slots, a.by_rank, a.spread);
     if (lds.total > kLdsBytes) return hipErrorInvalidValue;
     const int threads = a.W * 64 > 512 ? a.W * 64 : 512;

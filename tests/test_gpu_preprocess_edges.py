@@ -74,3 +74,24 @@ def test_more_blocks_than_one_launch_holds():
     out, = rsr.rsr_matvec_stacked(h, v)
     assert torch.equal(out, M.float() @ v)
     rsr.rsr_destroy(h)
+
+
+@pytest.mark.parametrize("cols", [7, 66, 4097, 18435])
+def test_empty_groups_in_a_row(cols):
+    """Codes 8, 9 and 10 apart, and far apart: up to eight boundaries are one thread's, more the wave's."""
+    k = 12
+    codes = np.array([0, 8, 17, 27, 28, 29, 500, 509, 4000, 4094])[np.random.default_rng(cols).integers(0, 10, cols)]
+    M = ((codes[None, :] >> np.arange(k)[:, None]) & 1).astype(np.int8)
+    _check(M, k, rsr.RSR_BINARY)
+    _check(np.concatenate([M, np.zeros_like(M)])[:k + 1], k, rsr.RSR_BINARY)
+
+
+# strips of 8 to 32 entries, alike or not over the waves of a block; 3 to 16 waves, odd numbers among them
+@pytest.mark.parametrize("kind,k,cols", [
+    (rsr.RSR_BINARY, 3, 700), (rsr.RSR_BINARY, 3, 1700), (rsr.RSR_TERNARY_FUSED, 5, 2300), (rsr.RSR_BINARY, 7, 4100),
+    (rsr.RSR_BINARY, 9, 9000), (rsr.RSR_TERNARY_FUSED, 5, 9000), (rsr.RSR_TERNARY_FUSED, 7, 14336),
+    (rsr.RSR_TERNARY_2PASS, 6, 20000), (rsr.RSR_TERNARY_2PASS, 8, 32766), (rsr.RSR_BINARY, 12, 32766)])
+def test_strip_lengths(kind, k, cols):
+    M = gen.binary_matrix(2 * k + 1, cols, 0.5, cols) if kind == rsr.RSR_BINARY else \
+        gen.ternary_matrix(2 * k + 1, cols, 0.4, cols)
+    _check(M, k, kind)
