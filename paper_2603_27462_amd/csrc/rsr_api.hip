@@ -919,10 +919,10 @@ int rsr_launch_shape(rsr_handle_t h, int v_dtype, int *workgroups, int *threads,
     }
     if (h->narrow) return fail(RSR_EUNSUPPORTED);
     if (workgroups) *workgroups = (int)h->nb;
-    if (threads) *threads = h->W * 64;
-    if (lds_bytes)
-        *lds_bytes = (int)rsr::matvec_lds_bytes(h->slots, h->cols, v_dtype == RSR_BF16 ? 2 : 4, h->W,
-                                                h->by_rank != 0);
+    int shape[2];
+    rsr::rsr_matvec_launch_shape(h, v_dtype, &shape[0], &shape[1]);
+    if (threads) *threads = shape[0];
+    if (lds_bytes) *lds_bytes = shape[1];
     return RSR_OK;
 }
 
@@ -1038,7 +1038,7 @@ const char *rsr_batch_kernel_name(rsr_handle_t h, int v_dtype, int batch) {
     else if (h->narrow)
         return v_dtype == RSR_BF16 ? "k_rsr_narrow<unsigned short>" : "k_rsr_narrow<float>";
     else
-        rsr::rsr_matvec_kernel_name(h, v_dtype, name, sizeof(name));
+        rsr::rsr_matvec_kernel_name(h, v_dtype, batch, name, sizeof(name));
     return name;
 }
 

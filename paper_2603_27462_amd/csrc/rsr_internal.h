@@ -160,7 +160,9 @@ hipError_t launch_packed(const rsr_handle_s *h, const void *v, int v_dtype, floa
                          int batch, int64_t ldv, int64_t ldo, hipStream_t stream,
                          const LayerTable *layers = nullptr);
 // Writes the name of the kernel that multiplies into buf, as a profiler prints it.
-void rsr_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, char *buf, size_t len);
+void rsr_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, int batch, char *buf, size_t len);
+// Workgroup size and LDS of the block-pattern kernel (wide layout, one vector).
+void rsr_matvec_launch_shape(const rsr_handle_s *h, int v_dtype, int *threads, int *lds_bytes);
 void packed_launch_shape(const rsr_handle_s *h, int v_dtype, int *workgroups, int *threads, int *lds_bytes);
 void packed_kernel_name(const rsr_handle_s *h, int v_dtype, int batch, char *buf, size_t len);
 

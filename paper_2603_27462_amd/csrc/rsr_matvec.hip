@@ -200,7 +200,20 @@ __device__ __forceinline__ uint32_t load_sign_word(const void *sgn, long long in
 
 constexpr int kMoreRows = 3;  // further rows of a wave (w + W, w + 2W, ...) whose tables are requested up front
 
-template <bool FIRST, int TC>
+// What a pass does with a row's total: writes it, adds it to what the first pass wrote, or leaves it in
+// LDS for the workgroup to add (kTotals floats behind everything else, [pass][row]).
+enum { kWrite = 0, kAdd = 1, kLeave = 2 };
+constexpr int kTotals = 2 * 16;
+
+template <int OUT>
+__device__ __forceinline__ void put_total(float term, int r, float *out_rows, long long rows_left, uint32_t total_at) {
+    if (OUT == kLeave)
+        *lds_float(total_at + (uint32_t)r * 4u) = term;
+    else if (r < rows_left)
+        __builtin_nontemporal_store(OUT == kWrite ? term : out_rows[r] + term, &out_rows[r]);
+}
+
+template <int OUT, int TC>
 __device__ __forceinline__ void scatter_by_code(const FoldArgs &f, const ScatterPrep &sp,
                                                 uint32_t wpre, uint32_t sw,
                                                 const uint32_t (&pk_more)[kMoreRows],
@@ -208,7 +221,7 @@ __device__ __forceinline__ void scatter_by_code(const FoldArgs &f, const Scatter
                                                 long long b, uint32_t t_at, uint32_t e_at,
                                                 uint32_t c1_at, int W, int w, int lane,
                                                 float sign_scale, float *out_rows,
-                                                long long rows_left) {
+                                                long long rows_left, uint32_t total_at) {
     if (f.Q > 1 && sp.has_share) {
         // the thread's cnt1 entries, E[first + i Tc]: whole batches of four, then the rest one
         // by one (wave-uniform branches; the loads of a batch are in flight together)
@@ -270,10 +283,7 @@ __device__ __forceinline__ void scatter_by_code(const FoldArgs &f, const Scatter
             x += sp.wf[2] * v2;
             x += sp.wf[3] * v3;
             const float tot = wave_inclusive_scan(x);
-            if (lane == 63 && r < rows_left) {
-                const float term = sign_scale * tot;
-                __builtin_nontemporal_store(FIRST ? term : out_rows[r] + term, &out_rows[r]);
-            }
+            if (lane == 63) put_total<OUT>(sign_scale * tot, r, out_rows, rows_left, total_at);
         }
         return;
     }
@@ -315,11 +325,7 @@ __device__ __forceinline__ void scatter_by_code(const FoldArgs &f, const Scatter
             x += (float)(int)(signed char)(pk >> 24) * v3;
         }
         const float tot = wave_inclusive_scan(x);
-        if (lane == 63 && r < rows_left) {
-            const float term = sign_scale * tot;
-            // pass 2 adds to what pass 1 wrote
-            __builtin_nontemporal_store(FIRST ? term : out_rows[r] + term, &out_rows[r]);
-        }
+        if (lane == 63) put_total<OUT>(sign_scale * tot, r, out_rows, rows_left, total_at);
     }
 }
 
@@ -398,24 +404,30 @@ __device__ __forceinline__ void slab_step(const u32x4 &q, uint32_t (&g)[8], floa
     }
 }
 
-// One pass (binary, M+, M- or fused) of one block.  FIRST: v still has to be staged into
-// LDS and the output rows are overwritten; otherwise the pass adds to them.
-template <typename VT, int ENC, bool BYRANK, bool FIRST, int TC>
+// One pass (binary, M+, M- or fused) of one block.  OUT: kWrite: v still has to be staged into
+// LDS and the output rows are overwritten; kAdd: the pass adds to them; kLeave: the workgroup's second W waves run
+// the other pass at the same time (`second`: these are they), all of them stage v, and the totals stay in LDS.
+template <typename VT, int ENC, bool BYRANK, int OUT, int TC>
 __device__ __forceinline__ void run_pass(const uint16_t *__restrict__ entries,
                                          const uint16_t *__restrict__ start, int S, int per, int rem,
                                          const PassArgs &a, const void *__restrict__ v, long long ldv,
                                          int n_in, int W, const FoldArgs &f, const OutArgs &o,
-                                         int vec) {
+                                         int vec, bool second = false) {
+    constexpr bool FIRST = OUT != kAdd;  // v is staged
     // LDS (byte addresses): v (n_in + zero slot) | T[max(W, 8)][64] | E[slots] | by code: Tc
     // zeros, C1[threads]; by rank: partial sums [W][16]
     const uint32_t vbytes = ((n_in + 1) * (uint32_t)sizeof(VT) + 15u) & ~15u;
-    const uint32_t t_at = vbytes;
+    // (kLeave: T to C1 once per pass, then the totals)
+    const uint32_t pass_bytes = (uint32_t)max(W, 8) * 256u + (uint32_t)f.slots * 4u + 2u * (uint32_t)W * 256u;
+    const uint32_t t_at = vbytes + (OUT == kLeave && second ? pass_bytes : 0u);
     const uint32_t e_at = t_at + (uint32_t)max(W, 8) * 256u;
     const uint32_t z_at = e_at + (uint32_t)f.slots * 4u;
     const uint32_t c1_at = z_at + class_step<TC>(f);
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t total_at = vbytes + 2u * pass_bytes + (second ? 64u : 0u);
     const int nthreads = W * 64;
+    const int tid = (int)threadIdx.x - (OUT == kLeave && second ? nthreads : 0), lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int stagers = OUT == kLeave ? 2 * nthreads : nthreads, me = (int)threadIdx.x;  // threads that stage v
     const long long b = blockIdx.x;
 
     // the wave's slabs, in groups of four; the first group may be short (n0 slabs)
@@ -435,7 +447,7 @@ __device__ __forceinline__ void run_pass(const uint16_t *__restrict__ entries,
     const u32x4 *v16 = reinterpret_cast<const u32x4 *>(vg);
     lds_u128 *l16 = reinterpret_cast<lds_u128 *>(static_cast<uintptr_t>(0));
     u32x4 s0, s1, s2, s3;
-    const int j_0 = tid, j_1 = j_0 + nthreads, j_2 = j_1 + nthreads, j_3 = j_2 + nthreads;
+    const int j_0 = me, j_1 = j_0 + stagers, j_2 = j_1 + stagers, j_3 = j_2 + stagers;
     if (FIRST && v_aligned && n16 > 0) {
         // loads past the end are redirected to the last valid 16 bytes
         s0 = v16[min(j_0, n16 - 1)];
@@ -483,16 +495,15 @@ __device__ __forceinline__ void run_pass(const uint16_t *__restrict__ entries,
                 if (j_1 < n16) l16[j_1] = s1;
                 if (j_2 < n16) l16[j_2] = s2;
                 if (j_3 < n16) l16[j_3] = s3;
-                for (int j = j_3 + nthreads; j < n16; j += nthreads) l16[j] = v16[j];
+                for (int j = j_3 + stagers; j < n16; j += stagers) l16[j] = v16[j];
             }
-            for (int j = (n16 << 4) + tid * (int)sizeof(VT); j < nbytes;
-                 j += nthreads * (int)sizeof(VT))
+            for (int j = (n16 << 4) + me * (int)sizeof(VT); j < nbytes; j += stagers * (int)sizeof(VT))
                 lds_store_v<VT>(j, *reinterpret_cast<const VT *>(vg + j));
         } else {
-            for (int j = tid * (int)sizeof(VT); j < nbytes; j += nthreads * (int)sizeof(VT))
+            for (int j = me * (int)sizeof(VT); j < nbytes; j += stagers * (int)sizeof(VT))
                 lds_store_v<VT>(j, *reinterpret_cast<const VT *>(vg + j));
         }
-        if (tid == 0) lds_store_v<VT>(nbytes, VT(0));
+        if (me == 0) lds_store_v<VT>(nbytes, VT(0));
     }
     // ---- work that needs no stream data, done while the loads are in flight ----------------
     ScatterPrep sp;
@@ -544,11 +555,18 @@ __device__ __forceinline__ void run_pass(const uint16_t *__restrict__ entries,
     float scale;
     block_output(o, b, f.k, vec, &out_rows, &rows_left, &scale);
     if (BYRANK)
-        scatter_by_rank<FIRST>(f, a.gword + b * f.slots, count, sw, prev, e_at, z_at, W, w, lane, tid,
+        scatter_by_rank<OUT == kWrite>(f, a.gword + b * f.slots, count, sw, prev, e_at, z_at, W, w, lane, tid,
                                scale * a.sign, out_rows, rows_left);
     else
-        scatter_by_code<FIRST, TC>(f, sp, wpre, sw, pk_more, sw_more, a.sgn, b, t_at, e_at, c1_at, W, w, lane,
-                                   scale * a.sign, out_rows, rows_left);
+        scatter_by_code<OUT, TC>(f, sp, wpre, sw, pk_more, sw_more, a.sgn, b, t_at, e_at, c1_at, W, w, lane,
+                                 scale * a.sign, out_rows, rows_left, total_at);
+    if (OUT == kLeave) {
+        __syncthreads();
+        if (me < f.k && me < rows_left) {
+            const uint32_t at = vbytes + 2u * pass_bytes + (uint32_t)me * 4u;
+            __builtin_nontemporal_store(*lds_float(at) + *lds_float(at + 64u), &out_rows[me]);
+        }
+    }
 }
 
 // TC: 0, or the class count of the code-indexed scatter phase when it is the common one
@@ -560,13 +578,28 @@ __global__ __launch_bounds__(1024, 4) void k_rsr_matvec(
     const uint16_t *__restrict__ entries0, const uint16_t *__restrict__ start0,
     const void *__restrict__ v, int S0, int per0, int rem0, int n_in, int W, long long ldv,
     const PassArgs a0, const FoldArgs f, const PassArgs a1, const OutArgs o) {
-    run_pass<VT, ENC, BYRANK, true, TC>(entries0, start0, S0, per0, rem0, a0, v, ldv, n_in, W, f, o,
-                                        (int)blockIdx.y);
+    run_pass<VT, ENC, BYRANK, kWrite, TC>(entries0, start0, S0, per0, rem0, a0, v, ldv, n_in, W, f, o,
+                                          (int)blockIdx.y);
     if (NPASS == 2) {
         __syncthreads();  // the second pass reuses E and the totals
-        run_pass<VT, ENC, BYRANK, false, TC>(a1.entries, a1.start, a1.S, a1.per, a1.rem, a1, v, ldv, n_in,
-                                             W, f, o, (int)blockIdx.y);
+        run_pass<VT, ENC, BYRANK, kAdd, TC>(a1.entries, a1.start, a1.S, a1.per, a1.rem, a1, v, ldv, n_in,
+                                            W, f, o, (int)blockIdx.y);
     }
+}
+
+// Two passes at the same time, W waves each, E by code.  One after the other they are two chains of staging, gather
+// and scatter, and the second one ends with a read of what the first one wrote.  (At most 64 registers, so that two
+// workgroups of 16 waves share a CU: 4096 x 4096, k = 8, 8.9 us with 72, 7.5 with 62.)
+template <typename VT, int ENC>
+__global__ __launch_bounds__(1024, 8) void k_rsr_matvec_both(
+    const uint16_t *__restrict__ entries0, const uint16_t *__restrict__ start0,
+    const void *__restrict__ v, int S0, int per0, int rem0, int n_in, int W, long long ldv,
+    const PassArgs a0, const FoldArgs f, const PassArgs a1, const OutArgs o) {
+    const bool second = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) >= W;
+    const PassArgs &a = second ? a1 : a0;
+    run_pass<VT, ENC, false, kLeave, 0>(second ? a1.entries : entries0, second ? a1.start : start0,
+                                        second ? a1.S : S0, second ? a1.per : per0, second ? a1.rem : rem0, a, v, ldv,
+                                        n_in, W, f, o, (int)blockIdx.y, second);
 }
 
 struct LaunchArgs {
@@ -594,8 +627,39 @@ hipError_t launch(const LaunchArgs &x) {
     return hipGetLastError();
 }
 
+// LDS of k_rsr_matvec_both: v once, the rest per pass, and the totals.
+int64_t both_lds_bytes(int64_t slots, int64_t cols, int v_elem_bytes, int W) {
+    const int64_t one = matvec_lds_bytes(slots, cols, v_elem_bytes, W, false);
+    const int64_t vbytes = ((cols + 1) * v_elem_bytes + 15) / 16 * 16;
+    return 2 * one - vbytes + kTotals * 4;
+}
+
+// Both passes at once where that hides a chain behind the other: while the chip has fewer than two workgroups per
+// CU, and for blocks of at most four waves.  Otherwise the CUs are busy either way, and workgroups of up to 16 waves
+// fill them less evenly.  Measured, one after the other / at once, float32: 1000 x 1000 k = 8 (125 blocks)
+// 5.36 / 4.70 us, 2040 x 4096 (255) 5.82 / 5.41, 3000 x 4096 (375) 7.25 / 7.16, 3600 x 4096 (450) 7.32 / 7.33, 4096 x 4096
+// (512) 7.45 / 7.54, 14336 x 4096 19.8 / 20.4; 2000 x 4000 k = 10 (200) 8.0 / 6.1, 10000 x 4000 (1000) 12.9 / 14.0; 4000 x
+// 2500 k = 5 (800) 8.8 / 9.4; four waves: 14336 x 4096 k = 4 (3584) 23.7 / 21.7, three: k = 3 29.9 / 25.6.
+bool use_both(const rsr_handle_s *h, int v_elem_bytes, int batch) {
+    return h->npass == 2 && !h->by_rank && 2 * h->W <= kMaxWaves && (h->W <= 4 || h->nb * batch <= 448) &&
+           both_lds_bytes(h->slots, h->cols, v_elem_bytes, h->W) <= kLdsBytes;
+}
+
 template <typename VT, int ENC>
-hipError_t launch_nr(const LaunchArgs &x, int npass, bool by_rank) {
+hipError_t launch_both(const LaunchArgs &x) {
+    static std::atomic<size_t> enabled[kMaxDevices];
+    auto kern = k_rsr_matvec_both<VT, ENC>;
+    const size_t lds = (size_t)both_lds_bytes(x.f.slots, x.n_in, (int)sizeof(VT), x.W);
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, x.device, enabled)) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)x.nblocks, (unsigned)x.batch), dim3(2 * x.W * 64), lds,
+                       x.stream, x.a0.entries, x.a0.start, x.v, x.a0.S, x.a0.per, x.a0.rem, x.n_in, x.W, x.ldv,
+                       x.a0, x.f, x.a1, x.o);
+    return hipGetLastError();
+}
+
+template <typename VT, int ENC>
+hipError_t launch_nr(const LaunchArgs &x, int npass, bool by_rank, bool both) {
+    if (both) return launch_both<VT, ENC>(x);
     if (by_rank) return npass == 1 ? launch<VT, ENC, 1, true, 0>(x) : launch<VT, ENC, 2, true, 0>(x);
     if (npass == 1 && x.f.Tc == kCommonClasses) return launch<VT, ENC, 1, false, kCommonClasses>(x);
     return npass == 1 ? launch<VT, ENC, 1, false, 0>(x) : launch<VT, ENC, 2, false, 0>(x);
@@ -770,12 +834,12 @@ hipError_t launch_rsr_matvec(const rsr_handle_s *h, const void *v, int v_dtype, 
     x.lds = (size_t)matvec_lds_bytes(h->slots, h->cols, (v_dtype == RSR_BF16) ? 2 : 4, h->W,
                                      h->by_rank != 0);
     x.stream = stream;
-    const bool r = h->by_rank != 0;
+    const bool r = h->by_rank != 0, both = use_both(h, v_dtype == RSR_BF16 ? 2 : 4, batch);
     if (v_dtype == RSR_BF16)
-        return h->enc == kEncSmall ? launch_nr<uint16_t, kEncSmall>(x, h->npass, r)
-                                   : launch_nr<uint16_t, kEncBig>(x, h->npass, r);
-    return h->enc == kEncSmall ? launch_nr<float, kEncSmall>(x, h->npass, r)
-                               : launch_nr<float, kEncBig>(x, h->npass, r);
+        return h->enc == kEncSmall ? launch_nr<uint16_t, kEncSmall>(x, h->npass, r, both)
+                                   : launch_nr<uint16_t, kEncBig>(x, h->npass, r, both);
+    return h->enc == kEncSmall ? launch_nr<float, kEncSmall>(x, h->npass, r, both)
+                               : launch_nr<float, kEncBig>(x, h->npass, r, both);
 }
 
 // A launch, a chain of staging, slabs and the two levels (or the words) of the scatter phase, and from 256
@@ -798,12 +862,24 @@ float rsr_matvec_us(const rsr_handle_s *h, int v_bytes, int batch, bool aligned)
            x * (0.031f * slabs + 0.06f * np * h->W + 0.106f * v + 6.5e-5f * codes + 1.4e-5f * words + 0.5f * stage);
 }
 
-void rsr_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, char *buf, size_t len) {
+void rsr_matvec_kernel_name(const rsr_handle_s *h, int v_dtype, int batch, char *buf, size_t len) {
     // as a profiler prints the instantiation
+    if (use_both(h, v_dtype == RSR_BF16 ? 2 : 4, batch)) {
+        std::snprintf(buf, len, "k_rsr_matvec_both<%s, %d>", v_dtype == RSR_BF16 ? "unsigned short" : "float", h->enc);
+        return;
+    }
     const bool common = !h->by_rank && h->npass == 1 && h->fold.Tc == kCommonClasses;
     std::snprintf(buf, len, "k_rsr_matvec<%s, %d, %d, %s, %d>",
                   v_dtype == RSR_BF16 ? "unsigned short" : "float", h->enc, h->npass,
                   h->by_rank ? "true" : "false", common ? kCommonClasses : 0);
+}
+
+void rsr_matvec_launch_shape(const rsr_handle_s *h, int v_dtype, int *threads, int *lds_bytes) {
+    const int bytes = v_dtype == RSR_BF16 ? 2 : 4;
+    const bool both = use_both(h, bytes, 1);
+    *threads = (both ? 2 : 1) * h->W * 64;
+    *lds_bytes = (int)(both ? both_lds_bytes(h->slots, h->cols, bytes, h->W)
+                            : matvec_lds_bytes(h->slots, h->cols, bytes, h->W, h->by_rank != 0));
 }
 
 }  // namespace rsr

@@ -439,3 +439,24 @@ def test_errors():
         rsr.rsr_get_perm(h, 1)
     # the library keeps working after errors
     _check_matvec(h, M.cpu().numpy(), 64, 3)
+
+
+# both passes in one workgroup (up to 448 blocks, or blocks of at most four waves) and one after the other; E and totals of
+# both in LDS; blocks whose last rows do not exist; more rows than waves; batches on few rows
+@pytest.mark.parametrize("rows,cols,k,batch,both", [
+    (1, 700, 1, 1, True), (1021, 1000, 8, 1, True), (448 * 6, 900, 6, 1, True), (448 * 6 + 1, 900, 6, 1, False),
+    (9001, 1500, 4, 1, True), (5000, 1200, 1, 1, True), (333, 14336, 10, 1, True), (300, 5000, 12, 1, True),
+    (301, 20001, 9, 1, False), (40, 14336, 8, 12, True)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_two_passes_at_once(rows, cols, k, batch, both, bf16):
+    M = gen.ternary_matrix(rows, cols, 0.4, rows + cols)
+    h = rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), k, rsr.RSR_TERNARY_2PASS)
+    # (a batch of bf16 vectors is multiplied on the matrix cores)
+    assert ("both" in rsr.rsr_batch_kernel_name(h, int(bf16), batch)) == (both and not (bf16 and batch > 1))
+    x = np.stack([gen.integer_f32(cols, seed=i) for i in range(batch)])
+    v = torch.from_numpy(x).to(DEV).to(torch.bfloat16 if bf16 else torch.float32)
+    out = torch.full((batch, rows + 1), -7.0, device=DEV)
+    rsr.rsr_matvec_ex(h, v if batch > 1 else v[0], scale=0.5, out=out[:, :rows] if batch > 1 else out[0, :rows])
+    want = np.stack([oracle.dense_matvec(M, r.astype(np.float64), 0.5) for r in x])
+    assert np.array_equal(out[:, :rows].cpu().numpy().astype(np.float64), want)
+    assert bool((out[:, rows] == -7.0).all())
