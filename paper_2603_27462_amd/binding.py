@@ -6,6 +6,8 @@ are ``torch.cuda.Stream`` objects (or None for torch's current stream).
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 import warnings
 from typing import Optional
@@ -36,6 +38,7 @@ class RsrError(RuntimeError):
 
 
 _lib = None
+_product = None     # rsr_call.cpp: rsr_matvec_ex with a new result on the current stream, or None if it is not built
 
 
 def load_library(path: Optional[str] = None) -> ctypes.CDLL:
@@ -109,7 +112,21 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.rsr_batch_kernel_name.restype = ctypes.c_char_p
     lib.rsr_batch_kernel_name.argtypes = [vp, ci, ci]
     _lib = lib
+    _load_call(lib)
     return lib
+
+
+def _load_call(lib) -> None:
+    global _product
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("_rsr_call", _build.CALL_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_rsr_call", loader))
+        loader.exec_module(module)
+    except ImportError as e:
+        warnings.warn("%s: small products are called through ctypes, which takes longer" % e)
+        return
+    module.bind(ctypes.cast(lib.rsr_matvec_ex, ctypes.c_void_p).value)
+    _product = module.product
 
 
 class Handle:
@@ -294,6 +311,10 @@ def rsr_matvec(h: Handle, v, out=None, stream=None):
 
 def rsr_matvec_ex(h: Handle, v, scale: float = 1.0, out=None, stream=None):
     """v: [cols] or [batch][cols], float32 or bfloat16; returns float32 [rows] or [batch][rows]."""
+    if out is None and stream is None and _product is not None:
+        out = _product(h.ptr, h.rows, h.cols, v, scale)
+        if out is not None:
+            return out
     import torch
     dim = v.dim() if v.is_cuda else 0
     if dim == 1:
