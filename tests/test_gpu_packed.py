@@ -325,3 +325,40 @@ def test_batches_in_a_graph(kind, rows, cols, k, batch):
         assert torch.equal(out, want), i
     assert np.array_equal(want[1].cpu().numpy().astype(np.float64),
                           oracle.dense_matvec(M, v[1].cpu().numpy().astype(np.float64)))
+
+
+# two or four row groups per wave: both sides of every rule, a last workgroup with fewer groups, ragged rows and columns
+@pytest.mark.parametrize("kind,rows,cols,batch,bf16,kernel", [
+    (rsr.RSR_DENSE_TERNARY_P2, 256 * 16, 6200, 4, True, "few"), (rsr.RSR_DENSE_TERNARY_P2, 256 * 16 + 1, 6200, 4, True, "tall"),
+    (rsr.RSR_BINARY, 256 * 16 + 17, 6145, 2, False, "tall"), (rsr.RSR_DENSE_TERNARY_P2, 512 * 16 + 35, 6401, 3, False, "tall"),
+    (rsr.RSR_DENSE_TERNARY_P2, 256 * 16 + 40, 14336, 1, False, "tall"), (rsr.RSR_DENSE_TERNARY_P2, 512 * 16, 2049, 1, False, "few"),
+    (rsr.RSR_DENSE_TERNARY_P2, 512 * 16 + 1, 2049, 1, False, "tall"), (rsr.RSR_TERNARY_FUSED, 513 * 16 + 3, 2300, 4, False, "tall"),
+    (rsr.RSR_BINARY, 768 * 16 + 2, 3000, 3, True, "tall"), (rsr.RSR_DENSE_TERNARY_P2, 1024 * 16 + 1, 3400, 2, True, "few"),
+    (rsr.RSR_DENSE_TERNARY_P2, 769 * 16 + 5, 1100, 1, False, "tall"), (rsr.RSR_BINARY, 2050 * 16 + 9, 300, 2, False, "tall"),
+    (rsr.RSR_DENSE_TERNARY_P2, 800 * 16 - 3, 511, 4, True, "tall"), (rsr.RSR_DENSE_TERNARY_P2, 60000, 2500, 1, True, "few")])
+def test_several_row_groups_per_wave(kind, rows, cols, batch, bf16, kernel):
+    M = _matrix(kind, rows, cols, 77 + cols)
+    h = rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), 4, kind)
+    assert rsr.rsr_batch_kernel_name(h, int(bf16), batch).startswith("k_packed_" + kernel)
+    _check(h, M, batch, bf16, 3, cols)
+    v = torch.ones((batch, cols), device=DEV, dtype=torch.bfloat16 if bf16 else torch.float32)
+    v[batch - 1, cols // 2] = float("inf")
+    got = rsr.rsr_matvec_ex(h, v).cpu().numpy()
+    want = np.repeat(M.sum(axis=1, dtype=np.float32)[None], batch, axis=0)
+    hit = M[:, cols // 2] != 0
+    want[-1, hit] = np.inf * M[hit, cols // 2]
+    if kind == rsr.RSR_DENSE_TERNARY_P2:        # every entry is multiplied; the planes of an infinity are inf and NaN
+        assert np.isnan(got[-1, ~hit]).all() and not np.isfinite(got[-1]).any()
+        got, want = got[:-1], want[:-1]
+    assert np.array_equal(got, want)
+
+
+def test_stacked_layers_with_several_row_groups_per_wave():
+    """Layers begin inside a workgroup's groups."""
+    rows, cols = (3001, 17, 5000, 2003), 2500
+    Ms = [_matrix(rsr.RSR_DENSE_TERNARY_P2, r, cols, 90 + r) for r in rows]
+    h = rsr.rsr_preprocess_stacked([torch.from_numpy(M).to(DEV) for M in Ms], 0, rsr.RSR_DENSE_TERNARY_P2)
+    v = gen.integer_f32(cols, seed=5)
+    outs = rsr.rsr_matvec_stacked(h, torch.from_numpy(v).to(DEV), [1.0, -2.0, 0.5, 4.0])
+    for M, out, scale in zip(Ms, outs, (1.0, -2.0, 0.5, 4.0)):
+        assert np.array_equal(out.cpu().numpy().astype(np.float64), oracle.dense_matvec(M, v.astype(np.float64), scale))
