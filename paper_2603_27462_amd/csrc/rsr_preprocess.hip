@@ -592,8 +592,9 @@ __global__ __launch_bounds__(256) void k_transpose_i8(const int8_t *__restrict__
     }
 }
 
-// Columns a block can have if it is sorted as (code, column) pairs.
+// Columns a block can have if it is sorted as (code, column) pairs, and from which on its LDS is more than half a CU's.
 constexpr int kPairColumns = 18 * 1024;
+constexpr int kAloneColumns = 10 * 1024;
 
 template <int NT, bool WIDE>
 hipError_t launch_sort(const int8_t *M, int64_t rows, int64_t cols, int k, int base, int mode, int64_t P,
@@ -640,7 +641,12 @@ hipError_t launch_sort_columns(const int8_t *M, int64_t rows, int64_t cols, int 
                                uint16_t *codes, uint16_t *pi, uint32_t *off, uint32_t *stats, int *err_flag) {
     if (sort_needs_codes(cols))
         return launch_sort<512, true>(M, rows, cols, k, base, mode, P, codes, pi, off, stats, err_flag);
-    // (workgroups of 1024 threads do not share a CU: 4096 columns sort 2.3 times slower with them)
+    // Workgroups of 1024 threads do not share a CU (512 blocks of 4096 columns sort 2.3 times slower with them), so they
+    // are for blocks that have one to themselves: because of their LDS (4096 x 14336 fused k = 8 144 -> 114 us, 1500 x
+    // 18000 k = 4 110 -> 85), or because there are no more blocks than CUs (1500 x 10200 55 -> 46, 500 x 8000 30 -> 25,
+    // 2040 x 3000 28 -> 25; 2000 x 2000 the same, 500 x 600 9 -> 11).
+    if (cols > kAloneColumns || (cols > 2560 && (rows + k - 1) / k <= 256))
+        return launch_sort<1024, false>(M, rows, cols, k, base, mode, P, codes, pi, off, stats, err_flag);
     return cols > 512 ? launch_sort<512, false>(M, rows, cols, k, base, mode, P, codes, pi, off, stats, err_flag)
                       : launch_sort<256, false>(M, rows, cols, k, base, mode, P, codes, pi, off, stats, err_flag);
 }

@@ -35,6 +35,12 @@ def test_column_counts(kind, k, cols):
     _check(M, k, kind)
 
 
+# workgroups of 512 and of 1024 threads: by the columns, and by the number of blocks
+@pytest.mark.parametrize("rows,cols", [(512, 2561), (513, 2561), (512, 2560), (513, 10240), (513, 10241), (515, 18432)])
+def test_blocks_that_have_a_cu_to_themselves(rows, cols):
+    _check(gen.ternary_matrix(rows, cols, 0.4, rows + cols), 2, rsr.RSR_TERNARY_FUSED)
+
+
 @pytest.mark.parametrize("kind,k", [(rsr.RSR_BINARY, 1), (rsr.RSR_BINARY, 6), (rsr.RSR_BINARY, 11),
                                     (rsr.RSR_TERNARY_2PASS, 10), (rsr.RSR_TERNARY_FUSED, 1),
                                     (rsr.RSR_TERNARY_FUSED, 3), (rsr.RSR_TERNARY_FUSED, 4),
