@@ -59,7 +59,9 @@ def test_columns_split_over_waves(kind, rows, cols, k, batch, bf16, pad):
     (rsr.RSR_TERNARY_FUSED, 60001, 299, 6, 6, True, 1), (rsr.RSR_BINARY, 33333, 700, 8, 13, False, 0),
     (rsr.RSR_DENSE_TERNARY_P2, 8209, 1100, 0, 17, False, 1), (rsr.RSR_BINARY, 16400, 260, 8, 32, True, 0),
     (rsr.RSR_TERNARY_2PASS, 30011, 303, 8, 25, False, 3), (rsr.RSR_DENSE_TERNARY_P2, 4097, 2100, 0, 97, True, 0),
-    (rsr.RSR_BINARY, 1500, 1999, 8, 300, False, 1), (rsr.RSR_DENSE_TERNARY_P2, 40001, 513, 0, 18, True, 1)])
+    (rsr.RSR_BINARY, 1500, 1999, 8, 300, False, 1), (rsr.RSR_DENSE_TERNARY_P2, 40001, 513, 0, 18, True, 1),
+    (rsr.RSR_DENSE_TERNARY_P2, 512 * 16, 2817, 0, 5, False, 1), (rsr.RSR_BINARY, 512 * 16 + 3, 2817, 8, 5, False, 1),
+    (rsr.RSR_DENSE_TERNARY_P2, 512 * 16 + 3, 2820, 0, 9, True, 1)])
 def test_split_shapes(kind, rows, cols, k, batch, bf16, pad):
     M = _matrix(kind, rows, cols, 1100 + cols)
     _check(rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), k, kind), M, batch, bf16, pad, cols, distinct=4)
