@@ -584,12 +584,13 @@ __device__ __forceinline__ void few_rows(
 #pragma unroll
             for (int st = 0; st < kTileSteps; st += 2) {
                 const bf16x8 x0 = lds_operand(operand + i * 512 + st * 64);
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+                    acc0[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, decode<BITS>(c[g][i], st), acc0[g], 0, 0, 0);
                 const bf16x8 x1 = lds_operand(operand + i * 512 + st * 64 + 64);
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    acc0[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x0, decode<BITS>(c[g][i], st), acc0[g], 0, 0, 0);
+                for (int g = 0; g < G; ++g)
                     acc1[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x1, decode<BITS>(c[g][i], st + 1), acc1[g], 0, 0, 0);
-                }
             }
         }
         if (t + S::tiles < t1) request_codes(t + S::tiles);
@@ -634,13 +635,13 @@ __device__ __forceinline__ void few_rows(
 #pragma unroll
     for (int g = 0; g < G; ++g) red[(g * W + w) * 64 + lane] = sum[g];
     __syncthreads();
-    for (int i = w; i < WR * G; i += W) {  // row groups of the workgroup
-        const float *part = red + ((i % G) * W + i / G * WK) * 64 + lane;
-        float x = 0.0f;
+    static_assert(WK == 1 || WR * G <= W, "a wave per row group of the workgroup");
+    if (w >= WR * G) return;
+    const float *part = red + ((w % G) * W + w / G * WK) * 64 + lane;
+    float x = 0.0f;
 #pragma unroll
-        for (int k = 0; k < WK; ++k) x += part[k * 64];
-        put(group0 + i, x);
-    }
+    for (int k = 0; k < WK; ++k) x += part[k * 64];
+    put(group0 + w, x);
 }
 
 template <typename VT, int BITS, int NV, int WK>
