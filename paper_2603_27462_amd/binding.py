@@ -118,12 +118,19 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
 
 def _load_call(lib) -> None:
     global _product
+    _product = None
     try:
         loader = importlib.machinery.ExtensionFileLoader("_rsr_call", _build.CALL_PATH)
         module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_rsr_call", loader))
         loader.exec_module(module)
     except ImportError as e:
         warnings.warn("%s: small products are called through ctypes, which takes longer" % e)
+        return
+    # it knows how that torch lays its tensors out
+    if getattr(module, "torch", None) != _build.torch_tag():
+        warnings.warn("_rsr_call.so was compiled against torch %s, this is %s: small products are called through "
+                      "ctypes, which takes longer; rebuild with paper_2603_27462_amd.build.build_library()"
+                      % (getattr(module, "torch", "?"), _build.torch_tag()))
         return
     module.bind(ctypes.cast(lib.rsr_matvec_ex, ctypes.c_void_p).value)
     _product = module.product

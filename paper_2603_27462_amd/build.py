@@ -35,13 +35,20 @@ def _run(cmd, verbose: bool) -> None:
         print(proc.stdout, file=sys.stderr)
 
 
+def torch_tag() -> str:
+    """The torch that the native part of the binding is compiled against; it uses that build's C++ classes."""
+    import torch
+    return "%s %s abi%d" % (torch.__version__, torch.version.git_version, int(torch._C._GLIBCXX_USE_CXX11_ABI))
+
+
 def build_call(verbose: bool = False) -> str:
     """Compile the native part of the binding against the installed torch."""
     import torch
     root = os.path.dirname(torch.__file__)
     tmp = CALL_PATH + ".tmp%d" % os.getpid()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
-           "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+           "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           '-DRSR_TORCH="%s"' % torch_tag()]
     for path in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
                  sysconfig.get_paths()["include"], os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")):
         cmd += ["-isystem", path]

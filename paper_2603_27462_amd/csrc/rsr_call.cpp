@@ -68,4 +68,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_rsr_call", nullptr, -1, methods, 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__rsr_call() { return PyModule_Create(&module); }
+// The attribute `torch` names the torch that this was compiled against; the binding compares it before the first call.
+PyMODINIT_FUNC PyInit__rsr_call() {
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch", RSR_TORCH) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -21,6 +21,16 @@ def test_leaves_what_is_not_plain():
         assert product(*args) is None
 
 
+def test_not_used_with_another_torch(monkeypatch):
+    """Compiled against one torch's tensor classes: under another the path through ctypes is taken."""
+    product = _product()
+    monkeypatch.setattr(binding, "_product", product)
+    monkeypatch.setattr(binding._build, "torch_tag", lambda: "another torch", raising=False)
+    with pytest.warns(UserWarning, match="another torch"):
+        binding._load_call(rsr.load_library())
+    assert binding._product is None
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_same_as_through_ctypes(dtype):
