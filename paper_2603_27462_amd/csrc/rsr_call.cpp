@@ -5,11 +5,13 @@
 // 1001 x 2999 6.5 -> 4.9, one on 4488 x 3946 6.2 -> 5.0: what the launch and the kernel take.
 //
 // It decides nothing: whatever is not a plain strided float32 or bf16 tensor on a GPU with the shape that the handle
-// asks for, and whatever fails, is left to the Python path (None), which does the same work and raises.
+// asks for, and whatever fails, is left to the Python path (None), which does the same work and raises; only errors of
+// Python code that torch runs underneath are passed on as they are.
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
 #include <Python.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "rsr.h"
@@ -54,6 +56,9 @@ PyObject *product(PyObject *, PyObject *const *arg, Py_ssize_t n) {
                     ldv, rows, stream);
         Py_END_ALLOW_THREADS
         if (rc == RSR_OK) return THPVariable_Wrap(std::move(out));
+    } catch (python_error &e) {  // of Python code under a call of torch, a dispatch mode's: the caller's
+        e.restore();
+        return nullptr;
     } catch (...) {
     }
     Py_RETURN_NONE;

@@ -70,3 +70,20 @@ def test_refusals_stay():
     rsr.rsr_destroy(h)
     with pytest.raises(rsr.RsrError):
         rsr.rsr_matvec_ex(h, x[0])
+
+
+@pytest.mark.gpu
+def test_errors_of_a_dispatch_mode():
+    """The result is allocated under the caller's dispatch modes, and what those raise reaches the caller."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Refuses(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            raise LookupError("no tensors here")
+
+    M = torch.randint(-1, 2, (40, 64), dtype=torch.int8, device="cuda:0")
+    h = rsr.rsr_preprocess(M, 4, rsr.RSR_TERNARY_FUSED)
+    x = torch.ones(64, device="cuda:0")
+    with Refuses(), pytest.raises(LookupError, match="no tensors here"):
+        rsr.rsr_matvec_ex(h, x)
+    assert torch.equal(rsr.rsr_matvec_ex(h, x), M.sum(dim=1, dtype=torch.float32))
