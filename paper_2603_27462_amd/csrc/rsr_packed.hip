@@ -6,7 +6,7 @@
 // rows has is worth less there than the vectors that share one decoded weight.  The dense kind, the comparison point without any
 // preprocessing beyond packing (the role the paper gives its low-bit multiplier baseline in
 // Benchmarking Results), multiplies a single vector this way too.  Kernels:
-//   few    16 rows x up to 4 vectors per wave, for 1 to 4 vectors; tall: 32 or 64 rows, on tall matrices
+//   few    16 rows x up to 4 vectors per wave, for 1 to 4 vectors; tall: 32 or 64 rows, on tall matrices, or 16 long ones
 //   split  16 to 64 rows x 16 or 32 vectors per workgroup, the columns dealt to its eight waves; bound
 //          by the latency of its loads (4096 x 14336, 16 bf16 vectors: 10.3 us; as 16 products of one
 //          vector 78 us; with 32 vectors per workgroup, half of them padding, 14.4)
@@ -502,12 +502,13 @@ __device__ __attribute__((noinline)) void sum_again(const uint32_t *codes, int n
 // the result holds everything about (vector q, row r), and one MFMA serves all planes.
 constexpr int few_waves(int wk) { return wk < 4 ? 4 : wk; }
 
-template <typename VT, int NV, int WK>
+// Tiles of columns that a wave stages at a time.
+template <typename VT, int NV>
+constexpr int few_tiles = NV == 1 ? 4 : sizeof(VT) == 4 ? 1 : 2;
+template <typename VT, int NV, int TILES = few_tiles<VT, NV>>
 struct Few {
     static constexpr int planes = sizeof(VT) == 4 ? 3 : 1;
-    // staged at a time (sixteen waves have a CU to themselves, and one step instead of two saves the latency of its
-    // codes: 4096 x 14336, 4 bf16 vectors 7.44 -> 7.15 us)
-    static constexpr int tiles = NV == 1 ? 4 : sizeof(VT) == 4 ? 1 : WK == 16 ? 4 : 2;
+    static constexpr int tiles = TILES;
     static constexpr int cols = tiles * kTileCols;
     static constexpr int pieces = cols / 8;
     static constexpr int loads = NV * pieces / 64;
@@ -515,13 +516,123 @@ struct Few {
     static constexpr int wave_bytes = NV * planes * stride;
 };
 
-// G: row groups of 16 that a wave takes with the same columns.
-template <typename VT, int BITS, int NV, int WK, int G>
-__device__ __forceinline__ void few_rows(
+template <typename VT, int BITS, int NV, int WK>
+__global__ __launch_bounds__(few_waves(WK) * 64) void k_packed_few(
     const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ntiles, int ngroups, int n_in, int n_out,
     long long ldv, int nv, float scale, float *__restrict__ out, long long ldo, int skip_zeros,
-    const LayerTable &layers) {
-    using S = Few<VT, NV, WK>;
+    const LayerTable layers) {
+    using S = Few<VT, NV>;
+    constexpr int WR = few_waves(WK) / WK;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wr = w / WK, wk = w % WK;
+    const int g = min((int)blockIdx.x * WR + wr, ngroups - 1);
+    const int t0 = ntiles * wk / WK, t1 = ntiles * (wk + 1) / WK;
+    const int end = min(n_in, t1 * kTileCols);
+    const uint32_t *c0 = codes + ((long long)g * ntiles * 64 + lane) * (2 * BITS);
+    unsigned char *mine = smem + w * S::wave_bytes;
+
+    Piece<VT> p[S::loads];
+    auto request_v = [&](int t) {
+        const int col0 = t * kTileCols;
+#pragma unroll
+        for (int j = 0; j < S::loads; ++j) {
+            const int i = j * 64 + lane, n = NV == 1 ? 0 : min(i / S::pieces, nv - 1);
+            p[j] = load_piece<VT>(v + n * ldv, col0 + 8 * (i % S::pieces), end);
+        }
+        if ((end & 7) && end <= col0 + S::cols) {
+#pragma unroll
+            for (int j = 0; j < S::loads; ++j) {
+                const int i = j * 64 + lane, n = NV == 1 ? 0 : min(i / S::pieces, nv - 1);
+                finish_piece<VT>(p[j], v + n * ldv, col0 + 8 * (i % S::pieces), end);
+            }
+        }
+    };
+    uint32_t c[S::tiles][2 * BITS];
+    auto request_codes = [&](int t) {
+#pragma unroll
+        for (int i = 0; i < S::tiles; ++i)
+            if (t + i < t1) load_codes<BITS>(c0 + (long long)(t + i) * 128 * BITS, c[i]);
+    };
+    // the MFMA row of this lane: vector m/4, float32 plane m%4
+    const int m = lane & 15;
+    const int slot = (NV == 1 ? 0 : m >> 2) * S::planes + (S::planes == 3 ? min(m & 3, 2) : 0);
+    const unsigned char *operand = mine + slot * S::stride + (lane >> 4) * 16;
+    f32x4 acc0 = {}, acc1 = {};
+    if (t0 < t1) {
+        request_v(t0);
+        request_codes(t0);
+    }
+    for (int t = t0; t < t1; t += S::tiles) {
+#pragma unroll
+        for (int j = 0; j < S::loads; ++j) {
+            const int i = j * 64 + lane;
+            store_piece(mine + (i / S::pieces) * S::planes * S::stride + 16 * (i % S::pieces), S::stride, p[j]);
+        }
+        if (t + S::tiles < t1) request_v(t + S::tiles);
+        // the wave's LDS operations execute in order: no barrier inside a wave
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < S::tiles; ++i) {
+            if (t + i >= t1) break;
+#pragma unroll
+            for (int st = 0; st < kTileSteps; st += 2) {
+                acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_operand(operand + i * 512 + st * 64),
+                                                               decode<BITS>(c[i], st), acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_operand(operand + i * 512 + st * 64 + 64),
+                                                               decode<BITS>(c[i], st + 1), acc1, 0, 0, 0);
+            }
+        }
+        if (t + S::tiles < t1) request_codes(t + S::tiles);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    float sum = acc0.x + acc1.x;
+    if (S::planes == 3) sum += (acc0.y + acc1.y) + (acc0.z + acc1.z);
+    int group = (int)blockIdx.x * WR + wr;
+    if (WK > 1) {
+        float *red = reinterpret_cast<float *>(smem + few_waves(WK) * S::wave_bytes);
+        red[w * 64 + lane] = sum;
+        __syncthreads();
+        if (tid >= WR * 64) return;
+        sum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < WK; ++i) sum += red[(w * WK + i) * 64 + lane];
+        group = (int)blockIdx.x * WR + w;
+    }
+    const int q = lane >> 4;
+    const long long row = (long long)group * kDenseRows + m;
+    auto store = [&](float x) {
+        if (layers.n == 0) {
+            if (q < nv && row < n_out) out[q * ldo + row] = scale * x;
+        } else if (q == 0 && group < ngroups) {
+            // stacked handle: the group belongs to one layer (layers start on group boundaries)
+            int s = 0;
+#pragma unroll
+            for (int i = 1; i < kMaxLayers; ++i)
+                if (i < layers.n && group >= layers.first[i]) s = i;
+            const int local = (group - layers.first[s]) * kDenseRows + m;
+            if (local < layers.rows[s]) layers.out[s][local] = layers.scale[s] * x;
+        }
+    };
+    store(sum);
+    if (__builtin_expect(!finite(sum), 0)) {
+        if (skip_zeros && q < nv && group < ngroups)
+            store(sum_of_nonzeros<VT, BITS>(codes, ntiles, v, ldv, row, q));
+    }
+}
+
+// Two or four row groups (G) per wave, on tall matrices: v is staged, and read as an operand, once for all of them; or one
+// row group with more tiles staged at a time.  A kernel of its own, not the same template with k_packed_few: written as
+// loops over G = 1, that one took 3 % longer with the same registers where a wave has all of a row (binary, one bf16 vector,
+// 100000 x 256 3.61 -> 3.72 us, 139000 x 256 4.08 -> 4.20).
+template <typename VT, int BITS, int NV, int WK, int G, int TILES>
+__global__ __launch_bounds__(few_waves(WK) * 64) void k_packed_tall(
+    const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ntiles, int ngroups, int n_in, int n_out,
+    long long ldv, int nv, float scale, float *__restrict__ out, long long ldo, int skip_zeros,
+    const LayerTable layers) {
+    using S = Few<VT, NV, TILES>;
     constexpr int W = few_waves(WK), WR = W / WK;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -626,39 +737,17 @@ __device__ __forceinline__ void few_rows(
         if (S::planes == 3) sum[g] += (acc0[g].y + acc1[g].y) + (acc0[g].z + acc1[g].z);
     }
     const int group0 = (int)blockIdx.x * WR * G;
-    if (WK == 1) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) put(group0 + w * G + g, sum[g]);
-        return;
-    }
     float *red = reinterpret_cast<float *>(smem + W * S::wave_bytes);  // [group][wave][lane]
 #pragma unroll
     for (int g = 0; g < G; ++g) red[(g * W + w) * 64 + lane] = sum[g];
     __syncthreads();
-    static_assert(WK == 1 || WR * G <= W, "a wave per row group of the workgroup");
+    static_assert(WK > 1 && WR * G <= W, "a wave per row group of the workgroup");
     if (w >= WR * G) return;
     const float *part = red + ((w % G) * W + w / G * WK) * 64 + lane;
     float x = 0.0f;
 #pragma unroll
     for (int k = 0; k < WK; ++k) x += part[k * 64];
     put(group0 + w, x);
-}
-
-template <typename VT, int BITS, int NV, int WK>
-__global__ __launch_bounds__(few_waves(WK) * 64) void k_packed_few(
-    const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ntiles, int ngroups, int n_in, int n_out,
-    long long ldv, int nv, float scale, float *__restrict__ out, long long ldo, int skip_zeros,
-    const LayerTable layers) {
-    few_rows<VT, BITS, NV, WK, 1>(codes, v, ntiles, ngroups, n_in, n_out, ldv, nv, scale, out, ldo, skip_zeros, layers);
-}
-
-// Two or four row groups per wave, on tall matrices: v is staged, and read as an operand, once for all of them.
-template <typename VT, int BITS, int NV, int WK, int G>
-__global__ __launch_bounds__(few_waves(WK) * 64) void k_packed_tall(
-    const uint32_t *__restrict__ codes, const VT *__restrict__ v, int ntiles, int ngroups, int n_in, int n_out,
-    long long ldv, int nv, float scale, float *__restrict__ out, long long ldo, int skip_zeros,
-    const LayerTable layers) {
-    few_rows<VT, BITS, NV, WK, G>(codes, v, ntiles, ngroups, n_in, n_out, ldv, nv, scale, out, ldo, skip_zeros, layers);
 }
 
 // ---- split: 16 to 64 rows x 16 or 32 vectors, the columns dealt to the waves -------------------
@@ -1422,59 +1511,80 @@ hipError_t put_name(const Args &x, const char *kernel, const char *numbers, Numb
     return hipSuccess;
 }
 
-template <typename VT, int BITS, int NV, int WK, int G>
+// G = 0: k_packed_few; else k_packed_tall.
+template <typename VT, int BITS, int NV, int WK, int G, int TILES = few_tiles<VT, NV>>
 hipError_t launch_few_groups(const Args &x) {
     static std::atomic<size_t> enabled[kMaxDevices];
     auto kern = [] {
-        if constexpr (G == 1)
+        if constexpr (G == 0)
             return k_packed_few<VT, BITS, NV, WK>;
         else
-            return k_packed_tall<VT, BITS, NV, WK, G>;
+            return k_packed_tall<VT, BITS, NV, WK, G, TILES>;
     }();
     if (x.name) {
-        if (G == 1) return put_name<VT>(x, "k_packed_few", "%d, %d, %d>", BITS, NV, WK);
-        return put_name<VT>(x, "k_packed_tall", "%d, %d, %d, %d>", BITS, NV, WK, G);
+        if (G == 0) return put_name<VT>(x, "k_packed_few", "%d, %d, %d>", BITS, NV, WK);
+        return put_name<VT>(x, "k_packed_tall", "%d, %d, %d, %d, %d>", BITS, NV, WK, G, TILES);
     }
-    constexpr size_t lds = (size_t)few_waves(WK) * (Few<VT, NV, WK>::wave_bytes + G * 64 * 4);
+    constexpr int each = G == 0 ? 1 : G;
+    constexpr size_t lds = (size_t)few_waves(WK) * (Few<VT, NV, TILES>::wave_bytes + each * 64 * 4);
     static_assert(lds <= (size_t)kLdsBytes, "every wave stages columns of its own");
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, x.device, enabled)) return e;
-    constexpr int groups = few_waves(WK) / WK * G;
+    constexpr int groups = few_waves(WK) / WK * each;
     hipLaunchKernelGGL(kern, dim3((unsigned)((x.ngroups + groups - 1) / groups)), dim3(few_waves(WK) * 64), lds, x.stream,
                        x.codes, static_cast<const VT *>(x.v), x.ntiles, x.ngroups, x.n_in, x.n_out, x.ldv, x.batch,
                        x.scale, x.out, x.ldo, x.skip_zeros, x.layers);
     return hipGetLastError();
 }
 
-// Row groups of a wave.  Two or four save the staging of v and the reads of its operands, which is most of the work
-// for float32 vectors (three planes) and for several; they pay once the workgroups of one row group are
-// too many for the chip, that is 256 of sixteen waves or 512 of eight.  One bf16 vector is staged in no time (13824 x
-// 2560 4.3 us, with two groups 4.7).  Measured with 1 / 2 / 4 groups:
+// Row groups of a wave, G = 0 for k_packed_few, and tiles staged at a time.  Two or four groups save the staging of v and
+// the reads of its operands, which is most of the work for float32 vectors (three planes) and for several; they pay once the
+// workgroups of one row group are too many for the chip, that is 256 of sixteen waves or 512 of eight.  One bf16 vector is
+// staged in no time (13824 x 2560 4.3 us, with two groups 4.7).  Measured with 1 / 2 / 4 groups:
 //   float32, 1 vector    6000 x 8000 7.4 / 5.8 / 12.0 us (4000 rows 4.9 / 5.6), 10000 x 2500 7.2 / 5.6 / 6.1, 14336 x 4096 6.9 /
 //                        6.0 / 6.4 (8192 rows 4.8 / 4.8), 40000 x 500 6.1 / 5.0 / 5.4 (20000 4.1 / 4.3), 14336 x 1000 3.8 / 3.7
 //   float32, 3 vectors   6000 x 8000 9.4 / 6.9 / 8.9, 10000 x 8000 13.2 / 11.5 / 9.1, 14336 x 4096 8.8 / 7.0 / 6.3
 //                        (8192 rows 5.7 / 5.5 / 5.9), 40000 x 1000 6.4 / 5.1 / 5.2
-//   bf16, 4 vectors      6000 x 8000 7.8 / 5.8, 14336 x 2500 7.6 / 6.5 / 6.4, 14336 x 1000 4.1 / 3.7 (8192 rows 3.3 / 3.3);
+//   bf16, 4 vectors      14336 x 2500 7.6 / 6.5 / 6.4, 14336 x 1000 4.1 / 3.7 (8192 rows 3.3 / 3.3);
 //                        with two tiles of columns to a wave 14336 x 4096 6.0 / 5.9, but in two rounds 20000 x 4096 7.1 / 7.3
+// Sixteen waves and several bf16 vectors: a CU holds two workgroups of k_packed_few (60 registers, 70 KB of LDS) and one of
+// k_packed_tall (66 registers and more), so a round is 512 row groups for either, and two groups pay where the last round is
+// more than half full: with one / two groups, 4 vectors of 8192 elements, 4160 rows 5.8 / 5.2, 8192 6.5 / 5.9, 8320 8.1 /
+// 8.3, 12480 9.9 / 8.9, 16384 11.7 / 9.6, 17600 12.7 / 12.1, 24576 16.0 / 13.5.  Four tiles staged at a time take one step
+// instead of two where most waves have three or four (4 vectors of 14336, 4096 rows 6.9 -> 6.2, two groups, 6144 rows
+// 9.2 -> 8.3), and otherwise only LDS: 4 vectors of 8192, 4096 rows 4.6 -> 5.0, of 20480, 2048 rows 8.2 -> 8.3.
+struct FewShape {
+    int G, tiles;
+};
 template <typename VT, int NV>
-int few_groups(int ntiles, int ngroups, int wk) {
+FewShape few_shape(int ntiles, int ngroups, int wk) {
     const bool wide = sizeof(VT) == 4;
-    if ((!wide && NV == 1) || wk == 1) return 1;
-    if (wk == 16) return ngroups <= 256 ? 1 : wide && NV == 4 && ngroups > 512 ? 4 : 2;
-    if (wk == 8 && wide) return ngroups <= 512 ? 1 : NV == 4 ? 4 : 2;
-    if (wk == 8) return ngroups > 768 && (ntiles <= 12 || ngroups <= 1024) ? 2 : 1;
-    return ngroups > (wide && wk == 2 ? 2048 : 768) ? 2 : 1;
+    const int tiles = few_tiles<VT, NV>;
+    if ((!wide && NV == 1) || wk == 1) return {0, tiles};
+    if (wk == 16 && !wide) {
+        const bool four = ntiles >= 36 && ntiles <= 64;
+        if (ngroups <= 256) return {four ? 1 : 0, four ? 4 : tiles};
+        if ((ngroups - 1) % 512 < 256 || (four && ngroups > 1024)) return {0, tiles};
+        return {2, four ? 4 : tiles};
+    }
+    if (wk == 16) return {ngroups <= 256 ? 0 : NV == 4 && ngroups > 512 ? 4 : 2, tiles};
+    if (wk == 8 && wide) return {ngroups <= 512 ? 0 : NV == 4 ? 4 : 2, tiles};
+    if (wk == 8) return {ngroups > 768 && (ntiles <= 12 || ngroups <= 1024) ? 2 : 0, tiles};
+    return {ngroups > (wide && wk == 2 ? 2048 : 768) ? 2 : 0, tiles};
 }
 
 template <typename VT, int BITS, int NV, int WK>
 hipError_t launch_few_wk(const Args &x) {
-    const int G = few_groups<VT, NV>(x.ntiles, x.ngroups, WK);
+    const FewShape s = few_shape<VT, NV>(x.ntiles, x.ngroups, WK);
     if constexpr (sizeof(VT) == 4 && NV == 4 && WK >= 8) {
-        if (G == 4) return launch_few_groups<VT, BITS, NV, WK, 4>(x);
+        if (s.G == 4) return launch_few_groups<VT, BITS, NV, WK, 4>(x);
+    }
+    if constexpr (sizeof(VT) == 2 && NV == 4 && WK == 16) {
+        if (s.tiles == 4) return s.G == 1 ? launch_few_groups<VT, BITS, NV, WK, 1, 4>(x) : launch_few_groups<VT, BITS, NV, WK, 2, 4>(x);
     }
     if constexpr ((sizeof(VT) == 4 || NV == 4) && WK > 1) {
-        if (G == 2) return launch_few_groups<VT, BITS, NV, WK, 2>(x);
+        if (s.G == 2) return launch_few_groups<VT, BITS, NV, WK, 2>(x);
     }
-    return launch_few_groups<VT, BITS, NV, WK, 1>(x);
+    return launch_few_groups<VT, BITS, NV, WK, 0>(x);
 }
 
 // Waves that share the columns of a row group: one per tile of columns up to eight, so that all
@@ -1793,8 +1903,9 @@ void packed_launch_shape(const rsr_handle_s *h, int v_dtype, int *workgroups, in
         return;
     }
     const int wk = few_wk(ntiles), waves = few_waves(wk);
-    const int groups = wide ? few_groups<float, 1>(ntiles, (int)h->code_groups, wk) : 1, rows = waves / wk * groups;
-    const int wave_bytes = wide ? Few<float, 1, 1>::wave_bytes : Few<uint16_t, 1, 1>::wave_bytes;
+    const int G = wide ? few_shape<float, 1>(ntiles, (int)h->code_groups, wk).G : 0;
+    const int groups = G ? G : 1, rows = waves / wk * groups;
+    const int wave_bytes = wide ? Few<float, 1>::wave_bytes : Few<uint16_t, 1>::wave_bytes;
     *workgroups = (int)((h->code_groups + rows - 1) / rows);
     *threads = waves * 64;
     *lds_bytes = waves * (wave_bytes + groups * 64 * 4);

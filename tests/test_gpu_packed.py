@@ -355,6 +355,22 @@ def test_several_row_groups_per_wave(kind, rows, cols, batch, bf16, kernel):
     assert np.array_equal(got, want)
 
 
+# sixteen waves, bf16: two row groups where the last round of 512 is more than half full; four tiles staged for 36 to 64
+@pytest.mark.parametrize("groups,tiles,batch,kernel", [
+    (256, 35, 2, "few<unsigned short, 2, 4, 16>"), (255, 36, 3, "tall<unsigned short, 2, 4, 16, 1, 4>"),
+    (17, 64, 4, "tall<unsigned short, 2, 4, 16, 1, 4>"), (256, 65, 4, "few<unsigned short, 2, 4, 16>"),
+    (257, 24, 4, "tall<unsigned short, 2, 4, 16, 2, 2>"), (512, 36, 4, "tall<unsigned short, 2, 4, 16, 2, 4>"),
+    (513, 24, 4, "few<unsigned short, 2, 4, 16>"), (768, 36, 2, "few<unsigned short, 2, 4, 16>"),
+    (769, 25, 3, "tall<unsigned short, 2, 4, 16, 2, 2>"), (1025, 24, 2, "few<unsigned short, 2, 4, 16>"),
+    (1281, 24, 3, "tall<unsigned short, 2, 4, 16, 2, 2>"), (1281, 36, 2, "few<unsigned short, 2, 4, 16>")])
+def test_sixteen_waves(groups, tiles, batch, kernel):
+    rows, cols = 16 * groups - 5, 256 * tiles - 7
+    M = _matrix(rsr.RSR_DENSE_TERNARY_P2, rows, cols, groups + tiles)
+    h = rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), 0, rsr.RSR_DENSE_TERNARY_P2)
+    assert rsr.rsr_batch_kernel_name(h, rsr.RSR_BF16, batch) == "k_packed_" + kernel
+    _check(h, M, batch, True, 3, cols)
+
+
 def test_stacked_layers_with_several_row_groups_per_wave():
     """Layers begin inside a workgroup's groups."""
     rows, cols = (3001, 17, 5000, 2003), 2500
