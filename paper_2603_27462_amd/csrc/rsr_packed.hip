@@ -1546,6 +1546,12 @@ hipError_t launch_few_groups(const Args &x) {
 //                        (8192 rows 5.7 / 5.5 / 5.9), 40000 x 1000 6.4 / 5.1 / 5.2
 //   bf16, 4 vectors      14336 x 2500 7.6 / 6.5 / 6.4, 14336 x 1000 4.1 / 3.7 (8192 rows 3.3 / 3.3);
 //                        with two tiles of columns to a wave 14336 x 4096 6.0 / 5.9, but in two rounds 20000 x 4096 7.1 / 7.3
+// The limits, with one / two (/ four) groups: eight waves, 4 float32 vectors of 2560 (ten tiles to eight waves), 513 groups 5.3 /
+// 5.2 / 5.8 and 1024 7.8 / 5.9 / 6.0, of 4096, 513 6.3 / 5.7 / 6.0, 640 6.9 / 6.7 / 6.0; sixteen waves, 1 float32 vector of 14336, 520
+// groups 2 to 4 % slower with two.  Four waves, 1 float32 vector: five workgroups of one row group share a CU, so 1281 is where
+// their second round begins (of 1280, 780 groups 3.8 / 3.8, 1400 4.9 / 4.2, 1700 5.3 / 5.6; of 1792, 2500 groups 7.2 /
+// 7.5); several: 770 groups of 1280 6 % slower, of 1024 9 % faster, from 900 on all faster.  Two waves, 4 bf16 vectors: two tiles, 900 groups
+// 3.3 / 3.2; three, of 700, 1300 4.9 / 5.5, 1700 5.8 / 5.6.
 // Sixteen waves and several bf16 vectors: a CU holds two workgroups of k_packed_few (60 registers, 70 KB of LDS) and one of
 // k_packed_tall (66 registers and more), so a round is 512 row groups for either, and two groups pay where the last round is
 // more than half full: with one / two groups, 4 vectors of 8192 elements, 4160 rows 5.8 / 5.2, 8192 6.5 / 5.9, 8320 8.1 /
@@ -1566,10 +1572,13 @@ FewShape few_shape(int ntiles, int ngroups, int wk) {
         if ((ngroups - 1) % 512 < 256 || (four && ngroups > 1024)) return {0, tiles};
         return {2, four ? 4 : tiles};
     }
+    if (wk == 16 && NV == 1 && ntiles > 44 && ngroups > 512 && ngroups <= 768) return {0, tiles};
     if (wk == 16) return {ngroups <= 256 ? 0 : NV == 4 && ngroups > 512 ? 4 : 2, tiles};
-    if (wk == 8 && wide) return {ngroups <= 512 ? 0 : NV == 4 ? 4 : 2, tiles};
+    if (wk == 8 && wide) return {ngroups <= 512 ? 0 : NV == 4 && ngroups > (ntiles >= 16 ? 576 : 768) ? 4 : 2, tiles};
     if (wk == 8) return {ngroups > 768 && (ntiles <= 12 || ngroups <= 1024) ? 2 : 0, tiles};
-    return {ngroups > (wide && wk == 2 ? 2048 : 768) ? 2 : 0, tiles};
+    if (wk == 4 && NV == 1) return {(ntiles == 4 ? ngroups > 768 : ngroups > 1280 && ngroups <= 1536) ? 2 : 0, tiles};
+    if (wk == 4) return {ngroups > (ntiles == 4 ? 768 : 896) ? 2 : 0, tiles};
+    return {ngroups > (wide ? 2048 : ntiles == 2 ? 768 : 1536) ? 2 : 0, tiles};
 }
 
 template <typename VT, int BITS, int NV, int WK>

@@ -336,8 +336,17 @@ def test_batches_in_a_graph(kind, rows, cols, k, batch):
     (rsr.RSR_DENSE_TERNARY_P2, 256 * 16 + 40, 14336, 1, False, "tall"), (rsr.RSR_DENSE_TERNARY_P2, 512 * 16, 2049, 1, False, "few"),
     (rsr.RSR_DENSE_TERNARY_P2, 512 * 16 + 1, 2049, 1, False, "tall"), (rsr.RSR_TERNARY_FUSED, 513 * 16 + 3, 2300, 4, False, "tall"),
     (rsr.RSR_BINARY, 768 * 16 + 2, 3000, 3, True, "tall"), (rsr.RSR_DENSE_TERNARY_P2, 1024 * 16 + 1, 3400, 2, True, "few"),
-    (rsr.RSR_DENSE_TERNARY_P2, 769 * 16 + 5, 1100, 1, False, "tall"), (rsr.RSR_BINARY, 2050 * 16 + 9, 300, 2, False, "tall"),
-    (rsr.RSR_DENSE_TERNARY_P2, 800 * 16 - 3, 511, 4, True, "tall"), (rsr.RSR_DENSE_TERNARY_P2, 60000, 2500, 1, True, "few")])
+    (rsr.RSR_DENSE_TERNARY_P2, 769 * 16 + 5, 1100, 1, False, "few"), (rsr.RSR_BINARY, 2050 * 16 + 9, 300, 2, False, "tall"),
+    (rsr.RSR_DENSE_TERNARY_P2, 800 * 16 - 3, 511, 4, True, "tall"), (rsr.RSR_DENSE_TERNARY_P2, 60000, 2500, 1, True, "few"),
+    (rsr.RSR_DENSE_TERNARY_P2, 1281 * 16 - 1, 1300, 1, False, "tall"), (rsr.RSR_DENSE_TERNARY_P2, 1536 * 16 + 1, 1100, 1, False, "few"),
+    (rsr.RSR_DENSE_TERNARY_P2, 768 * 16 + 1, 1024, 1, False, "tall"), (rsr.RSR_DENSE_TERNARY_P2, 896 * 16, 1200, 2, False, "few"),
+    (rsr.RSR_DENSE_TERNARY_P2, 896 * 16 + 1, 1200, 3, True, "tall"), (rsr.RSR_BINARY, 1536 * 16, 515, 4, True, "few"),
+    (rsr.RSR_DENSE_TERNARY_P2, 1536 * 16 + 1, 700, 2, True, "tall"), (rsr.RSR_DENSE_TERNARY_P2, 768 * 16, 11500, 1, False, "few"),
+    (rsr.RSR_DENSE_TERNARY_P2, 768 * 16 - 7, 11000, 1, False, "tall<float, 2, 1, 16, 2, 4>"),
+    (rsr.RSR_DENSE_TERNARY_P2, 576 * 16, 4000, 3, False, "tall<float, 2, 4, 8, 2, 1>"),
+    (rsr.RSR_DENSE_TERNARY_P2, 576 * 16 + 1, 4000, 2, False, "tall<float, 2, 4, 8, 4, 1>"),
+    (rsr.RSR_DENSE_TERNARY_P2, 768 * 16, 2560, 4, False, "tall<float, 2, 4, 8, 2, 1>"),
+    (rsr.RSR_BINARY, 768 * 16 + 1, 2560, 4, False, "tall<float, 1, 4, 8, 4, 1>")])
 def test_several_row_groups_per_wave(kind, rows, cols, batch, bf16, kernel):
     M = _matrix(kind, rows, cols, 77 + cols)
     h = rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), 4, kind)
