@@ -1659,7 +1659,10 @@ hipError_t launch_table_many(const Args &x) {
 // vectors: 4096 rows (x 14336) 22.8 / 23.4 / 28.7 us, 6912 (x 2560) 10.0 / 8.3 / 9.7, 14336 (x 4096)
 // 20.9 / 13.8 / 11.8.  From 512 row groups on two of them are more than one workgroup per CU, which costs most where
 // columns are many: 9000 rows with 2 / 4, 16 float32 vectors, x 8000 23.2 / 19.4, x 4096 13.6 / 11.1, x 2400 10.9 / 10.7,
-// x 1000 6.2 / 6.5; 16 bf16 x 4096 7.9 / 6.7, 6 bf16 x 8000 10.9 / 10.8, x 2400 6.1 / 6.6.  32 vectors with 2 / 4: a workgroup of four row groups takes about 1.3 times as
+// x 1000 6.2 / 6.5; 16 bf16 x 4096 7.9 / 6.7, 6 bf16 x 8000 10.9 / 10.8, x 2400 6.1 / 6.6.  Where the limits lie (codes in the L2;
+// from the Infinity Cache two groups lose a few per cent more): float32 x 2900 (12 tiles), 9 vectors, 513 groups 10.3 / 10.4, 540
+// 10.7 / 10.4, x 3300, 513 11.0 / 10.5; bf16 x 3300, 9 vectors, 513 6.5 / 7.2, 540 7.0 / 7.3, 600 7.3 / 7.3, 16 vectors,
+// 513 6.7 / 7.4, 540 8.0 / 7.5.  32 vectors with 2 / 4: a workgroup of four row groups takes about 1.3 times as
 // long (24 float32 vectors, 6912 x 2560: 12.4 / 15.0), so four pay where they save a round of
 // workgroups (14336 x 4096: 24.0 / 16.8), for bf16 where they fit in one round (4096 x 14336, 100
 // vectors: 30.4 / 21.5; 6912 x 2560, 432 workgroups: 13.7 / 14.5).  Waves without columns take
@@ -1672,7 +1675,7 @@ SplitShape split_shape(int ntiles, int ngroups, int batch, bool wide) {
     SplitShape s = {batch <= 16 ? 1 : 2, 1, 3};
     const long long units = (long long)ngroups * ((batch + 16 * s.NT - 1) / (16 * s.NT));
     if (s.NT == 1) {
-        const int four = ntiles >= 12 && (wide || batch > 8) ? 512 : 640;
+        const int four = wide && ntiles >= 13 ? 512 : (wide && ntiles == 12) || (ntiles >= 13 && batch > 8) ? 536 : 640;
         s.G = units > four ? 4 : units > 320 ? 2 : 1;
     } else {
         const long long two = (units / 2 + kCUs - 1) / kCUs, four = (units / 4 + kCUs - 1) / kCUs;  // rounds

@@ -329,6 +329,20 @@ def test_batches_in_a_graph(kind, rows, cols, k, batch):
                           oracle.dense_matvec(M, v[1].cpu().numpy().astype(np.float64)))
 
 
+# 5 to 16 vectors, two or four row groups of 16 per workgroup: both sides of every limit
+@pytest.mark.parametrize("groups,tiles,batch,bf16,G", [
+    (512, 13, 5, False, 2), (513, 13, 5, False, 4), (536, 12, 16, False, 2), (537, 12, 7, False, 4), (640, 11, 6, False, 2),
+    (641, 11, 6, False, 4), (536, 13, 9, True, 2), (537, 13, 9, True, 4), (640, 12, 9, True, 2), (640, 13, 8, True, 2),
+    (641, 20, 8, True, 4)])
+def test_row_groups_of_a_workgroup(groups, tiles, batch, bf16, G):
+    rows, cols = 16 * groups - 9, 256 * tiles - 3
+    M = _matrix(rsr.RSR_BINARY, rows, cols, groups + tiles)
+    h = rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), 8, rsr.RSR_BINARY)
+    name = "k_packed_split<%s, 1, 1, %d, false>" % ("unsigned short" if bf16 else "float", G)
+    assert rsr.rsr_batch_kernel_name(h, int(bf16), batch) == name
+    _check(h, M, batch, bf16, 1, cols, distinct=4)
+
+
 # two or four row groups per wave: both sides of every rule, a last workgroup with fewer groups, ragged rows and columns
 @pytest.mark.parametrize("kind,rows,cols,batch,bf16,kernel", [
     (rsr.RSR_DENSE_TERNARY_P2, 256 * 16, 6200, 4, True, "few"), (rsr.RSR_DENSE_TERNARY_P2, 256 * 16 + 1, 6200, 4, True, "tall"),
