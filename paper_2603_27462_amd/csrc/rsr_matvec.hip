@@ -640,9 +640,20 @@ int64_t both_lds_bytes(int64_t slots, int64_t cols, int v_elem_bytes, int W) {
 // 5.36 / 4.70 us, 2040 x 4096 (255) 5.82 / 5.41, 3000 x 4096 (375) 7.25 / 7.16, 3600 x 4096 (450) 7.32 / 7.33, 4096 x 4096
 // (512) 7.45 / 7.54, 14336 x 4096 19.8 / 20.4; 2000 x 4000 k = 10 (200) 8.0 / 6.1, 10000 x 4000 (1000) 12.9 / 14.0; 4000 x
 // 2500 k = 5 (800) 8.8 / 9.4; four waves: 14336 x 4096 k = 4 (3584) 23.7 / 21.7, three: k = 3 29.9 / 25.6.
+// Not where a CU would hold one workgroup instead of two (k = 12, 5376 x 9500, 81 KB, 11.6 / 9.9, but 5376 x 10000, 83 KB, 11.8 /
+// 12.6).  And not for many blocks of few columns, whose workgroups are short: one of twice the waves takes the place of
+// three or four (registers: 72 to 80 and 62), and rounds are what they cost.  With the streams in the L2 / beyond it, 3584
+// blocks of 1000 columns, bf16, k = 4 1.14 / 1.03 times as long, k = 3 1.22 / 0.96, 1000 blocks 1.01 / 0.91; of 4096 columns 0.95 / 0.94; k = 1,
+// one or two waves, 2000 blocks of 2500 columns 1.19 / 1.20, 3584 of 4096 0.96.
 bool use_both(const rsr_handle_s *h, int v_elem_bytes, int batch) {
-    return h->npass == 2 && !h->by_rank && 2 * h->W <= kMaxWaves && (h->W <= 4 || h->nb * batch <= 448) &&
-           both_lds_bytes(h->slots, h->cols, v_elem_bytes, h->W) <= kLdsBytes;
+    if (h->npass != 2 || h->by_rank || 2 * h->W > kMaxWaves) return false;
+    const int64_t n = h->nb * batch, both = both_lds_bytes(h->slots, h->cols, v_elem_bytes, h->W);
+    if (both > kLdsBytes) return false;
+    if (n <= 256) return true;
+    if (both > kLdsBytes / 2 && matvec_lds_bytes(h->slots, h->cols, v_elem_bytes, h->W, false) <= kLdsBytes / 2) return false;
+    if (n <= 448 || h->W > 4) return n <= 448;
+    const bool long_rows = h->cols >= 4096;
+    return h->k == 1 ? h->W >= 3 || (long_rows && n >= 3000) : n <= 1024 || long_rows;
 }
 
 template <typename VT, int ENC>

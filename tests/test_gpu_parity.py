@@ -441,12 +441,14 @@ def test_errors():
     _check_matvec(h, M.cpu().numpy(), 64, 3)
 
 
-# both passes in one workgroup (up to 448 blocks, or blocks of at most four waves) and one after the other; E and totals of
-# both in LDS; blocks whose last rows do not exist; more rows than waves; batches on few rows
+# both passes in one workgroup (up to 448 blocks, or blocks of at most four waves, with limits) and one after the other; E and
+# totals of both in LDS; blocks whose last rows do not exist; more rows than waves; batches on few rows; entries of either
+# encoding (16384 columns and more)
 @pytest.mark.parametrize("rows,cols,k,batch,both", [
     (1, 700, 1, 1, True), (1021, 1000, 8, 1, True), (448 * 6, 900, 6, 1, True), (448 * 6 + 1, 900, 6, 1, False),
-    (9001, 1500, 4, 1, True), (5000, 1200, 1, 1, True), (333, 14336, 10, 1, True), (300, 5000, 12, 1, True),
-    (301, 20001, 9, 1, False), (40, 14336, 8, 12, True)])
+    (9001, 1500, 4, 1, False), (4001, 1500, 4, 1, True), (4005, 4096, 3, 1, True), (5000, 1200, 1, 1, False),
+    (3001, 4200, 1, 1, True), (2990, 4200, 1, 1, False), (600, 14336, 1, 1, True), (333, 14336, 10, 1, True), (300, 5000, 12, 1, True),
+    (301, 20001, 9, 1, False), (40, 14336, 8, 12, True), (301, 16383, 3, 1, True), (301, 16384, 3, 1, True), (2, 24000, 2, 1, True)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_two_passes_at_once(rows, cols, k, batch, both, bf16):
     M = gen.ternary_matrix(rows, cols, 0.4, rows + cols)
@@ -460,3 +462,19 @@ def test_two_passes_at_once(rows, cols, k, batch, both, bf16):
     want = np.stack([oracle.dense_matvec(M, r.astype(np.float64), 0.5) for r in x])
     assert np.array_equal(out[:, :rows].cpu().numpy().astype(np.float64), want)
     assert bool((out[:, rows] == -7.0).all())
+
+
+@pytest.mark.parametrize("blocks,cols,bf16,both", [(256, 10000, False, True), (257, 10000, False, False), (257, 10000, True, True),
+                                                   (257, 9000, False, True), (449, 9000, True, False)])
+def test_two_passes_at_once_leave_room_for_two_workgroups(blocks, cols, bf16, both):
+    """From 257 blocks on not where the doubled LDS takes away a CU's second workgroup."""
+    k = 12
+    M = gen.ternary_matrix(blocks * k, cols, 0.35, cols)
+    h = rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), k, rsr.RSR_TERNARY_2PASS)
+    assert ("both" in rsr.rsr_kernel_name(h, int(bf16))) == both
+    threads, lds = rsr.rsr_launch_shape(h, int(bf16))[1:]
+    assert threads <= 1024 and (lds <= 80 * 1024 or blocks <= 256)
+    x = gen.integer_f32(cols, seed=3)
+    v = torch.from_numpy(x).to(DEV).to(torch.bfloat16 if bf16 else torch.float32)
+    got = rsr.rsr_matvec_ex(h, v).cpu().numpy().astype(np.float64)
+    assert np.array_equal(got, oracle.dense_matvec(M, x.astype(np.float64)))
