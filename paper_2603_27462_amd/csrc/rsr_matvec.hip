@@ -201,16 +201,23 @@ __device__ __forceinline__ uint32_t load_sign_word(const void *sgn, long long in
 constexpr int kMoreRows = 3;  // further rows of a wave (w + W, w + 2W, ...) whose tables are requested up front
 
 // What a pass does with a row's total: writes it, adds it to what the first pass wrote, or leaves it in
-// LDS for the workgroup to add (kTotals floats behind everything else, [pass][row]).
+// LDS for the workgroup to add (kTotals floats behind everything else, [pass][row]).  The sum of two passes is one
+// rounded product and one fused multiply-add, whichever kernel forms it, so that a result does not depend on the number of
+// blocks or vectors that decides between them.
 enum { kWrite = 0, kAdd = 1, kLeave = 2 };
 constexpr int kTotals = 2 * 16;
+__device__ __forceinline__ float add_pass(float first, float sign_scale, float total) {
+    return __builtin_fmaf(sign_scale, total, first);
+}
 
 template <int OUT>
-__device__ __forceinline__ void put_total(float term, int r, float *out_rows, long long rows_left, uint32_t total_at) {
+__device__ __forceinline__ void put_total(float sign_scale, float total, int r, float *out_rows, long long rows_left,
+                                          uint32_t total_at) {
     if (OUT == kLeave)
-        *lds_float(total_at + (uint32_t)r * 4u) = term;
+        *lds_float(total_at + (uint32_t)r * 4u) = sign_scale * total;
     else if (r < rows_left)
-        __builtin_nontemporal_store(OUT == kWrite ? term : out_rows[r] + term, &out_rows[r]);
+        __builtin_nontemporal_store(OUT == kWrite ? sign_scale * total : add_pass(out_rows[r], sign_scale, total),
+                                    &out_rows[r]);
 }
 
 template <int OUT, int TC>
@@ -283,7 +290,7 @@ __device__ __forceinline__ void scatter_by_code(const FoldArgs &f, const Scatter
             x += sp.wf[2] * v2;
             x += sp.wf[3] * v3;
             const float tot = wave_inclusive_scan(x);
-            if (lane == 63) put_total<OUT>(sign_scale * tot, r, out_rows, rows_left, total_at);
+            if (lane == 63) put_total<OUT>(sign_scale, tot, r, out_rows, rows_left, total_at);
         }
         return;
     }
@@ -325,7 +332,7 @@ __device__ __forceinline__ void scatter_by_code(const FoldArgs &f, const Scatter
             x += (float)(int)(signed char)(pk >> 24) * v3;
         }
         const float tot = wave_inclusive_scan(x);
-        if (lane == 63) put_total<OUT>(sign_scale * tot, r, out_rows, rows_left, total_at);
+        if (lane == 63) put_total<OUT>(sign_scale, tot, r, out_rows, rows_left, total_at);
     }
 }
 
@@ -371,8 +378,7 @@ __device__ __forceinline__ void scatter_by_rank(const FoldArgs &f, const uint32_
     if (tid < f.k && tid < rows_left) {
         float sum = 0.0f;
         for (int i = 0; i < W; ++i) sum += *lds_float(red_at + (uint32_t)(i * kMaxRows + tid) * 4u);
-        const float term = sign_scale * sum;
-        out_rows[tid] = FIRST ? term : out_rows[tid] + term;
+        out_rows[tid] = FIRST ? sign_scale * sum : add_pass(out_rows[tid], sign_scale, sum);
     }
 }
 
@@ -406,13 +412,14 @@ __device__ __forceinline__ void slab_step(const u32x4 &q, uint32_t (&g)[8], floa
 
 // One pass (binary, M+, M- or fused) of one block.  OUT: kWrite: v still has to be staged into
 // LDS and the output rows are overwritten; kAdd: the pass adds to them; kLeave: the workgroup's second W waves run
-// the other pass at the same time (`second`: these are they), all of them stage v, and the totals stay in LDS.
+// the other pass at the same time (`second`: these are they; second_sign: of that pass), all of them stage v, and the totals
+// stay in LDS, those of the second pass as they are.
 template <typename VT, int ENC, bool BYRANK, int OUT, int TC>
 __device__ __forceinline__ void run_pass(const uint16_t *__restrict__ entries,
                                          const uint16_t *__restrict__ start, int S, int per, int rem,
                                          const PassArgs &a, const void *__restrict__ v, long long ldv,
                                          int n_in, int W, const FoldArgs &f, const OutArgs &o,
-                                         int vec, bool second = false) {
+                                         int vec, bool second = false, float second_sign = 0.0f) {
     constexpr bool FIRST = OUT != kAdd;  // v is staged
     // LDS (byte addresses): v (n_in + zero slot) | T[max(W, 8)][64] | E[slots] | by code: Tc
     // zeros, C1[threads]; by rank: partial sums [W][16]
@@ -559,12 +566,12 @@ __device__ __forceinline__ void run_pass(const uint16_t *__restrict__ entries,
                                scale * a.sign, out_rows, rows_left);
     else
         scatter_by_code<OUT, TC>(f, sp, wpre, sw, pk_more, sw_more, a.sgn, b, t_at, e_at, c1_at, W, w, lane,
-                                 scale * a.sign, out_rows, rows_left, total_at);
+                                 OUT == kLeave && second ? 1.0f : scale * a.sign, out_rows, rows_left, total_at);
     if (OUT == kLeave) {
         __syncthreads();
         if (me < f.k && me < rows_left) {
             const uint32_t at = vbytes + 2u * pass_bytes + (uint32_t)me * 4u;
-            __builtin_nontemporal_store(*lds_float(at) + *lds_float(at + 64u), &out_rows[me]);
+            __builtin_nontemporal_store(add_pass(*lds_float(at), scale * second_sign, *lds_float(at + 64u)), &out_rows[me]);
         }
     }
 }
@@ -599,7 +606,7 @@ __global__ __launch_bounds__(1024, 8) void k_rsr_matvec_both(
     const PassArgs &a = second ? a1 : a0;
     run_pass<VT, ENC, false, kLeave, 0>(second ? a1.entries : entries0, second ? a1.start : start0,
                                         second ? a1.S : S0, second ? a1.per : per0, second ? a1.rem : rem0, a, v, ldv,
-                                        n_in, W, f, o, (int)blockIdx.y, second);
+                                        n_in, W, f, o, (int)blockIdx.y, second, a1.sign);
 }
 
 struct LaunchArgs {

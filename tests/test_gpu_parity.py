@@ -478,3 +478,17 @@ def test_two_passes_at_once_leave_room_for_two_workgroups(blocks, cols, bf16, bo
     v = torch.from_numpy(x).to(DEV).to(torch.bfloat16 if bf16 else torch.float32)
     got = rsr.rsr_matvec_ex(h, v).cpu().numpy().astype(np.float64)
     assert np.array_equal(got, oracle.dense_matvec(M, x.astype(np.float64)))
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("k,cols", [(8, 900), (6, 2500), (8, 4099)])
+def test_two_passes_give_the_same_bits_at_once_and_in_turn(k, cols, bf16):
+    """448 blocks run both passes at once, 449 one after the other; the rows of the first 448 do not change by that."""
+    M = torch.from_numpy(gen.ternary_matrix(449 * k, cols, 0.35, cols)).to(DEV)
+    some, every = (rsr.rsr_preprocess(m, k, rsr.RSR_TERNARY_2PASS) for m in (M[:448 * k].contiguous(), M))
+    dtype = int(bf16)
+    assert "both" in rsr.rsr_kernel_name(some, dtype) and "both" not in rsr.rsr_kernel_name(every, dtype)
+    assert rsr.rsr_launch_shape(some, dtype)[1] == 2 * rsr.rsr_launch_shape(every, dtype)[1]    # the same waves per pass
+    v = torch.from_numpy(np.random.default_rng(cols).standard_normal(cols)).to(DEV).to(torch.bfloat16 if bf16 else torch.float32)
+    for scale in (1.0, 0.3, -1.7):
+        assert torch.equal(rsr.rsr_matvec_ex(some, v, scale=scale), rsr.rsr_matvec_ex(every, v, scale=scale)[:448 * k])
