@@ -1088,8 +1088,8 @@ __global__ __launch_bounds__(256 * KW, 2) void k_packed_tile(
 // One tile of columns: all of a vector fits the registers (or the LDS) of a wave, so it is brought
 // into operand order once and the wave then works through many row groups, with nothing but their
 // codes to wait for.  1048576 x 256 binary, float32 vectors, before (a wave stages v for every 512
-// bytes of codes; tiles of 128 vectors) and now: 1 vector 24.7 -> 14.5 us with bf16 operands, 8.4 with digits (4.5 TB/s; a
-// plain read of the codes takes 6.6), 16 vectors 171 -> 32, 64 vectors 201 -> 100 (3.0 TB/s, of which
+// bytes of codes; tiles of 128 vectors) and now: 1 vector 24.7 -> 14.5 us with bf16 operands, 8.0 with digits (4.2 TB/s; a
+// plain read of the codes takes 6.6; with sixteen such tables in turn, whose codes come from HBM, 16.7 and 10.2), 16 vectors 171 -> 32, 64 vectors 201 -> 100 (3.0 TB/s, of which
 // the 268 MB of results take two thirds).
 
 // table_few: up to 16 vectors.  The operands of the eight 32-column steps stay in registers; for up
@@ -1111,12 +1111,18 @@ struct TableFew {
 // entries where they took an AND and four conversions.  Every row of the result is a sum of whole
 // numbers below 2^13 in units of its own plane, which is exact (the instruction cuts off what lies 2^-15
 // and more below its largest term: 14 binades in one sum were measured to be wrong by 4e-5 of it), so
-// the only roundings are those of the final sum over the planes.  Not taken, by the whole
-// workgroup, where an element reaches below the last digit (nonzero and smaller than 2^(E-55)) or is not finite.
+// the only roundings are those of the final sum over the planes.  Elements that reach below the last digit (nonzero and
+// smaller than 2^(E-55)) go into further sets of digits, each with the exponent 56 below the one before (float32 needs
+// five at most): two more MFMAs per row group and set, exact too.  With one element at 2^-70, float32, 1048576 x 256 binary
+// 12.1 us (9.7 without; 16.5 with bf16 operands, 17.0 after digits that turned out not to hold it), 241000 x 256 two-bit codes
+// 6.6 (5.7; 6.2, 7.7).
+// Not taken, by the whole workgroup, where an element is not finite.
 constexpr int kDigits = 16;
 constexpr int kDigitStride = kTileCols + 16;  // bytes between planes
-constexpr int kDigitExponents = 55;
-constexpr int kTableOneLds = kDigits * kDigitStride + 2 * kTableWaves * 4;  // digits; two floats per wave
+constexpr int kDigitExponents = 56;                       // of the elements in one set
+constexpr int kDigitSetBytes = kDigits * kDigitStride;
+constexpr int kDigitSets = (127 + 149) / kDigitExponents + 1;
+constexpr int kTableOneLds = kDigitSets * kDigitSetBytes + 2 * kTableWaves * 4;  // digits; two words per wave
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
@@ -1164,11 +1170,11 @@ __device__ __forceinline__ float wave_max(float x) {
     return dpp_max<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
 }
 
-// Writes the digits of v to LDS, a thread per column; false (for the whole workgroup) if they do not hold it.
-// *exponent: of the unit of plane 0.  `most`: two floats per wave.
+// Writes the digits of v to LDS, a thread per column, and returns the number of sets; 0 (for the whole workgroup) if an
+// element is not finite.  *exponent: of the unit of plane 0 of the first set.  `most`: two words per wave.
 template <typename VT, int BITS>
-__device__ __forceinline__ bool table_digits(const VT *__restrict__ v, int n_in, unsigned char *digits, float *most,
-                                             int *exponent) {
+__device__ __forceinline__ int table_digits(const VT *__restrict__ v, int n_in, unsigned char *digits, float *most,
+                                            int *exponent) {
     const int col = threadIdx.x;
     const float x = col < n_in ? widen(v[col]) : 0.0f;
     float top = wave_max(__builtin_fabsf(x));  // (a NaN is lost by the maximum and found below)
@@ -1177,11 +1183,16 @@ __device__ __forceinline__ bool table_digits(const VT *__restrict__ v, int n_in,
 #pragma unroll
     for (int i = 0; i < kTableWaves; ++i) top = __builtin_fmaxf(top, most[i]);
     const int E = top > 0.0f ? (int)__builtin_amdgcn_frexp_expf(top) - 1 : 0;
-    const bool bad = !finite(x) || (x != 0.0f && (int)__builtin_amdgcn_frexp_expf(x) - 1 < E - kDigitExponents);
+    // (nothing of this means anything beside an element that is not finite, but it stays in range)
+    const int below = x != 0.0f ? E - ((int)__builtin_amdgcn_frexp_expf(x) - 1) : 0;
+    int set = 0;
+    const bool far = __ballot(below >= kDigitExponents) != 0;
+    if (__builtin_expect(far, 0)) set = min(max(below, 0) / kDigitExponents, kDigitSets - 1);
     float weight;
     unsigned char *at = digits + digit_place<BITS>(col, &weight);
     const float unit = 1.0f / weight;
-    float rest = __builtin_amdgcn_ldexpf(x, 3 - E);
+    float rest = __builtin_amdgcn_ldexpf(x, 3 - E + set * kDigitExponents);
+    unsigned char *mine = at + set * kDigitSetBytes;
 #pragma unroll
     for (int p = 0; p < kDigits; p += 2) {
         const float d0 = __builtin_rintf(rest);
@@ -1189,46 +1200,65 @@ __device__ __forceinline__ bool table_digits(const VT *__restrict__ v, int n_in,
         const float d1 = __builtin_rintf(rest);
         rest = (rest - d1) * 32.0f;
         const int two = __builtin_amdgcn_cvt_pk_fp8_f32(d0 * unit, d1 * unit, 0, false);
-        at[p * kDigitStride] = (unsigned char)two;
-        at[(p + 1) * kDigitStride] = (unsigned char)(two >> 8);
+        mine[p * kDigitStride] = (unsigned char)two;
+        mine[(p + 1) * kDigitStride] = (unsigned char)(two >> 8);
     }
-    *exponent = E - 3;
-    const uint64_t lanes = __ballot(bad);
-    if ((col & 63) == 0) most[kTableWaves + (col >> 6)] = lanes ? 1.0f : 0.0f;
-    __syncthreads();
-    float any = 0.0f;
+    // the column has no digits in the other sets
+    auto none_in = [&](int other) {
+        if (other == set) return;
 #pragma unroll
-    for (int i = 0; i < kTableWaves; ++i) any += most[kTableWaves + i];
-    return any == 0.0f;
+        for (int p = 0; p < kDigits; ++p) at[other * kDigitSetBytes + p * kDigitStride] = 0;
+    };
+    if (__builtin_expect(far, 0)) none_in(0);
+    *exponent = E - 3;
+    int sets = 1;
+    if (__ballot(!finite(x)))
+        sets = kDigitSets + 1;
+    else
+        while (__ballot(set >= sets)) ++sets;
+    int *need = reinterpret_cast<int *>(most + kTableWaves);
+    if ((col & 63) == 0) need[col >> 6] = sets;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kTableWaves; ++i) sets = max(sets, need[i]);
+    sets = __builtin_amdgcn_readfirstlane(sets);
+    if (sets > kDigitSets) return 0;
+    if (__builtin_expect(sets > 1, 0)) {
+        for (int s = 1; s < sets; ++s) none_in(s);
+        __syncthreads();
+    }
+    return sets;
 }
 
-// The row groups [g0, g1) of a wave with the digits in LDS; c: the codes of the first ones.
-template <int BITS, int U>
+// The row groups [g0, g1) of a wave with the digits in LDS; c: the codes of the first ones.  MANY: more than one set.
+template <int BITS, int U, bool MANY>
 __device__ __forceinline__ void table_by_digits(const uint32_t *__restrict__ c0, uint32_t (&c)[U][2 * BITS],
-                                                const unsigned char *digits, int exponent, int g0, int g1, int n_out,
-                                                float scale, float *__restrict__ out, const LayerTable &layers) {
+                                                const unsigned char *digits, int sets, int exponent, int g0, int g1,
+                                                int n_out, float scale, float *__restrict__ out, const LayerTable &layers) {
     const int lane = threadIdx.x & 63, m = lane & 15, q = lane >> 4;
-    i32x8 op[2];  // row m: plane m; bytes 0..15 and 16..31: columns 16 q and 64 + 16 q of a half
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const i32x4 lo = *reinterpret_cast<const i32x4 *>(digits + m * kDigitStride + 128 * h + 16 * q);
-        const i32x4 hi = *reinterpret_cast<const i32x4 *>(digits + m * kDigitStride + 128 * h + 64 + 16 * q);
-        op[h] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    }
+    // row m: plane m; bytes 0..15 and 16..31: columns 16 q and 64 + 16 q of a half
+    auto operand = [&](int set, int h) {
+        const unsigned char *at = digits + set * kDigitSetBytes + m * kDigitStride + 128 * h + 16 * q;
+        const i32x4 lo = *reinterpret_cast<const i32x4 *>(at), hi = *reinterpret_cast<const i32x4 *>(at + 64);
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+    i32x8 op0, op1;
+    auto load_set = [&](int set) {
+        op0 = operand(set, 0);
+        op1 = operand(set, 1);
+    };
+    if (!MANY) load_set(0);
     const int plane_scale = 127 - 5 * m;  // a power of two, biased by 127
-    for (int g = g0; g < g1; g += U) {
-        uint32_t next[U][2 * BITS];
-#pragma unroll
-        for (int i = 0; i < U; ++i)
-            if (g + U + i < g1) load_codes<BITS>(c0 + (long long)(g + U + i) * 128 * BITS, next[i]);
+    // x[i]: of row group 4 i + q, row m
+    auto product = [&](int exponent, float (&x)[U / 4]) {
         f32x4 acc[U];
 #pragma unroll
         for (int i = 0; i < U; ++i)
-            acc[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(op[0], nibbles<BITS>(c[i], 0), f32x4{}, 0, 4, 0,
+            acc[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(op0, nibbles<BITS>(c[i], 0), f32x4{}, 0, 4, 0,
                                                                       plane_scale, 0, 127);
 #pragma unroll
         for (int i = 0; i < U; ++i)
-            acc[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(op[1], nibbles<BITS>(c[i], 1), acc[i], 0, 4, 0,
+            acc[i] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(op1, nibbles<BITS>(c[i], 1), acc[i], 0, 4, 0,
                                                                       plane_scale, 0, 127);
         float sum[U];  // lane quarter q: planes 4 q .. 4 q + 3
 #pragma unroll
@@ -1239,19 +1269,42 @@ __device__ __forceinline__ void table_by_digits(const uint32_t *__restrict__ c0,
             auto add = [](auto r) { return __uint_as_float(r[0]) + __uint_as_float(r[1]); };
             const float a = add(__builtin_amdgcn_permlane32_swap(__float_as_uint(sum[i]), __float_as_uint(sum[i + 2]), false, false));
             const float b = add(__builtin_amdgcn_permlane32_swap(__float_as_uint(sum[i + 1]), __float_as_uint(sum[i + 3]), false, false));
-            const float x = __builtin_amdgcn_ldexpf(
+            x[i / 4] = __builtin_amdgcn_ldexpf(
                 add(__builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false)), exponent);
+        }
+    };
+    for (int g = g0; g < g1; g += U) {
+        uint32_t next[U][2 * BITS];
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+            if (g + U + i < g1) load_codes<BITS>(c0 + (long long)(g + U + i) * 128 * BITS, next[i]);
+        float x[U / 4];
+        if constexpr (MANY) {  // the smallest first
+            load_set(sets - 1);
+            product(exponent - (sets - 1) * kDigitExponents, x);
+            for (int s = sets - 2; s >= 0; --s) {
+                load_set(s);
+                float y[U / 4];
+                product(exponent - s * kDigitExponents, y);
+#pragma unroll
+                for (int i = 0; i < U / 4; ++i) x[i] += y[i];
+            }
+        } else {
+            product(exponent, x);
+        }
+#pragma unroll
+        for (int i = 0; i < U; i += 4) {
             if (g + i + q >= g1) continue;
             if (layers.n == 0) {
                 const long long row = (long long)(g + i) * kDenseRows + lane;
-                if (row < n_out) out[row] = scale * x;
+                if (row < n_out) out[row] = scale * x[i / 4];
             } else {
                 int s = 0;
 #pragma unroll
                 for (int l = 1; l < kMaxLayers; ++l)
                     if (l < layers.n && g + i + q >= layers.first[l]) s = l;
                 const int local = (g + i + q - layers.first[s]) * kDenseRows + m;
-                if (local < layers.rows[s]) layers.out[s][local] = layers.scale[s] * x;
+                if (local < layers.rows[s]) layers.out[s][local] = layers.scale[s] * x[i / 4];
             }
         }
 #pragma unroll
@@ -1281,10 +1334,21 @@ __global__ __launch_bounds__(kTableWaves * 64, (TableFew<VT, NV>::occupancy)) vo
     for (int i = 0; i < U; ++i)
         if (g0 + i < g1) load_codes<BITS>(c0 + (long long)(g0 + i) * 128 * BITS, c[i]);
     if constexpr (NV == 1) {
-        static_assert(kTableWaves * 64 == kTileCols && kBytes <= kDigits * kDigitStride, "a thread per column");
+        static_assert(kTableWaves * 64 == kTileCols && kBytes <= kDigitSetBytes, "a thread per column");
         int exponent;
-        if (table_digits<VT, BITS>(v, n_in, smem, reinterpret_cast<float *>(smem + kDigits * kDigitStride), &exponent)) {
-            table_by_digits<BITS, U>(c0, c, smem, exponent, g0, g1, n_out, scale, out, layers);
+        const int sets = table_digits<VT, BITS>(v, n_in, smem, reinterpret_cast<float *>(smem + kDigitSets * kDigitSetBytes), &exponent);
+        if (__builtin_expect(sets == 1, 1)) {
+            table_by_digits<BITS, U, false>(c0, c, smem, 1, exponent, g0, g1, n_out, scale, out, layers);
+            return;
+        }
+        if (sets > 1) {
+            // (four row groups at a time: the operands change with the set, and more do not fit the registers)
+            uint32_t four[4][2 * BITS];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int d = 0; d < 2 * BITS; ++d) four[i][d] = c[i][d];
+            table_by_digits<BITS, 4, true>(c0, four, smem, sets, exponent, g0, g1, n_out, scale, out, layers);
             return;
         }
         __syncthreads();  // (the flags have been read)
@@ -1764,7 +1828,8 @@ bool use_tile(const Args &x, bool wide) {
 // Waves that work through many row groups pay for bringing v into registers first and win only
 // when there are rows enough, measured (table kernel / other, 200 ternary columns):
 //   1 float32 vector   120000 rows 4.7 / 4.9 us (binary 5.3 / 4.8), 160000 4.9 / 5.8 (binary 5.3 / 5.7)
-//   1 bf16 vector      160000 rows 4.9 / 4.7 (binary 5.3 / 4.6), 240000 5.3 / 5.8 (binary 5.6 / 5.7)
+//   1 bf16 vector      160000 rows 4.9 / 4.7 (binary 5.3 / 4.6), 240000 5.3 / 5.8 (binary 5.6 / 5.7; with an element that needs a
+//                      second set of digits 6.5 / 5.8 and 5.8 / 5.7, 400000 7.7 / 8.1)
 //   4 bf16 vectors     20000 rows 3.3 / 3.1, 100000 4.1 / 5.0
 //   5 to 16            500 rows 3.3 / 3.6 (bf16), 20000 rows 4.6 / 14.7 (float32): always
 //   up to 64, float32  3000 rows 10.9 / 6.0, 12000 11.7 / 15.1
