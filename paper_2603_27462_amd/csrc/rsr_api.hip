@@ -32,7 +32,10 @@ bool is_rsr_kind(int kind) {
 // measured products that they are fitted to (binary k = 2..12, fused 2..10, two passes 4..12, 1..10000
 // rows, 300..32766 columns, 2..300 vectors, both types) by 12 % in the mean for the block patterns and 7 %
 // for the codes, hence the 0.85; the 1.35 keeps blocks of more than eight rows on the safe side.  With them
-// the block patterns are taken wrongly, by more than 4 %, in 16 of 4692 cases.
+// the block patterns are taken wrongly, by more than 4 %, in 16 of 4692 cases.  The products with two passes ran them one after
+// the other.  Where they run at once now (up to 448 workgroups; k = 4..12, 500..20000 columns, 2..32 vectors, 4536 products) the
+// estimate is on the safe side: the block patterns are never taken wrongly, and left in 769 cases although they are more
+// than 4 % faster, in 310 of which they were so one after the other as well.
 bool use_packed(const rsr_handle_s *h, int v_dtype, int batch, bool aligned) {
     if (h->kind == RSR_DENSE_TERNARY_P2) return true;
     if (!h->packed) return false;

@@ -863,7 +863,7 @@ hipError_t launch_rsr_matvec(const rsr_handle_s *h, const void *v, int v_dtype, 
 // A launch, a chain of staging, slabs and the two levels (or the words) of the scatter phase, and from 256
 // workgroups on the work of the ones that share a CU.  Beyond 80 KiB of LDS a CU holds one workgroup
 // at a time.  Vectors off the 16-byte boundaries are staged element by element.  Coefficients: least
-// squares over the products described at use_packed.
+// squares over the products described at use_packed, two passes one after the other; of both at once (use_both) this is too high.
 float rsr_matvec_us(const rsr_handle_s *h, int v_bytes, int batch, bool aligned) {
     const float n = (float)(h->nb * batch), np = (float)h->npass;
     const float slabs = np * (float)(h->pass[0].S > h->pass[h->npass - 1].S ? h->pass[0].S : h->pass[h->npass - 1].S);

@@ -283,7 +283,7 @@ __device__ __forceinline__ int pair_lane(int x) {
     return __builtin_amdgcn_mov_dpp(x, 0xb1, 0xf, 0xf, true);  // quad_perm: 1, 0, 3, 2
 }
 
-// part: of the stream, 64 strips of epl entries; lane0: of the part's first slot, `slots` (16 or 32) per half.
+// part: of the stream, 64 strips of epl entries; slots: 16 or 32 lanes per half-wave of the part; loads: of the wave.
 __device__ __forceinline__ void spread_banks(uint16_t *part, int epl, int slots, uint8_t *loads) {
     const int lane = threadIdx.x & 63, half = slots == 16 ? (lane >> 4) & 1 : lane >> 5, own = lane & (slots - 1);
     uint32_t *words = reinterpret_cast<uint32_t *>(loads + lane * kSpreadRow);
@@ -685,7 +685,8 @@ hipError_t launch_pack_pass(const rsr_handle_s *h, int pass, int *err_flag) {
     a.gword = pd.gword;
     a.gcount = pd.gcount;
     a.err_flag = err_flag;
-    // (what the multiply kernel's LDS holds, 4 (columns + slots) bytes and more, bounds this to 156 KiB)
+    // (what the multiply kernel's LDS holds, 4 (columns + slots) bytes and more, bounds this to 158.1 KiB: 32302 columns, E by
+    // rank)
     const StreamLds lds = stream_lds(a.n, a.P, a.S, a.W, a.slots, a.by_rank, a.spread);
     if (lds.total > kLdsBytes) return hipErrorInvalidValue;
     const int threads = a.W * 64 > 512 ? a.W * 64 : 512;
