@@ -1088,9 +1088,9 @@ __global__ __launch_bounds__(256 * KW, 2) void k_packed_tile(
 // One tile of columns: all of a vector fits the registers (or the LDS) of a wave, so it is brought
 // into operand order once and the wave then works through many row groups, with nothing but their
 // codes to wait for.  1048576 x 256 binary, float32 vectors, before (a wave stages v for every 512
-// bytes of codes; tiles of 128 vectors) and now: 1 vector 24.7 -> 14.5 us with bf16 operands, 8.0 with digits (4.2 TB/s; a
-// plain read of the codes takes 6.6; with sixteen such tables in turn, whose codes come from HBM, 16.7 and 10.2), 16 vectors 171 -> 32, 64 vectors 201 -> 100 (3.0 TB/s, of which
-// the 268 MB of results take two thirds).
+// bytes of codes; tiles of 128 vectors) and now: 1 vector 24.7 -> 14.3 us with bf16 operands, 7.9 with digits (4.2 TB/s; a
+// plain read of the codes takes 6.6; with sixteen such tables in turn, whose codes come from HBM, 15.6 and 8.8), 16 vectors
+// 171 -> 32, 64 vectors 201 -> 100 (3.0 TB/s, of which the 268 MB of results take two thirds).
 
 // table_few: up to 16 vectors.  The operands of the eight 32-column steps stay in registers; for up
 // to four vectors the float32 planes are rows of the MFMA as in k_packed_few, beyond that every
@@ -1113,9 +1113,9 @@ struct TableFew {
 // and more below its largest term: 14 binades in one sum were measured to be wrong by 4e-5 of it), so
 // the only roundings are those of the final sum over the planes.  Elements that reach below the last digit (nonzero and
 // smaller than 2^(E-55)) go into further sets of digits, each with the exponent 56 below the one before (float32 needs
-// five at most): two more MFMAs per row group and set, exact too.  With one element at 2^-70, float32, 1048576 x 256 binary
-// 12.1 us (9.7 without; 16.5 with bf16 operands, 17.0 after digits that turned out not to hold it), 241000 x 256 two-bit codes
-// 6.6 (5.7; 6.2, 7.7).
+// five at most): two more MFMAs per row group and set, exact too.  1048576 x 256 binary, float32, with one set 7.9 us, with a
+// second one for an element at 2^-70 10.6, with all five 14.9 (14.3 with bf16 operands, 15.1 after digits that turned out not to
+// hold the vector); 241000 x 256 two-bit codes, launches not in a graph, 5.7, with a second set 6.6 (6.2, 7.7).
 // Not taken, by the whole workgroup, where an element is not finite.
 constexpr int kDigits = 16;
 constexpr int kDigitStride = kTileCols + 16;  // bytes between planes
