@@ -1616,6 +1616,10 @@ hipError_t launch_few_groups(const Args &x) {
 // their second round begins (of 1280, 780 groups 3.8 / 3.8, 1400 4.9 / 4.2, 1700 5.3 / 5.6; of 1792, 2500 groups 7.2 /
 // 7.5); several: 770 groups of 1280 6 % slower, of 1024 9 % faster, from 900 on all faster.  Two waves, 4 bf16 vectors: two tiles, 900 groups
 // 3.3 / 3.2; three, of 700, 1300 4.9 / 5.5, 1700 5.8 / 5.6.
+// One float32 vector, eight waves: that is 512 workgroups of two-bit codes (86 registers), but 768 of one-bit codes (78), three to
+// a CU; k_packed_tall (94) has two either way, 1024 row groups in a round.  One-bit, of 2560, 640 groups 4.28 / 4.89, 768 4.42 /
+// 5.06, 820 5.40 / 5.05, 1024 5.58 / 4.93, 1100 6.22 / 6.76, 1536 7.35 / 7.75, 1800 9.09 / 8.34; between 1024 and 1536, where both are in their
+// second round, two pay on 2048 (1300 6.31 / 5.85) and long rows (of 5120, 1100 7.51 / 8.07, 1300 8.61 / 8.28, 1536 9.26 / 8.52).
 // Sixteen waves and several bf16 vectors: a CU holds two workgroups of k_packed_few (60 registers, 70 KB of LDS) and one of
 // k_packed_tall (66 registers and more), so a round is 512 row groups for either, and two groups pay where the last round is
 // more than half full: with one / two groups, 4 vectors of 8192 elements, 4160 rows 5.8 / 5.2, 8192 6.5 / 5.9, 8320 8.1 /
@@ -1625,7 +1629,7 @@ hipError_t launch_few_groups(const Args &x) {
 struct FewShape {
     int G, tiles;
 };
-template <typename VT, int NV>
+template <typename VT, int BITS, int NV>
 FewShape few_shape(int ntiles, int ngroups, int wk) {
     const bool wide = sizeof(VT) == 4;
     const int tiles = few_tiles<VT, NV>;
@@ -1638,6 +1642,10 @@ FewShape few_shape(int ntiles, int ngroups, int wk) {
     }
     if (wk == 16 && NV == 1 && ntiles > 44 && ngroups > 512 && ngroups <= 768) return {0, tiles};
     if (wk == 16) return {ngroups <= 256 ? 0 : NV == 4 && ngroups > 512 ? 4 : 2, tiles};
+    if (wk == 8 && wide && NV == 1 && BITS == 1) {
+        const bool two = ngroups > 1024 && ngroups <= 1536 ? ntiles == 8 || (ntiles >= 16 && ngroups > 1280) : ngroups > 768;
+        return {two ? 2 : 0, tiles};
+    }
     if (wk == 8 && wide) return {ngroups <= 512 ? 0 : NV == 4 && ngroups > (ntiles >= 16 ? 576 : 768) ? 4 : 2, tiles};
     if (wk == 8) return {ngroups > 768 && (ntiles <= 12 || ngroups <= 1024) ? 2 : 0, tiles};
     if (wk == 4 && NV == 1) return {(ntiles == 4 ? ngroups > 768 : ngroups > 1280 && ngroups <= 1536) ? 2 : 0, tiles};
@@ -1647,7 +1655,7 @@ FewShape few_shape(int ntiles, int ngroups, int wk) {
 
 template <typename VT, int BITS, int NV, int WK>
 hipError_t launch_few_wk(const Args &x) {
-    const FewShape s = few_shape<VT, NV>(x.ntiles, x.ngroups, WK);
+    const FewShape s = few_shape<VT, BITS, NV>(x.ntiles, x.ngroups, WK);
     if constexpr (sizeof(VT) == 4 && NV == 4 && WK >= 8) {
         if (s.G == 4) return launch_few_groups<VT, BITS, NV, WK, 4>(x);
     }
@@ -1980,7 +1988,8 @@ void packed_launch_shape(const rsr_handle_s *h, int v_dtype, int *workgroups, in
         return;
     }
     const int wk = few_wk(ntiles), waves = few_waves(wk);
-    const int G = wide ? few_shape<float, 1>(ntiles, (int)h->code_groups, wk).G : 0;
+    const int ngroups = (int)h->code_groups;
+    const int G = !wide ? 0 : h->code_bits == 1 ? few_shape<float, 1, 1>(ntiles, ngroups, wk).G : few_shape<float, 2, 1>(ntiles, ngroups, wk).G;
     const int groups = G ? G : 1, rows = waves / wk * groups;
     const int wave_bytes = wide ? Few<float, 1>::wave_bytes : Few<uint16_t, 1>::wave_bytes;
     *workgroups = (int)((h->code_groups + rows - 1) / rows);

@@ -394,6 +394,21 @@ def test_sixteen_waves(groups, tiles, batch, kernel):
     _check(h, M, batch, True, 3, cols)
 
 
+# one float32 vector and one-bit codes, eight waves: a CU holds three workgroups of one row group, or two of two
+@pytest.mark.parametrize("groups,tiles,kernel", [
+    (520, 8, "few"), (611, 10, "few"), (768, 23, "few"), (769, 8, "tall"), (1024, 12, "tall"), (1025, 8, "tall"), (1025, 9, "few"),
+    (1280, 16, "few"), (1281, 16, "tall"), (1281, 15, "few"), (1536, 15, "few"), (1537, 10, "tall")])
+def test_one_bit_codes_with_eight_waves(groups, tiles, kernel):
+    rows, cols = 16 * groups - 3, 256 * tiles - 11
+    M = _matrix(rsr.RSR_BINARY, rows, cols, groups + tiles)
+    h = _from_codes(rsr.rsr_preprocess(torch.from_numpy(M).to(DEV), 8, rsr.RSR_BINARY))
+    assert rsr.rsr_kernel_name(h, rsr.RSR_F32).startswith("k_packed_%s<float, 1, 1, 8" % kernel)
+    per = 2 if kernel == "tall" else 1
+    workgroups, threads, lds = rsr.rsr_launch_shape(h, rsr.RSR_F32)
+    assert (workgroups, threads) == ((groups + per - 1) // per, 512) and lds > 0
+    _check(h, M, 1, False, 1, cols)
+
+
 def test_stacked_layers_with_several_row_groups_per_wave():
     """Layers begin inside a workgroup's groups."""
     rows, cols = (3001, 17, 5000, 2003), 2500
