@@ -1614,11 +1614,12 @@ hipError_t launch_few_groups(const Args &x) {
 // 5.2 / 5.8 and 1024 7.8 / 5.9 / 6.0, of 4096, 513 6.3 / 5.7 / 6.0, 640 6.9 / 6.7 / 6.0; sixteen waves, 1 float32 vector of 14336, 520
 // groups 2 to 4 % slower with two.  Four waves, 1 float32 vector: five workgroups of one row group share a CU, so 1281 is where
 // their second round begins (of 1280, 780 groups 3.8 / 3.8, 1400 4.9 / 4.2, 1700 5.3 / 5.6; of 1792, 2500 groups 7.2 /
-// 7.5); several: 770 groups of 1280 6 % slower, of 1024 9 % faster, from 900 on all faster.  Two waves, 4 bf16 vectors: two tiles, 900 groups
-// 3.3 / 3.2; three, of 700, 1300 4.9 / 5.5, 1700 5.8 / 5.6.
+// 7.5); with two-bit codes three of two row groups, whose second round begins at 1537: of 1020, 1536 groups
+// 4.63 / 4.00, 1600 4.82 / 5.16, 1800 5.13 / 5.36, 1920 5.33 / 5.35); several: 770 groups of 1280 6 % slower, of 1024 9 % faster,
+// from 900 on all faster.  Two waves, 4 bf16 vectors: two tiles, 900 groups 3.3 / 3.2; three, of 700, 1300 4.9 / 5.5, 1700 5.8 / 5.6.
 // One float32 vector, eight waves: that is 512 workgroups of two-bit codes (86 registers), but 768 of one-bit codes (78), three to
 // a CU; k_packed_tall (94) has two either way, 1024 row groups in a round.  One-bit, of 2560, 640 groups 4.28 / 4.89, 768 4.42 /
-// 5.06, 820 5.40 / 5.05, 1024 5.58 / 4.93, 1100 6.22 / 6.76, 1536 7.35 / 7.75, 1800 9.09 / 8.34; between 1024 and 1536, where both are in their
+// 5.06, 820 5.40 / 5.05, 1024 5.58 / 4.93, 1100 6.22 / 6.76, 1536 7.35 / 7.75, 1800 9.09 / 8.34; between 1024 and 1536, both being in their
 // second round, two pay on 2048 (1300 6.31 / 5.85) and long rows (of 5120, 1100 7.51 / 8.07, 1300 8.61 / 8.28, 1536 9.26 / 8.52).
 // Sixteen waves and several bf16 vectors: a CU holds two workgroups of k_packed_few (60 registers, 70 KB of LDS) and one of
 // k_packed_tall (66 registers and more), so a round is 512 row groups for either, and two groups pay where the last round is
@@ -1648,6 +1649,7 @@ FewShape few_shape(int ntiles, int ngroups, int wk) {
     }
     if (wk == 8 && wide) return {ngroups <= 512 ? 0 : NV == 4 && ngroups > (ntiles >= 16 ? 576 : 768) ? 4 : 2, tiles};
     if (wk == 8) return {ngroups > 768 && (ntiles <= 12 || ngroups <= 1024) ? 2 : 0, tiles};
+    if (wk == 4 && NV == 1 && BITS == 2 && ntiles == 4 && ngroups > 1536 && ngroups <= 1856) return {0, tiles};
     if (wk == 4 && NV == 1) return {(ntiles == 4 ? ngroups > 768 : ngroups > 1280 && ngroups <= 1536) ? 2 : 0, tiles};
     if (wk == 4) return {ngroups > (ntiles == 4 ? 768 : 896) ? 2 : 0, tiles};
     return {ngroups > (wide ? 2048 : ntiles == 2 ? 768 : 1536) ? 2 : 0, tiles};
