@@ -361,6 +361,8 @@ def test_row_groups_of_a_workgroup(groups, tiles, batch, bf16, G):
     (rsr.RSR_DENSE_TERNARY_P2, 576 * 16 + 1, 4000, 2, False, "tall<float, 2, 4, 8, 4, 1>"),
     (rsr.RSR_DENSE_TERNARY_P2, 768 * 16, 2560, 4, False, "tall<float, 2, 4, 8, 2, 1>"),
     (rsr.RSR_BINARY, 768 * 16 + 1, 2560, 4, False, "tall<float, 1, 4, 8, 4, 1>"),
+    (rsr.RSR_BINARY, 577 * 16, 4090, 2, False, "tall<float, 1, 4, 8, 4, 1>"),
+    (rsr.RSR_BINARY, 700 * 16 - 5, 4461, 3, False, "tall<float, 1, 4, 8, 2, 1>"),
     (rsr.RSR_DENSE_TERNARY_P2, 1536 * 16 - 1, 1020, 1, False, "tall<float, 2, 1, 4, 2, 4>"),
     (rsr.RSR_DENSE_TERNARY_P2, 1536 * 16 + 1, 1020, 1, False, "few<float, 2, 1, 4>"),
     (rsr.RSR_DENSE_TERNARY_P2, 1857 * 16, 843, 1, False, "tall<float, 2, 1, 4, 2, 4>")])
