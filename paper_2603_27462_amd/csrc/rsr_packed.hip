@@ -1611,8 +1611,8 @@ hipError_t launch_few_groups(const Args &x) {
 //   bf16, 4 vectors      14336 x 2500 7.6 / 6.5 / 6.4, 14336 x 1000 4.1 / 3.7 (8192 rows 3.3 / 3.3);
 //                        with two tiles of columns to a wave 14336 x 4096 6.0 / 5.9, but in two rounds 20000 x 4096 7.1 / 7.3
 // The limits, with one / two (/ four) groups: eight waves, 4 float32 vectors of 2560 (ten tiles to eight waves), 513 groups 5.3 /
-// 5.2 / 5.8 and 1024 7.8 / 5.9 / 6.0, of 4096, 513 6.3 / 5.7 / 6.0, 640 6.9 / 6.7 / 6.0, but one-bit codes, whose tiles take half
-// the time, on more than 16 tiles: 3 vectors of 4461, 700 groups 7.2 / 7.1 / 7.4; sixteen waves, 1 float32 vector of 14336, 520
+// 5.2 / 5.8 and 1024 7.8 / 5.9 / 6.0, of 4096, 513 6.3 / 5.7 / 6.0, 640 6.9 / 6.7 / 6.0, with one-bit codes and more than
+// 16 tiles 3 vectors of 4461, 700 groups 7.2 / 7.1 / 7.4; sixteen waves, 1 float32 vector of 14336, 520
 // groups 2 to 4 % slower with two.  Four waves, 1 float32 vector: five workgroups of one row group share a CU, so 1281 is where
 // their second round begins (of 1280, 780 groups 3.8 / 3.8, 1400 4.9 / 4.2, 1700 5.3 / 5.6; of 1792, 2500 groups 7.2 /
 // 7.5); with two-bit codes three of two row groups, whose second round begins at 1537: of 1020, 1536 groups
